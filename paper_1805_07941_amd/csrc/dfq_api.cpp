@@ -19,6 +19,10 @@ inline bool overlaps(const void *a, size_t na, const void *b, size_t nb)
     return pa < pb + nb && pb < pa + na;
 }
 
+// bytes from the first to the last one touched of `pixels` rows of K bytes, ld bytes apart: a channel slice of a wider tensor ends
+// with its own last channel, not with the row
+inline size_t slice_bytes(size_t pixels, int ld, int K) { return pixels ? (pixels - 1) * (size_t)ld + (size_t)K : 0; }
+
 inline dfq_status from_hip(hipError_t e) { return e == hipSuccess ? DFQ_OK : DFQ_EDEVICE; }
 
 inline int out_extent(int in, int pad, int k, int stride)
@@ -67,7 +71,7 @@ ConvCheck check_conv(const int8_t *x, const int8_t *w, const int32_t *b, int8_t 
                    relu ? 1 : 0};
     if (need_ptrs) {
         size_t nx = (size_t)N * H * W * C, npix = (size_t)N * P * Q;
-        if (overlaps(x, nx, y, npix * (size_t)ldy) || overlaps(x, nx, acc_out, npix * K * 4)) r.st = DFQ_EINVAL;
+        if (overlaps(x, nx, y, slice_bytes(npix, ldy, K)) || overlaps(x, nx, acc_out, npix * K * 4)) r.st = DFQ_EINVAL;
     }
     return r;
 }
@@ -124,8 +128,8 @@ dfq_status run_conv_add(ConvCheck &c, const int8_t *x, const int8_t *other, int8
     if (F - fmt_mid.frac > 22 || F - fmt_other.frac > 22) return DFQ_EFMT;
     if (N == 0) return DFQ_OK;
     const size_t npix = (size_t)N * c.a.P * c.a.Q;
-    if (overlaps(other, npix * (size_t)ld_other, y, npix * (size_t)ldy) ||
-        overlaps(other, npix * (size_t)ld_other, x, (size_t)N * H * W * C))
+    if (overlaps(other, slice_bytes(npix, ld_other, K), y, slice_bytes(npix, ldy, K)) ||
+        overlaps(other, slice_bytes(npix, ld_other, K), x, (size_t)N * H * W * C))
         return DFQ_EINVAL;
     c.a.add = other;
     c.a.ldadd = ld_other;
@@ -464,7 +468,7 @@ static dfq_status conv_maxpool(const void *x, bool x_is_float, const int8_t *w, 
     const int PP = out_extent(c.a.P, pool_pad, pool_k, pool_stride), PQ = out_extent(c.a.Q, pool_pad, pool_k, pool_stride);
     if (PP < 1 || PQ < 1 || ldy < K) return DFQ_ESHAPE;
     if (N == 0) return DFQ_OK;
-    if (overlaps(x, (size_t)N * H * W * C * (x_is_float ? 4 : 1), y, (size_t)N * PP * PQ * (size_t)ldy)) return DFQ_EINVAL;
+    if (overlaps(x, (size_t)N * H * W * C * (x_is_float ? 4 : 1), y, slice_bytes((size_t)N * PP * PQ, ldy, K))) return DFQ_EINVAL;
     if (pool_k != 3 || pool_stride != 2 || pool_pad != 1) return DFQ_EUNSUPPORTED;
     if (((uintptr_t)y & 15) || (ldy & 15)) return DFQ_EUNSUPPORTED;
     c.a.frac_w = frac_w;
@@ -505,7 +509,7 @@ dfq_status dfq_quantize_conv_q(const float *x, const int8_t *w, const int32_t *b
     if (!x || !w || !y) return DFQ_EINVAL;
     if (ldy < K) return DFQ_ESHAPE;
     if (N == 0) return DFQ_OK;
-    if (overlaps(x, (size_t)N * H * W * C * 4, y, (size_t)N * c.a.P * c.a.Q * (size_t)ldy)) return DFQ_EINVAL;
+    if (overlaps(x, (size_t)N * H * W * C * 4, y, slice_bytes((size_t)N * c.a.P * c.a.Q, ldy, K))) return DFQ_EINVAL;
     if (((uintptr_t)x & 15) || !conv_stem_supports(c.a, false, true)) return DFQ_EUNSUPPORTED;
     return from_hip(launch_conv_stem(c.a, nullptr, 0, (hipStream_t)stream, x, fmt_in.frac));
 }
@@ -546,8 +550,8 @@ dfq_status dfq_conv_q_add_lazy(const int8_t *x, const int8_t *w, const int32_t *
     if (sb < 0 || sb > 22) return DFQ_EFMT;
     if (N == 0) return DFQ_OK;
     const size_t npix = (size_t)N * c.a.P * c.a.Q;
-    if (overlaps(other, npix * (size_t)ld_other, y, npix * (size_t)ldy) ||
-        overlaps(other, npix * (size_t)ld_other, x, (size_t)N * H * W * C))
+    if (overlaps(other, slice_bytes(npix, ld_other, K), y, slice_bytes(npix, ldy, K)) ||
+        overlaps(other, slice_bytes(npix, ld_other, K), x, (size_t)N * H * W * C))
         return DFQ_EINVAL;
     c.a.add = other;
     c.a.ldadd = ld_other;
