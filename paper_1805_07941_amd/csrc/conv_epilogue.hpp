@@ -226,6 +226,48 @@ __device__ __forceinline__ void store_tile_lane_general(const v16i &v, const Con
     }
 }
 
+// 16 bytes at any byte address
+struct __attribute__((packed, aligned(1))) Bytes16 {
+    uint32_t w[4];
+};
+
+__device__ __forceinline__ void store_bytes(const Bytes16 &o, int8_t *dst, int count)
+{
+    if (count == 16) {
+        *(Bytes16 *)dst = o;
+        return;
+    }
+#pragma unroll
+    for (int r = 0; r < 15; r++)
+        if (r < count) dst[r] = (int8_t)(o.w[r >> 2] >> (8 * (r & 3)));
+}
+
+// Any row pitch and any number `count` (1 .. 16) of the lane's channels kc, kc + 1, ...: whole groups go out as one 16-byte
+// store at whatever address the pitch gives them (byte stores to a pitch of 131 took as long as the products of the layer).
+__device__ __forceinline__ void store_tile_lane_ragged(const v16i &v, const ConvArgs &a, long long m, int kc, int count)
+{
+    if (a.acc_out) {
+#pragma unroll
+        for (int r = 0; r < 16; r++)
+            if (r < count) a.acc_out[(size_t)m * a.K + kc + r] = v[r];
+    }
+    if (!a.y) return;
+    Bytes16 o;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        int q[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const int r = 4 * j + e;
+            ChannelRequant cr;
+            cr.init(a.frac_w ? a.shift + (r < count ? a.frac_w[kc + r] : 0) : a.shift);
+            q[e] = cr.apply(v[r], a.relu);
+        }
+        o.w[j] = pack4_clamped(q[0], q[1], q[2], q[3]);
+    }
+    store_bytes(o, a.y + (size_t)m * a.ldy + kc, count);
+}
+
 // One weight format per output channel with the lane's 16 shifts already in registers: whole 16-channel
 // group, aligned row, no accumulator dump - one 16-byte store, no loads.
 __device__ __forceinline__ void store_tile_lane_per_channel(const v16i &v, const ConvArgs &a, const int (&shifts)[16], int relu,

@@ -84,6 +84,7 @@ dfq_conv_variant select_variant(const ConvArgs &a, bool geometry_only = false)
     if (conv_mfma_supports(a)) return DFQ_CONV_MFMA;
     if (conv_smallc_supports(a)) return DFQ_CONV_SMALLC;
     if (conv_grouped_supports(a)) return DFQ_CONV_GROUPED;
+    if (conv_rag_pays(a)) return DFQ_CONV_RAGGED;
     return DFQ_CONV_DIRECT;
 }
 
@@ -109,6 +110,9 @@ dfq_status run_conv(dfq_conv_variant variant, const ConvArgs &a, hipStream_t st)
         case DFQ_CONV_GROUPED:
             if (!conv_grouped_supports(a)) return DFQ_EUNSUPPORTED;
             return from_hip(launch_conv_grouped(a, st));
+        case DFQ_CONV_RAGGED:
+            if (!conv_rag_supports(a)) return DFQ_EUNSUPPORTED;
+            return from_hip(launch_conv_rag(a, st));
         default:
             return DFQ_EINVAL;
     }
