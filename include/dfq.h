@@ -395,7 +395,7 @@ dfq_status dfq_conv_np_add(const int8_t *xh, const int8_t *xl, const int8_t *wh,
  * ReLU where the layer has one, before anything is rounded): the largest |sum + bias| of Eq. 6 over all outputs of the
  * layer (negative sums count as 0 when relu is set), as a 64-bit integer at the scale 2^-(frac_x + frac_w), written to
  * *amax_dev (DEVICE, 8-byte aligned; cleared by the call on the stream, then raised by atomic maxima).  Operands as for
- * dfq_conv_np; nothing else is written.  One output per lane (a calibration batch is small). */
+ * dfq_conv_np; nothing else is written.  On the matrix cores where dfq_conv_np is, else one output per lane. */
 dfq_status dfq_conv_np_absmax(const int8_t *xh, const int8_t *xl, const int8_t *wh, const int8_t *wl, const int32_t *b, uint64_t *amax_dev,
                               int N, int H, int W, int C, int K, int R, int S, int stride, int pad, int groups, int relu, dfq_stream stream);
 

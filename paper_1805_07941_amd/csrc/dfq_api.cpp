@@ -323,6 +323,7 @@ dfq_status dfq_conv_np_absmax(const int8_t *xh, const int8_t *xl, const int8_t *
     a.amax = reinterpret_cast<unsigned long long *>(amax_dev);
     hipError_t e = launch_clear_u64(a.amax, (hipStream_t)stream);
     if (e != hipSuccess || N == 0) return from_hip(e);
+    if (conv_np_mfma_supports(a)) return from_hip(launch_conv_np_mfma(a, (hipStream_t)stream));
     return from_hip(launch_conv_np_direct(a, (hipStream_t)stream));
 }
 
