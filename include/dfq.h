@@ -340,6 +340,9 @@ dfq_status dfq_threshold_search(const uint32_t *hist, int nbins, int shift, int6
  * [-32, 32] with gamma * 2^frac <= 127; gamma = 0 gives 32.  Host, pure.  DFQ_EINVAL for a
  * negative, infinite or NaN gamma. */
 dfq_status dfq_fmt_from_absmax_f32(float gamma, dfq_fmt *out);
+/* The same for n thresholds at once (one per output channel, as dfq_absmax_f32_rows leaves them, copied to the host): frac[i] from
+ * gamma[i].  gamma, frac: HOST arrays.  Host, pure.  On an invalid entry nothing behind it is written. */
+dfq_status dfq_fmt_from_absmax_f32_rows(const float *gamma, int n, int32_t *frac);
 /* Integer form for accumulators held at acc_frac: the largest frac <= acc_frac (rescale factor
  * in (0, 1], Sec. 3) with m * 2^(frac - acc_frac) <= 127, floored at -32.  Host, pure. */
 dfq_status dfq_fmt_from_absmax_i32(int64_t m, int32_t acc_frac, dfq_fmt *out);

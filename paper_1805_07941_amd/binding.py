@@ -25,7 +25,7 @@ CONV_VARIANT_NAMES = {CONV_AUTO: "auto", CONV_DIRECT: "direct", CONV_MFMA: "mfma
 EXPORTS = [
     "dfq_status_string", "dfq_quantize", "dfq_quantize_i32", "dfq_dequantize", "dfq_quantize_np", "dfq_dequantize_np", "dfq_conv_q",
     "dfq_conv_q_variant", "dfq_conv_q_select", "dfq_conv_q_add", "dfq_conv_q_pc", "dfq_conv_q_pc_add", "dfq_absmax_i32_channels", "dfq_hist_i32", "dfq_threshold_search", "dfq_absmax_f32_rows", "dfq_quantize_rows", "dfq_quantize_i32_rows", "dfq_fold_scale_f32", "dfq_eltwise_q", "dfq_concat_q", "dfq_concat_q_into", "dfq_pool_q",
-    "dfq_absmax_f32", "dfq_absmax_i32", "dfq_fmt_from_absmax_f32", "dfq_fmt_from_absmax_i32", "dfq_hist_shift", "dfq_fmt_from_absmax_i32_channels",
+    "dfq_absmax_f32", "dfq_absmax_i32", "dfq_fmt_from_absmax_f32", "dfq_fmt_from_absmax_f32_rows", "dfq_fmt_from_absmax_i32", "dfq_hist_shift", "dfq_fmt_from_absmax_i32_channels",
     "dfq_beta_max", "dfq_mac_acc_bits", "dfq_mac_max_len", "dfq_add_acc_bits", "dfq_add_max_len",
     "dfq_np_digits", "dfq_conv_np", "dfq_conv_np_variant", "dfq_np_frac_from_absmax_f32", "dfq_conv_q_add_lazy", "dfq_eltwise_np",
     "dfq_conv_np_absmax", "dfq_eltwise_np_absmax", "dfq_np_frac_from_absmax_u64", "dfq_pool_np", "dfq_stem_pack_x", "dfq_stem_pack_w", "dfq_conv_np_add",
@@ -101,6 +101,8 @@ def lib():
     L.dfq_absmax_f32.argtypes = [vp, sz, vp, vp]
     L.dfq_absmax_i32.argtypes = [vp, sz, i32, vp, vp]
     L.dfq_fmt_from_absmax_f32.argtypes = [C.c_float, C.POINTER(Fmt)]
+    L.dfq_fmt_from_absmax_f32_rows.argtypes = [vp, i32, vp]
+    L.dfq_fmt_from_absmax_f32_rows.restype = i32
     L.dfq_fmt_from_absmax_i32.argtypes = [i64, C.c_int32, C.POINTER(Fmt)]
     L.dfq_fmt_from_absmax_i32_channels.argtypes = [vp, i32, C.c_int32, vp, C.POINTER(Fmt)]
     L.dfq_np_digits.argtypes = [vp, sz, i32, vp, vp, vp]
@@ -646,7 +648,7 @@ def absmax_f32_rows(x: torch.Tensor, stream=None) -> torch.Tensor:
     """max |.| of every row of a float32 [rows, ...] tensor: float32 device tensor [rows] (no synchronization)."""
     _dev(x, torch.float32, "x")
     rows = int(x.shape[0])
-    out = torch.zeros(rows, dtype=torch.float32, device=x.device)
+    out = torch.empty(rows, dtype=torch.float32, device=x.device)
     _check(lib().dfq_absmax_f32_rows(_ptr(x), rows, x.numel() // max(rows, 1), _ptr(out), _stream(stream)),
            "dfq_absmax_f32_rows")
     return out
@@ -746,6 +748,16 @@ def fmt_from_absmax_f32(gamma: float) -> int:
     f = Fmt()
     _check(lib().dfq_fmt_from_absmax_f32(float(gamma), C.byref(f)), "dfq_fmt_from_absmax_f32")
     return int(f.frac)
+
+
+def fmt_from_absmax_f32_rows(gammas):
+    """One format per threshold (numpy float32 [K]): numpy int32 [K]."""
+    import numpy as np
+    g = np.ascontiguousarray(gammas, np.float32)
+    f = np.empty(g.shape, np.int32)
+    _check(lib().dfq_fmt_from_absmax_f32_rows(g.ctypes.data_as(C.c_void_p), g.size, f.ctypes.data_as(C.c_void_p)),
+           "dfq_fmt_from_absmax_f32_rows")
+    return f
 
 
 def np_frac_from_absmax_f32(gamma: float, nbits: int, p: int) -> int:

@@ -807,6 +807,18 @@ dfq_status dfq_fmt_from_absmax_f32(float gamma, dfq_fmt *out)
     return DFQ_OK;
 }
 
+dfq_status dfq_fmt_from_absmax_f32_rows(const float *gamma, int n, int32_t *frac)
+{
+    if (n < 0 || (n && (!gamma || !frac))) return DFQ_EINVAL;
+    for (int i = 0; i < n; i++) {
+        dfq_fmt f;
+        const dfq_status st = dfq_fmt_from_absmax_f32(gamma[i], &f);
+        if (st != DFQ_OK) return st;
+        frac[i] = f.frac;
+    }
+    return DFQ_OK;
+}
+
 dfq_status dfq_np_frac_from_absmax_f32(float gamma, int nbits, int p, int32_t *frac_out)
 {
     if (!frac_out) return DFQ_EINVAL;

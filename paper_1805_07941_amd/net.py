@@ -96,7 +96,7 @@ def calibrate(net, x: torch.Tensor, device="cuda:0", keep_tensors: bool = True, 
                 # channel k's weights and bias at their own scale; its accumulators are then at f_in + f_w[k],
                 # and the output format is the finest that holds every channel's maximum
                 gam = B.absmax_f32_rows(wf).cpu().numpy()
-                f_wk = np.array([B.fmt_from_absmax_f32(float(g)) for g in gam], np.int32)
+                f_wk = B.fmt_from_absmax_f32_rows(gam)
                 fw_dev = torch.from_numpy(f_wk).to(device)
                 qz.w_frac[nd.name], qz.w_frac_dev[nd.name] = f_wk, fw_dev
                 qz.w[nd.name] = B.quantize_rows(wf, fw_dev)

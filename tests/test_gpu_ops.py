@@ -813,3 +813,31 @@ def test_conv_q_maxpool_declines_what_it_does_not_cover(B):
     x = dev(rng.integers(-128, 128, (1, 64, 64, 3)).astype(np.int8))
     assert B.conv_q_maxpool(x, w, None, 4, 7, 4, 2, 3, True, pool_k=2, pool_stride=2, pool_pad=0) is None   # another pooling
     assert B.conv_q_maxpool(x, w, None, 4, 7, 12, 2, 3, True) is None                                        # shift < 0
+
+
+def test_absmax_per_channel_wide_and_tall(B):
+    """Channel counts around the 256 four-channel pieces of a workgroup, pixels around its rows, and a view that is only 4-byte aligned."""
+    rng = np.random.default_rng(33)
+    for pixels, K in [(1, 4), (300, 1020), (37, 1024), (9, 1028), (5, 4100), (4097, 12), (257, 257), (70000, 8)]:
+        a = rng.integers(-2 ** 31, 2 ** 31, (pixels, K)).astype(np.int32)
+        got = B.absmax_i32_channels_value(B.absmax_i32_channels(dev(a), relu=True)).astype(np.int64)
+        assert np.array_equal(got, orc.absmax_i32_channels(a, relu=True)), (pixels, K)
+        buf = torch.empty(pixels * K + 1, dtype=torch.int32, device=DEV)
+        v = buf[1:].view(pixels, K)
+        v.copy_(dev(a))
+        got = B.absmax_i32_channels_value(B.absmax_i32_channels(v)).astype(np.int64)
+        assert np.array_equal(got, orc.absmax_i32_channels(a)), (pixels, K, "unaligned")
+    x = rng.standard_normal(1 << 21).astype(np.float32)
+    x[12345] = np.nan
+    x[1 << 20] = -9.0
+    assert float(host(B.absmax_f32(dev(x)))[0]) == 9.0
+    xd = dev(x)
+    assert float(host(B.absmax_f32(xd[1:]))[0]) == 9.0
+
+
+def test_formats_from_a_row_of_thresholds(B):
+    g = np.array([0.0, 127.0, 127.1, 1e-30, 3e38, 1.0, 63.5], np.float32)
+    assert B.fmt_from_absmax_f32_rows(g).tolist() == [B.fmt_from_absmax_f32(float(v)) for v in g]
+    for bad in (np.nan, np.inf, -1.0):
+        with pytest.raises(B.DfqError):
+            B.fmt_from_absmax_f32_rows(np.array([1.0, bad], np.float32))
