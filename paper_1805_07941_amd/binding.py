@@ -159,8 +159,16 @@ def _check(status: int, where: str):
         raise DfqError(status, where)
 
 
+# The current stream's handle straight from the runtime: torch.cuda.current_stream() builds a Stream object on every call, 6 us of the
+# 10 a small library call costs the host.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_current_device())
         return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
@@ -644,11 +652,11 @@ def absmax_i32(x: torch.Tensor, relu: bool = False, out_dev: Optional[torch.Tens
     return out
 
 
-def absmax_f32_rows(x: torch.Tensor, stream=None) -> torch.Tensor:
+def absmax_f32_rows(x: torch.Tensor, stream=None, out_dev: Optional[torch.Tensor] = None) -> torch.Tensor:
     """max |.| of every row of a float32 [rows, ...] tensor: float32 device tensor [rows] (no synchronization)."""
     _dev(x, torch.float32, "x")
     rows = int(x.shape[0])
-    out = torch.empty(rows, dtype=torch.float32, device=x.device)
+    out = out_dev if out_dev is not None else torch.empty(rows, dtype=torch.float32, device=x.device)
     _check(lib().dfq_absmax_f32_rows(_ptr(x), rows, x.numel() // max(rows, 1), _ptr(out), _stream(stream)),
            "dfq_absmax_f32_rows")
     return out

@@ -799,11 +799,12 @@ dfq_status dfq_fmt_from_absmax_f32(float gamma, dfq_fmt *out)
 {
     if (!out) return DFQ_EINVAL;
     if (!(gamma >= 0.0f) || std::isinf(gamma)) return DFQ_EINVAL;
-    // gamma * 2^f is exact in double, so the comparison needs no logarithm
-    int f = 32;
-    while (f > -32 && std::ldexp((double)gamma, f) > 127.0) f--;
+    // gamma = m * 2^e with m in [1/2, 1): gamma * 2^f <= 127 = (127/128) * 2^7 for f = 7 - e, one less when m > 127/128
+    int e = 0;
+    const double m = std::frexp((double)gamma, &e);
+    const int f = gamma > 0.0f ? 7 - e - (m > 127.0 / 128.0 ? 1 : 0) : 32;
     out->bits = 8;
-    out->frac = f;
+    out->frac = f > 32 ? 32 : f < -32 ? -32 : f;
     return DFQ_OK;
 }
 

@@ -39,6 +39,54 @@ def _read_f32(t: torch.Tensor) -> float:
     return float(t.cpu()[0])
 
 
+def float_weights(net, device, fold: bool = True) -> Dict[str, tuple]:
+    """Float weights and bias of every convolution on the device (fold: the affine layers behind them folded in where the
+    network has them).  The many small bias vectors travel as one array: an upload costs 15 us whatever it holds."""
+    convs = [nd for nd in net.nodes if nd.op == "conv"]
+    host = [net.weights(nd) for nd in convs]
+    biases = torch.from_numpy(np.concatenate([b for _, b in host]) if host else np.zeros(0, np.float32)).to(device)
+    out, off = {}, 0
+    for nd, (w, b) in zip(convs, host):
+        wf, bf = torch.from_numpy(w).to(device), biases[off:off + b.size]
+        off += b.size
+        if fold and getattr(net, "scale_layers", False):
+            # the affine layer behind the convolution is folded into the float weights before they are quantized
+            scale, shift = net.scale_shift(nd)
+            wf, bf = B.fold_scale(wf, bf, torch.from_numpy(scale).to(device), torch.from_numpy(shift).to(device))
+        out[nd.name] = (wf, bf)
+    return out
+
+
+def _quantize_weights(net, qz: "Quantized", device, per_channel: bool) -> Dict[str, torch.Tensor]:
+    """Weight formats and codes of all layers into qz; returns the float biases (their scale waits for the layer's input).
+    Weight thresholds depend on the weights alone, so those of the whole network are read back together: one synchronization where
+    a layer-by-layer loop has one per layer, with the device idle around each."""
+    raw = float_weights(net, device)
+    gamma = torch.empty(sum(int(w.shape[0]) if per_channel else 1 for w, _ in raw.values()), dtype=torch.float32, device=device)
+    off = 0
+    for w, _ in raw.values():
+        if per_channel:
+            B.absmax_f32_rows(w, out_dev=gamma[off:off + int(w.shape[0])])
+            off += int(w.shape[0])
+        else:
+            B.absmax_f32(w, out_dev=gamma[off:off + 1])
+            off += 1
+    f_all = B.fmt_from_absmax_f32_rows(gamma.cpu().numpy())
+    f_dev = torch.from_numpy(f_all).to(device) if per_channel else None
+    off = 0
+    for name, (w, _) in raw.items():
+        if per_channel:
+            end = off + int(w.shape[0])
+            qz.w_frac[name], qz.w_frac_dev[name] = f_all[off:end], f_dev[off:end]
+            qz.w[name] = B.quantize_rows(w, qz.w_frac_dev[name])
+            off = end
+        else:
+            qz.w_frac[name] = int(f_all[off])
+            qz.w[name] = B.quantize(w, qz.w_frac[name])
+            off += 1
+    return {name: b for name, (_, b) in raw.items()}
+
+
 def _threshold(acc: torch.Tensor, relu: bool, rule: str) -> int:
     """Activation threshold in accumulator units: the maximum magnitude after the ReLU, or - rule
     "search" - Algorithm 1 on the histogram of the magnitudes (device histogram, host search)."""
@@ -63,6 +111,7 @@ def calibrate(net, x: torch.Tensor, device="cuda:0", keep_tensors: bool = True, 
     if rule not in ("maxabs", "search") or (rule == "search" and per_channel):
         raise ValueError("rule must be 'maxabs' or 'search' (the search with per-layer weight formats)")
     qz = Quantized()
+    biases = _quantize_weights(net, qz, device, per_channel)
     t: Dict[str, torch.Tensor] = {}
     if net.input_is_int8:
         qz.frac[net.input_name] = net.f_input_codes
@@ -85,41 +134,30 @@ def calibrate(net, x: torch.Tensor, device="cuda:0", keep_tensors: bool = True, 
         if nd.op == "conv":
             src = nd.srcs[0]
             f_in = qz.frac[src]
-            wf, bf = net.weights(nd)
-            wf = torch.from_numpy(wf).to(device)
-            bf = torch.from_numpy(bf).to(device)
-            if getattr(net, "scale_layers", False):
-                # the affine layer behind the convolution is folded into the float weights before they are quantized
-                scale, shift = net.scale_shift(nd)
-                wf, bf = B.fold_scale(wf, bf, torch.from_numpy(scale).to(device), torch.from_numpy(shift).to(device))
+            bf = biases[nd.name]
             if per_channel:
                 # channel k's weights and bias at their own scale; its accumulators are then at f_in + f_w[k],
                 # and the output format is the finest that holds every channel's maximum
-                gam = B.absmax_f32_rows(wf).cpu().numpy()
-                f_wk = B.fmt_from_absmax_f32_rows(gam)
-                fw_dev = torch.from_numpy(f_wk).to(device)
-                qz.w_frac[nd.name], qz.w_frac_dev[nd.name] = f_wk, fw_dev
-                qz.w[nd.name] = B.quantize_rows(wf, fw_dev)
+                f_wk, fw_dev = qz.w_frac[nd.name], qz.w_frac_dev[nd.name]
+                f_range = (int(f_wk.min()), int(f_wk.max()))
                 qz.b[nd.name] = B.quantize_i32_rows(bf, fw_dev, f_in)
                 w, b = qz.w[nd.name], qz.b[nd.name]
                 if nd.fixed_f_out is not None:
                     qz.frac[nd.dst] = nd.fixed_f_out
                 else:
                     _, acc = B.conv_q_pc(t[src], w, b, f_in, fw_dev, 0, nd.stride, nd.pad, nd.groups, nd.relu,
-                                         want_y=False, want_acc=True, frac_w_range=(int(f_wk.min()), int(f_wk.max())))
+                                         want_y=False, want_acc=True, frac_w_range=f_range)
                     m = B.absmax_i32_channels_value(B.absmax_i32_channels(acc, relu=nd.relu))
                     del acc
                     qz.frac[nd.dst] = B.fmt_from_absmax_i32_channels(m, f_in, f_wk)
                 t[nd.dst], _ = B.conv_q_pc(t[src], w, b, f_in, fw_dev, qz.frac[nd.dst], nd.stride, nd.pad, nd.groups, nd.relu,
-                                           frac_w_range=(int(f_wk.min()), int(f_wk.max())))
+                                           frac_w_range=f_range)
                 if not keep_tensors:
                     for s in nd.srcs:
                         if last_use.get(s) == idx and s != net.output_name:
                             t.pop(s, None)
                 continue
-            f_w = B.fmt_from_absmax_f32(_read_f32(B.absmax_f32(wf)))
-            qz.w_frac[nd.name] = f_w
-            qz.w[nd.name] = B.quantize(wf, f_w)
+            f_w = qz.w_frac[nd.name]
             qz.b[nd.name] = B.quantize_i32(bf, f_in + f_w)
             w, b = qz.w[nd.name], qz.b[nd.name]
             if nd.fixed_f_out is not None:
