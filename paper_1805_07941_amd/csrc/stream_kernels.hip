@@ -397,50 +397,78 @@ hipError_t launch_eltwise(const int8_t *a, int fa, const int8_t *b, int fb, int8
 }
 
 // ------------------------------------------------------------------------------------------
-// concat_q: one launch, every lane produces VEC output bytes of one branch
+// concat_q: one launch, every lane produces a piece of VEC output bytes of one branch
 // ------------------------------------------------------------------------------------------
 
 struct ConcatParams {
     const int8_t *x[8];
     int C[8];       // channels of each branch
-    int off[9];     // channel offset of each branch in y; off[nb] = total
+    int off[8];     // channel offset of each branch in y
     int s[8];       // f_i - f_y
+    int pieces[9];  // pieces of the branches before this one; pieces[nb]: of a whole pixel
     int nb;
+    FastDiv div_pieces;
 };
 
-// ldy: bytes between consecutive pixels of y (>= the branches' channels together)
+// VEC bytes at any byte address.  Channel counts that are no multiple of VEC are covered by pieces that overlap: the last piece of a
+// pixel (of a branch) starts VEC channels before its end, so every access is whole and the bytes two lanes write are the same.
 template <int VEC>
+struct __attribute__((packed, aligned(1))) Piece {
+    uint32_t w[VEC / 4];
+};
+template <>
+struct Piece<1> {
+    int8_t w[1];
+};
+
+// ldy: bytes between consecutive pixels of y (>= the branches' channels together).  FAST: every branch's shift lies in [0, 23].
+// Memory-bound: 3 branches of 90 channels over 24 x 45 x 61 pixels (35 MB) took 43 us with byte accesses, now 10.
+template <int VEC, bool FAST>
 __global__ void __launch_bounds__(kBlock) concat_kernel(ConcatParams p, int8_t *__restrict__ y, size_t pixels, int ldy)
 {
-    const int Ct = p.off[p.nb];
-    const int per_px = Ct / VEC;
-    const size_t total = pixels * (size_t)per_px;
+    const size_t total = pixels * (size_t)p.pieces[p.nb];
     for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < total; i += (size_t)gridDim.x * kBlock) {
-        size_t px = i / per_px;
-        int c = (int)(i - px * per_px) * VEC;
-        int br = 0;
+        const size_t px = total < (1ull << 31) ? (size_t)fastdiv((int)i, p.div_pieces) : i / (size_t)p.pieces[p.nb];
+        const int pc = (int)(i - px * p.pieces[p.nb]);
+        const int8_t *src = p.x[0];
+        int C = p.C[0], off = 0, first = 0, s = p.s[0];
 #pragma unroll
         for (int j = 1; j < 8; j++)
-            if (j < p.nb && c >= p.off[j]) br = j;
-        const int8_t *src = p.x[br] + px * (size_t)p.C[br] + (c - p.off[br]);
-        int8_t *dst = y + px * (size_t)ldy + c;
-        const int s = p.s[br];
-        if (VEC == 16) {
-            uint4 v = *(const uint4 *)src;
-            uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            if (j < p.nb && pc >= p.pieces[j]) { src = p.x[j]; C = p.C[j]; off = p.off[j]; first = p.pieces[j]; s = p.s[j]; }
+        const int c = min((pc - first) * VEC, C - VEC);
+        const Piece<VEC> v = *(const Piece<VEC> *)(src + px * (size_t)C + c);
+        Piece<VEC> o;
+        if constexpr (VEC == 1) {
+            o.w[0] = (int8_t)requant8(v.w[0], s);
+        } else if constexpr (FAST) {
+            const int hi = 127 << s, badd = s > 0 ? (1 << (s - 1)) - 1 : 0;
+            const int4 s4 = make_int4(s, s, s, s), h4 = make_int4(hi, hi, hi, hi), b4 = make_int4(badd, badd, badd, badd);
 #pragma unroll
-            for (int j = 0; j < 4; j++)
-                w[j] = pack4(requant8(byte_of(w[j], 0), s), requant8(byte_of(w[j], 1), s),
-                             requant8(byte_of(w[j], 2), s), requant8(byte_of(w[j], 3), s));
-            *(uint4 *)dst = make_uint4(w[0], w[1], w[2], w[3]);
-        } else if (VEC == 4) {
-            uint32_t w = *(const uint32_t *)src;
-            *(uint32_t *)dst = pack4(requant8(byte_of(w, 0), s), requant8(byte_of(w, 1), s),
-                                     requant8(byte_of(w, 2), s), requant8(byte_of(w, 3), s));
+            for (int j = 0; j < VEC / 4; j++)
+                o.w[j] = requant_four_per_channel(byte_of(v.w[j], 0), byte_of(v.w[j], 1), byte_of(v.w[j], 2), byte_of(v.w[j], 3), s4, h4, b4, 0);
         } else {
-            *dst = (int8_t)requant8(*src, s);
+#pragma unroll
+            for (int j = 0; j < VEC / 4; j++)
+                o.w[j] = pack4(requant8(byte_of(v.w[j], 0), s), requant8(byte_of(v.w[j], 1), s), requant8(byte_of(v.w[j], 2), s),
+                               requant8(byte_of(v.w[j], 3), s));
         }
+        *(Piece<VEC> *)(y + px * (size_t)ldy + off + c) = o;
     }
+}
+
+template <int VEC>
+static void launch_concat_vec(ConcatParams &p, int8_t *y, int ldy, size_t pixels, hipStream_t st)
+{
+    bool fast = true;
+    p.pieces[0] = 0;
+    for (int i = 0; i < p.nb; i++) {
+        p.pieces[i + 1] = p.pieces[i] + (p.C[i] + VEC - 1) / VEC;
+        fast = fast && p.s[i] >= 0 && p.s[i] <= 23;
+    }
+    p.div_pieces = make_fastdiv(p.pieces[p.nb]);
+    const int g = grid_for(pixels * (size_t)p.pieces[p.nb]);
+    if (VEC > 1 && fast) concat_kernel<VEC, true><<<g, kBlock, 0, st>>>(p, y, pixels, ldy);
+    else concat_kernel<VEC, false><<<g, kBlock, 0, st>>>(p, y, pixels, ldy);
 }
 
 hipError_t launch_concat(int nb, const int8_t *const *xs, const int *Cs, const int *fs, int8_t *y, int ldy, int fy,
@@ -448,23 +476,19 @@ hipError_t launch_concat(int nb, const int8_t *const *xs, const int *Cs, const i
 {
     ConcatParams p{};
     p.nb = nb;
-    int off = 0;
-    int vec = 16;
-    if (!aligned(y, 16) || ldy % 16) vec = (aligned(y, 4) && ldy % 4 == 0) ? 4 : 1;
+    int off = 0, least = Cs[0];
     for (int i = 0; i < nb; i++) {
         p.x[i] = xs[i];
         p.C[i] = Cs[i];
         p.off[i] = off;
         p.s[i] = fs[i] - fy;
         off += Cs[i];
-        while (vec > 1 && (Cs[i] % vec || !aligned(xs[i], vec))) vec /= 4;
+        least = Cs[i] < least ? Cs[i] : least;
     }
-    for (int i = nb; i <= 8; i++) p.off[i] = off;
-    size_t total = pixels * (size_t)(off / vec);
-    int g = grid_for(total);
-    if (vec == 16) concat_kernel<16><<<g, kBlock, 0, st>>>(p, y, pixels, ldy);
-    else if (vec == 4) concat_kernel<4><<<g, kBlock, 0, st>>>(p, y, pixels, ldy);
-    else concat_kernel<1><<<g, kBlock, 0, st>>>(p, y, pixels, ldy);
+    // a piece lies inside one branch, so the narrowest branch decides
+    if (least >= 16) launch_concat_vec<16>(p, y, ldy, pixels, st);
+    else if (least >= 4) launch_concat_vec<4>(p, y, ldy, pixels, st);
+    else launch_concat_vec<1>(p, y, ldy, pixels, st);
     return hipGetLastError();
 }
 
@@ -493,132 +517,49 @@ __device__ __forceinline__ int avg_round(int sum, int win, int d)
     return (int)t;
 }
 
-template <int VEC>
-__global__ void __launch_bounds__(kBlock) pool_kernel(const int8_t *__restrict__ x, int8_t *__restrict__ y, PoolParams p)
+// Any window over any number of channels: one output element per lane.  Pools of fewer than four channels (and images beyond 2^31 pieces).
+__global__ void __launch_bounds__(kBlock) pool_scalar_kernel(const int8_t *__restrict__ x, int8_t *__restrict__ y, PoolParams p)
 {
-    const int cv = p.C / VEC;
-    const size_t total = (size_t)p.N * p.P * p.Q * cv;
+    const size_t total = (size_t)p.N * p.P * p.Q * p.C;
     for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < total; i += (size_t)gridDim.x * kBlock) {
-        int c = (int)(i % cv) * VEC;
-        size_t px = i / cv;
-        int q = (int)(px % p.Q);
-        size_t t = px / p.Q;
-        int pp = (int)(t % p.P);
-        int n = (int)(t / p.P);
-        int acc[VEC];
-#pragma unroll
-        for (int j = 0; j < VEC; j++) acc[j] = p.mode == 0 ? -1000 : 0;
+        const int c = (int)(i % p.C);
+        const size_t px = i / p.C;
+        const int q = (int)(px % p.Q);
+        const size_t t = px / p.Q;
+        const int pp = (int)(t % p.P);
+        const int n = (int)(t / p.P);
+        int acc = p.mode == 0 ? -1000 : 0;
         for (int r = 0; r < p.k; r++) {
-            int ih = pp * p.stride - p.pad + r;
+            const int ih = pp * p.stride - p.pad + r;
             if (ih < 0 || ih >= p.H) continue;
             for (int s = 0; s < p.k; s++) {
-                int iw = q * p.stride - p.pad + s;
+                const int iw = q * p.stride - p.pad + s;
                 if (iw < 0 || iw >= p.W) continue;
-                const int8_t *src = x + (((size_t)n * p.H + ih) * p.W + iw) * p.C + c;
-                int v[VEC];
-                if (VEC == 16) {
-                    uint4 u = *(const uint4 *)src;
-                    uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-                    for (int j = 0; j < 16; j++) v[j] = byte_of(w[j / 4], j % 4);
-                } else if (VEC == 4) {
-                    uint32_t w = *(const uint32_t *)src;
-#pragma unroll
-                    for (int j = 0; j < 4; j++) v[j] = byte_of(w, j);
-                } else {
-                    v[0] = *src;
-                }
-                if (p.mode == 0) {
-#pragma unroll
-                    for (int j = 0; j < VEC; j++) acc[j] = max(acc[j], v[j]);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < VEC; j++) acc[j] += v[j];
-                }
+                const int v = x[(((size_t)n * p.H + ih) * p.W + iw) * p.C + c];
+                acc = p.mode == 0 ? max(acc, v) : acc + v;
             }
         }
-        int out[VEC];
-#pragma unroll
-        for (int j = 0; j < VEC; j++)
-            out[j] = p.mode == 0 ? requant8(acc[j], -p.d) : avg_round(acc[j], p.k * p.k, p.d);
-        int8_t *dst = y + px * (size_t)p.C + c;
-        if (VEC == 16) {
-            *(uint4 *)dst = make_uint4(pack4(out[0], out[1], out[2], out[3]), pack4(out[4], out[5], out[6], out[7]),
-                                       pack4(out[8], out[9], out[10], out[11]), pack4(out[12], out[13], out[14], out[15]));
-        } else if (VEC == 4) {
-            *(uint32_t *)dst = pack4(out[0], out[1], out[2], out[3]);
-        } else {
-            *dst = (int8_t)out[0];
-        }
+        y[i] = (int8_t)(p.mode == 0 ? requant8(acc, -p.d) : avg_round(acc, p.k * p.k, p.d));
     }
 }
 
-// 3x3 max pooling, 16 channels per lane: window positions in the padding are replaced by the nearest
-// position inside the image, which lies in the same window (pad < k), so the nine 16-byte loads are
-// unconditional and all in flight together; the running maxima are kept as one integer per channel and
-// updated straight from the bytes of the loaded words (sub-dword operand select with sign extension:
-// one instruction per byte and window position, no unpacking).
-struct MaxPool3Params {
+// VEC channels per lane, at any byte address (Piece: the last piece of a pixel overlaps the one before where C is no multiple of VEC).
+// Window positions in the padding are replaced by the nearest one inside the image - for the maximum it lies in the same window
+// (pad < k), for the mean its bytes are dropped - so no load depends on a branch: with K > 0 the K*K loads of a window are all in
+// flight together, with a window size only known at run time (K == 0) four of a row at a time.
+// Bound by memory and issue; 24 x 45 x 61 x 90, 3x3 / 1: 48.9 us with byte accesses, now 10 us.
+struct PoolVecParams {
     PoolParams p;
-    int cv;              // C / 16
-    int total;           // N * P * Q * cv (below 2^31)
-    FastDiv div_cv, div_q, div_p;
+    int pieces;          // of a pixel
+    int total;           // N * P * Q * pieces (below 2^31)
+    FastDiv div_pieces, div_q, div_p;
+    FastDiv div_den;     // mean: the divisor k*k << max(-d, 0)
+    int num_shift;       // mean: max(d, 0)
+    int exact32;         // mean: sum << num_shift and the divisor fit 31 bits
 };
 
-template <int E>
-__device__ __forceinline__ int max_with_byte(int acc, uint32_t w)
-{
-    if constexpr (E == 0) asm("v_max_i32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0" : "=v"(acc) : "v"(acc), "v"(w));
-    else if constexpr (E == 1) asm("v_max_i32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1" : "=v"(acc) : "v"(acc), "v"(w));
-    else if constexpr (E == 2) asm("v_max_i32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2" : "=v"(acc) : "v"(acc), "v"(w));
-    else asm("v_max_i32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3" : "=v"(acc) : "v"(acc), "v"(w));
-    return acc;
-}
+typedef short v2s __attribute__((ext_vector_type(2)));
 
-__global__ void __launch_bounds__(kBlock) maxpool3_kernel(const int8_t *__restrict__ x, int8_t *__restrict__ y, MaxPool3Params prm)
-{
-    const PoolParams &p = prm.p;
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < prm.total; i += gridDim.x * kBlock) {
-        const int px = fastdiv(i, prm.div_cv);
-        const int c = (i - px * prm.cv) * 16;
-        const int t = fastdiv(px, prm.div_q);
-        const int q = px - t * p.Q;
-        const int n = fastdiv(t, prm.div_p);
-        const int pp = t - n * p.P;
-        uint4 u[9];
-#pragma unroll
-        for (int r = 0; r < 3; r++) {
-            const int ih = min(max(pp * p.stride - p.pad + r, 0), p.H - 1);
-#pragma unroll
-            for (int s2 = 0; s2 < 3; s2++) {
-                const int iw = min(max(q * p.stride - p.pad + s2, 0), p.W - 1);
-                u[r * 3 + s2] = *(const uint4 *)(x + (((size_t)n * p.H + ih) * p.W + iw) * p.C + c);
-            }
-        }
-        int acc[16];
-#pragma unroll
-        for (int j = 0; j < 16; j++) acc[j] = -128;
-#pragma unroll
-        for (int k = 0; k < 9; k++) {
-            const uint32_t w[4] = {u[k].x, u[k].y, u[k].z, u[k].w};
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                acc[4 * j + 0] = max_with_byte<0>(acc[4 * j + 0], w[j]);
-                acc[4 * j + 1] = max_with_byte<1>(acc[4 * j + 1], w[j]);
-                acc[4 * j + 2] = max_with_byte<2>(acc[4 * j + 2], w[j]);
-                acc[4 * j + 3] = max_with_byte<3>(acc[4 * j + 3], w[j]);
-            }
-        }
-        int out[16];
-#pragma unroll
-        for (int j = 0; j < 16; j++) out[j] = p.d == 0 ? max(acc[j], -127) : requant8(acc[j], -p.d);
-        *(uint4 *)(y + (size_t)px * p.C + c) = make_uint4(pack4(out[0], out[1], out[2], out[3]), pack4(out[4], out[5], out[6], out[7]),
-                                                         pack4(out[8], out[9], out[10], out[11]), pack4(out[12], out[13], out[14], out[15]));
-    }
-}
-
-// Global average pooling (the window is the whole image, one output pixel): a lane sums 4 channels over
-// all H*W pixels, seven loads in flight at a time, bytes added straight out of the loaded words.
 template <int E>
 __device__ __forceinline__ int add_byte(int acc, uint32_t w)
 {
@@ -629,6 +570,106 @@ __device__ __forceinline__ int add_byte(int acc, uint32_t w)
     return acc;
 }
 
+// The mean of avg_round by one multiplication with the divisor's reciprocal: rounding to nearest, ties to even, is symmetric, so
+// quotient and remainder of the magnitude decide it.
+__device__ __forceinline__ int mean_round(int sum, const PoolVecParams &prm)
+{
+    if (!prm.exact32) return avg_round(sum, prm.p.k * prm.p.k, prm.p.d);
+    const int mag = (sum < 0 ? -sum : sum) << prm.num_shift;
+    int q = fastdiv(mag, prm.div_den);
+    const int rem2 = 2 * (mag - q * prm.div_den.d);
+    q += (rem2 > prm.div_den.d || (rem2 == prm.div_den.d && (q & 1))) ? 1 : 0;
+    q = min(q, 127);
+    return sum < 0 ? -q : q;
+}
+
+template <int VEC, int K, bool MEAN>
+__global__ void __launch_bounds__(kBlock) pool_kernel(const int8_t *__restrict__ x, int8_t *__restrict__ y, PoolVecParams prm)
+{
+    constexpr int W = VEC / 4;                   // words of a piece
+    const PoolParams &p = prm.p;
+    const int k = K > 0 ? K : p.k;
+    for (int i = blockIdx.x * kBlock + threadIdx.x; i < prm.total; i += gridDim.x * kBlock) {
+        const int px = fastdiv(i, prm.div_pieces);
+        const int c = min((i - px * prm.pieces) * VEC, p.C - VEC);
+        const int t = fastdiv(px, prm.div_q);
+        const int q = px - t * p.Q;
+        const int n = fastdiv(t, prm.div_p);
+        const int pp = t - n * p.P;
+        const int8_t *img = x + (size_t)n * p.H * p.W * p.C + c;
+        const int h0 = pp * p.stride - p.pad, w0 = q * p.stride - p.pad;
+        // maximum: odd and even bytes of a word are kept as the high bytes of packed 16-bit numbers (what stands in the low byte never
+        // decides between different high bytes): one shift and two packed maxima per word
+        v2s odd[W], even[W];
+        int sum[VEC];
+#pragma unroll
+        for (int j = 0; j < W; j++) odd[j] = even[j] = v2s{(short)-32768, (short)-32768};
+#pragma unroll
+        for (int j = 0; j < VEC; j++) sum[j] = 0;
+        auto load = [&](int r, int s) {
+            const int ih = min(max(h0 + r, 0), p.H - 1), iw = min(max(w0 + s, 0), p.W - 1);
+            return *(const Piece<VEC> *)(img + (size_t)(ih * p.W + iw) * p.C);
+        };
+        auto take = [&](const Piece<VEC> &u, bool inside) {
+#pragma unroll
+            for (int j = 0; j < W; j++) {
+                uint32_t w = u.w[j];
+                if constexpr (MEAN) {
+                    w = inside ? w : 0u;
+                    sum[4 * j + 0] = add_byte<0>(sum[4 * j + 0], w);
+                    sum[4 * j + 1] = add_byte<1>(sum[4 * j + 1], w);
+                    sum[4 * j + 2] = add_byte<2>(sum[4 * j + 2], w);
+                    sum[4 * j + 3] = add_byte<3>(sum[4 * j + 3], w);
+                } else {
+                    odd[j] = __builtin_elementwise_max(odd[j], __builtin_bit_cast(v2s, w));
+                    even[j] = __builtin_elementwise_max(even[j], __builtin_bit_cast(v2s, w << 8));
+                }
+            }
+        };
+        auto inside = [&](int r, int s) { return (unsigned)(h0 + r) < (unsigned)p.H && (unsigned)(w0 + s) < (unsigned)p.W; };
+        if constexpr (K > 0) {
+            Piece<VEC> u[K * K];
+#pragma unroll
+            for (int r = 0; r < K; r++)
+#pragma unroll
+                for (int s = 0; s < K; s++) u[r * K + s] = load(r, s);
+#pragma unroll
+            for (int r = 0; r < K; r++)
+#pragma unroll
+                for (int s = 0; s < K; s++) take(u[r * K + s], inside(r, s));
+        } else {
+            for (int r = 0; r < k; r++)
+                for (int s = 0; s < k; s += 4) {
+                    Piece<VEC> u[4];
+#pragma unroll
+                    for (int j = 0; j < 4; j++) u[j] = load(r, min(s + j, k - 1));
+#pragma unroll
+                    for (int j = 0; j < 4; j++) take(u[j], s + j < k && inside(r, s + j));
+                }
+        }
+        Piece<VEC> o;
+#pragma unroll
+        for (int j = 0; j < W; j++) {
+            int v[4];
+            if constexpr (MEAN) {
+#pragma unroll
+                for (int e = 0; e < 4; e++) v[e] = mean_round(sum[4 * j + e], prm);
+            } else {
+                v[0] = even[j][0] >> 8;
+                v[1] = odd[j][0] >> 8;
+                v[2] = even[j][1] >> 8;
+                v[3] = odd[j][1] >> 8;
+#pragma unroll
+                for (int e = 0; e < 4; e++) v[e] = p.d == 0 ? max(v[e], -127) : requant8(v[e], -p.d);
+            }
+            o.w[j] = pack4(v[0], v[1], v[2], v[3]);
+        }
+        *(Piece<VEC> *)(y + (size_t)px * p.C + c) = o;
+    }
+}
+
+// Global average pooling (the window is the whole image, one output pixel): a lane sums 4 channels over
+// all H*W pixels, seven loads in flight at a time, bytes added straight out of the loaded words.
 __global__ void __launch_bounds__(kBlock) avgpool_global_kernel(const int8_t *__restrict__ x, int8_t *__restrict__ y, int N, int pixels,
                                                                  int C, int d)
 {
@@ -669,27 +710,46 @@ hipError_t launch_pool(const int8_t *x, int8_t *y, int mode, int N, int H, int W
         avgpool_global_kernel<<<(lanes + kBlock - 1) / kBlock, kBlock, 0, st>>>(x, y, N, H * W, C, fout - fin);
         return hipGetLastError();
     }
-    if (mode == 0 && k == 3 && C % 16 == 0 && aligned(x, 16) && aligned(y, 16) &&
-        (long long)N * P * Q * (C / 16) < (1LL << 31) - 256LL * 16 * kBlock && (long long)N * P * Q * (C / 16) >= 16 * 1024) {
-        MaxPool3Params prm;
-        prm.p = p;
-        prm.cv = C / 16;
-        prm.total = (int)((long long)N * P * Q * prm.cv);
-        prm.div_cv = make_fastdiv(prm.cv);
-        prm.div_q = make_fastdiv(Q);
-        prm.div_p = make_fastdiv(P);
-        maxpool3_kernel<<<grid_for((size_t)prm.total), kBlock, 0, st>>>(x, y, prm);
+    if (C < 4 || (long long)P * Q * ((C + 3) / 4) >= (1LL << 31) - 256LL * 16 * kBlock) {
+        pool_scalar_kernel<<<grid_for((size_t)N * P * Q * C), kBlock, 0, st>>>(x, y, p);
         return hipGetLastError();
     }
-    int vec = 16;
-    while (vec > 1 && (C % vec || !aligned(x, vec) || !aligned(y, vec))) vec /= 4;
+    PoolVecParams prm{};
+    prm.div_q = make_fastdiv(Q);
+    prm.div_p = make_fastdiv(P);
+    const int d = fout - fin;
+    // |sum| <= 128 k^2 <= 2^19
+    prm.exact32 = d <= 11 && d >= -17;
+    prm.num_shift = d > 0 ? d : 0;
+    prm.div_den = make_fastdiv(prm.exact32 && d < 0 ? (k * k) << -d : k * k);
     // few outputs (a global pool): narrower lanes give the machine four times the wavefronts
-    if (vec == 16 && (size_t)N * P * Q * (C / 16) < (size_t)256 * 1024) vec = 4;
-    size_t total = (size_t)N * P * Q * (C / vec);
-    int g = grid_for(total);
-    if (vec == 16) pool_kernel<16><<<g, kBlock, 0, st>>>(x, y, p);
-    else if (vec == 4) pool_kernel<4><<<g, kBlock, 0, st>>>(x, y, p);
-    else pool_kernel<1><<<g, kBlock, 0, st>>>(x, y, p);
+    const bool wide = C >= 16 && (size_t)N * P * Q * (C / 16) >= (size_t)64 * 1024;
+    const int vec = wide ? 16 : 4;
+    prm.pieces = (C + vec - 1) / vec;
+    prm.div_pieces = make_fastdiv(prm.pieces);
+    // as many images per launch as 31-bit piece numbers reach
+    const long long per_image = (long long)P * Q * prm.pieces;
+    long long most = ((1LL << 31) - 256LL * 16 * kBlock - 1) / per_image;
+    for (long long n = 0; n < N; n += most) {
+        prm.p = p;
+        prm.p.N = (int)(N - n < most ? N - n : most);
+        prm.total = (int)(prm.p.N * per_image);
+        const int8_t *xs = x + (size_t)n * H * W * C;
+        int8_t *ys = y + (size_t)n * P * Q * C;
+        const int g = grid_for((size_t)prm.total);
+#define DFQ_POOL(V, KK) \
+    do { \
+        if (mode == 1) pool_kernel<V, KK, true><<<g, kBlock, 0, st>>>(xs, ys, prm); \
+        else pool_kernel<V, KK, false><<<g, kBlock, 0, st>>>(xs, ys, prm); \
+    } while (0)
+        if (wide && k == 2) DFQ_POOL(16, 2);
+        else if (wide && k == 3) DFQ_POOL(16, 3);
+        else if (wide) DFQ_POOL(16, 0);
+        else if (k == 2) DFQ_POOL(4, 2);
+        else if (k == 3) DFQ_POOL(4, 3);
+        else DFQ_POOL(4, 0);
+#undef DFQ_POOL
+    }
     return hipGetLastError();
 }
 

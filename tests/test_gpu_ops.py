@@ -841,3 +841,42 @@ def test_formats_from_a_row_of_thresholds(B):
     for bad in (np.nan, np.inf, -1.0):
         with pytest.raises(B.DfqError):
             B.fmt_from_absmax_f32_rows(np.array([1.0, bad], np.float32))
+
+
+@pytest.mark.parametrize("C", [3, 4, 5, 15, 16, 17, 31, 33, 90, 130])
+@pytest.mark.parametrize("mode", ["max", "avg"])
+def test_pool_q_any_channels_and_alignment(B, mode, C):
+    """Pieces that overlap at the end of a pixel, windows of every kind at every border, tensors at odd addresses."""
+    rng = np.random.default_rng(C)
+    for (N, H, W), (k, st, pad) in [((2, 9, 7), (3, 1, 1)), ((1, 8, 11), (2, 2, 1)), ((3, 6, 6), (5, 2, 2)), ((1, 13, 9), (4, 3, 3)),
+                                    ((1, 5, 40), (5, 5, 0)), ((2, 3, 3), (7, 1, 3)), ((1, 1, 1), (3, 2, 1)), ((40, 45, 41), (3, 2, 1))]:
+        if N == 40 and C not in (17, 90):
+            continue
+        x = rng.integers(-128, 128, (N, H, W, C)).astype(np.int8)
+        x[0, 0] = -128                              # all-negative windows: padding must not win
+        for f_in, f_out in [(4, 4), (4, 2), (3, 5), (0, 16), (20, 0)]:
+            ref = orc.pool_q(x, mode, k, st, pad, f_in, f_out)
+            buf = torch.empty(x.size + 8, dtype=torch.int8, device=DEV)
+            xd = buf[3:3 + x.size].view(x.shape)
+            xd.copy_(dev(x))
+            out = torch.full((ref.size + 9,), 99, dtype=torch.int8, device=DEV)
+            B.pool_q(xd, mode, k, st, pad, f_in, f_out, out=out[5:5 + ref.size].view(ref.shape))
+            got = host(out)
+            assert np.array_equal(got[5:5 + ref.size].reshape(ref.shape), ref), (N, H, W, C, k, st, pad, f_in, f_out)
+            assert (got[:5] == 99).all() and (got[5 + ref.size:] == 99).all()
+
+
+def test_concat_q_any_channels(B):
+    rng = np.random.default_rng(7)
+    for Cs in [(1, 2, 3), (4, 5), (16,), (17, 16, 33), (90, 90, 90), (15, 64), (100, 4, 7, 18, 16, 31, 5, 6)]:
+        for pixels in [(1, 1), (5, 37)]:
+            xs = [rng.integers(-128, 128, pixels + (c,)).astype(np.int8) for c in Cs]
+            for f_y, fs in [(2, [2 + i % 3 for i in range(len(Cs))]), (4, [4 - i for i in range(len(Cs))]), (0, [25 * (i % 2) for i in range(len(Cs))])]:
+                ref = orc.concat_q(xs, fs, f_y)
+                ct = sum(Cs)
+                wide = torch.full((pixels[0], pixels[1], ct + 5), 55, dtype=torch.int8, device=DEV)
+                B.concat_q_into([dev(x) for x in xs], fs, f_y, wide, 3)
+                got = host(wide)
+                assert np.array_equal(got[..., 3:3 + ct], ref), (Cs, fs)
+                assert (got[..., :3] == 55).all() and (got[..., 3 + ct:] == 55).all()
+                assert np.array_equal(host(B.concat_q([dev(x) for x in xs], fs, f_y)), ref)
