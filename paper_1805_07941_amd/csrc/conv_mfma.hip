@@ -606,7 +606,7 @@ bool conv_mfma_fuses(const ConvArgs &a)
     if (s_lo < 0 || s_hi > 23 || a.acc_out || !a.y || (a.ldy & 15) || ((uintptr_t)a.y & 15)) return false;
     const long long M = (long long)a.N * a.P * a.Q;
     if (M * a.ldy >= (1LL << 31) || M * a.ldadd >= (1LL << 31)) return false;
-    if (a.frac_w && M <= 1024) return false;      // the tile shape for very few pixels has no per-channel lean form
+    if (a.frac_w && M <= 1024) return false;      // two calls: the convolution's own int8 tensor and the add
     if (((uintptr_t)a.add & 15) || (a.ldadd & 15) || a.ldadd < a.K) return false;
     if (!(a.add_shift >= 0 && a.add_shift <= 23) || a.add_sa < 0 || a.add_sa > 22 || a.add_sb < 0 || a.add_sb > 22) return false;
     if (a.add_lazy && a.frac_w) return false;
@@ -627,13 +627,8 @@ hipError_t launch_conv_mfma(const ConvArgs &a, hipStream_t st)
     // else:    256 x 128 tiles (eight wavefronts), two workgroups per CU, for kernels larger than 1x1 with enough of them;
     //          for 1x1 kernels (few items per tile) 128 x 128 tiles (four wavefronts), three per CU.
     const bool pointwise = a.R == 1 && a.S == 1;
-    // very few pixels (fully connected layers): one wavefront per 32 x 32 tile, each with its own deep ring and no
-    // barrier, where that kernel applies (unpadded 1x1, whole 64-byte steps); else 64 x 64 tiles, wavefronts of 32 x 32,
-    // so that the channel tiles alone spread over more compute units, with a ring six stages deep
-    if ((long long)a.N * a.P * a.Q <= 1024 && a.K > 64) {
-        if (conv_fc_supports(a)) return launch_conv_fc(a, st);
-        return launch_cfg<64, 64, 2, 2, 6, 2>(a, st);
-    }
+    // very few pixels (fully connected layers), also where the dense kernel is asked for by name
+    if ((long long)a.N * a.P * a.Q <= 1024 && a.K > 64 && conv_sk_pays(a)) return launch_conv_sk(a, st);
     // one weight format per output channel: the tile shapes for which that epilogue is built
     if (a.frac_w && a.K > 64) return launch_cfg<128, 128, 2, 2, 3, 3>(a, st);
     if (a.K <= 64) return pointwise ? launch_cfg<256, 64, 4, 1, 3, 2>(a, st) : launch_cfg<256, 64, 4, 1, 2, 3>(a, st);

@@ -90,7 +90,10 @@ dfq_conv_variant select_variant(const ConvArgs &a, bool geometry_only = false)
 
 dfq_status run_conv(dfq_conv_variant variant, const ConvArgs &a, hipStream_t st)
 {
-    if (variant == DFQ_CONV_AUTO) variant = select_variant(a);
+    if (variant == DFQ_CONV_AUTO) {
+        if (conv_sk_pays(a)) return from_hip(launch_conv_sk(a, st));
+        variant = select_variant(a);
+    }
     switch (variant) {
         case DFQ_CONV_DIRECT:
             return from_hip(launch_conv_direct(a, st));
@@ -118,6 +121,15 @@ dfq_status run_conv(dfq_conv_variant variant, const ConvArgs &a, hipStream_t st)
     }
 }
 
+// a.add set: the calls that the input-resident or the dense kernel can fuse, by whichever kernel is fastest for the size
+dfq_status run_fused_add(const ConvArgs &a, hipStream_t st)
+{
+    const bool pw = conv_pw_supports(a);
+    if (!pw && !conv_mfma_fuses(a)) return DFQ_EUNSUPPORTED;
+    if (conv_sk_pays(a)) return from_hip(launch_conv_sk(a, st));
+    return from_hip(pw ? launch_conv_pw(a, st) : launch_conv_mfma(a, st));
+}
+
 // the part of the fused convolution + add calls behind the convolution's own checks
 dfq_status run_conv_add(ConvCheck &c, const int8_t *x, const int8_t *other, int8_t *y, int N, int H, int W, int C, int K,
                         int ldy, int ld_other, dfq_fmt fmt_mid, dfq_fmt fmt_other, dfq_fmt fmt_out, int relu_out,
@@ -141,9 +153,7 @@ dfq_status run_conv_add(ConvCheck &c, const int8_t *x, const int8_t *other, int8
     c.a.add_sb = F - fmt_other.frac;
     c.a.add_shift = F - fmt_out.frac;
     c.a.add_relu = relu_out ? 1 : 0;
-    if (conv_pw_supports(c.a)) return from_hip(launch_conv_pw(c.a, (hipStream_t)stream));
-    if (conv_mfma_fuses(c.a)) return from_hip(launch_conv_mfma(c.a, (hipStream_t)stream));
-    return DFQ_EUNSUPPORTED;
+    return run_fused_add(c.a, (hipStream_t)stream);
 }
 
 }  // namespace
@@ -565,9 +575,7 @@ dfq_status dfq_conv_q_add_lazy(const int8_t *x, const int8_t *w, const int32_t *
     c.a.add_shift = c.a.shift;                    // f_in + f_w - f_out
     c.a.add_relu = relu_out ? 1 : 0;
     c.a.add_lazy = 1;
-    if (conv_pw_supports(c.a)) return from_hip(launch_conv_pw(c.a, (hipStream_t)stream));
-    if (conv_mfma_fuses(c.a)) return from_hip(launch_conv_mfma(c.a, (hipStream_t)stream));
-    return DFQ_EUNSUPPORTED;
+    return run_fused_add(c.a, (hipStream_t)stream);
 }
 
 dfq_status dfq_conv_q_pc_add(const int8_t *x, const int8_t *w, const int32_t *b, const int8_t *other, int8_t *y, int N,
