@@ -268,27 +268,7 @@ __device__ __forceinline__ void store_tile_lane_ragged(const v16i &v, const Conv
     store_bytes(o, a.y + (size_t)m * a.ldy + kc, count);
 }
 
-// One weight format per output channel with the lane's 16 shifts already in registers: whole 16-channel
-// group, aligned row, no accumulator dump - one 16-byte store, no loads.
-__device__ __forceinline__ void store_tile_lane_per_channel(const v16i &v, const ConvArgs &a, const int (&shifts)[16], int relu,
-                                                            long long m, int kc)
-{
-    uint32_t o[4];
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-        int q[4];
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-            ChannelRequant cr;
-            cr.init(shifts[4 * j + e]);
-            q[e] = cr.apply(v[4 * j + e], relu);
-        }
-        o[j] = pack4_clamped(q[0], q[1], q[2], q[3]);
-    }
-    *(uint4 *)(a.y + (size_t)m * a.ldy + kc) = make_uint4(o[0], o[1], o[2], o[3]);
-}
-
-// the conditions of store_tile_lane_per_channel for a block whose channel range ends at k_end
+// one weight format per output channel, whole 16-channel groups in aligned rows, for a block whose channel range ends at k_end
 __device__ __forceinline__ bool epilogue_is_per_channel_packed(const ConvArgs &a, int k_end)
 {
     return a.frac_w && !a.acc_out && a.y && ((a.ldy & 15) == 0) && (((uintptr_t)a.y & 15) == 0) && k_end <= a.K;

@@ -41,6 +41,40 @@ struct SmallCParams {
     FastDiv div_pq, div_q;
 };
 
+// Packed weights into LDS: block (r, k) = w[k][r][0 .. run) then zeros, as two 16-byte pieces.  One piece per thread and round,
+// read at whatever address the run has: a byte per thread and round took 56 dependent trips to memory for a 7x7 layer of 64
+// channels (one image of 201 x 201: 14.2 -> 9.3 us).
+template <int BC>
+__device__ __forceinline__ void pack_weights(const SmallCParams &prm, int8_t *wb, int k0)
+{
+    const ConvArgs &a = prm.a;
+    const long long total = (long long)a.K * a.R * prm.run;           // bytes of w
+    for (int i = threadIdx.x; i < a.R * BC * 2; i += kThreads) {
+        const int h = i & 1, kl = (i >> 1) % BC, r = (i >> 1) / BC, k = k0 + kl;
+        const long long o = ((long long)k * a.R + r) * prm.run + 16 * h;
+        const int count = k < a.K ? min(16, prm.run - 16 * h) : 0;     // bytes of the piece that are weights, may be <= 0
+        Bytes16 v = {{0, 0, 0, 0}};
+        if (count > 0 && o + 16 <= total) {
+            v = *(const Bytes16 *)(a.w + o);
+#pragma unroll
+            for (int d = 0; d < 4; d++) {
+                const int n = min(max(count - 4 * d, 0), 4);           // bytes of this word to keep
+                v.w[d] = n == 4 ? v.w[d] : v.w[d] & ((1u << (8 * n)) - 1u);
+            }
+        } else if (count > 0) {                                        // the last bytes of the tensor
+#pragma unroll
+            for (int e = 0; e < 16; e++)
+                if (e < count) v.w[e >> 2] |= (uint32_t)(uint8_t)a.w[o + e] << (8 * (e & 3));
+        }
+        // LDS row of channel kl follows the same permutation as the dense kernel: a lane's 16 accumulators are 16
+        // consecutive channels
+        const int c32 = kl & 31;
+        const int row = (kl & ~31) + 8 * ((c32 & 15) >> 2) + 4 * (c32 >> 4) + (c32 & 3);
+        const int piece = h ^ ((row >> 3) & 1);
+        *(uint4 *)(wb + ((r * BC + row) * 2 + piece) * 16) = make_uint4(v.w[0], v.w[1], v.w[2], v.w[3]);
+    }
+}
+
 template <int CT>   // channel tile = CT * 32
 __global__ void __launch_bounds__(kThreads, 2) conv_smallc_kernel(SmallCParams prm)
 {
@@ -52,36 +86,23 @@ __global__ void __launch_bounds__(kThreads, 2) conv_smallc_kernel(SmallCParams p
     const int l32 = lane & 31, lh = lane >> 5;
     const int k0 = blockIdx.y * BC;
 
-    // ---- packed weights into LDS: block (r, k) = w[k][r][0 .. run) then zeros
-    {
-        int8_t *wb = (int8_t *)wlds;
-        const int total = a.R * BC * 32;
-        for (int i = tid; i < total; i += kThreads) {
-            int j = i & 31;
-            int kl = (i >> 5) % BC;
-            int r = (i >> 5) / BC;
-            int k = k0 + kl;
-            int8_t v = 0;
-            if (j < prm.run && k < a.K) v = a.w[((size_t)k * a.R + r) * prm.run + j];
-            // LDS row of channel kl follows the same permutation as the dense kernel: a lane's
-            // 16 accumulators are 16 consecutive channels
-            int c32 = kl & 31;
-            int row = (kl & ~31) + 8 * ((c32 & 15) >> 2) + 4 * (c32 >> 4) + (c32 & 3);
-            int piece = (j >> 4) ^ ((row >> 3) & 1);
-            wb[((r * BC + row) * 2 + piece) * 16 + (j & 15)] = v;
-        }
-    }
+    pack_weights<BC>(prm, (int8_t *)wlds, k0);
     __syncthreads();
 
     Requant rq;
     rq.init(a.shift, a.relu);
     const bool fast = epilogue_is_fast(a, rq, k0 + BC);
-    // one weight format per output channel: a lane's channels are the same for every tile, so their
-    // shifts are read once
-    const bool pc_packed = epilogue_is_per_channel_packed(a, k0 + BC);
-    __shared__ int pc_shift[CT * 32];
+    // one weight format per output channel, declared shifts in the lean range: their constants from tables (7x7, 64 channels, 256
+    // images of 224 x 224: 200 -> 123 us; deriving them per output took as long as the products)
+    const bool pc_packed = epilogue_is_per_channel_packed(a, k0 + BC) && a.shift + a.frac_w_lo >= 0 && a.shift + a.frac_w_hi <= 23;
+    __shared__ __attribute__((aligned(16))) int pc_shift[BC], pc_hi[BC], pc_badd[BC];
     if (pc_packed) {
-        for (int i = threadIdx.x; i < CT * 32; i += blockDim.x) pc_shift[i] = a.shift + a.frac_w[k0 + i];
+        for (int i = threadIdx.x; i < BC; i += blockDim.x) {
+            const int s = (a.shift + a.frac_w[k0 + i]) & 31;
+            pc_shift[i] = s;
+            pc_hi[i] = 127 << min(s, 23);
+            pc_badd[i] = s > 0 ? (1 << (s - 1)) - 1 : 0;
+        }
         __syncthreads();
     }
     const v4i *wl = (const v4i *)wlds;
@@ -163,13 +184,15 @@ __global__ void __launch_bounds__(kThreads, 2) conv_smallc_kernel(SmallCParams p
                 if (m < prm.M) {
                     if (fast) store_tile_lane_fast(acc[c][p], a, rq, m, kc);
                     else if (pc_packed) {
-                        int sh[16];
+                        uint32_t o[4];
 #pragma unroll
                         for (int r4 = 0; r4 < 4; r4++) {
-                            const int4 t = *(const int4 *)(pc_shift + c * 32 + 16 * lh + 4 * r4);
-                            sh[4 * r4] = t.x; sh[4 * r4 + 1] = t.y; sh[4 * r4 + 2] = t.z; sh[4 * r4 + 3] = t.w;
+                            const int kr = c * 32 + 16 * lh + 4 * r4;
+                            o[r4] = requant_four_per_channel(acc[c][p][4 * r4], acc[c][p][4 * r4 + 1], acc[c][p][4 * r4 + 2], acc[c][p][4 * r4 + 3],
+                                                             *(const int4 *)(pc_shift + kr), *(const int4 *)(pc_hi + kr),
+                                                             *(const int4 *)(pc_badd + kr), a.relu);
                         }
-                        store_tile_lane_per_channel(acc[c][p], a, sh, a.relu, m, kc);
+                        *(uint4 *)(a.y + (size_t)m * a.ldy + kc) = make_uint4(o[0], o[1], o[2], o[3]);
                     }
                     else if (kc < a.K) store_tile_lane_general(acc[c][p], a, a.shift, a.relu, m, kc);
                 }
@@ -206,33 +229,23 @@ __global__ void __launch_bounds__(kThreads, 2) conv_smallc_rows_kernel(SmallCRow
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, lh = lane >> 5;
     const int k0 = blockIdx.y * BC;
-    {
-        int8_t *wb = (int8_t *)wlds;
-        const int total = a.R * BC * 32;
-        for (int i = tid; i < total; i += kThreads) {
-            int j = i & 31;
-            int kl = (i >> 5) % BC;
-            int r = (i >> 5) / BC;
-            int k = k0 + kl;
-            int8_t v = 0;
-            if (j < prm.run && k < a.K) v = a.w[((size_t)k * a.R + r) * prm.run + j];
-            int c32 = kl & 31;
-            int row = (kl & ~31) + 8 * ((c32 & 15) >> 2) + 4 * (c32 >> 4) + (c32 & 3);
-            int piece = (j >> 4) ^ ((row >> 3) & 1);
-            wb[((r * BC + row) * 2 + piece) * 16 + (j & 15)] = v;
-        }
-    }
+    pack_weights<BC>(prm, (int8_t *)wlds, k0);
     __syncthreads();
 
     Requant rq;
     rq.init(a.shift, a.relu);
     const bool fast = epilogue_is_fast(a, rq, k0 + BC);
-    // one weight format per output channel: a lane's channels are the same for every tile, so their
-    // shifts are read once
-    const bool pc_packed = epilogue_is_per_channel_packed(a, k0 + BC);
-    __shared__ int pc_shift[CT * 32];
+    // one weight format per output channel, declared shifts in the lean range: their constants from tables (7x7, 64 channels, 256
+    // images of 224 x 224: 200 -> 123 us; deriving them per output took as long as the products)
+    const bool pc_packed = epilogue_is_per_channel_packed(a, k0 + BC) && a.shift + a.frac_w_lo >= 0 && a.shift + a.frac_w_hi <= 23;
+    __shared__ __attribute__((aligned(16))) int pc_shift[BC], pc_hi[BC], pc_badd[BC];
     if (pc_packed) {
-        for (int i = threadIdx.x; i < CT * 32; i += blockDim.x) pc_shift[i] = a.shift + a.frac_w[k0 + i];
+        for (int i = threadIdx.x; i < BC; i += blockDim.x) {
+            const int s = (a.shift + a.frac_w[k0 + i]) & 31;
+            pc_shift[i] = s;
+            pc_hi[i] = 127 << min(s, 23);
+            pc_badd[i] = s > 0 ? (1 << (s - 1)) - 1 : 0;
+        }
         __syncthreads();
     }
     const v4i *wl = (const v4i *)wlds;
@@ -375,13 +388,15 @@ __global__ void __launch_bounds__(kThreads, 2) conv_smallc_rows_kernel(SmallCRow
                 if (m < prm.M) {
                     if (fast) store_tile_lane_fast(acc[c][p], a, rq, m, kc);
                     else if (pc_packed) {
-                        int sh[16];
+                        uint32_t o[4];
 #pragma unroll
                         for (int r4 = 0; r4 < 4; r4++) {
-                            const int4 t = *(const int4 *)(pc_shift + c * 32 + 16 * lh + 4 * r4);
-                            sh[4 * r4] = t.x; sh[4 * r4 + 1] = t.y; sh[4 * r4 + 2] = t.z; sh[4 * r4 + 3] = t.w;
+                            const int kr = c * 32 + 16 * lh + 4 * r4;
+                            o[r4] = requant_four_per_channel(acc[c][p][4 * r4], acc[c][p][4 * r4 + 1], acc[c][p][4 * r4 + 2], acc[c][p][4 * r4 + 3],
+                                                             *(const int4 *)(pc_shift + kr), *(const int4 *)(pc_hi + kr),
+                                                             *(const int4 *)(pc_badd + kr), a.relu);
                         }
-                        store_tile_lane_per_channel(acc[c][p], a, sh, a.relu, m, kc);
+                        *(uint4 *)(a.y + (size_t)m * a.ldy + kc) = make_uint4(o[0], o[1], o[2], o[3]);
                     }
                     else if (kc < a.K) store_tile_lane_general(acc[c][p], a, a.shift, a.relu, m, kc);
                 }

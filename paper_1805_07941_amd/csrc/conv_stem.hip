@@ -68,21 +68,38 @@ __device__ __forceinline__ void stem_setup(const ConvArgs &a, int8_t *lds, int *
 {
     const int tid = threadIdx.x;
     const int odd = a.pad & 1;
-    // one dword (input pixel i of the run of kernel row r, channel k) per iteration
-    for (int t = tid; t < R * BC * 8; t += THREADS) {
-        const int i = t & 7;
-        const int kl = (t >> 3) % BC;
-        const int r = (t >> 3) / BC;
-        const int s = i - odd;
-        uint32_t v = 0;
-        if (s >= 0 && s < a.S && kl < a.K) {
-            const uint8_t *src = (const uint8_t *)a.w + (((size_t)kl * R + r) * a.S + s) * 3;
-            v = (uint32_t)src[0] | ((uint32_t)src[1] << 8) | ((uint32_t)src[2] << 16);
+    // One block per thread and round, its S*3 bytes read at whatever address they have.  (A byte gather, one pixel per thread
+    // and round, took 14 dependent trips to memory for a 7x7 layer of 64 channels.)
+    const int total = a.K * R * a.S * 3;
+    for (int t = tid; t < R * BC; t += THREADS) {
+        const int kl = t % BC, r = t / BC;
+        const int o = (kl * R + r) * a.S * 3;
+        uint32_t d[7] = {0, 0, 0, 0, 0, 0, 0};
+        if (kl < a.K && o + 24 <= total) {
+            const Bytes16 lo = *(const Bytes16 *)(a.w + o);
+            uint2 hi;
+            __builtin_memcpy(&hi, a.w + o + 16, 8);
+#pragma unroll
+            for (int e = 0; e < 4; e++) d[e] = lo.w[e];
+            d[4] = hi.x;
+            d[5] = hi.y;
+        } else if (kl < a.K) {                                  // the last bytes of the tensor
+#pragma unroll
+            for (int e = 0; e < 24; e++)
+                if (e < a.S * 3) d[e >> 2] |= (uint32_t)(uint8_t)a.w[o + e] << (8 * (e & 3));
+        }
+        uint32_t tap[8];                                        // the three weights of tap s, zeros past the last tap
+#pragma unroll
+        for (int s = 0; s < 8; s++) {
+            const uint32_t v = __builtin_amdgcn_alignbit(d[3 * s / 4 + 1], d[3 * s / 4], 8 * (3 * s % 4)) & 0xffffffu;
+            tap[s] = s < a.S ? v : 0;
         }
         const int c32 = kl & 31;
         const int row = (kl & ~31) + 8 * ((c32 & 15) >> 2) + 4 * (c32 >> 4) + (c32 & 3);
-        const int piece = (i >> 2) ^ ((row >> 3) & 1);
-        *(uint32_t *)(lds + ((r * BC + row) * 2 + piece) * 16 + 4 * (i & 3)) = v;
+        uint4 *dst = (uint4 *)(lds + (r * BC + row) * 32);
+        const int swap = (row >> 3) & 1;
+        dst[swap] = odd ? make_uint4(0, tap[0], tap[1], tap[2]) : make_uint4(tap[0], tap[1], tap[2], tap[3]);
+        dst[swap ^ 1] = odd ? make_uint4(tap[3], tap[4], tap[5], tap[6]) : make_uint4(tap[4], tap[5], tap[6], tap[7]);
     }
     for (int i = tid; i < BC; i += THREADS) biasl[i] = (a.b && i < a.K) ? a.b[i] : 0;
     for (int i = tid; i < ring_bytes / 8; i += THREADS) ((uint2 *)xin)[i] = make_uint2(0, 0);
@@ -202,13 +219,6 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4,
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, lh = lane >> 5;
 
-    stem_setup<BC, R, kThreads>(a, lds, biasl, xin, kRowSlots * prm.pitch);
-    __syncthreads();
-
-    Requant rq;
-    rq.init(a.shift, a.relu);
-    const v4i *const wl = (const v4i *)lds;
-
     const int n = blockIdx.x / prm.strips;
     const int strip = blockIdx.x - n * prm.strips;
     const int t0 = strip * prm.steps_per_strip;
@@ -221,11 +231,19 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4,
         else stem_stage_rows<NW, MAXR, false>(xin, prm.pitch, prm.triples, wave, lane, first, count, rows);
     };
 
-    Rows pf[MAXR];
+    // the first step's input rows, the weights and the bias are on their way together
+    Rows pf[MAXR], pf_tail[MAXR];
     stem_fetch_rows<NW, MAXR>(a, ximg, prm.triples, wave, lane, 8 * t0 - a.pad, 8, pf);
+    stem_fetch_rows<NW, MAXR>(a, ximg, prm.triples, wave, lane, 8 * t0 - a.pad + 8, kRowsFirst - 8, pf_tail);
+    stem_setup<BC, R, kThreads>(a, lds, biasl, xin, kRowSlots * prm.pitch);
+    __syncthreads();
+
+    Requant rq;
+    rq.init(a.shift, a.relu);
+    const v4i *const wl = (const v4i *)lds;
+
     stage(8 * t0 - a.pad, 8, pf);
-    stem_fetch_rows<NW, MAXR>(a, ximg, prm.triples, wave, lane, 8 * t0 - a.pad + 8, kRowsFirst - 8, pf);
-    stage(8 * t0 - a.pad + 8, kRowsFirst - 8, pf);
+    stage(8 * t0 - a.pad + 8, kRowsFirst - 8, pf_tail);
     __syncthreads();
 
     const int ncb = a.Q >> 4;
@@ -318,21 +336,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, lh = lane >> 5;
 
-    stem_setup<BC, R, kThreads>(a, lds, biasl, xin, kRowSlots * prm.pitch + 16);
-    if constexpr (PC) {
-        for (int i = tid; i < BC; i += kThreads) {
-            const int sh = a.shift + a.frac_w[i];
-            pc_shift[i] = sh;
-            pc_hi[i] = 127 << sh;
-            pc_badd[i] = sh > 0 ? (1 << (sh - 1)) - 1 : 0;
-        }
-    }
-    __syncthreads();
-
-    Requant rq;
-    rq.init(a.shift, a.relu);
-    const v4i *const wl = (const v4i *)lds;
-
     const int n = blockIdx.x / prm.strips;
     const int strip = blockIdx.x - n * prm.strips;
     const int t_emit = strip * prm.steps_per_strip;                 // first step whose pooled rows this strip stores
@@ -360,11 +363,27 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
         for (int i = 0; i < 16; i++) above[c][i] = kIntMin;
 
-    Rows pf[MAXR];
+    // the first step's input rows, the weights and the bias are on their way together
+    Rows pf[MAXR], pf_tail[MAXR];
     stem_fetch_rows<NW, MAXR>(a, ximg, prm.triples, wave, lane, 8 * t0 - a.pad, 8, pf);
+    stem_fetch_rows<NW, MAXR>(a, ximg, prm.triples, wave, lane, 8 * t0 - a.pad + 8, kRowsFirst - 8, pf_tail);
+    stem_setup<BC, R, kThreads>(a, lds, biasl, xin, kRowSlots * prm.pitch + 16);
+    if constexpr (PC) {
+        for (int i = tid; i < BC; i += kThreads) {
+            const int sh = a.shift + a.frac_w[i];
+            pc_shift[i] = sh;
+            pc_hi[i] = 127 << sh;
+            pc_badd[i] = sh > 0 ? (1 << (sh - 1)) - 1 : 0;
+        }
+    }
+    __syncthreads();
+
+    Requant rq;
+    rq.init(a.shift, a.relu);
+    const v4i *const wl = (const v4i *)lds;
+
     stage(8 * t0 - a.pad, 8, pf);
-    stem_fetch_rows<NW, MAXR>(a, ximg, prm.triples, wave, lane, 8 * t0 - a.pad + 8, kRowsFirst - 8, pf);
-    stage(8 * t0 - a.pad + 8, kRowsFirst - 8, pf);
+    stage(8 * t0 - a.pad + 8, kRowsFirst - 8, pf_tail);
     __syncthreads();
 
     for (int t = t0; t < t1; t++) {
@@ -560,9 +579,12 @@ hipError_t launch_conv_stem(const ConvArgs &a, int8_t *yp, int ldyp, hipStream_t
     prm.off0 = kLeftPad - 4 * (a.pad + (a.pad & 1));
     prm.steps = (a.P + 3) / 4;
     prm.triples = a.W / 4;
-    // enough workgroups for two per compute unit, strips of at least four steps
-    int strips = max(1, (2 * kNumCU + a.N - 1) / a.N);
-    strips = min(strips, max(1, prm.steps / 4));
+    // two workgroups per compute unit; for few images down to strips of one step (one more is recomputed in the pooling form):
+    // what a workgroup walks is a chain, and the chip is idle beside it (one image of 224 x 224, strips of four steps and of
+    // one: the pooling form 20.2 and 11.1 us, the plain one for
+    // 32 channels 8.5 and 5.1; 16 images 21.3 and 14.4)
+    int strips = max(1, 2 * kNumCU / a.N);
+    strips = min(strips, prm.steps);
     prm.steps_per_strip = (prm.steps + strips - 1) / strips;
     prm.strips = (prm.steps + prm.steps_per_strip - 1) / prm.steps_per_strip;
     const size_t lds = stem_lds_bytes(a, pool);

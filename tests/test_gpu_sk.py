@@ -87,3 +87,24 @@ def test_fused_add_by_size(B, shape):
         ref, _ = orc.eltwise_q(mid, f_mid, other, f_other, f_out, relu_out)
         got = B.conv_q_pc_add(xd, wd, bd, od, f_in, dev(f_wk), (f_w - 2, f_w + 1), f_mid, relu_mid, f_other, f_out, relu_out)
         assert got is None or np.array_equal(host(got), ref)
+
+
+@pytest.mark.parametrize("shape", [(1, 64, 64, 3, 64, 7, 7, 2, 3), (3, 36, 64, 3, 32, 3, 3, 2, 1), (2, 44, 96, 3, 64, 3, 3, 2, 0), (1, 33, 37, 3, 50, 7, 7, 2, 3),
+                                   (2, 20, 31, 1, 7, 5, 5, 1, 2), (1, 40, 33, 2, 100, 3, 16, 1, 1), (1, 12, 33, 3, 3, 1, 1, 1, 0)], ids=lambda s: "x".join(map(str, s)))
+def test_first_layer_weights(B, shape):
+    """First layers: weight runs of every length, the last run of the tensor, strips of one step, channels with shifts inside and
+    outside the lean range."""
+    N, H, W, C, K, R, S, st, pad = shape
+    rng = np.random.default_rng(sum(shape))
+    x, w = rng.integers(-128, 128, (N, H, W, C)).astype(np.int8), rng.integers(-128, 128, (K, R, S, C)).astype(np.int8)
+    b = rng.integers(-2 ** 12, 2 ** 12, (K,)).astype(np.int32)
+    # the weights end where an allocation ends: nothing may be read past them
+    wd = torch.empty(w.nbytes, dtype=torch.int8, device="cuda").view(w.shape)
+    wd.copy_(dev(w))
+    for relu in (False, True):
+        y_ref, _ = orc.conv_q(x, w, b, 4, 8, 4, st, pad, 1, relu)
+        assert np.array_equal(host(B.conv_q(dev(x), wd, dev(b), 4, 8, 4, st, pad, 1, relu)[0]), y_ref)
+        for lo, hi in ((5, 10), (-3, 28)):
+            f_w = rng.integers(lo, hi + 1, K).astype(np.int32)
+            y_ref, _ = orc.conv_q(x, w, b, 4, f_w, 4, st, pad, 1, relu)
+            assert np.array_equal(host(B.conv_q_pc(dev(x), wd, dev(b), 4, dev(f_w), 4, st, pad, 1, relu, frac_w_range=(lo, hi))[0]), y_ref)
