@@ -43,7 +43,7 @@ struct SmallCParams {
 
 // Packed weights into LDS: block (r, k) = w[k][r][0 .. run) then zeros, as two 16-byte pieces.  One piece per thread and round,
 // read at whatever address the run has: a byte per thread and round took 56 dependent trips to memory for a 7x7 layer of 64
-// channels (one image of 201 x 201: 14.2 -> 9.3 us).
+// channels (one image of 201 x 201: 14.2 -> 9.5 us).
 template <int BC>
 __device__ __forceinline__ void pack_weights(const SmallCParams &prm, int8_t *wb, int k0)
 {
@@ -51,27 +51,25 @@ __device__ __forceinline__ void pack_weights(const SmallCParams &prm, int8_t *wb
     const long long total = (long long)a.K * a.R * prm.run;           // bytes of w
     for (int i = threadIdx.x; i < a.R * BC * 2; i += kThreads) {
         const int h = i & 1, kl = (i >> 1) % BC, r = (i >> 1) / BC, k = k0 + kl;
-        const long long o = ((long long)k * a.R + r) * prm.run + 16 * h;
+        const long long o = ((long long)min(k, a.K - 1) * a.R + r) * prm.run + 16 * h;
         const int count = k < a.K ? min(16, prm.run - 16 * h) : 0;     // bytes of the piece that are weights, may be <= 0
-        Bytes16 v = {{0, 0, 0, 0}};
-        if (count > 0 && o + 16 <= total) {
-            v = *(const Bytes16 *)(a.w + o);
-#pragma unroll
-            for (int d = 0; d < 4; d++) {
-                const int n = min(max(count - 4 * d, 0), 4);           // bytes of this word to keep
-                v.w[d] = n == 4 ? v.w[d] : v.w[d] & ((1u << (8 * n)) - 1u);
-            }
-        } else if (count > 0) {                                        // the last bytes of the tensor
-#pragma unroll
-            for (int e = 0; e < 16; e++)
-                if (e < count) v.w[e >> 2] |= (uint32_t)(uint8_t)a.w[o + e] << (8 * (e & 3));
+        unsigned __int128 v = 0;
+        if (total >= 16) {
+            // from o, or from the last place that lies inside the tensor and shifted down: one path for all (byte loads for the
+            // last piece alone were a chain that every workgroup waited for)
+            const long long at = min(o, total - 16);
+            __builtin_memcpy(&v, a.w + at, 16);
+            v = o - at < 16 ? v >> (8 * (int)(o - at)) : 0;
+        } else {
+            for (int e = 0; e < count; e++) v |= (unsigned __int128)(uint8_t)a.w[o + e] << (8 * e);
         }
+        v = count <= 0 ? 0 : count < 16 ? v & (((unsigned __int128)1 << (8 * count)) - 1) : v;
         // LDS row of channel kl follows the same permutation as the dense kernel: a lane's 16 accumulators are 16
         // consecutive channels
         const int c32 = kl & 31;
         const int row = (kl & ~31) + 8 * ((c32 & 15) >> 2) + 4 * (c32 >> 4) + (c32 & 3);
         const int piece = h ^ ((row >> 3) & 1);
-        *(uint4 *)(wb + ((r * BC + row) * 2 + piece) * 16) = make_uint4(v.w[0], v.w[1], v.w[2], v.w[3]);
+        *(unsigned __int128 *)(wb + ((r * BC + row) * 2 + piece) * 16) = v;
     }
 }
 

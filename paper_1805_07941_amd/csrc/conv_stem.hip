@@ -73,26 +73,26 @@ __device__ __forceinline__ void stem_setup(const ConvArgs &a, int8_t *lds, int *
     const int total = a.K * R * a.S * 3;
     for (int t = tid; t < R * BC; t += THREADS) {
         const int kl = t % BC, r = t / BC;
-        const int o = (kl * R + r) * a.S * 3;
-        uint32_t d[7] = {0, 0, 0, 0, 0, 0, 0};
-        if (kl < a.K && o + 24 <= total) {
-            const Bytes16 lo = *(const Bytes16 *)(a.w + o);
-            uint2 hi;
-            __builtin_memcpy(&hi, a.w + o + 16, 8);
-#pragma unroll
-            for (int e = 0; e < 4; e++) d[e] = lo.w[e];
-            d[4] = hi.x;
-            d[5] = hi.y;
-        } else if (kl < a.K) {                                  // the last bytes of the tensor
-#pragma unroll
-            for (int e = 0; e < 24; e++)
-                if (e < a.S * 3) d[e >> 2] |= (uint32_t)(uint8_t)a.w[o + e] << (8 * (e & 3));
+        const int o = (min(kl, a.K - 1) * R + r) * a.S * 3;
+        // 24 bytes from o, or from the last place that lies inside the tensor (K >= 32: it has that many) and shifted down: one
+        // path for all (byte loads for the last blocks alone were a chain of 9 to 21 trips that every workgroup waited for)
+        const int at = max(0, min(o, total - 24)), sh = o - at;
+        unsigned long long q[3];
+        __builtin_memcpy(q, a.w + at, 24);
+        if (sh >= 16) { q[0] = q[2]; q[1] = q[2] = 0; }
+        else if (sh >= 8) { q[0] = q[1]; q[1] = q[2]; q[2] = 0; }
+        const int bits = 8 * (sh & 7);
+        if (bits) {
+            q[0] = q[0] >> bits | q[1] << (64 - bits);
+            q[1] = q[1] >> bits | q[2] << (64 - bits);
+            q[2] >>= bits;
         }
+        const uint32_t d[7] = {(uint32_t)q[0], (uint32_t)(q[0] >> 32), (uint32_t)q[1], (uint32_t)(q[1] >> 32), (uint32_t)q[2], (uint32_t)(q[2] >> 32), 0};
         uint32_t tap[8];                                        // the three weights of tap s, zeros past the last tap
 #pragma unroll
         for (int s = 0; s < 8; s++) {
             const uint32_t v = __builtin_amdgcn_alignbit(d[3 * s / 4 + 1], d[3 * s / 4], 8 * (3 * s % 4)) & 0xffffffu;
-            tap[s] = s < a.S ? v : 0;
+            tap[s] = s < a.S && kl < a.K ? v : 0;
         }
         const int c32 = kl & 31;
         const int row = (kl & ~31) + 8 * ((c32 & 15) >> 2) + 4 * (c32 >> 4) + (c32 & 3);
@@ -231,10 +231,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4,
         else stem_stage_rows<NW, MAXR, false>(xin, prm.pitch, prm.triples, wave, lane, first, count, rows);
     };
 
-    // the first step's input rows, the weights and the bias are on their way together
-    Rows pf[MAXR], pf_tail[MAXR];
-    stem_fetch_rows<NW, MAXR>(a, ximg, prm.triples, wave, lane, 8 * t0 - a.pad, 8, pf);
-    stem_fetch_rows<NW, MAXR>(a, ximg, prm.triples, wave, lane, 8 * t0 - a.pad + 8, kRowsFirst - 8, pf_tail);
+    Rows pf[MAXR];
     stem_setup<BC, R, kThreads>(a, lds, biasl, xin, kRowSlots * prm.pitch);
     __syncthreads();
 
@@ -242,8 +239,10 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4,
     rq.init(a.shift, a.relu);
     const v4i *const wl = (const v4i *)lds;
 
+    stem_fetch_rows<NW, MAXR>(a, ximg, prm.triples, wave, lane, 8 * t0 - a.pad, 8, pf);
     stage(8 * t0 - a.pad, 8, pf);
-    stage(8 * t0 - a.pad + 8, kRowsFirst - 8, pf_tail);
+    stem_fetch_rows<NW, MAXR>(a, ximg, prm.triples, wave, lane, 8 * t0 - a.pad + 8, kRowsFirst - 8, pf);
+    stage(8 * t0 - a.pad + 8, kRowsFirst - 8, pf);
     __syncthreads();
 
     const int ncb = a.Q >> 4;
@@ -581,8 +580,8 @@ hipError_t launch_conv_stem(const ConvArgs &a, int8_t *yp, int ldyp, hipStream_t
     prm.triples = a.W / 4;
     // two workgroups per compute unit; for few images down to strips of one step (one more is recomputed in the pooling form):
     // what a workgroup walks is a chain, and the chip is idle beside it (one image of 224 x 224, strips of four steps and of
-    // one: the pooling form 20.2 and 11.1 us, the plain one for
-    // 32 channels 8.5 and 5.1; 16 images 21.3 and 14.4)
+    // one: the pooling form 20.2 and 9.9 us, the plain one for
+    // 32 channels 8.5 and 5.0; 16 images 21.3 and 13.4)
     int strips = max(1, 2 * kNumCU / a.N);
     strips = min(strips, prm.steps);
     prm.steps_per_strip = (prm.steps + strips - 1) / strips;
