@@ -63,7 +63,7 @@ struct MfmaParams {
 // convolution result is rounded to its own format in registers, aligned with the operand at the
 // finer scale and the sum rounded once more.
 template <int BP, int BC, int WAVES_P, int WAVES_C, int NSTAGES, bool UT, bool PW, bool GENERAL, int OCC, bool PC = false,
-          bool FUSE = false, bool LAZY = false>
+          bool FUSE = false, bool LAZY = false, int STEP = kStepBytes>
 __global__ void __launch_bounds__(WAVES_P * WAVES_C * 64, OCC) conv_mfma_kernel(MfmaParams prm)
 {
     static_assert(!PC || !GENERAL, "the per-channel form is a lean one");
@@ -73,8 +73,10 @@ __global__ void __launch_bounds__(WAVES_P * WAVES_C * 64, OCC) conv_mfma_kernel(
     static_assert(UT || !PW, "the pointwise form keeps its position in scalar registers");
     constexpr int NW = WAVES_P * WAVES_C;                 // wavefronts per workgroup
     static_assert(NW == 4 || NW == 8 || NW == 16, "4, 8 or 16 wavefronts per workgroup");
-    constexpr int RPC = 64 / kPieces;                     // LDS rows filled by one wavefront-wide load (a "chunk")
-    constexpr int KK = kStepBytes / 32;                   // matrix-instruction k-steps per stage
+    static_assert(STEP == 64 || (STEP == 128 && UT), "a step of 128 bytes: whole taps only");
+    constexpr int PIECES = STEP / 16;                     // 16-byte pieces per LDS row
+    constexpr int RPC = 64 / PIECES;                     // LDS rows filled by one wavefront-wide load (a "chunk")
+    constexpr int KK = STEP / 32;                         // matrix-instruction k-steps per stage
     constexpr int WP = BP / WAVES_P, WC = BC / WAVES_C;   // wavefront tile
     constexpr int PT = WP / 32, CT = WC / 32;             // 32x32 MFMA tiles per wavefront
     // chunks each wavefront loads per step; when there are fewer weight chunks than wavefronts
@@ -83,7 +85,7 @@ __global__ void __launch_bounds__(WAVES_P * WAVES_C * 64, OCC) conv_mfma_kernel(
     constexpr bool kPartialW = BC < RPC * NW;
     static_assert(XS * RPC * NW == BP && (kPartialW || WS * RPC * NW == BC) && BC % 16 == 0, "whole chunks");
     constexpr int LPW = XS + WS;                          // loads per wavefront per step (with a weight chunk)
-    constexpr int STAGE_PIECES = (BP + BC) * kPieces;
+    constexpr int STAGE_PIECES = (BP + BC) * PIECES;
     static_assert(WP % 32 == 0 && WC % 32 == 0, "tile shape");
     static_assert(NSTAGES * LPW < 64, "outstanding loads must fit the 6-bit counter");
 
@@ -150,8 +152,10 @@ __global__ void __launch_bounds__(WAVES_P * WAVES_C * 64, OCC) conv_mfma_kernel(
     // the stage; lane l supplies row l/4 of the chunk, physical piece l%4, which holds logical piece
     // (l%4) ^ ((row>>2)&3) - the same for every chunk of this lane; 16 consecutive rows then put
     // any one logical piece on 16 different bank groups.
-    const int lrow = lane / kPieces;
-    const int lp = (lane & 3) ^ ((lane >> 4) & 3);
+    const int lrow = lane / PIECES;
+    // (steps of 128 bytes: a chunk is 8 rows, piece l%8 holds logical piece (l%8) ^ ((row>>1)&7), bit 3 of the row being that of
+    // the chunk's number, which is the wavefront's)
+    const int lp = STEP == 64 ? (lane & 3) ^ ((lane >> 4) & 3) : (lane & 7) ^ ((lane >> 4) | ((wave & 1) << 2));
     unsigned xoff[XS];               // byte offset of tap (0,0) of the lane's pixel, plus the lane's piece (mod 2^32)
     uint32_t rinv[XS], cinv[XS];     // bit r / bit s set: that kernel row / column falls OUTSIDE the image
     unsigned woff[WS];               // byte offset of the lane's weight row (+ piece), or out of range past K
@@ -222,11 +226,11 @@ __global__ void __launch_bounds__(WAVES_P * WAVES_C * 64, OCC) conv_mfma_kernel(
             if (w_active) {
 #pragma unroll
                 for (int j = 0; j < WS; j++)
-                    load_piece_to_lds(woff[j] + (unsigned)skb, wrsrc, sbase + (unsigned)(BP * 64) + (unsigned)j * (NW * 1024u));
+                    load_piece_to_lds(woff[j] + (unsigned)skb, wrsrc, sbase + (unsigned)(BP * STEP) + (unsigned)j * (NW * 1024u));
             }
-            skb += kStepBytes;
+            skb += STEP;
             if (!PW) {
-                scb += kStepBytes;
+                scb += STEP;
                 if (scb == a.C) {
                     scb = 0;
                     if (++ss == a.S) { ss = 0; ++sr; }
@@ -244,11 +248,11 @@ __global__ void __launch_bounds__(WAVES_P * WAVES_C * 64, OCC) conv_mfma_kernel(
             if (w_active) {
 #pragma unroll
                 for (int j = 0; j < WS; j++)
-                    load_piece_to_lds((woff[j] + (unsigned)kb) | past, wrsrc, sbase + (unsigned)(BP * 64) + (unsigned)j * (NW * 1024u));
+                    load_piece_to_lds((woff[j] + (unsigned)kb) | past, wrsrc, sbase + (unsigned)(BP * STEP) + (unsigned)j * (NW * 1024u));
             }
-            kb += kStepBytes;
-            tc += kStepBytes;
-            for (int i = 0; i < kStepBytes / 16; i++) {   // a step crosses at most four taps (C >= 16)
+            kb += STEP;
+            tc += STEP;
+            for (int i = 0; i < STEP / 16; i++) {   // a step crosses at most four taps (C >= 16)
                 const bool wrapc = tc >= a.C;
                 tc -= wrapc ? a.C : 0;
                 ts += wrapc ? 1 : 0;
@@ -267,7 +271,7 @@ __global__ void __launch_bounds__(WAVES_P * WAVES_C * 64, OCC) conv_mfma_kernel(
     const int wp0 = (wave % WAVES_P) * WP;
     const int wc0 = (wave / WAVES_P) * WC;
     const int l32 = lane & 31, lh = lane >> 5;
-    const int swz = (l32 >> 2) & 3;
+    const int swz = STEP == 64 ? (l32 >> 2) & 3 : (l32 >> 1) & 7;
     // every stage of the ring is filled before the first item is read
 #pragma unroll
     for (int i = 0; i < nstages; i++)
@@ -307,12 +311,12 @@ __global__ void __launch_bounds__(WAVES_P * WAVES_C * 64, OCC) conv_mfma_kernel(
     Half f0, f1;
     auto read_half = [&](Half &f, int kk, int stage) __attribute__((always_inline)) {
         const v4i *xs = (const v4i *)lds + stage * STAGE_PIECES;
-        const v4i *ws = xs + BP * kPieces;
+        const v4i *ws = xs + BP * PIECES;
         const int g = (kk * 2 + lh) ^ swz;   // physical piece
 #pragma unroll
-        for (int c = 0; c < CT; c++) f.w[c] = ws[(wc0 + c * 32 + l32) * kPieces + g];
+        for (int c = 0; c < CT; c++) f.w[c] = ws[(wc0 + c * 32 + l32) * PIECES + g];
 #pragma unroll
-        for (int p = 0; p < PT; p++) f.x[p] = xs[(wp0 + p * 32 + l32) * kPieces + g];
+        for (int p = 0; p < PT; p++) f.x[p] = xs[(wp0 + p * 32 + l32) * PIECES + g];
     };
     auto mfma_half = [&](const Half &f) __attribute__((always_inline)) {
 #pragma unroll
@@ -505,16 +509,24 @@ inline hipError_t big_lds(void (*k)(MfmaParams))
 // The per-channel lean form holds a group's rescale constants in registers on top of everything
 // else: it is built for the tile shapes whose register budget has room for them (wavefront tiles of
 // 64 x 64 at no more than three wavefronts per SIMD).
-template <int BP, int BC, int WAVES_P, int WAVES_C, int NSTAGES, bool UT, bool PW, int OCC, bool FUSE = false>
+template <int BP, int BC, int WAVES_P, int WAVES_C, int NSTAGES, bool UT, bool PW, int OCC, bool FUSE = false, int STEP = kStepBytes>
 constexpr void (*per_channel_kernel())(MfmaParams)
 {
     if constexpr (OCC <= 3 && (BP / WAVES_P) * (BC / WAVES_C) <= 64 * 64)
-        return conv_mfma_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, UT, PW, false, OCC, true, FUSE>;
+        return conv_mfma_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, UT, PW, false, OCC, true, FUSE, false, STEP>;
     else
         return nullptr;
 }
 
-template <int BP, int BC, int WAVES_P, int WAVES_C, int NSTAGES, int PER_CU>
+// the forms that exist with steps of 64 bytes only: taps that a step straddles, and the general epilogue
+template <int BP, int BC, int WAVES_P, int WAVES_C, int NSTAGES, bool UT, bool PW, bool GENERAL, int OCC, int STEP>
+constexpr void (*short_step_kernel())(MfmaParams)
+{
+    if constexpr (STEP == kStepBytes) return conv_mfma_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, UT, PW, GENERAL, OCC>;
+    else return nullptr;
+}
+
+template <int BP, int BC, int WAVES_P, int WAVES_C, int NSTAGES, int PER_CU, int STEP = kStepBytes>
 hipError_t launch_cfg(const ConvArgs &a, hipStream_t st)
 {
     MfmaParams prm;
@@ -522,7 +534,7 @@ hipError_t launch_cfg(const ConvArgs &a, hipStream_t st)
     const long long M = (long long)a.N * a.P * a.Q;
     prm.M = (int)M;
     prm.Kgemm = a.R * a.S * a.C;
-    prm.nsteps = (prm.Kgemm + kStepBytes - 1) / kStepBytes;
+    prm.nsteps = (prm.Kgemm + STEP - 1) / STEP;
     prm.tiles_c = (a.K + BC - 1) / BC;
     const long long tiles = ((M + BP - 1) / BP) * prm.tiles_c;
     if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
@@ -540,27 +552,27 @@ hipError_t launch_cfg(const ConvArgs &a, hipStream_t st)
     if (grid > prm.tiles) grid = prm.tiles;
     grid = grid / prm.tiles_c * prm.tiles_c;            // the channel tile of a workgroup must not change
     if (grid < prm.tiles_c) grid = prm.tiles_c;
-    constexpr size_t lds_bytes = (size_t)NSTAGES * (BP + BC) * kStepBytes + BC * 4 * 4;   // rings, bias, three per-channel tables
+    constexpr size_t lds_bytes = (size_t)NSTAGES * (BP + BC) * STEP + BC * 4 * 4;   // rings, bias, three per-channel tables
     static_assert(lds_bytes * PER_CU <= kLdsBytes, "rings do not fit the LDS");
 
     constexpr int occ = PER_CU * WAVES_P * WAVES_C / 4;
     using K = void (*)(MfmaParams);
-    const bool ut = a.C % kStepBytes == 0;
+    const bool ut = a.C % STEP == 0;
     const bool pw = ut && a.R == 1 && a.S == 1 && a.stride == 1 && a.pad == 0;
-    static const K kernels[12] = {conv_mfma_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, false, false, false, occ>,
-                                 conv_mfma_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, false, false, true, occ>,
-                                 conv_mfma_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, false, false, occ>,
-                                 conv_mfma_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, false, true, occ>,
-                                 conv_mfma_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, true, false, occ>,
-                                 conv_mfma_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, true, true, occ>,
-                                 per_channel_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, false, occ>(),
-                                 per_channel_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, true, occ>(),
-                                 per_channel_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, false, false, occ>(),
+    static const K kernels[12] = {short_step_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, false, false, false, occ, STEP>(),
+                                 short_step_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, false, false, true, occ, STEP>(),
+                                 conv_mfma_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, false, false, occ, false, false, false, STEP>,
+                                 short_step_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, false, true, occ, STEP>(),
+                                 conv_mfma_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, true, false, occ, false, false, false, STEP>,
+                                 short_step_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, true, true, occ, STEP>(),
+                                 per_channel_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, false, occ, false, STEP>(),
+                                 per_channel_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, true, occ, false, STEP>(),
+                                 STEP == kStepBytes ? per_channel_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, false, false, occ>() : nullptr,
                                  // unpadded 1x1 stride-1 layers with the add behind them fused into the epilogue
-                                 conv_mfma_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, true, false, occ, false, true>,
-                                 per_channel_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, true, occ, true>(),
+                                 conv_mfma_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, true, false, occ, false, true, false, STEP>,
+                                 per_channel_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, true, occ, true, STEP>(),
                                  // ... with the single-rounding join
-                                 conv_mfma_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, true, false, occ, false, true, true>};
+                                 conv_mfma_kernel<BP, BC, WAVES_P, WAVES_C, NSTAGES, true, true, false, occ, false, true, true, STEP>};
     static const hipError_t attr[12] = {big_lds(kernels[0]), big_lds(kernels[1]), big_lds(kernels[2]), big_lds(kernels[3]),
                                         big_lds(kernels[4]), big_lds(kernels[5]), big_lds(kernels[6]), big_lds(kernels[7]),
                                         big_lds(kernels[8]), big_lds(kernels[9]), big_lds(kernels[10]), big_lds(kernels[11])};
@@ -574,6 +586,7 @@ hipError_t launch_cfg(const ConvArgs &a, hipStream_t st)
         if (general || !pw || (a.frac_w && !kernels[10])) return hipErrorInvalidValue;
         which = a.frac_w ? 10 : a.add_lazy ? 11 : 9;
     }
+    if (!kernels[which]) return hipErrorInvalidValue;
     if (attr[which] != hipSuccess) return attr[which];
     K kernel = kernels[which];
     kernel<<<(unsigned)grid, WAVES_P * WAVES_C * 64, lds_bytes, st>>>(prm);
@@ -613,9 +626,50 @@ bool conv_mfma_fuses(const ConvArgs &a)
     return true;
 }
 
+namespace {
+
+// Tile shapes with steps of 128 bytes, whole cache lines of every row: a compute unit draws 52 bytes a clock from L2 that way and
+// 29 in rows of 64, and a reduction has half as many barriers.  They exist in the lean forms, for C a multiple of 128.
+enum class Wide { none, t64, t128x64, t128, t128w8, t256 };
+
+Wide choose_wide(const ConvArgs &a)
+{
+    if (a.C % 128 || a.K % 64 || !conv_mfma_supports(a) || (a.add && !conv_mfma_fuses(a))) return Wide::none;
+    const int s_lo = a.shift + (a.frac_w ? a.frac_w_lo : 0), s_hi = a.shift + (a.frac_w ? a.frac_w_hi : 0);
+    const long long M = (long long)a.N * a.P * a.Q;
+    if (s_lo < 0 || s_hi > 23) return Wide::none;
+    if (a.acc_out || !a.y || (a.ldy & 15) || ((uintptr_t)a.y & 15) || M * a.ldy >= (1LL << 31)) return Wide::none;
+    // All figures in us, steps of 64 bytes (or the input-resident kernel for unpadded 1x1 layers of 128 and 256 channels) against these.
+    if (a.K % 128) return (M + 127) / 128 * (a.K / 64) >= 256 ? Wide::t128x64 : Wide::t64;      // 256 -> 64 at 56 x 56: 256 images 51.6, 43.1; 12 images 7.2, 6.2
+    // fewer than three 128 x 128 tiles for four compute units: 64 x 64, three workgroups per unit (3x3 256 -> 256 at 14 x 14, 32
+    // images 15.5, 10.6; 3x3 512 -> 512 at 7 x 7, 96 images 26.4, 21.4 - with 128 x 128 tiles 25.9)
+    const long long t128 = (M + 127) / 128 * (a.K / 128);
+    if (t128 < 192) return Wide::t64;
+    const int n = a.R * a.S * (a.C / 128);
+    const bool pointwise = a.R == 1 && a.S == 1;
+    // the per-channel epilogue has room at 64 x 64 outputs per wavefront, two wavefronts per SIMD (3x3 128 -> 128 at 28 x 28, 256
+    // images 46.4, 39.8)
+    if (a.frac_w) return Wide::t128;
+    // half the fill traffic again, where the tiles occupy most of the chip in every round and the chain is long enough to pay for
+    // one workgroup per unit (256 images: 3x3 256 -> 256 at 14 x 14 36.2, 32.9 - 128 x 128 39.8; 1x1 512 -> 1024, four steps and
+    // 3.06 rounds, 48.7, 44.4 - 128 x 128 43.6); in a single round from four steps on, also because the next layer then finds a
+    // tile's rows in one L2 (a depthwise-separable network of 128 images: 512 -> 512 at 14 x 14 13.6 and the depthwise layer behind
+    // it 12.1, with 128 x 128 15.5 and 15.0)
+    const long long t256 = (M + 255) / 256 * (a.K / 256), rounds = (t256 + kNumCU - 1) / kNumCU;
+    if (a.K % 256 == 0 && t256 * 20 >= rounds * kNumCU * 11 && (n >= 8 || (n >= 4 && rounds == 1))) return Wide::t256;
+    // eight wavefronts of 32 x 64 hide latency best (128 -> 512 at 28 x 28, 256 images 42.6, 34.6, with four of 64 x 64 36.6); four
+    // need fewer operand reads (512 -> 128 at 28 x 28 30.5, 28.4 - eight 30.7; 128 -> 512 with the add 69.6, 64.8 - eight 66.9)
+    return (pointwise && a.K <= 256 && n >= 4) || (a.add && n == 1) ? Wide::t128 : Wide::t128w8;
+}
+
+}  // namespace
+
+bool conv_mfma_wide(const ConvArgs &a) { return choose_wide(a) != Wide::none; }
+
 hipError_t launch_conv_mfma(const ConvArgs &a, hipStream_t st)
 {
-    // Measured choices at batch 256 (wavefronts own 64 x 64 outputs unless noted):
+    // What is left for steps of 64 bytes - channel counts that are no multiple of 128, ragged results, accumulators - by choices
+    // measured at batch 256 (wavefronts own 64 x 64 outputs unless noted):
     // K <= 64: 256 x 64 tiles (four wavefronts); for kernels larger than 1x1 three workgroups per CU
     //          with a two-stage ring beat two with three stages (more independent workgroups to
     //          overlap epilogues with matrix work);
@@ -629,6 +683,14 @@ hipError_t launch_conv_mfma(const ConvArgs &a, hipStream_t st)
     const bool pointwise = a.R == 1 && a.S == 1;
     // very few pixels (fully connected layers), also where the dense kernel is asked for by name
     if ((long long)a.N * a.P * a.Q <= 1024 && a.K > 64 && conv_sk_pays(a)) return launch_conv_sk(a, st);
+    switch (choose_wide(a)) {
+        case Wide::t64: return launch_cfg<64, 64, 2, 2, 3, 3, 128>(a, st);
+        case Wide::t128x64: return launch_cfg<128, 64, 4, 1, 2, 3, 128>(a, st);
+        case Wide::t128: return launch_cfg<128, 128, 2, 2, 2, 2, 128>(a, st);
+        case Wide::t128w8: return launch_cfg<128, 128, 4, 2, 2, 2, 128>(a, st);
+        case Wide::t256: return launch_cfg<256, 256, 4, 2, 2, 1, 128>(a, st);
+        case Wide::none: break;
+    }
     // one weight format per output channel: the tile shapes for which that epilogue is built
     if (a.frac_w && a.K > 64) return launch_cfg<128, 128, 2, 2, 3, 3>(a, st);
     if (a.K <= 64) return pointwise ? launch_cfg<256, 64, 4, 1, 3, 2>(a, st) : launch_cfg<256, 64, 4, 1, 2, 3>(a, st);

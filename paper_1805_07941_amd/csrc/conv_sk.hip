@@ -15,7 +15,7 @@
 // The epilogue takes any shift, ragged channel tail, pitch, accumulator dump, one weight format per channel and the add.
 //
 // Measured (one layer among others, weights not in L2): 3x3 256 -> 256 at 14 x 14, one image 10.3 -> 4.1 us; 3x3 512 -> 512
-// at 7 x 7, one image 17.0 -> 5.0, twelve images 17.0 -> 9.7; 1x1 512 -> 2048 at 7 x 7, twelve images 16.6 -> 6.9; fully
+// at 7 x 7, one image 17.0 -> 5.0, twelve images 17.0 -> 9.7; 1x1 2048 -> 512 at 7 x 7, twelve images 11.3 -> 6.5; fully
 // connected 2048 -> 1000, one image 7.5 -> 4.0, 32 images 8.0 -> 4.2.
 #include "conv_ring.hpp"
 
@@ -318,19 +318,19 @@ Shape choose(const ConvArgs &a)
     const long long t16 = ((M + 15) / 16) * ((a.K + 15) / 16), t32 = ((M + 31) / 32) * ((a.K + 31) / 32);
     if (t16 <= 512) return Shape::t16;
     const int n = (a.R * a.S * a.C + kRow - 1) / kRow;
-    if (conv_pw_geometry_ok(a)) {
-        // the input-resident kernel streams its input and has no chain: it wins from about 1024 tiles on (128 -> 512 at
-        // 28 x 28: one image 4.4 -> 3.3 us, four images 5.0 against 6.1; 256 -> 1024 at 14 x 14, four images 6.3 -> 4.4), and
-        // at once where C is no multiple of 128 (64 -> 64 at 56 x 56: 3.4 against 3.9)
-        if (a.C % kRow || t32 > 1024) return Shape::none;
-    } else {
-        // Fitted to 60 layer sizes: this kernel takes 3 us + (2 + 0.4 n) ns per tile; the general one, while its tiles do not
-        // fill the chip, 3 us + 0.7 us per 128 bytes of the reduction, twice that where a ragged K takes its general epilogue.
-        // At the line: 3x3 64 -> 64 at 56 x 56, four images 7.6 -> 6.7 us, twelve 8.7 against 14.4; 3x3 256 -> 256 at 14 x 14,
-        // twelve images 15.3 -> 7.9 us, thirty-two 15.4 against 15.3; 1x1 512 -> 256 at 28 x 28, four images 6.2 and 6.1.
-        const long long per_step = a.K % (a.K <= 64 ? 64 : 128) ? 1400 : 700;
-        if (t32 * (20 + 4 * n) > per_step * n * 10) return Shape::none;
+    // Fitted to 60 layer sizes: this kernel takes 3 us + (2 + 0.4 n) ns per 32 x 32 tile; the general one, while its tiles do not
+    // fill the chip, 3 us + 0.28 us per 128 bytes of the reduction in steps of that length, 0.7 us in steps of 64, twice that
+    // where a ragged K takes its general epilogue.  At the line: 3x3 256 -> 256 at 14 x 14, four images 8.4 -> 5.8 us, twelve
+    // (592 tiles) 8.45 against 8.0; 1x1 512 -> 256 at 28 x 28, one image 4.4 -> 4.3, four 4.7 against 6.2; 3x3 64 -> 64 at
+    // 56 x 56, four images 7.6 -> 6.7, twelve 8.7 against 14.4.
+    int per_step = 280;
+    if (!conv_mfma_wide(a)) {
+        // the input-resident kernel has no chain and is faster at once where C is no multiple of 128 (64 -> 64 at 56 x 56: 3.4
+        // against 3.9)
+        if (conv_pw_geometry_ok(a) && a.C % kRow) return Shape::none;
+        per_step = a.K % (a.K <= 64 ? 64 : 128) ? 1400 : 700;
     }
+    if (t32 * (20 + 4 * n) > (long long)per_step * n * 10) return Shape::none;
     return t32 <= kNumCU && n > 4 ? Shape::t32x8 : Shape::t32x4;
 }
 

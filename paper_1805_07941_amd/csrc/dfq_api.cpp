@@ -92,6 +92,7 @@ dfq_status run_conv(dfq_conv_variant variant, const ConvArgs &a, hipStream_t st)
 {
     if (variant == DFQ_CONV_AUTO) {
         if (conv_sk_pays(a)) return from_hip(launch_conv_sk(a, st));
+        if (conv_mfma_wide(a)) return from_hip(launch_conv_mfma(a, st));
         variant = select_variant(a);
     }
     switch (variant) {
@@ -127,7 +128,7 @@ dfq_status run_fused_add(const ConvArgs &a, hipStream_t st)
     const bool pw = conv_pw_supports(a);
     if (!pw && !conv_mfma_fuses(a)) return DFQ_EUNSUPPORTED;
     if (conv_sk_pays(a)) return from_hip(launch_conv_sk(a, st));
-    return from_hip(pw ? launch_conv_pw(a, st) : launch_conv_mfma(a, st));
+    return from_hip(pw && !conv_mfma_wide(a) ? launch_conv_pw(a, st) : launch_conv_mfma(a, st));
 }
 
 // the part of the fused convolution + add calls behind the convolution's own checks
