@@ -417,7 +417,7 @@ def main():
     for nd in convs:
         H, W, C = net.shapes[nd.srcs[0]]
         variant_of[nd.name] = B.conv_q_select(args.batch, H, W, C, nd.K, nd.R, nd.R, nd.stride, nd.pad, nd.groups)
-    matrix_core = (B.CONV_MFMA, B.CONV_POINTWISE)   # the dense kernels on the int8 matrix cores
+    matrix_core = (B.CONV_MFMA, B.CONV_POINTWISE, B.CONV_SPLIT)   # the dense kernels on the int8 matrix cores
     mfma_nodes = [nd for nd in convs if variant_of[nd.name] in matrix_core]
 
     # instrumented pass: the plan's own call list with an event pair around each launch of the

@@ -65,6 +65,8 @@ typedef enum {
                               S in {1, 3, 5, 7}, stride 1 or 2, K*R*S*C/groups <= 64 KB, 4-byte aligned x and w */
     DFQ_CONV_RAGGED = 7,   /* int8 MFMA for any channel count, grouping, kernel size and alignment (W*C >= 16 and at least 16 weights);
                               dfq_conv_q picks it for what no kernel above takes, from 8 output channels per group on */
+    DFQ_CONV_SPLIT = 8,    /* int8 MFMA with the reduction split inside a workgroup: any call that DFQ_CONV_MFMA takes; dfq_conv_q picks
+                              it for layers too small to fill the chip */
     DFQ_CONV_POINTWISE = 5 /* int8 MFMA with the input tile resident in LDS; unpadded 1x1 stride 1, groups == 1,
                               C in {64, 128, 192, 256}, K % 64 == 0, K <= 4096, (K / BC) * (C / 64) >= 2 and
                               512*C + 192*BC + 4*K <= 160 KB of LDS with BC = (K % 128 ? 64 : 128),

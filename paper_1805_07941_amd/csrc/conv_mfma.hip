@@ -681,8 +681,6 @@ hipError_t launch_conv_mfma(const ConvArgs &a, hipStream_t st)
     // else:    256 x 128 tiles (eight wavefronts), two workgroups per CU, for kernels larger than 1x1 with enough of them;
     //          for 1x1 kernels (few items per tile) 128 x 128 tiles (four wavefronts), three per CU.
     const bool pointwise = a.R == 1 && a.S == 1;
-    // very few pixels (fully connected layers), also where the dense kernel is asked for by name
-    if ((long long)a.N * a.P * a.Q <= 1024 && a.K > 64 && conv_sk_pays(a)) return launch_conv_sk(a, st);
     switch (choose_wide(a)) {
         case Wide::t64: return launch_cfg<64, 64, 2, 2, 3, 3, 128>(a, st);
         case Wide::t128x64: return launch_cfg<128, 64, 4, 1, 2, 3, 128>(a, st);
@@ -691,6 +689,10 @@ hipError_t launch_conv_mfma(const ConvArgs &a, hipStream_t st)
         case Wide::t256: return launch_cfg<256, 256, 4, 2, 2, 1, 128>(a, st);
         case Wide::none: break;
     }
+    // very few pixels: 64 x 64 tiles, wavefronts of 32 x 32, so that the channel tiles alone spread over more compute units, with a
+    // ring six stages deep (accumulators of 64 -> 2048, 128 pixels: 4.4 us, with 128 x 128 tiles 10.7; of 128 -> 512 at 28 x 28,
+    // one image 6.8 and 11.9)
+    if ((long long)a.N * a.P * a.Q <= 1024 && a.K > 64) return launch_cfg<64, 64, 2, 2, 6, 2>(a, st);
     // one weight format per output channel: the tile shapes for which that epilogue is built
     if (a.frac_w && a.K > 64) return launch_cfg<128, 128, 2, 2, 3, 3>(a, st);
     if (a.K <= 64) return pointwise ? launch_cfg<256, 64, 4, 1, 3, 2>(a, st) : launch_cfg<256, 64, 4, 1, 2, 3>(a, st);

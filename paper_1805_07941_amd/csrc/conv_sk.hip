@@ -99,7 +99,7 @@ __global__ void __launch_bounds__(NW * 64) conv_sk_kernel(SkParams prm)
             bias[i][e] = (on && a.b) ? a.b[kc + e] : 0;
             fw[i][e] = (on && a.frac_w) ? a.frac_w[kc + e] : 0;
         }
-        if (live && a.add && kc < a.K) other[i] = *(const uint32_t *)(a.add + (size_t)m * a.ldadd + kc);   // K % 256 == 0 where a.add is set
+        if (live && a.add && kc < a.K) other[i] = *(const uint32_t *)(a.add + (size_t)m * a.ldadd + kc);   // words: conv_sk_supports()
     }
 
     // ---- producer.  A wavefront-wide load covers 8 rows of a stage: lane l supplies row l/8, physical piece l%8, which holds
@@ -310,10 +310,11 @@ namespace {
 // took 6 us where these take 3 to 4, and more where there are many.)
 enum class Shape { none, t16, t32x8, t32x4 };
 
+Shape t32_shape(long long t32, int n) { return t32 <= kNumCU && n > 4 ? Shape::t32x8 : Shape::t32x4; }
+
 Shape choose(const ConvArgs &a)
 {
-    if (!conv_mfma_supports(a)) return Shape::none;
-    if (a.add && (((uintptr_t)a.add & 3) || (a.ldadd & 3) || (a.K & 3))) return Shape::none;     // operand read in words
+    if (!conv_sk_supports(a)) return Shape::none;
     const long long M = (long long)a.N * a.P * a.Q;
     const long long t16 = ((M + 15) / 16) * ((a.K + 15) / 16), t32 = ((M + 31) / 32) * ((a.K + 31) / 32);
     if (t16 <= 512) return Shape::t16;
@@ -331,20 +332,29 @@ Shape choose(const ConvArgs &a)
         per_step = a.K % (a.K <= 64 ? 64 : 128) ? 1400 : 700;
     }
     if (t32 * (20 + 4 * n) > (long long)per_step * n * 10) return Shape::none;
-    return t32 <= kNumCU && n > 4 ? Shape::t32x8 : Shape::t32x4;
+    return t32_shape(t32, n);
 }
 
 }  // namespace
+
+bool conv_sk_supports(const ConvArgs &a)
+{
+    if (!conv_mfma_supports(a)) return false;
+    if (a.add && (((uintptr_t)a.add & 3) || (a.ldadd & 3) || (a.K & 3))) return false;           // operand read in words
+    return true;
+}
 
 bool conv_sk_pays(const ConvArgs &a) { return choose(a) != Shape::none; }
 
 hipError_t launch_conv_sk(const ConvArgs &a, hipStream_t st)
 {
-    switch (choose(a)) {
+    Shape s = choose(a);
+    if (s == Shape::none)                          // asked for by name where another kernel is faster
+        s = t32_shape(((long long)a.N * a.P * a.Q + 31) / 32 * ((a.K + 31) / 32), (a.R * a.S * a.C + kRow - 1) / kRow);
+    switch (s) {
         case Shape::t16: return launch_cfg<1, 1, 8, 2>(a, st);
         case Shape::t32x8: return launch_cfg<2, 2, 8, 1>(a, st);
-        case Shape::t32x4: return launch_cfg<2, 2, 4, 1>(a, st);
-        default: return hipErrorInvalidValue;
+        default: return launch_cfg<2, 2, 4, 1>(a, st);
     }
 }
 

@@ -114,6 +114,9 @@ dfq_status run_conv(dfq_conv_variant variant, const ConvArgs &a, hipStream_t st)
         case DFQ_CONV_GROUPED:
             if (!conv_grouped_supports(a)) return DFQ_EUNSUPPORTED;
             return from_hip(launch_conv_grouped(a, st));
+        case DFQ_CONV_SPLIT:
+            if (!conv_sk_supports(a)) return DFQ_EUNSUPPORTED;
+            return from_hip(launch_conv_sk(a, st));
         case DFQ_CONV_RAGGED:
             if (!conv_rag_supports(a)) return DFQ_EUNSUPPORTED;
             return from_hip(launch_conv_rag(a, st));

@@ -93,6 +93,7 @@ bool conv_mfma_supports(const ConvArgs &a);
 bool conv_mfma_fuses(const ConvArgs &a);     // a.add set: the dense kernel has a fused form for this call
 bool conv_mfma_wide(const ConvArgs &a);      // launch_conv_mfma() takes the call in steps of 128 bytes, faster than any other kernel but conv_sk
 hipError_t launch_conv_mfma(const ConvArgs &a, hipStream_t st);
+bool conv_sk_supports(const ConvArgs &a);       // what the dense kernel takes
 bool conv_sk_pays(const ConvArgs &a);           // a dense layer small enough that splitting its reduction beats the other kernels
 hipError_t launch_conv_sk(const ConvArgs &a, hipStream_t st);
 bool conv_depthwise_supports(const ConvArgs &a);

@@ -211,7 +211,7 @@ def test_conv_q_random_shapes(B, shape):
     rng = np.random.default_rng(abs(hash(shape)) % (2 ** 31))
     x, w, b = _rand_conv(rng, N, H, W, C, K, R, S, g)
     xd, wd, bd = dev(x), dev(w), dev(b)
-    variants = [B.CONV_AUTO, B.CONV_DIRECT, B.CONV_MFMA, B.CONV_DEPTHWISE, B.CONV_SMALLC, B.CONV_POINTWISE, B.CONV_GROUPED]
+    variants = [B.CONV_AUTO, B.CONV_DIRECT, B.CONV_MFMA, B.CONV_DEPTHWISE, B.CONV_SMALLC, B.CONV_POINTWISE, B.CONV_GROUPED, B.CONV_SPLIT]
     first = True
     for f_in, f_w, f_out, relu, bias in [(4, 7, 4, 1, True), (3, 6, 2, 0, True), (2, 2, 4, 0, False), (5, 5, -3, 1, True),
                                          (1, 1, 6, 1, True)]:

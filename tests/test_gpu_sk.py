@@ -30,6 +30,7 @@ SHAPES = [
     (12, 7, 7, 512, 512, 3, 3, 1, 1),            # 36 steps over four
     (9, 23, 23, 48, 96, 3, 3, 1, 1),
     (4, 28, 28, 128, 128, 3, 3, 2, 1),
+    (40, 15, 15, 48, 68, 1, 1, 1, 0),            # by name only: another kernel is faster
 ]
 
 
@@ -43,17 +44,17 @@ def test_conv_split_reduction(B, shape):
     shift = max(0, int(np.log2(np.sqrt(R * S * C) * 70 * 70 / 40)))
     for i, (relu, bias, s) in enumerate([(True, True, shift), (False, False, shift - 2), (True, True, 24), (False, True, -9)]):
         y_ref, acc_ref = orc.conv_q(x, w, b if bias else None, 4, s, 4, st, pad, 1, relu, want_acc=True)
-        y, acc = B.conv_q(xd, wd, bd if bias else None, 4, s, 4, st, pad, 1, relu, want_acc=i == 0)
+        y, acc = B.conv_q(xd, wd, bd if bias else None, 4, s, 4, st, pad, 1, relu, want_acc=i == 0, variant=B.CONV_SPLIT)
         assert np.array_equal(host(y), y_ref), (relu, bias, s)
         if i == 0:
             assert np.array_equal(host(acc), acc_ref)
-            _, acc = B.conv_q(xd, wd, bd, 4, s, 4, st, pad, 1, relu, want_y=False, want_acc=True)
+            _, acc = B.conv_q(xd, wd, bd, 4, s, 4, st, pad, 1, relu, want_y=False, want_acc=True, variant=B.CONV_SPLIT)
             assert np.array_equal(host(acc), acc_ref)
     # a channel slice of a wider tensor: at a word boundary, and at an odd address and pitch
     y_ref, _ = orc.conv_q(x, w, b, 4, shift, 4, st, pad, 1, True)
     for ldy, off in ((4 * (K // 4) + 8, 4), (K + 7 + K % 2, 1)):
         wide = torch.full((N, y_ref.shape[1], y_ref.shape[2], ldy), 77, dtype=torch.int8, device="cuda")
-        B.conv_q(xd, wd, bd, 4, shift, 4, st, pad, 1, True, out=wide.view(-1)[off:], ldy=ldy)
+        B.conv_q(xd, wd, bd, 4, shift, 4, st, pad, 1, True, out=wide.view(-1)[off:], ldy=ldy, variant=B.CONV_SPLIT)
         got = host(wide).reshape(-1, ldy)
         assert np.array_equal(got[:, off:off + K], y_ref.reshape(-1, K))
         assert (got[:, :off] == 77).all() and (got[:, off + K:] == 77).all()
