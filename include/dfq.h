@@ -241,7 +241,7 @@ dfq_status dfq_conv_q_pc_add(const int8_t *x, const int8_t *w, const int32_t *b,
                              int frac_w_hi, dfq_fmt fmt_mid, int relu_mid, dfq_fmt fmt_other, dfq_fmt fmt_out,
                              int relu_out, dfq_stream stream);
 
-/* The variant dfq_conv_q would run for this geometry (host, pure) when the tensors are 16-byte
+/* The variant dfq_conv_q runs for this geometry (host, pure; the same function decides both) when the tensors are 16-byte
  * aligned, ldy == K, the rescale shift lies in [0, 23] and no accumulator dump is asked for;
  * DFQ_CONV_AUTO if the geometry is invalid. */
 dfq_conv_variant dfq_conv_q_select(int N, int H, int W, int C, int K, int R, int S, int stride, int pad, int groups);

@@ -76,11 +76,13 @@ ConvCheck check_conv(const int8_t *x, const int8_t *w, const int32_t *b, int8_t 
     return r;
 }
 
-// geometry_only: the pointers, row pitch and shift of `a` are placeholders
-dfq_conv_variant select_variant(const ConvArgs &a, bool geometry_only = false)
+// the kernel of an automatic call; dfq_conv_q_select asks the same function
+dfq_conv_variant select_variant(const ConvArgs &a)
 {
+    if (conv_sk_pays(a)) return DFQ_CONV_SPLIT;
+    if (conv_mfma_wide(a)) return DFQ_CONV_MFMA;
     if (conv_depthwise_supports(a)) return DFQ_CONV_DEPTHWISE;
-    if (geometry_only ? conv_pw_geometry_ok(a) : conv_pw_supports(a)) return DFQ_CONV_POINTWISE;
+    if (conv_pw_supports(a)) return DFQ_CONV_POINTWISE;
     if (conv_mfma_supports(a)) return DFQ_CONV_MFMA;
     if (conv_smallc_supports(a)) return DFQ_CONV_SMALLC;
     if (conv_grouped_supports(a)) return DFQ_CONV_GROUPED;
@@ -90,11 +92,7 @@ dfq_conv_variant select_variant(const ConvArgs &a, bool geometry_only = false)
 
 dfq_status run_conv(dfq_conv_variant variant, const ConvArgs &a, hipStream_t st)
 {
-    if (variant == DFQ_CONV_AUTO) {
-        if (conv_sk_pays(a)) return from_hip(launch_conv_sk(a, st));
-        if (conv_mfma_wide(a)) return from_hip(launch_conv_mfma(a, st));
-        variant = select_variant(a);
-    }
+    if (variant == DFQ_CONV_AUTO) variant = select_variant(a);
     switch (variant) {
         case DFQ_CONV_DIRECT:
             return from_hip(launch_conv_direct(a, st));
@@ -604,7 +602,8 @@ dfq_conv_variant dfq_conv_q_select(int N, int H, int W, int C, int K, int R, int
     ConvCheck c = check_conv(nullptr, nullptr, nullptr, nullptr, nullptr, N, H, W, C, K, R, S, stride, pad, groups, K, f, f,
                              f, 0, false);
     if (c.st != DFQ_OK) return DFQ_CONV_AUTO;
-    return select_variant(c.a, true);
+    c.a.y = reinterpret_cast<int8_t *>(uintptr_t{256});      // an aligned result: the call this answers for has one (never dereferenced)
+    return select_variant(c.a);
 }
 
 dfq_status dfq_eltwise_q(const int8_t *a, dfq_fmt fa, const int8_t *b, dfq_fmt fb, int8_t *y, dfq_fmt fy, int32_t *acc_out,

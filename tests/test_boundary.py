@@ -359,8 +359,17 @@ def test_other_calls_reject_bad_arguments(B):
 
 def test_kernel_selection(B):
     s = B.conv_q_select
-    assert s(1, 56, 56, 64, 64, 3, 3, 1, 1, 1) == B.CONV_MFMA
-    assert s(1, 7, 7, 512, 2048, 1, 1, 1, 0, 1) == B.CONV_MFMA
+    assert s(128, 56, 56, 64, 64, 3, 3, 1, 1, 1) == B.CONV_MFMA
+    assert s(1, 56, 56, 64, 64, 3, 3, 1, 1, 1) == B.CONV_SPLIT     # too small to fill the chip
+    assert s(1, 7, 7, 512, 2048, 1, 1, 1, 0, 1) == B.CONV_SPLIT
+    # unpadded 1x1 layers: steps of whole cache lines where C allows them, the input-resident kernel where it does not
+    assert s(256, 28, 28, 128, 512, 1, 1, 1, 0, 1) == B.CONV_MFMA
+    assert s(256, 56, 56, 256, 64, 1, 1, 1, 0, 1) == B.CONV_MFMA
+    assert s(256, 56, 56, 64, 256, 1, 1, 1, 0, 1) == B.CONV_POINTWISE
+    assert s(64, 28, 28, 192, 384, 1, 1, 1, 0, 1) == B.CONV_POINTWISE
+    assert s(1, 14, 14, 128, 256, 1, 1, 1, 0, 1) == B.CONV_SPLIT
+    assert s(1, 7, 7, 256, 512, 1, 1, 1, 0, 1) == B.CONV_SPLIT
+    assert s(1, 14, 14, 64, 256, 1, 1, 1, 0, 1) == B.CONV_SPLIT
     assert s(1, 8, 8, 0, 4, 1, 1, 1, 0, 1) == B.CONV_AUTO          # invalid geometry
     assert s(1, 8, 8, 20, 10, 2, 3, 1, 1, 5) == B.CONV_GROUPED     # groups of four channels
     assert s(1, 8, 8, 15, 10, 2, 3, 1, 1, 5) == B.CONV_DIRECT      # groups of three channels: no kernel but the direct one
