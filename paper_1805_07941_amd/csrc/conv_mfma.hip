@@ -576,10 +576,7 @@ hipError_t launch_cfg(const ConvArgs &a, hipStream_t st)
     static const hipError_t attr[12] = {big_lds(kernels[0]), big_lds(kernels[1]), big_lds(kernels[2]), big_lds(kernels[3]),
                                         big_lds(kernels[4]), big_lds(kernels[5]), big_lds(kernels[6]), big_lds(kernels[7]),
                                         big_lds(kernels[8]), big_lds(kernels[9]), big_lds(kernels[10]), big_lds(kernels[11])};
-    // shifts the epilogue will meet: one, or with per-channel weight formats the declared range
-    const int s_lo = a.shift + (a.frac_w ? a.frac_w_lo : 0), s_hi = a.shift + (a.frac_w ? a.frac_w_hi : 0);
-    const bool general = !((!a.frac_w || kernels[6]) && s_lo >= 0 && s_hi <= 23 && !a.acc_out && a.y && (a.ldy & 15) == 0 &&
-                           ((uintptr_t)a.y & 15) == 0 && a.K % BC == 0 && y_bytes < (1LL << 31));
+    const bool general = !((!a.frac_w || kernels[6]) && conv_mfma_lean(a) && a.K % BC == 0);
     int which = (!general && a.frac_w) ? (pw ? 7 : ut ? 6 : 8) : (pw ? 4 : ut ? 2 : 0) + (general ? 1 : 0);
     if (a.add) {
         // conv_mfma_fuses() has vouched for the lean pointwise form
@@ -609,16 +606,23 @@ bool conv_mfma_supports(const ConvArgs &a)
     return true;
 }
 
+// Shifts the epilogue will meet (one, or with per-channel weight formats the declared range) in the range of the four-instruction
+// rounding, an int8 result alone, rows of whole 16-byte pieces that 32-bit offsets reach.
+bool conv_mfma_lean(const ConvArgs &a)
+{
+    const int s_lo = a.shift + (a.frac_w ? a.frac_w_lo : 0), s_hi = a.shift + (a.frac_w ? a.frac_w_hi : 0);
+    return s_lo >= 0 && s_hi <= 23 && !a.acc_out && a.y && (a.ldy & 15) == 0 && ((uintptr_t)a.y & 15) == 0 &&
+           (long long)a.N * a.P * a.Q * a.ldy < (1LL << 31);
+}
+
 // The fused add (a.add set) exists for unpadded 1x1 stride-1 layers with whole 64-byte steps and whole
 // channel tiles of any tile shape (K a multiple of 256), in the lean epilogue.
 bool conv_mfma_fuses(const ConvArgs &a)
 {
     if (!a.add || !conv_mfma_supports(a)) return false;
     if (a.R != 1 || a.S != 1 || a.stride != 1 || a.pad != 0 || a.C % kStepBytes || a.K % 256) return false;
-    const int s_lo = a.shift + (a.frac_w ? a.frac_w_lo : 0), s_hi = a.shift + (a.frac_w ? a.frac_w_hi : 0);
-    if (s_lo < 0 || s_hi > 23 || a.acc_out || !a.y || (a.ldy & 15) || ((uintptr_t)a.y & 15)) return false;
     const long long M = (long long)a.N * a.P * a.Q;
-    if (M * a.ldy >= (1LL << 31) || M * a.ldadd >= (1LL << 31)) return false;
+    if (!conv_mfma_lean(a) || M * a.ldadd >= (1LL << 31)) return false;
     if (a.frac_w && M <= 1024) return false;      // two calls: the convolution's own int8 tensor and the add
     if (((uintptr_t)a.add & 15) || (a.ldadd & 15) || a.ldadd < a.K) return false;
     if (!(a.add_shift >= 0 && a.add_shift <= 23) || a.add_sa < 0 || a.add_sa > 22 || a.add_sb < 0 || a.add_sb > 22) return false;
@@ -635,10 +639,8 @@ enum class Wide { none, t64, t128x64, t128, t128w8, t256 };
 Wide choose_wide(const ConvArgs &a)
 {
     if (a.C % 128 || a.K % 64 || !conv_mfma_supports(a) || (a.add && !conv_mfma_fuses(a))) return Wide::none;
-    const int s_lo = a.shift + (a.frac_w ? a.frac_w_lo : 0), s_hi = a.shift + (a.frac_w ? a.frac_w_hi : 0);
+    if (!conv_mfma_lean(a)) return Wide::none;
     const long long M = (long long)a.N * a.P * a.Q;
-    if (s_lo < 0 || s_hi > 23) return Wide::none;
-    if (a.acc_out || !a.y || (a.ldy & 15) || ((uintptr_t)a.y & 15) || M * a.ldy >= (1LL << 31)) return Wide::none;
     // All figures in us, steps of 64 bytes (or the input-resident kernel for unpadded 1x1 layers of 128 and 256 channels) against these.
     if (a.K % 128) return (M + 127) / 128 * (a.K / 64) >= 256 ? Wide::t128x64 : Wide::t64;      // 256 -> 64 at 56 x 56: 256 images 51.6, 43.1; 12 images 7.2, 6.2
     // fewer than three 128 x 128 tiles for four compute units: 64 x 64, three workgroups per unit (3x3 256 -> 256 at 14 x 14, 32

@@ -319,17 +319,19 @@ Shape choose(const ConvArgs &a)
     const long long t16 = ((M + 15) / 16) * ((a.K + 15) / 16), t32 = ((M + 31) / 32) * ((a.K + 31) / 32);
     if (t16 <= 512) return Shape::t16;
     const int n = (a.R * a.S * a.C + kRow - 1) / kRow;
-    // Fitted to 60 layer sizes: this kernel takes 3 us + (2 + 0.4 n) ns per 32 x 32 tile; the general one, while its tiles do not
+    // Fitted to 1300 layer sizes: this kernel takes 3 us + (2 + 0.4 n) ns per 32 x 32 tile; the general one, while its tiles do not
     // fill the chip, 3 us + 0.28 us per 128 bytes of the reduction in steps of that length, 0.7 us in steps of 64, twice that
-    // where a ragged K takes its general epilogue.  At the line: 3x3 256 -> 256 at 14 x 14, four images 8.4 -> 5.8 us, twelve
+    // where a ragged K takes its general epilogue.  Its 64 x 64 tiles for at most 1024 pixels, six stages in flight, do as well as
+    // the long steps (96 -> 576, 980 pixels 4.1, here 4.9; 320 -> 320 4.3, 4.8), and so does any of its tiles where the reduction
+    // is a single step (64 -> 64 at 56 x 56, one image 3.9, 4.4).  At the line: 3x3 256 -> 256 at 14 x 14, four images 8.4 -> 5.8 us, twelve
     // (592 tiles) 8.45 against 8.0; 1x1 512 -> 256 at 28 x 28, one image 4.4 -> 4.3, four 4.7 against 6.2; 3x3 64 -> 64 at
     // 56 x 56, four images 7.6 -> 6.7, twelve 8.7 against 14.4.
     int per_step = 280;
     if (!conv_mfma_wide(a)) {
-        // the input-resident kernel has no chain and is faster at once where C is no multiple of 128 (64 -> 64 at 56 x 56: 3.4
-        // against 3.9)
-        if (conv_pw_geometry_ok(a) && a.C % kRow) return Shape::none;
-        per_step = a.K % (a.K <= 64 ? 64 : 128) ? 1400 : 700;
+        // the input-resident kernel has no chain and is faster at once where C is no multiple of 128 (64 -> 448 at 35 x 35, two
+        // images: 4.0 against 6.8)
+        if (conv_pw_supports(a) && a.C % kRow) return Shape::none;
+        if (!(conv_mfma_lean(a) && a.K % 64 == 0 && (M <= 1024 || n == 1))) per_step = a.K % (a.K <= 64 ? 64 : 128) ? 1400 : 700;
     }
     if (t32 * (20 + 4 * n) > (long long)per_step * n * 10) return Shape::none;
     return t32_shape(t32, n);

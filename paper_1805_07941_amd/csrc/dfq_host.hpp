@@ -90,6 +90,7 @@ bool conv_rag_supports(const ConvArgs &a);      // any channel count, grouping a
 bool conv_rag_pays(const ConvArgs &a);          // it supports the call and beats the direct kernel on it
 hipError_t launch_conv_rag(const ConvArgs &a, hipStream_t st);
 bool conv_mfma_supports(const ConvArgs &a);
+bool conv_mfma_lean(const ConvArgs &a);      // the result, its address and the shifts suit the lean epilogue
 bool conv_mfma_fuses(const ConvArgs &a);     // a.add set: the dense kernel has a fused form for this call
 bool conv_mfma_wide(const ConvArgs &a);      // launch_conv_mfma() takes the call in steps of 128 bytes, faster than any other kernel but conv_sk
 hipError_t launch_conv_mfma(const ConvArgs &a, hipStream_t st);

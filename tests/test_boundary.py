@@ -370,6 +370,11 @@ def test_kernel_selection(B):
     assert s(1, 14, 14, 128, 256, 1, 1, 1, 0, 1) == B.CONV_SPLIT
     assert s(1, 7, 7, 256, 512, 1, 1, 1, 0, 1) == B.CONV_SPLIT
     assert s(1, 14, 14, 64, 256, 1, 1, 1, 0, 1) == B.CONV_SPLIT
+    # short reductions whose 64 x 64 (or single-step) tiles need no splitting
+    assert s(5, 14, 14, 96, 576, 1, 1, 1, 0, 1) == B.CONV_MFMA
+    assert s(5, 14, 14, 320, 320, 1, 1, 1, 0, 1) == B.CONV_MFMA
+    assert s(1, 56, 56, 64, 64, 1, 1, 1, 0, 1) == B.CONV_MFMA
+    assert s(5, 14, 14, 192, 384, 3, 3, 1, 1, 1) == B.CONV_SPLIT
     assert s(1, 8, 8, 0, 4, 1, 1, 1, 0, 1) == B.CONV_AUTO          # invalid geometry
     assert s(1, 8, 8, 20, 10, 2, 3, 1, 1, 5) == B.CONV_GROUPED     # groups of four channels
     assert s(1, 8, 8, 15, 10, 2, 3, 1, 1, 5) == B.CONV_DIRECT      # groups of three channels: no kernel but the direct one
