@@ -649,19 +649,42 @@ Wide choose_wide(const ConvArgs &a)
     if (t128 < 192) return Wide::t64;
     const int n = a.R * a.S * (a.C / 128);
     const bool pointwise = a.R == 1 && a.S == 1;
+    // (the lines below: 770 layer sizes under every shape)
+    // one or two steps over a result that no cache holds: the input-resident kernel streams it (256 images of 28 x 28, 256 -> 768 90.6,
+    // there 77.7; 139 images, 128 -> 1408 66.3, 56.8; half of that size, 256 -> 768, 128 images: 37.5, there 41.3)
+    if (!a.add && pointwise && a.stride == 1 && a.pad == 0 && n <= 2 && a.K >= 512 && t128 >= 8000 && conv_pw_supports(a)) return Wide::none;
+    if (!a.frac_w && a.K % 256 == 0) {
+        const long long t256 = (M + 255) / 256 * (a.K / 256), rounds = (t256 + kNumCU - 1) / kNumCU;
+        // half the fill traffic again, where the tiles occupy most of the chip in every round and the chain is long enough to pay for
+        // one workgroup per unit (256 images: 3x3 256 -> 256 at 14 x 14 36.2, 32.9 - 128 x 128 39.8; 1x1 512 -> 1024, four steps and
+        // 3.06 rounds, 48.7, 44.4 - 128 x 128 43.6)
+        if (n >= 8 && t256 * 20 >= rounds * kNumCU * 11) return Wide::t256;
+        // a single round from four or six steps on, also because the next layer then finds a tile's rows in one L2 (a
+        // depthwise-separable network of 128 images: 512 -> 512 at 14 x 14 13.6 and the depthwise layer behind it 12.1, with 128 x 128
+        // 15.5 and 15.0).  512 -> 2048 at 7 x 7, 100 images, four steps in 160 tiles: 12.5, 128 x 128 10.9; 768 -> 1280 at 14 x 14, 41
+        // images, six steps in 160 tiles: 15.5, 17.8
+        if (rounds == 1 && ((n >= 6 && t256 * 20 >= kNumCU * 11) || (n >= 4 && t256 * 10 >= kNumCU * 7))) return Wide::t256;
+        // many rounds: less traffic counts more than a round's tail (73 images of 56 x 56, 384 -> 512 92.8, 74.4; 256 images of
+        // 20 x 20, 384 -> 768 58.5, 53.0; 158 images of 17 x 17, 768 -> 1024, six steps in 2856 tiles of 128 x 128, 44.9, 39.9; but
+        // two steps in 3136, 256 -> 1024 at 14 x 14: 128 x 128 is 12 % faster)
+        if (!a.add && ((n >= 2 && t128 >= 3900) || (n >= 5 && t128 >= 2700))) return Wide::t256;
+    }
+    // little more than one round of 128 x 128 tiles, two per unit: 128 x 64, three per unit, waste less of the second (384 -> 768 at
+    // 20 x 20, 32 images 11.7, 9.8, with the add 15.5, 11.5; 384 -> 384, 3x3, 64 images 54.6, 45.2).  Channel tiles that are a power
+    // of two in number meet one L2 whole and lose nothing (512 -> 512, 100 images of 14 x 14: 12.4, 13.2), but with a format per
+    // channel (13.2, 12.2); and with one the same holds behind the second round (384 -> 768 at 20 x 20, 64 images 19.8, 18.1)
+    const int tiles_c = a.K / 128;
+    const bool scattered = tiles_c & (tiles_c - 1);
+    if (t128 >= 560 && t128 <= 624 && (a.frac_w || scattered)) return Wide::t128x64;
+    if (t128 >= 1080 && t128 <= 1210 && a.frac_w && scattered) return Wide::t128x64;
     // the per-channel epilogue has room at 64 x 64 outputs per wavefront, two wavefronts per SIMD (3x3 128 -> 128 at 28 x 28, 256
     // images 46.4, 39.8)
     if (a.frac_w) return Wide::t128;
-    // half the fill traffic again, where the tiles occupy most of the chip in every round and the chain is long enough to pay for
-    // one workgroup per unit (256 images: 3x3 256 -> 256 at 14 x 14 36.2, 32.9 - 128 x 128 39.8; 1x1 512 -> 1024, four steps and
-    // 3.06 rounds, 48.7, 44.4 - 128 x 128 43.6); in a single round from four steps on, also because the next layer then finds a
-    // tile's rows in one L2 (a depthwise-separable network of 128 images: 512 -> 512 at 14 x 14 13.6 and the depthwise layer behind
-    // it 12.1, with 128 x 128 15.5 and 15.0)
-    const long long t256 = (M + 255) / 256 * (a.K / 256), rounds = (t256 + kNumCU - 1) / kNumCU;
-    if (a.K % 256 == 0 && t256 * 20 >= rounds * kNumCU * 11 && (n >= 8 || (n >= 4 && rounds == 1))) return Wide::t256;
     // eight wavefronts of 32 x 64 hide latency best (128 -> 512 at 28 x 28, 256 images 42.6, 34.6, with four of 64 x 64 36.6); four
-    // need fewer operand reads (512 -> 128 at 28 x 28 30.5, 28.4 - eight 30.7; 128 -> 512 with the add 69.6, 64.8 - eight 66.9)
-    return (pointwise && a.K <= 256 && n >= 4) || (a.add && n == 1) ? Wide::t128 : Wide::t128w8;
+    // need fewer operand reads (512 -> 128 at 28 x 28 30.5, 28.4 - eight 30.7; 128 -> 512 with the add 69.6, 64.8 - eight 66.9) and
+    // start sooner, which shows where a round of short chains does not fill the chip (12 images of 28 x 28, 128 -> 512 5.9, 5.3)
+    if ((pointwise && a.K <= 256 && n >= 4) || (a.add && n == 1)) return Wide::t128;
+    return pointwise && n <= 3 && t128 > 256 && t128 <= 512 ? Wide::t128 : Wide::t128w8;
 }
 
 }  // namespace

@@ -370,6 +370,9 @@ def test_kernel_selection(B):
     assert s(1, 14, 14, 128, 256, 1, 1, 1, 0, 1) == B.CONV_SPLIT
     assert s(1, 7, 7, 256, 512, 1, 1, 1, 0, 1) == B.CONV_SPLIT
     assert s(1, 14, 14, 64, 256, 1, 1, 1, 0, 1) == B.CONV_SPLIT
+    # one step over a result that no cache holds
+    assert s(256, 28, 28, 256, 768, 1, 1, 1, 0, 1) == B.CONV_POINTWISE
+    assert s(128, 28, 28, 256, 768, 1, 1, 1, 0, 1) == B.CONV_MFMA
     # short reductions whose 64 x 64 (or single-step) tiles need no splitting
     assert s(5, 14, 14, 96, 576, 1, 1, 1, 0, 1) == B.CONV_MFMA
     assert s(5, 14, 14, 320, 320, 1, 1, 1, 0, 1) == B.CONV_MFMA

@@ -67,6 +67,7 @@ def test_conv_split_reduction(B, shape):
 
 @pytest.mark.parametrize("shape", [(1, 7, 7, 512, 2048), (1, 14, 14, 256, 1024), (6, 28, 28, 128, 512),          # split reduction
                                    (23, 27, 31, 64, 256), (9, 37, 41, 256, 384), (31, 14, 14, 256, 1024),       # input-resident
+                                   (13, 31, 31, 128, 768),                                                      # dense, 128 x 64
                                    (19, 21, 19, 320, 256)],                                                     # dense
                          ids=lambda s: "x".join(map(str, s)))
 def test_fused_add_by_size(B, shape):

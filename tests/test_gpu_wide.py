@@ -25,6 +25,9 @@ SHAPES = [
     (40, 31, 29, 128, 256, 3, 3, 1, 1),          # 256 x 256, 141 tiles
     (40, 61, 57, 128, 256, 3, 3, 2, 1),
     (47, 21, 19, 1024, 512, 1, 1, 1, 0),         # two channel tiles
+    (26, 30, 32, 128, 384, 1, 1, 1, 0),          # 128 x 64 for a little more than one round of 128 x 128
+    (27, 30, 30, 128, 384, 3, 3, 1, 1),
+    (25, 14, 14, 256, 1024, 1, 1, 1, 0),         # 128 x 128, four wavefronts, a short chain
 ]
 
 
