@@ -64,7 +64,8 @@ typedef enum {
     DFQ_CONV_GROUPED = 6,  /* 1 < groups with (C/groups) % 4 == 0: vector-ALU kernel (4-way int8 dot products, weights in LDS);
                               S in {1, 3, 5, 7}, stride 1 or 2, K*R*S*C/groups <= 64 KB, 4-byte aligned x and w */
     DFQ_CONV_RAGGED = 7,   /* int8 MFMA for any channel count, grouping, kernel size and alignment (W*C >= 16 and at least 16 weights);
-                              dfq_conv_q picks it for what no kernel above takes, from 8 output channels per group on */
+                              dfq_conv_q picks it for what no kernel above takes, where it is faster than one output
+                              per lane (not with one or two output channels in a group) */
     DFQ_CONV_SPLIT = 8,    /* int8 MFMA with the reduction split inside a workgroup: any call that DFQ_CONV_MFMA takes; dfq_conv_q picks
                               it for layers too small to fill the chip */
     DFQ_CONV_POINTWISE = 5 /* int8 MFMA with the input tile resident in LDS; unpadded 1x1 stride 1, groups == 1,

@@ -16,7 +16,7 @@
 // A workgroup of four wavefronts owns BM pixels x BK channels of one group and walks the pieces four (64 bytes) at a time
 // through two LDS stages: while one is multiplied, the loads of the step behind the next are in flight in registers.
 // 24 KB of LDS let five or six workgroups share a compute unit, which is what hides the load latency.
-// Measured on 16 x 57 x 43 x 83 -> 131, 3x3 (7.7 GOP): 9.2 ms with one output per lane (conv_direct.hip) -> 26 us, 295 TOP/s, the vector
+// Measured on 16 x 57 x 43 x 83 -> 131, 3x3 (7.7 GOP): 9.2 ms with one output per lane (conv_direct.hip) -> 22.6 us, 340 TOP/s, the vector
 // ALUs busy 60 % of the time and the matrix pipes 12 %; 20 x 28 x 28 x 250 -> 250, 1x1: 2.49 ms -> 10.5 us; 19 x 14 x 13 in 32 groups of
 // 13 -> 3, 3x3: 63 -> 11 us.
 #include "conv_epilogue.hpp"
@@ -284,10 +284,30 @@ bool conv_rag_supports(const ConvArgs &a)
     return (((long long)a.P * a.Q + 63) / 64) * a.groups * ((a.K / a.groups + 31) / 32) < (1LL << 31);
 }
 
-// A tile has at least 32 output channels of one group: with one or two in the group nearly all of its products are padding.
-// Measured against one output per lane (conv_direct.hip), 8 x 24 x 24 pixels, 3x3: groups of 5 -> 5 channels 14 us against 44,
-// 19 x 14 x 13 pixels in groups of 13 -> 3 12 against 63, one channel per group (71 of them) 20 against 12.
-bool conv_rag_pays(const ConvArgs &a) { return (a.groups == 1 || a.K / a.groups >= 3) && conv_rag_supports(a); }
+// Against one output per lane (conv_direct.hip).  A tile has at least 32 output channels of one group and 16 bytes for every tap of
+// one, so with few channels in a group most of its products are padding, while the other kernel's time grows with the products that
+// are wanted.  Both times as fitted to 3400 layers (1 to 64 groups of 1 .. 23 -> 1 .. 16 channels, 1x1 to 5x5, 49 to 12544 pixels), in
+// ns; the line lies where they meet, with a sixteenth for the fit.  One or two outputs in a group were not fitted and stay with
+// the other kernel; so do fewer than four products per output with fewer than twelve outputs in a group, where both mostly load.
+// Measured, this kernel against the other: 8 x 28 x 28 pixels, 3x3, 32 groups of 1 -> 3 16.7 us, 9.9; of 2 -> 3 18.0, 12.0; of
+// 3 -> 3 18.7, 20.7; of 15 -> 16, 5x5, 32.7, 3470; 14 x 14 pixels, 3x3, 32 groups of 1 -> 8 6.6, 4.9; 28 x 28, 1x1, 8 images, one
+// group of 2 -> 11 4.6, 3.6; of 83 -> 131, 16 x 57 x 43, 3x3 22.6 us against 9.2 ms.
+bool conv_rag_pays(const ConvArgs &a)
+{
+    const long long Cg = a.C / a.groups, Kg = a.K / a.groups, taps = (long long)a.R * a.S;
+    if ((a.groups > 1 && Kg < 3) || !conv_rag_supports(a)) return false;
+    if (taps * Cg < 4 && Kg < 12) return false;
+    const double M = (double)a.N * a.P * a.Q, outputs = M * a.K;
+    const double direct = 2990.0 + taps * (100.0 + 70.0 * Cg) + outputs * 0.0035 + outputs * taps * Cg * (Cg > 2 && taps > 1 ? 58e-5 : 44e-5);
+    const long long pieces = a.groups == 1 ? a.R * ((a.S * Cg + 15) / 16) : taps * ((Cg + 15) / 16), steps = (pieces + 3) / 4;
+    const int bm = Kg <= 32 ? 128 : 64;
+    const double tiles = (double)((long long)(M + bm - 1) / bm) * a.groups * ((Kg + 31) / 32), tail = tiles > 1280 ? tiles - 1280 : 0;
+    double here = 3630.0 + 725.0 * steps + tiles * (1.36 + 1.4 * steps) + 1.1 * tail * steps;
+    // the general epilogue (870 pixels, 1x1, 8 groups of 18 -> 16, formats per channel: 6.7 us, 4.7; accumulators of 8 x 48 x 42
+    // pixels in 32 groups of 2 -> 18 49.4, 41)
+    if (a.acc_out || a.frac_w || a.shift < 0 || a.shift > 23) here += 2200.0 + (a.acc_out ? 8.0 : 4.0) * tiles;
+    return direct * 15.0 > here * 16.0;
+}
 
 static hipError_t launch_images(const ConvArgs &a, hipStream_t st)
 {

@@ -370,6 +370,16 @@ def test_kernel_selection(B):
     assert s(1, 14, 14, 128, 256, 1, 1, 1, 0, 1) == B.CONV_SPLIT
     assert s(1, 7, 7, 256, 512, 1, 1, 1, 0, 1) == B.CONV_SPLIT
     assert s(1, 14, 14, 64, 256, 1, 1, 1, 0, 1) == B.CONV_SPLIT
+    # no whole pieces: the matrix cores where the padding they multiply costs less than one output per lane
+    assert s(16, 57, 43, 83, 131, 3, 3, 1, 1, 1) == B.CONV_RAGGED
+    assert s(8, 28, 28, 83, 1, 3, 3, 1, 1, 1) == B.CONV_RAGGED
+    assert s(8, 28, 28, 480, 512, 5, 5, 1, 2, 32) == B.CONV_RAGGED
+    assert s(4, 56, 56, 32, 512, 1, 1, 1, 0, 32) == B.CONV_RAGGED
+    assert s(8, 28, 28, 32, 96, 3, 3, 1, 1, 32) == B.CONV_DIRECT
+    assert s(8, 28, 28, 64, 96, 3, 3, 1, 1, 32) == B.CONV_DIRECT
+    assert s(1, 14, 14, 32, 256, 3, 3, 1, 1, 32) == B.CONV_DIRECT
+    assert s(6, 10, 24, 20, 20, 1, 1, 1, 0, 4) == B.CONV_DIRECT
+    assert s(2, 20, 20, 26, 52, 3, 3, 1, 1, 26) == B.CONV_DIRECT
     # one step over a result that no cache holds
     assert s(256, 28, 28, 256, 768, 1, 1, 1, 0, 1) == B.CONV_POINTWISE
     assert s(128, 28, 28, 256, 768, 1, 1, 1, 0, 1) == B.CONV_MFMA
