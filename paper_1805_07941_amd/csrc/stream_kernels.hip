@@ -769,10 +769,13 @@ static inline int grid_for_reduction(size_t work_items)
     return g < 512 ? g : 512;
 }
 
-// the maximum only grows: a workgroup whose own is no news (a plain read of the word says so) spares it the atomic
-__device__ __forceinline__ void raise_to(uint32_t *out, uint32_t m)
+// The result of one of `sharers` workgroups that raise the same word.  A single one stores it, and nobody clears the word first;
+// up to one per compute unit send their atomics straight away (100000 values, 98 workgroups: 5.1 us, with a read before 5.6); of many, most see by a
+// read that theirs is no news - the maximum only grows - and spare the word the atomic.
+__device__ __forceinline__ void raise_to(uint32_t *out, uint32_t m, unsigned sharers)
 {
-    if (m > __hip_atomic_load(out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(out, m);
+    if (sharers == 1) *out = m;
+    else if (sharers <= 256 || m > __hip_atomic_load(out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(out, m);
 }
 
 __device__ __forceinline__ void block_max_to(uint32_t v, uint32_t *out)
@@ -785,7 +788,7 @@ __device__ __forceinline__ void block_max_to(uint32_t v, uint32_t *out)
         uint32_t m = part[0];
 #pragma unroll
         for (int i = 1; i < kBlock / kWave; i++) m = max(m, part[i]);
-        raise_to(out, m);
+        raise_to(out, m, gridDim.x);
     }
 }
 
@@ -795,22 +798,25 @@ __device__ __forceinline__ uint32_t float_magnitude(float v)
     return a == a ? __float_as_uint(a) : 0u;          // NaN elements are skipped
 }
 
-// 16 bytes per lane and access where the array is aligned for it; the first lanes of the launch take the tail
+// 16 bytes at any boundary of four
+template <class T>
+struct __attribute__((packed, aligned(4))) Four {
+    T v[4];
+};
+
+// 16 bytes per lane and access; the first lanes of the launch take the tail.  (50 M values that start 4 bytes behind such a boundary:
+// a value per lane and access 170 us, here 36.)
 __global__ void __launch_bounds__(kBlock) absmax_f32_kernel(const float *__restrict__ x, size_t n, uint32_t *out)
 {
     uint32_t m = 0;
-    const size_t t = (size_t)blockIdx.x * kBlock + threadIdx.x, threads = (size_t)gridDim.x * kBlock;
-    size_t n4 = 0;
-    if (((uintptr_t)x & 15) == 0) {
-        n4 = n / 4;
-        const float4 *x4 = (const float4 *)x;
+    const size_t t = (size_t)blockIdx.x * kBlock + threadIdx.x, threads = (size_t)gridDim.x * kBlock, n4 = n / 4;
+    const Four<float> *x4 = (const Four<float> *)x;
 #pragma unroll 4
-        for (size_t i = t; i < n4; i += threads) {
-            const float4 v = x4[i];
-            m = max(max(m, float_magnitude(v.x)), max(float_magnitude(v.y), max(float_magnitude(v.z), float_magnitude(v.w))));
-        }
+    for (size_t i = t; i < n4; i += threads) {
+        const Four<float> q = x4[i];
+        m = max(max(m, float_magnitude(q.v[0])), max(float_magnitude(q.v[1]), max(float_magnitude(q.v[2]), float_magnitude(q.v[3]))));
     }
-    for (size_t i = n4 * 4 + t; i < n; i += threads) m = max(m, float_magnitude(x[i]));
+    if (t < n % 4) m = max(m, float_magnitude(x[n4 * 4 + t]));
     block_max_to(m, out);
 }
 
@@ -819,22 +825,17 @@ __device__ __forceinline__ uint32_t magnitude(int v, int relu)
     return v >= 0 ? (uint32_t)v : (relu ? 0u : (uint32_t)0 - (uint32_t)v);
 }
 
-// 16 bytes per lane and access where the array is aligned for it; the first lanes of the launch take the tail
 __global__ void __launch_bounds__(kBlock) absmax_i32_kernel(const int32_t *__restrict__ x, size_t n, int relu, uint32_t *out)
 {
     uint32_t m = 0;
-    const size_t t = (size_t)blockIdx.x * kBlock + threadIdx.x, threads = (size_t)gridDim.x * kBlock;
-    size_t n4 = 0;
-    if (((uintptr_t)x & 15) == 0) {
-        n4 = n / 4;
-        const int4 *x4 = (const int4 *)x;
+    const size_t t = (size_t)blockIdx.x * kBlock + threadIdx.x, threads = (size_t)gridDim.x * kBlock, n4 = n / 4;
+    const Four<int32_t> *x4 = (const Four<int32_t> *)x;
 #pragma unroll 4
-        for (size_t i = t; i < n4; i += threads) {
-            const int4 v = x4[i];
-            m = max(max(m, magnitude(v.x, relu)), max(magnitude(v.y, relu), max(magnitude(v.z, relu), magnitude(v.w, relu))));
-        }
+    for (size_t i = t; i < n4; i += threads) {
+        const Four<int32_t> q = x4[i];
+        m = max(max(m, magnitude(q.v[0], relu)), max(magnitude(q.v[1], relu), max(magnitude(q.v[2], relu), magnitude(q.v[3], relu))));
     }
-    for (size_t i = n4 * 4 + t; i < n; i += threads) m = max(m, magnitude(x[i], relu));
+    if (t < n % 4) m = max(m, magnitude(x[n4 * 4 + t], relu));
     block_max_to(m, out);
 }
 
@@ -844,25 +845,25 @@ __global__ void clear_u32_n(uint32_t *p, int n)
     if (i < n) p[i] = 0u;
 }
 
-// The same maximum per channel of a [pixels][K] array.  A lane keeps VEC neighbouring channels and walks down the pixels (lanes of
-// a row of channels read it whole, a workgroup holds as many rows as fit); the workgroup's rows meet in LDS, and one lane
-// per channel raises the result.  512 workgroups: with a thread per element and one atomic per thread, a layer of 8 x 112 x
-// 112 x 64 sums (26 MB) took 300 us, now 15.
+// The same maximum per channel of a [pixels][K] array.  A lane keeps VEC neighbouring channels and walks down the pixels; `lanes` of
+// them (at most a wavefront) read a window of a row, a workgroup holds as many rows of its window as fit; they meet in LDS,
+// and one lane per channel raises the result.  Windows of 64 lanes and not of the whole workgroup: with the same number of
+// workgroups fewer share a channel's word, and few pixels still make several of them (us, a thread per element and
+// an atomic per thread / windows of 256 lanes / here: 6272 x 1024 sums 25, 32, 11; 49 x 2048 4.8, 7.4, 5.0; 100352 x 64 311, 20, 18).
 template <int VEC>
 __global__ void __launch_bounds__(kBlock) absmax_i32_channels_kernel(const int32_t *__restrict__ x, size_t pixels, int K, int relu,
-                                                                      uint32_t *out)
+                                                                      uint32_t *out, int lanes, int windows)
 {
-    __shared__ uint32_t best[kBlock * VEC];
+    __shared__ uint32_t best[kWave * VEC];
     const int chunks = K / VEC;                                         // VEC-channel pieces of a pixel
-    for (int c0 = blockIdx.y * kBlock; c0 < chunks; c0 += gridDim.y * kBlock) {
-        const int mine = min(chunks - c0, kBlock), rows = kBlock / mine;
-        const int r = threadIdx.x / mine, c = threadIdx.x - r * mine;
-        for (int i = threadIdx.x; i < mine * VEC; i += kBlock) best[i] = 0u;
-        __syncthreads();
-        if (r < rows) {
-            uint32_t m[VEC];
+    const int rows = kBlock / lanes, r = threadIdx.x / lanes, c = threadIdx.x - r * lanes;
+    for (int w = blockIdx.y; w < windows; w += gridDim.y) {
+        const int c0 = w * lanes, mine = min(chunks - c0, lanes);
+        if ((int)threadIdx.x < mine * VEC) best[threadIdx.x] = 0u;      // lanes * VEC <= kBlock
+        uint32_t m[VEC];
 #pragma unroll
-            for (int e = 0; e < VEC; e++) m[e] = 0u;
+        for (int e = 0; e < VEC; e++) m[e] = 0u;
+        if (r < rows && c < mine) {
             const size_t step = (size_t)gridDim.x * rows;
 #pragma unroll 4
             for (size_t p = (size_t)blockIdx.x * rows + r; p < pixels; p += step) {
@@ -877,11 +878,14 @@ __global__ void __launch_bounds__(kBlock) absmax_i32_channels_kernel(const int32
                     m[0] = max(m[0], magnitude(*src, relu));
                 }
             }
+        }
+        __syncthreads();
+        if (r < rows && c < mine) {
 #pragma unroll
             for (int e = 0; e < VEC; e++) atomicMax(&best[c * VEC + e], m[e]);
         }
         __syncthreads();
-        for (int i = threadIdx.x; i < mine * VEC; i += kBlock) raise_to(out + (size_t)c0 * VEC + i, best[i]);
+        if ((int)threadIdx.x < mine * VEC) raise_to(out + (size_t)c0 * VEC + threadIdx.x, best[threadIdx.x], gridDim.x);
         __syncthreads();
     }
 }
@@ -916,15 +920,17 @@ hipError_t launch_absmax_f32_rows(const float *x, size_t rows, size_t row_len, f
 
 hipError_t launch_absmax_f32(const float *x, size_t n, float *out, hipStream_t st)
 {
-    clear_u32<<<1, 1, 0, st>>>((uint32_t *)out);
-    if (n) absmax_f32_kernel<<<grid_for_reduction(n / 4 + 1), kBlock, 0, st>>>(x, n, (uint32_t *)out);
+    const int g = n ? grid_for_reduction(n / 4 + 1) : 0;
+    if (g != 1) clear_u32<<<1, 1, 0, st>>>((uint32_t *)out);           // one workgroup stores its maximum
+    if (g) absmax_f32_kernel<<<g, kBlock, 0, st>>>(x, n, (uint32_t *)out);
     return hipGetLastError();
 }
 
 hipError_t launch_absmax_i32(const int32_t *x, size_t n, int relu, uint32_t *out, hipStream_t st)
 {
-    clear_u32<<<1, 1, 0, st>>>(out);
-    if (n) absmax_i32_kernel<<<grid_for_reduction(n / 4 + 1), kBlock, 0, st>>>(x, n, relu, out);
+    const int g = n ? grid_for_reduction(n / 4 + 1) : 0;
+    if (g != 1) clear_u32<<<1, 1, 0, st>>>(out);                       // one workgroup stores its maximum
+    if (g) absmax_i32_kernel<<<g, kBlock, 0, st>>>(x, n, relu, out);
     return hipGetLastError();
 }
 
@@ -968,16 +974,17 @@ hipError_t launch_hist_i32(const int32_t *x, size_t n, int relu, int shift, uint
 
 hipError_t launch_absmax_i32_channels(const int32_t *x, size_t pixels, int K, int relu, uint32_t *out, hipStream_t st)
 {
-    clear_u32_n<<<(K + kBlock - 1) / kBlock, kBlock, 0, st>>>(out, K);
-    if (pixels) {
-        const bool vec = K % 4 == 0 && aligned(x, 16);
-        const int chunks = vec ? K / 4 : K;
-        const int windows = (chunks + kBlock - 1) / kBlock;             // of 256 pieces
-        // at least eight rows per lane: a workgroup ends with one atomic per channel, on words it shares with all others
-        const int gx = grid_for_reduction(pixels * (size_t)(chunks < kBlock ? chunks : kBlock) / 8 + 1);
-        const dim3 grid((unsigned)(windows < gx ? (windows > 4 && gx > 128 ? 128 : gx) : 1), (unsigned)(windows < 4096 ? windows : 4096));
-        if (vec) absmax_i32_channels_kernel<4><<<grid, kBlock, 0, st>>>(x, pixels, K, relu, out);
-        else absmax_i32_channels_kernel<1><<<grid, kBlock, 0, st>>>(x, pixels, K, relu, out);
+    const bool vec = K % 4 == 0 && aligned(x, 16);
+    const int chunks = vec ? K / 4 : K, windows = (chunks + kWave - 1) / kWave, lanes = (chunks + windows - 1) / windows;
+    // four rows per lane or more; two workgroups per compute unit, or four where they are spread over many windows
+    const int target = windows < 8 ? 512 : 1024;
+    const size_t rows = (size_t)(kBlock / lanes) * 4, full = (pixels + rows - 1) / rows, most = windows < target ? target / windows : 1;
+    const unsigned gx = (unsigned)(full < most ? full : most);
+    if (gx != 1) clear_u32_n<<<(K + kBlock - 1) / kBlock, kBlock, 0, st>>>(out, K);        // one workgroup stores its maxima
+    if (gx) {
+        const dim3 grid(gx, (unsigned)(windows < 4096 ? windows : 4096));
+        if (vec) absmax_i32_channels_kernel<4><<<grid, kBlock, 0, st>>>(x, pixels, K, relu, out, lanes, windows);
+        else absmax_i32_channels_kernel<1><<<grid, kBlock, 0, st>>>(x, pixels, K, relu, out, lanes, windows);
     }
     return hipGetLastError();
 }

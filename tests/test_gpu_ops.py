@@ -835,6 +835,40 @@ def test_absmax_per_channel_wide_and_tall(B):
     assert float(host(B.absmax_f32(xd[1:]))[0]) == 9.0
 
 
+@pytest.mark.parametrize("pixels,K", [(1, 1), (1, 1000), (16, 256), (17, 260), (3, 65), (7, 129), (600, 8), (2100, 64), (2100, 66), (9, 131076)],
+                         ids=lambda v: str(v))
+def test_absmax_per_channel_windows(B, pixels, K):
+    """One window of channels and several, full and not; one workgroup per window, which stores without the result being cleared,
+    few, and more than a hundred, which look before they raise it.  The result's memory holds large values beforehand."""
+    rng = np.random.default_rng(pixels * 7 + K)
+    a = rng.integers(-2 ** 31, 2 ** 31, (pixels, K), dtype=np.int64).astype(np.int32)
+    a[:, K // 2] = 0
+    out = torch.full((K,), -1, dtype=torch.int32, device=DEV)
+    for relu in (False, True):
+        out.fill_(-1)
+        got = B.absmax_i32_channels_value(B.absmax_i32_channels(dev(a), relu=relu, out_dev=out)).astype(np.int64)
+        assert np.array_equal(got, orc.absmax_i32_channels(a, relu=relu)), relu
+
+
+@pytest.mark.parametrize("n", [0, 1, 1023, 1024, 9408, 131072, 140001])
+def test_absmax_of_few_and_many(B, n):
+    """One workgroup (stores), few, and more than a hundred; from 16-byte boundaries and not, into memory that holds large values."""
+    rng = np.random.default_rng(n)
+    f = rng.standard_normal(n + 1).astype(np.float32)
+    if n > 3:
+        f[n // 2] = np.nan
+    i = rng.integers(-2 ** 20, 2 ** 20, n + 1).astype(np.int32)
+    for first in (0, 1):
+        fo = torch.full((1,), 1e30, dtype=torch.float32, device=DEV)
+        io = torch.full((1,), -1, dtype=torch.int32, device=DEV)
+        fs, is_ = f[first:n + first], i[first:n + first]
+        got = float(B.absmax_f32(dev(f)[first:n + first], out_dev=fo).cpu()[0])
+        assert got == (float(np.nanmax(np.abs(fs))) if n else 0.0), first
+        got = B.absmax_i32_value(B.absmax_i32(dev(i)[first:n + first], out_dev=io))
+        assert got == (int(np.abs(is_.astype(np.int64)).max()) if n else 0), first
+
+
+
 def test_formats_from_a_row_of_thresholds(B):
     g = np.array([0.0, 127.0, 127.1, 1e-30, 3e38, 1.0, 63.5], np.float32)
     assert B.fmt_from_absmax_f32_rows(g).tolist() == [B.fmt_from_absmax_f32(float(v)) for v in g]
