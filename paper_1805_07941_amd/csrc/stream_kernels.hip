@@ -432,9 +432,18 @@ __global__ void __launch_bounds__(kBlock) concat_kernel(ConcatParams p, int8_t *
         const int pc = (int)(i - px * p.pieces[p.nb]);
         const int8_t *src = p.x[0];
         int C = p.C[0], off = 0, first = 0, s = p.s[0];
+        if constexpr (VEC == 1) {
+            // (one byte per lane: the branch's number alone is cheaper to select; 50176 pixels of 3 + 64 channels 10.0 us, else 10.7)
+            int br = 0;
 #pragma unroll
-        for (int j = 1; j < 8; j++)
-            if (j < p.nb && pc >= p.pieces[j]) { src = p.x[j]; C = p.C[j]; off = p.off[j]; first = p.pieces[j]; s = p.s[j]; }
+            for (int j = 1; j < 8; j++)
+                if (j < p.nb && pc >= p.pieces[j]) br = j;
+            src = p.x[br]; C = p.C[br]; off = p.off[br]; first = p.pieces[br]; s = p.s[br];
+        } else {
+#pragma unroll
+            for (int j = 1; j < 8; j++)
+                if (j < p.nb && pc >= p.pieces[j]) { src = p.x[j]; C = p.C[j]; off = p.off[j]; first = p.pieces[j]; s = p.s[j]; }
+        }
         const int c = min((pc - first) * VEC, C - VEC);
         const Piece<VEC> v = *(const Piece<VEC> *)(src + px * (size_t)C + c);
         Piece<VEC> o;
@@ -532,10 +541,11 @@ __global__ void __launch_bounds__(kBlock) pool_scalar_kernel(const int8_t *__res
         for (int r = 0; r < p.k; r++) {
             const int ih = pp * p.stride - p.pad + r;
             if (ih < 0 || ih >= p.H) continue;
-            for (int s = 0; s < p.k; s++) {
-                const int iw = q * p.stride - p.pad + s;
-                if (iw < 0 || iw >= p.W) continue;
-                const int v = x[(((size_t)n * p.H + ih) * p.W + iw) * p.C + c];
+            const int first = max(0, p.pad - q * p.stride), end = min(p.k, p.W + p.pad - q * p.stride);
+            const int8_t *src = x + (((size_t)n * p.H + ih) * p.W + (q * p.stride - p.pad + first)) * p.C + c;
+#pragma unroll 4
+            for (int s = first; s < end; s++, src += p.C) {
+                const int v = *src;
                 acc = p.mode == 0 ? max(acc, v) : acc + v;
             }
         }
@@ -648,21 +658,29 @@ __global__ void __launch_bounds__(kBlock) pool_kernel(const int8_t *__restrict__
                 }
         }
         Piece<VEC> o;
+        if (!MEAN && p.d == 0) {
+            // no rescale: the high bytes as they are, -128 saturated (sixteen branches that skip the rescale value by value took longer
+            // than the maxima: 64 x 28 x 28 x 192, 3x3 / 2, 5.6 us, now 4.7)
+            const v2s least = {(short)(-127 * 256), (short)(-127 * 256)};
 #pragma unroll
-        for (int j = 0; j < W; j++) {
-            int v[4];
-            if constexpr (MEAN) {
+            for (int j = 0; j < W; j++)
+                o.w[j] = (__builtin_bit_cast(uint32_t, __builtin_elementwise_max(odd[j], least)) & 0xff00ff00u) |
+                         ((__builtin_bit_cast(uint32_t, __builtin_elementwise_max(even[j], least)) >> 8) & 0x00ff00ffu);
+        } else {
 #pragma unroll
-                for (int e = 0; e < 4; e++) v[e] = mean_round(sum[4 * j + e], prm);
-            } else {
-                v[0] = even[j][0] >> 8;
-                v[1] = odd[j][0] >> 8;
-                v[2] = even[j][1] >> 8;
-                v[3] = odd[j][1] >> 8;
+            for (int j = 0; j < W; j++) {
+                int v[4];
+                if constexpr (MEAN) {
 #pragma unroll
-                for (int e = 0; e < 4; e++) v[e] = p.d == 0 ? max(v[e], -127) : requant8(v[e], -p.d);
+                    for (int e = 0; e < 4; e++) v[e] = mean_round(sum[4 * j + e], prm);
+                } else {
+                    v[0] = requant8(even[j][0] >> 8, -p.d);
+                    v[1] = requant8(odd[j][0] >> 8, -p.d);
+                    v[2] = requant8(even[j][1] >> 8, -p.d);
+                    v[3] = requant8(odd[j][1] >> 8, -p.d);
+                }
+                o.w[j] = pack4(v[0], v[1], v[2], v[3]);
             }
-            o.w[j] = pack4(v[0], v[1], v[2], v[3]);
         }
         *(Piece<VEC> *)(y + (size_t)px * p.C + c) = o;
     }
