@@ -39,16 +39,24 @@ def _read_f32(t: torch.Tensor) -> float:
     return float(t.cpu()[0])
 
 
-def float_weights(net, device, fold: bool = True) -> Dict[str, tuple]:
-    """Float weights and bias of every convolution on the device (fold: the affine layers behind them folded in where the
-    network has them).  The many small bias vectors travel as one array: an upload costs 15 us whatever it holds."""
-    convs = [nd for nd in net.nodes if nd.op == "conv"]
-    host = [net.weights(nd) for nd in convs]
-    biases = torch.from_numpy(np.concatenate([b for _, b in host]) if host else np.zeros(0, np.float32)).to(device)
-    out, off = {}, 0
-    for nd, (w, b) in zip(convs, host):
-        wf, bf = torch.from_numpy(w).to(device), biases[off:off + b.size]
-        off += b.size
+# Float weights that are on the device (and on the host) together while a network is calibrated.  One read-back of thresholds serves a
+# group of layers of this size: every network up to 64 M weights is one group, and a larger one never holds more than a group, or
+# its largest layer, in floats.
+WEIGHT_GROUP_BYTES = 256 << 20
+
+
+def _upload(layers, net, device, fold: bool) -> Dict[str, tuple]:
+    """[(node, weights, bias)] as {name: (weights, bias)} on the device.  The many small bias vectors travel as one array: an upload
+    costs 15 us whatever it holds.  (Arrays that are no float32 vectors go one by one, so that each keeps its type.)"""
+    bias = [b for _, _, b in layers]
+    if all(b.dtype == np.float32 and b.ndim == 1 for b in bias):
+        joined = torch.from_numpy(np.concatenate(bias)).to(device)
+        bias = joined.split([b.size for b in bias])
+    else:
+        bias = [torch.from_numpy(b).to(device) for b in bias]
+    out = {}
+    for (nd, w, _), bf in zip(layers, bias):
+        wf = torch.from_numpy(w).to(device)
         if fold and getattr(net, "scale_layers", False):
             # the affine layer behind the convolution is folded into the float weights before they are quantized
             scale, shift = net.scale_shift(nd)
@@ -57,34 +65,53 @@ def float_weights(net, device, fold: bool = True) -> Dict[str, tuple]:
     return out
 
 
+def float_weights(net, device, fold: bool = True):
+    """Yields the float weights and bias of every convolution on the device, {name: (weights, bias)}, in groups of at most
+    WEIGHT_GROUP_BYTES (or one layer); fold: the affine layers behind them folded in where the network has them."""
+    group, held = [], 0
+    for nd in net.nodes:
+        if nd.op != "conv":
+            continue
+        w, b = net.weights(nd)
+        if group and held + w.nbytes > WEIGHT_GROUP_BYTES:
+            yield _upload(group, net, device, fold)
+            group, held = [], 0
+        group.append((nd, w, b))
+        held += w.nbytes
+    if group:
+        yield _upload(group, net, device, fold)
+
+
 def _quantize_weights(net, qz: "Quantized", device, per_channel: bool) -> Dict[str, torch.Tensor]:
     """Weight formats and codes of all layers into qz; returns the float biases (their scale waits for the layer's input).
-    Weight thresholds depend on the weights alone, so those of the whole network are read back together: one synchronization where
+    Weight thresholds depend on the weights alone, so those of a group of layers are read back together: one synchronization where
     a layer-by-layer loop has one per layer, with the device idle around each."""
-    raw = float_weights(net, device)
-    gamma = torch.empty(sum(int(w.shape[0]) if per_channel else 1 for w, _ in raw.values()), dtype=torch.float32, device=device)
-    off = 0
-    for w, _ in raw.values():
-        if per_channel:
-            B.absmax_f32_rows(w, out_dev=gamma[off:off + int(w.shape[0])])
-            off += int(w.shape[0])
-        else:
-            B.absmax_f32(w, out_dev=gamma[off:off + 1])
-            off += 1
-    f_all = B.fmt_from_absmax_f32_rows(gamma.cpu().numpy())
-    f_dev = torch.from_numpy(f_all).to(device) if per_channel else None
-    off = 0
-    for name, (w, _) in raw.items():
-        if per_channel:
-            end = off + int(w.shape[0])
-            qz.w_frac[name], qz.w_frac_dev[name] = f_all[off:end], f_dev[off:end]
-            qz.w[name] = B.quantize_rows(w, qz.w_frac_dev[name])
-            off = end
-        else:
-            qz.w_frac[name] = int(f_all[off])
-            qz.w[name] = B.quantize(w, qz.w_frac[name])
-            off += 1
-    return {name: b for name, (_, b) in raw.items()}
+    biases = {}
+    for raw in float_weights(net, device):
+        gamma = torch.empty(sum(int(w.shape[0]) if per_channel else 1 for w, _ in raw.values()), dtype=torch.float32, device=device)
+        off = 0
+        for w, _ in raw.values():
+            if per_channel:
+                B.absmax_f32_rows(w, out_dev=gamma[off:off + int(w.shape[0])])
+                off += int(w.shape[0])
+            else:
+                B.absmax_f32(w, out_dev=gamma[off:off + 1])
+                off += 1
+        f_all = B.fmt_from_absmax_f32_rows(gamma.cpu().numpy())
+        f_dev = torch.from_numpy(f_all).to(device) if per_channel else None
+        off = 0
+        for name, (w, b) in raw.items():
+            if per_channel:
+                end = off + int(w.shape[0])
+                qz.w_frac[name], qz.w_frac_dev[name] = f_all[off:end], f_dev[off:end]
+                qz.w[name] = B.quantize_rows(w, qz.w_frac_dev[name])
+                off = end
+            else:
+                qz.w_frac[name] = int(f_all[off])
+                qz.w[name] = B.quantize(w, qz.w_frac[name])
+                off += 1
+            biases[name] = b
+    return biases
 
 
 def _threshold(acc: torch.Tensor, relu: bool, rule: str) -> int:
