@@ -653,9 +653,12 @@ def absmax_i32(x: torch.Tensor, relu: bool = False, out_dev: Optional[torch.Tens
 
 
 def absmax_f32_rows(x: torch.Tensor, stream=None, out_dev: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """max |.| of every row of a float32 [rows, ...] tensor: float32 device tensor [rows] (no synchronization)."""
+    """max |.| of every row of a float32 [rows, ...] tensor: float32 device tensor [rows] (no synchronization; into out_dev, which
+    holds that many, if given)."""
     _dev(x, torch.float32, "x")
     rows = int(x.shape[0])
+    if out_dev is not None and _dev(out_dev, torch.float32, "out_dev").numel() < rows:
+        raise ValueError("out_dev: %d values for %d rows" % (out_dev.numel(), rows))
     out = out_dev if out_dev is not None else torch.empty(rows, dtype=torch.float32, device=x.device)
     _check(lib().dfq_absmax_f32_rows(_ptr(x), rows, x.numel() // max(rows, 1), _ptr(out), _stream(stream)),
            "dfq_absmax_f32_rows")

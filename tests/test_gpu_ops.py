@@ -850,6 +850,16 @@ def test_absmax_per_channel_windows(B, pixels, K):
         assert np.array_equal(got, orc.absmax_i32_channels(a, relu=relu)), relu
 
 
+def test_absmax_rows_into_a_given_tensor(B):
+    x = dev(np.random.default_rng(8).standard_normal((5, 7)).astype(np.float32))
+    out = torch.full((6,), -1.0, dtype=torch.float32, device=DEV)
+    assert B.absmax_f32_rows(x, out_dev=out) is out
+    assert np.array_equal(host(out)[:5], np.abs(host(x)).max(1)) and host(out)[5] == -1.0
+    for bad, error in ((out[:4], ValueError), (out.double(), TypeError), (out.cpu(), TypeError), (torch.zeros(12, device=DEV)[::2], TypeError)):
+        with pytest.raises(error):
+            B.absmax_f32_rows(x, out_dev=bad)
+
+
 @pytest.mark.parametrize("n", [0, 1, 1023, 1024, 9408, 131072, 140001])
 def test_absmax_of_few_and_many(B, n):
     """One workgroup (stores), few, and more than a hundred; from 16-byte boundaries and not, into memory that holds large values."""
