@@ -24,6 +24,7 @@
 // dword reads and a byte-funnel shift.  It needs rows of a multiple of 4 bytes, at least 32 output
 // pixels per row, and spans that fit 64 dwords; the first kernel remains for the rest.
 #include "conv_ring.hpp"
+#include "weight_reads.hpp"
 
 namespace dfq {
 
@@ -53,17 +54,7 @@ __device__ __forceinline__ void pack_weights(const SmallCParams &prm, int8_t *wb
         const int h = i & 1, kl = (i >> 1) % BC, r = (i >> 1) / BC, k = k0 + kl;
         const long long o = ((long long)min(k, a.K - 1) * a.R + r) * prm.run + 16 * h;
         const int count = k < a.K ? min(16, prm.run - 16 * h) : 0;     // bytes of the piece that are weights, may be <= 0
-        unsigned __int128 v = 0;
-        if (total >= 16) {
-            // from o, or from the last place that lies inside the tensor and shifted down: one path for all (byte loads for the
-            // last piece alone were a chain that every workgroup waited for)
-            const long long at = min(o, total - 16);
-            __builtin_memcpy(&v, a.w + at, 16);
-            v = o - at < 16 ? v >> (8 * (int)(o - at)) : 0;
-        } else {
-            for (int e = 0; e < count; e++) v |= (unsigned __int128)(uint8_t)a.w[o + e] << (8 * e);
-        }
-        v = count <= 0 ? 0 : count < 16 ? v & (((unsigned __int128)1 << (8 * count)) - 1) : v;
+        const unsigned __int128 v = weight_piece(a.w, total, o, count);
         // LDS row of channel kl follows the same permutation as the dense kernel: a lane's 16 accumulators are 16
         // consecutive channels
         const int c32 = kl & 31;

@@ -31,6 +31,7 @@
 #include <type_traits>
 
 #include "conv_ring.hpp"
+#include "weight_reads.hpp"
 
 namespace dfq {
 
@@ -74,19 +75,8 @@ __device__ __forceinline__ void stem_setup(const ConvArgs &a, int8_t *lds, int *
     for (int t = tid; t < R * BC; t += THREADS) {
         const int kl = t % BC, r = t / BC;
         const int o = (min(kl, a.K - 1) * R + r) * a.S * 3;
-        // 24 bytes from o, or from the last place that lies inside the tensor (K >= 32: it has that many) and shifted down: one
-        // path for all (byte loads for the last blocks alone were a chain of 9 to 21 trips that every workgroup waited for)
-        const int at = max(0, min(o, total - 24)), sh = o - at;
         unsigned long long q[3];
-        __builtin_memcpy(q, a.w + at, 24);
-        if (sh >= 16) { q[0] = q[2]; q[1] = q[2] = 0; }
-        else if (sh >= 8) { q[0] = q[1]; q[1] = q[2]; q[2] = 0; }
-        const int bits = 8 * (sh & 7);
-        if (bits) {
-            q[0] = q[0] >> bits | q[1] << (64 - bits);
-            q[1] = q[1] >> bits | q[2] << (64 - bits);
-            q[2] >>= bits;
-        }
+        weight_run24(a.w, total, o, q);                         // (K >= 32: the tensor has 24 bytes)
         const uint32_t d[7] = {(uint32_t)q[0], (uint32_t)(q[0] >> 32), (uint32_t)q[1], (uint32_t)(q[1] >> 32), (uint32_t)q[2], (uint32_t)(q[2] >> 32), 0};
         uint32_t tap[8];                                        // the three weights of tap s, zeros past the last tap
 #pragma unroll

