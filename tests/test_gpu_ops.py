@@ -910,6 +910,22 @@ def test_pool_q_any_channels_and_alignment(B, mode, C):
             assert (got[:5] == 99).all() and (got[5 + ref.size:] == 99).all()
 
 
+@pytest.mark.parametrize("mode", ["max", "avg"])
+def test_pool_batch_beyond_31_bit_pieces(B, mode):
+    """Over 2^31 pieces of four channels (5.7 GB): the batch is cut into launches.  Against pools of a few images on both sides of the
+    cut and at the ends, and between them nothing is left out."""
+    H, C = 33, 5
+    most = (2 ** 31 - 256 * 16 * 256 - 1) // (32 * 32 * 2)              # images of the first launch: two pieces a pixel
+    N = most + 100
+    x = torch.randint(-128, 128, (N, H, H, C), dtype=torch.int8, device=DEV, generator=torch.Generator(device=DEV).manual_seed(4))
+    y = torch.full((N, 32, 32, C), -128, dtype=torch.int8, device=DEV)  # a code that no result has
+    B.pool_q(x, mode, 2, 1, 0, 4, 5, out=y)
+    for first in (0, most - 2, most, N - 3):
+        part = slice(first, first + 3)
+        assert np.array_equal(host(y[part]), orc.pool_q(host(x[part]), mode, 2, 1, 0, 4, 5)), first
+    assert bool((y.amin(dim=(1, 2, 3)) > -128).all())
+
+
 def test_concat_q_any_channels(B):
     rng = np.random.default_rng(7)
     for Cs in [(1, 2, 3), (4, 5), (16,), (17, 16, 33), (90, 90, 90), (15, 64), (100, 4, 7, 18, 16, 31, 5, 6)]:

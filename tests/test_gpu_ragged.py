@@ -73,3 +73,24 @@ def test_conv_ragged(B, shape):
     y_ref, _ = orc.conv_q(x, w, b, 4, f_w, 4, st, pad, g, False)
     y, _ = B.conv_q_pc(dev(x), dev(w), dev(b), 4, dev(f_w), 4, st, pad, g, False)
     assert np.array_equal(host(y), y_ref)
+
+
+def test_batch_beyond_31_bit_offsets(B):
+    """2.3 GB of input: the batch is cut into launches whose byte offsets fit 31 bits.  Result in a channel slice of a wider tensor and
+    accumulators, against calls of a few images on both sides of the cut and at the ends."""
+    N, H, C, K = 17200, 64, 33, 5
+    most = (2 ** 31 - 1 - (1 + 3) * H * C) // (H * H * C)               # images of the first launch
+    assert most < N
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randint(-128, 128, (N, H, H, C), dtype=torch.int8, device="cuda", generator=gen)
+    w = torch.randint(-128, 128, (K, 3, 3, C), dtype=torch.int8, device="cuda", generator=gen)
+    b = torch.randint(-10000, 10001, (K,), dtype=torch.int32, device="cuda", generator=gen)
+    wide = torch.full((N, 32, 32, K + 3), 77, dtype=torch.int8, device="cuda")
+    acc = torch.empty((N, 32, 32, K), dtype=torch.int32, device="cuda")
+    B.conv_q(x, w, b, 4, 13, 4, 2, 1, 1, False, out=wide.view(-1)[2:], ldy=K + 3, acc_out=acc, variant=B.CONV_RAGGED)
+    for first in (0, most - 2, most, N - 3):
+        part = slice(first, first + 3)
+        y_ref, acc_ref = orc.conv_q(host(x[part]), host(w), host(b), 4, 13, 4, 2, 1, 1, False, want_acc=True)
+        assert np.array_equal(host(acc[part]), acc_ref), first
+        assert np.array_equal(host(wide[part])[..., 2:2 + K], y_ref), first
+    assert bool((wide[..., :2] == 77).all()) and bool((wide[..., 2 + K:] == 77).all())
