@@ -65,10 +65,10 @@ def test_conv_split_reduction(B, shape):
     assert np.array_equal(host(y), y_ref)
 
 
-@pytest.mark.parametrize("shape", [(1, 7, 7, 512, 2048), (1, 14, 14, 256, 1024), (6, 28, 28, 128, 512),          # split reduction
-                                   (23, 27, 31, 64, 256), (9, 37, 41, 256, 384), (31, 14, 14, 256, 1024),       # input-resident
-                                   (13, 31, 31, 128, 768),                                                      # dense, 128 x 64
-                                   (19, 21, 19, 320, 256)],                                                     # dense
+@pytest.mark.parametrize("shape", [(1, 7, 7, 512, 2048), (1, 14, 14, 256, 768), (1, 14, 14, 640, 768),                # split reduction, its three shapes
+                                   (23, 27, 31, 64, 256), (19, 21, 19, 192, 320), (9, 37, 41, 256, 384),             # input-resident
+                                   (1, 14, 14, 256, 1024), (6, 28, 28, 128, 512), (31, 14, 14, 256, 1024),           # dense: 64 x 64, 128 x 128
+                                   (13, 31, 31, 128, 768), (19, 21, 19, 320, 256)],                                  # dense: 128 x 64, steps of 64 bytes
                          ids=lambda s: "x".join(map(str, s)))
 def test_fused_add_by_size(B, shape):
     N, H, W, C, K = shape
@@ -88,7 +88,11 @@ def test_fused_add_by_size(B, shape):
         mid, _ = orc.conv_q(x, w, b, f_in, f_wk, f_mid, 1, 0, 1, relu_mid)
         ref, _ = orc.eltwise_q(mid, f_mid, other, f_other, f_out, relu_out)
         got = B.conv_q_pc_add(xd, wd, bd, od, f_in, dev(f_wk), (f_w - 2, f_w + 1), f_mid, relu_mid, f_other, f_out, relu_out)
-        assert got is None or np.array_equal(host(got), ref)
+        # per-channel formats over at most 1024 pixels are declined where the input-resident kernel's buffers and tables do not fit
+        if N * H * W <= 1024 and (C > 256 or 512 * C + 192 * (64 if K % 128 else 128) + 16 * K > 160 * 1024):
+            assert got is None
+        else:
+            assert got is not None and np.array_equal(host(got), ref)
 
 
 @pytest.mark.parametrize("shape", [(1, 64, 64, 3, 64, 7, 7, 2, 3), (3, 36, 64, 3, 32, 3, 3, 2, 1), (2, 44, 96, 3, 64, 3, 3, 2, 0), (1, 33, 37, 3, 50, 7, 7, 2, 3),
