@@ -60,23 +60,24 @@ def calibrate(net, x: torch.Tensor, p: int = 4, device="cuda:0"):
     f_in = net.fixed_f_input if net.fixed_f_input is not None else B.np_frac_from_absmax_f32(float(B.absmax_f32(x).cpu()[0]), 8, p)
     qz.frac[net.input_name] = f_in
     t = {net.input_name: B.np_digits(B.quantize_np(x, 8, p, f_in), p)}
-    # thresholds of a group of layers read back together (they depend on the weights alone)
-    biases = {}
-    for raw in float_weights(net, device, fold=False):
-        gamma = torch.empty(len(raw), dtype=torch.float32, device=device)
-        for i, (wf, _) in enumerate(raw.values()):
-            B.absmax_f32(wf, out_dev=gamma[i:i + 1])
-        for (name, (wf, bf)), g in zip(raw.items(), gamma.cpu().numpy()):
-            qz.w_frac[name] = B.np_frac_from_absmax_f32(float(g), 8, p)
-            qz.w_codes[name] = B.quantize_np(wf, 8, p, qz.w_frac[name])
-            biases[name] = bf
+    # thresholds of a group of layers are read back together (they depend on the weights alone), when its first layer is reached
+    groups, raw, w_frac = float_weights(net, device, fold=False), {}, {}
     for nd in net.nodes:
         if nd.op == "conv":
             src = nd.srcs[0]
             f_x = qz.frac[src]
-            f_w = qz.w_frac[nd.name]
+            if nd.name not in raw:
+                raw = next(groups)
+                gamma = torch.empty(len(raw), dtype=torch.float32, device=device)
+                for i, (wf, _) in enumerate(raw.values()):
+                    B.absmax_f32(wf, out_dev=gamma[i:i + 1])
+                w_frac = {name: B.np_frac_from_absmax_f32(float(g), 8, p) for name, g in zip(raw, gamma.cpu().numpy())}
+            wf, bf = raw.pop(nd.name)
+            f_w = w_frac[nd.name]
+            qz.w_frac[nd.name] = f_w
+            qz.w_codes[nd.name] = B.quantize_np(wf, 8, p, f_w)
             wh, wl = B.np_digits(qz.w_codes[nd.name], p)
-            qz.b[nd.name] = B.quantize_i32(biases[nd.name], f_x + f_w)
+            qz.b[nd.name] = B.quantize_i32(bf, f_x + f_w)
             K = wh.shape[0]
             if packs(net, nd):
                 wh, wl = B.stem_pack_w(wh), B.stem_pack_w(wl)
