@@ -59,7 +59,7 @@ struct NpConvArgs {
     int add_sa, add_sb;            // left shifts of the layer's result and of the other operand to the finer scale
     int add_shift;                 // that scale's fractional length minus the output's, 0..31
     int add_relu;                  // ReLU on the sum
-    unsigned long long *amax;      // calibration: receives max |sum + bias| (after ReLU if relu) by atomic max; direct form only
+    unsigned long long *amax;      // calibration: receives max |sum + bias| (after ReLU if relu) by atomic max
 };
 
 hipError_t launch_quantize(const float *x, int8_t *q, size_t n, int frac, hipStream_t st);
