@@ -557,7 +557,7 @@ __global__ void __launch_bounds__(kBlock) pool_scalar_kernel(const int8_t *__res
 // Window positions in the padding are replaced by the nearest one inside the image - for the maximum it lies in the same window
 // (pad < k), for the mean its bytes are dropped - so no load depends on a branch: with K > 0 the K*K loads of a window are all in
 // flight together, with a window size only known at run time (K == 0) four of a row at a time.
-// Bound by memory and issue; 24 x 45 x 61 x 90, 3x3 / 1: 48.9 us with byte accesses, now 10 us.
+// Bound by memory and issue; 24 x 45 x 61 x 90, 3x3 / 1: 48.9 us with byte accesses, now 10.3.
 struct PoolVecParams {
     PoolParams p;
     int pieces;          // of a pixel

@@ -23,6 +23,8 @@ def launched(calls):
             call()
         torch.cuda.synchronize()
     events = [e for e in prof.events() if e.device_type == torch.autograd.DeviceType.CUDA and "conv_" in e.name]
+    if not events:
+        pytest.skip("the device's activity is not recorded here")
     return [e.name for e in sorted(events, key=lambda e: e.time_range.start)]
 
 
