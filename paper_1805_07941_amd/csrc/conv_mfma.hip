@@ -678,6 +678,8 @@ Wide choose_wide(const ConvArgs &a)
     const int tiles_c = a.K / 128;
     const bool scattered = tiles_c & (tiles_c - 1);
     if (t128 >= 560 && t128 <= 624 && (a.frac_w || scattered)) return Wide::t128x64;
+    // (three channel tiles up to one and a half rounds: 384 -> 384, 58 images of 20 x 20 11.9, 9.8; 640 -> 384, 10 of 56 x 56 17.6, 15.6)
+    if (t128 >= 530 && t128 <= 760 && tiles_c == 3 && !a.frac_w) return Wide::t128x64;
     if (t128 >= 1080 && t128 <= 1210 && a.frac_w && scattered) return Wide::t128x64;
     // the per-channel epilogue has room at 64 x 64 outputs per wavefront, two wavefronts per SIMD (3x3 128 -> 128 at 28 x 28, 256
     // images 46.4, 39.8)
