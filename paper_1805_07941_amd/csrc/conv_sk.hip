@@ -320,20 +320,22 @@ Shape choose(const ConvArgs &a)
     if (t16 <= 512) return Shape::t16;
     const int n = (a.R * a.S * a.C + kRow - 1) / kRow;
     // Fitted to 1300 layer sizes: this kernel takes 3 us + (2 + 0.4 n) ns per 32 x 32 tile; the general one, while its tiles do not
-    // fill the chip, 3 us + 0.28 us per 128 bytes of the reduction in steps of that length, 0.7 us in steps of 64, twice that
-    // where a ragged K takes its general epilogue.  Its 64 x 64 tiles for at most 1024 pixels, six stages in flight, do as well as
-    // the long steps (96 -> 576, 980 pixels 4.1, here 4.9; 320 -> 320 4.3, 4.8), and so does any of its tiles where the reduction
-    // is a single step (64 -> 64 at 56 x 56, one image 3.9, 4.4).  At the line: 3x3 256 -> 256 at 14 x 14, four images 8.4 -> 5.8 us, twelve
+    // fill the chip, 3 us + 0.28 us per 128 bytes of the reduction in steps of that length, 0.7 us in steps of 64, and up
+    // to 22 us more where a ragged K takes its general epilogue (5x5 448 -> 832 at 45 x 77, one image, a format per channel:
+    // 72.7, here 94.7; 176 -> 36 at 9 x 62, 82 images 46.8, here 40.6).  Its 64 x 64 tiles for at most 1024 pixels, six stages
+    // in flight, do as well as the long steps (96 -> 576, 980 pixels 4.1, here 4.9; 320 -> 320 4.3, 4.8), and so does any of its
+    // tiles where the reduction is a single step (64 -> 64 at 56 x 56, one image 3.9, 4.4).  At the line: 3x3 256 -> 256 at 14 x 14, four images 8.4 -> 5.8 us, twelve
     // (592 tiles) 8.45 against 8.0; 1x1 512 -> 256 at 28 x 28, one image 4.4 -> 4.3, four 4.7 against 6.2; 3x3 64 -> 64 at
     // 56 x 56, four images 7.6 -> 6.7, twelve 8.7 against 14.4.
-    int per_step = 280;
+    long long price = 280LL * n;
     if (!conv_mfma_wide(a)) {
         // the input-resident kernel has no chain and is faster at once where C is no multiple of 128 (64 -> 448 at 35 x 35, two
         // images: 4.0 against 6.8)
         if (conv_pw_supports(a) && a.C % kRow) return Shape::none;
-        if (!(conv_mfma_lean(a) && a.K % 64 == 0 && (M <= 1024 || n == 1))) per_step = a.K % (a.K <= 64 ? 64 : 128) ? 1400 : 700;
+        if (!(conv_mfma_lean(a) && a.K % 64 == 0 && (M <= 1024 || n == 1)))
+            price = 700LL * n + (a.K % (a.K <= 64 ? 64 : 128) ? 700LL * (n < 32 ? n : 32) : 0);
     }
-    if (t32 * (20 + 4 * n) > (long long)per_step * n * 10) return Shape::none;
+    if (t32 * (20 + 4 * n) > price * 10) return Shape::none;
     return t32_shape(t32, n);
 }
 
