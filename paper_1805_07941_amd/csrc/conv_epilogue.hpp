@@ -193,39 +193,6 @@ __device__ __forceinline__ void store_tile_lane_fast(const v16i &v, const ConvAr
     *(uint4 *)(a.y + (size_t)m * a.ldy + kc) = requant_tile_lane_fast(v, rq);
 }
 
-// General form (ragged channel tail, unaligned rows, extreme shifts, accumulator dump, one weight
-// format per output channel).
-__device__ __forceinline__ void store_tile_lane_general(const v16i &v, const ConvArgs &a, int shift, int relu, long long m, int kc)
-{
-    // a whole 16-channel group into an aligned row, no accumulator dump: any shifts, one 16-byte store
-    if (!a.acc_out && a.y && kc + 16 <= a.K && (((unsigned)a.ldy | (unsigned)kc) & 15u) == 0 && ((uintptr_t)a.y & 15) == 0) {
-        uint32_t o[4];
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            int q[4];
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                const int r = 4 * j + e;
-                ChannelRequant cr;
-                cr.init(a.frac_w ? shift + a.frac_w[kc + r] : shift);
-                q[e] = cr.apply(v[r], relu);
-            }
-            o[j] = pack4_clamped(q[0], q[1], q[2], q[3]);
-        }
-        *(uint4 *)(a.y + (size_t)m * a.ldy + kc) = make_uint4(o[0], o[1], o[2], o[3]);
-        return;
-    }
-#pragma unroll
-    for (int r = 0; r < 16; r++) {
-        if (kc + r < a.K) {
-            const int val = v[r];
-            if (a.acc_out) a.acc_out[(size_t)m * a.K + kc + r] = val;
-            const int s = a.frac_w ? shift + a.frac_w[kc + r] : shift;
-            if (a.y) a.y[(size_t)m * a.ldy + kc + r] = (int8_t)requant8(relu ? max(val, 0) : val, s);
-        }
-    }
-}
-
 // 16 bytes at any byte address
 struct __attribute__((packed, aligned(1))) Bytes16 {
     uint32_t w[4];
@@ -242,15 +209,27 @@ __device__ __forceinline__ void store_bytes(const Bytes16 &o, int8_t *dst, int c
         if (r < count) dst[r] = (int8_t)(o.w[r >> 2] >> (8 * (r & 3)));
 }
 
-// Any row pitch and any number `count` (1 .. 16) of the lane's channels kc, kc + 1, ...: whole groups go out as one 16-byte
+// The sums of a lane's `count` (1 .. 16) channels kc, kc + 1, ... of pixel m, in words of 16 bytes where the layout has them (a
+// dword per store took longer than the products: 128 channels of 25088 pixels 27 us of a layer, 13 MB).
+__device__ __forceinline__ void store_sums(const v16i &v, const ConvArgs &a, long long m, int kc, int count)
+{
+    int32_t *dst = a.acc_out + (size_t)m * a.K + kc;
+    if ((a.K & 3) == 0 && ((uintptr_t)a.acc_out & 15) == 0) {    // kc is a multiple of four, so count is one too
+#pragma unroll
+        for (int r = 0; r < 16; r += 4)
+            if (r < count) *(int4 *)(dst + r) = make_int4(v[r], v[r + 1], v[r + 2], v[r + 3]);
+    } else {
+#pragma unroll
+        for (int r = 0; r < 16; r++)
+            if (r < count) dst[r] = v[r];
+    }
+}
+
+// Any row pitch, shift and number `count` (1 .. 16) of the lane's channels kc, kc + 1, ...: whole groups go out as one 16-byte
 // store at whatever address the pitch gives them (byte stores to a pitch of 131 took as long as the products of the layer).
 __device__ __forceinline__ void store_tile_lane_ragged(const v16i &v, const ConvArgs &a, long long m, int kc, int count)
 {
-    if (a.acc_out) {
-#pragma unroll
-        for (int r = 0; r < 16; r++)
-            if (r < count) a.acc_out[(size_t)m * a.K + kc + r] = v[r];
-    }
+    if (a.acc_out) store_sums(v, a, m, kc, count);
     if (!a.y) return;
     Bytes16 o;
 #pragma unroll
@@ -265,6 +244,21 @@ __device__ __forceinline__ void store_tile_lane_ragged(const v16i &v, const Conv
         }
         o.w[j] = pack4_clamped(q[0], q[1], q[2], q[3]);
     }
+    store_bytes(o, a.y + (size_t)m * a.ldy + kc, count);
+}
+
+// General form of a tile's epilogue (channel tails, unaligned rows, any shift, accumulator dump, one weight format per channel):
+// a uniform shift in the range of the four-instruction rounding takes that, everything else the form above.
+__device__ __forceinline__ void store_tile_lane_general(const v16i &v, const ConvArgs &a, const Requant &rq, long long m, int kc)
+{
+    const int count = min(16, a.K - kc);
+    if (!a.y || a.frac_w || !rq.fast) {
+        store_tile_lane_ragged(v, a, m, kc, count);
+        return;
+    }
+    if (a.acc_out) store_sums(v, a, m, kc, count);
+    const uint4 q = requant_tile_lane_fast(v, rq);
+    const Bytes16 o = {{q.x, q.y, q.z, q.w}};
     store_bytes(o, a.y + (size_t)m * a.ldy + kc, count);
 }
 

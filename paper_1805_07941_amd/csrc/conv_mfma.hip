@@ -339,6 +339,9 @@ __global__ void __launch_bounds__(WAVES_P * WAVES_C * 64, OCC) conv_mfma_kernel(
     constexpr unsigned kHistMask = (1u << (NSTAGES - 1)) - 1u;
     unsigned ep_hist = 0;
     const unsigned lane_yoff = (unsigned)((wp0 + l32) * a.ldy + k0 + wc0 + 16 * lh);   // lean form: y fits 31 bits
+    // a channel tail of whole groups of 16: the lanes past K store nothing (an offset past the buffer).  With one format per channel the
+    // test costs the registers that epilogue does not have (64 -> 64, 3x3 at 51 x 51, 12 images 9.2 -> 10.6 us): whole tiles only there.
+    const int lane_k = k0 + wc0 + 16 * lh;
     const unsigned lane_aoff = (unsigned)((wp0 + l32) * a.ldadd + k0 + wc0 + 16 * lh);
     int c_step = 0, c_tile = lb;
     auto finish_item = [&]() __attribute__((always_inline)) {
@@ -399,10 +402,12 @@ __global__ void __launch_bounds__(WAVES_P * WAVES_C * 64, OCC) conv_mfma_kernel(
                     }
                 } else {
 #pragma unroll
-                    for (int c = 0; c < CT; c++)
+                    for (int c = 0; c < CT; c++) {
+                        // (a fused add has whole channel tiles)
+                        const unsigned dead = FUSE || lane_k + c * 32 < a.K ? 0u : kOutOfRange;
 #pragma unroll
                         for (int p = 0; p < PT; p++) {
-                            const unsigned off = lane_yoff + tile_off + (unsigned)(p * 32 * a.ldy + c * 32);
+                            const unsigned off = (lane_yoff + tile_off + (unsigned)(p * 32 * a.ldy + c * 32)) | dead;
                             if constexpr (FUSE) {
                                 const v4i oth = {(int)other[c * PT + p][0], (int)other[c * PT + p][1], (int)other[c * PT + p][2],
                                                  (int)other[c * PT + p][3]};
@@ -412,6 +417,7 @@ __global__ void __launch_bounds__(WAVES_P * WAVES_C * 64, OCC) conv_mfma_kernel(
                                 store_piece(requant_tile_lane_fast(acc[c][p], rq), off, yrsrc);
                             }
                         }
+                    }
                 }
                 ep_hist |= 1u;
             } else {
@@ -421,7 +427,7 @@ __global__ void __launch_bounds__(WAVES_P * WAVES_C * 64, OCC) conv_mfma_kernel(
 #pragma unroll
                     for (int p = 0; p < PT; p++) {
                         const int m = m0 + wp0 + p * 32 + l32;
-                        if (m < prm.M && kc < a.K) store_tile_lane_general(acc[c][p], a, a.shift, a.relu, m, kc);
+                        if (m < prm.M && kc < a.K) store_tile_lane_general(acc[c][p], a, rq, m, kc);
                     }
                 }
             }
@@ -576,7 +582,7 @@ hipError_t launch_cfg(const ConvArgs &a, hipStream_t st)
     static const hipError_t attr[12] = {big_lds(kernels[0]), big_lds(kernels[1]), big_lds(kernels[2]), big_lds(kernels[3]),
                                         big_lds(kernels[4]), big_lds(kernels[5]), big_lds(kernels[6]), big_lds(kernels[7]),
                                         big_lds(kernels[8]), big_lds(kernels[9]), big_lds(kernels[10]), big_lds(kernels[11])};
-    const bool general = !((!a.frac_w || kernels[6]) && conv_mfma_lean(a) && a.K % BC == 0);
+    const bool general = !((!a.frac_w || kernels[6]) && conv_mfma_lean(a) && (a.frac_w ? a.K % BC : a.K % 16) == 0);
     int which = (!general && a.frac_w) ? (pw ? 7 : ut ? 6 : 8) : (pw ? 4 : ut ? 2 : 0) + (general ? 1 : 0);
     if (a.add) {
         // conv_mfma_fuses() has vouched for the lean pointwise form
@@ -640,11 +646,12 @@ enum class Wide { none, t64, t128x64, t128, t128w8, t256 };
 
 Wide choose_wide(const ConvArgs &a)
 {
-    if (a.C % 128 || a.K % 64 || !conv_mfma_supports(a) || (a.add && !conv_mfma_fuses(a))) return Wide::none;
+    // (few channels in a tile of 64: the 256 x 64 tiles fetch less of the weights' padding, 896 -> 16, 3x3, 43703 pixels 33.8, 44.9)
+    if (a.C % 128 || a.K % (a.frac_w ? 64 : 16) || a.K < 48 || !conv_mfma_supports(a) || (a.add && !conv_mfma_fuses(a))) return Wide::none;
     if (!conv_mfma_lean(a)) return Wide::none;
     const long long M = (long long)a.N * a.P * a.Q;
     // All figures in us, steps of 64 bytes (or the input-resident kernel for unpadded 1x1 layers of 128 and 256 channels) against these.
-    if (a.K % 128) return (M + 127) / 128 * (a.K / 64) >= 256 ? Wide::t128x64 : Wide::t64;      // 256 -> 64 at 56 x 56: 256 images 51.6, 43.1; 12 images 7.2, 6.2
+    if (a.K % 128) return (M + 127) / 128 * ((a.K + 63) / 64) >= 256 ? Wide::t128x64 : Wide::t64;      // 256 -> 64 at 56 x 56: 256 images 51.6, 43.1; 12 images 7.2, 6.2
     // fewer than three 128 x 128 tiles for four compute units: 64 x 64, three workgroups per unit (3x3 256 -> 256 at 14 x 14, 32
     // images 15.5, 10.6; 3x3 512 -> 512 at 7 x 7, 96 images 26.4, 21.4 - with 128 x 128 tiles 25.9)
     const long long t128 = (M + 127) / 128 * (a.K / 128);
@@ -697,18 +704,13 @@ bool conv_mfma_wide(const ConvArgs &a) { return choose_wide(a) != Wide::none; }
 
 hipError_t launch_conv_mfma(const ConvArgs &a, hipStream_t st)
 {
-    // What is left for steps of 64 bytes - channel counts that are no multiple of 128, ragged results, accumulators - by choices
-    // measured at batch 256 (wavefronts own 64 x 64 outputs unless noted):
-    // K <= 64: 256 x 64 tiles (four wavefronts); for kernels larger than 1x1 three workgroups per CU
-    //          with a two-stage ring beat two with three stages (more independent workgroups to
-    //          overlap epilogues with matrix work);
-    // K a multiple of 256, at least 192 tiles of 256 x 256, not a strided kernel larger than 1x1:
-    //          those tiles, eight wavefronts of 64 x 128, one workgroup per CU - half the LDS fill
-    //          traffic per matrix instruction and half the re-reads of the input (4-12 % faster on
-    //          the 14x14 layers and the strided 1x1 shortcuts; with fewer tiles too many CUs stay
-    //          idle, and strided 3x3 layers were 8 % slower);
-    // else:    256 x 128 tiles (eight wavefronts), two workgroups per CU, for kernels larger than 1x1 with enough of them;
-    //          for 1x1 kernels (few items per tile) 128 x 128 tiles (four wavefronts), three per CU.
+    // What is left for steps of 64 bytes: channel counts that are no multiple of 128, K that is no multiple of 16, accumulators
+    // (420 layer sizes under every shape; wavefronts own 64 x 64 outputs unless noted).
+    // K > 64:  128 x 128 tiles (four wavefronts), three workgroups per CU.  256 x 128 and 256 x 256 tiles in steps of 64 bytes were
+    //          slower on all but one (96 -> 128, 3x3, 64 images of 28 x 28: 15.0 -> 13.1 us; 16 -> 128, 5x5, 45 images of 56 x 56 23.9 ->
+    //          19.3; the one: 192 -> 192, 3x3, 195 tiles of 256 pixels 28.6, 31.2).
+    // K <= 64: 128 x 64 tiles (wavefronts of 32 x 64), four workgroups per CU, mean 5 % faster than 256 x 64 - except where those
+    //          leave the last round of long chains fuller, or stream many tiles of a few steps (lines below).
     const bool pointwise = a.R == 1 && a.S == 1;
     switch (choose_wide(a)) {
         case Wide::t64: return launch_cfg<64, 64, 2, 2, 3, 3, 128>(a, st);
@@ -722,19 +724,16 @@ hipError_t launch_conv_mfma(const ConvArgs &a, hipStream_t st)
     // ring six stages deep (accumulators of 64 -> 2048, 128 pixels: 4.4 us, with 128 x 128 tiles 10.7; of 128 -> 512 at 28 x 28,
     // one image 6.8 and 11.9)
     if ((long long)a.N * a.P * a.Q <= 1024 && a.K > 64) return launch_cfg<64, 64, 2, 2, 6, 2>(a, st);
-    // one weight format per output channel: the tile shapes for which that epilogue is built
-    if (a.frac_w && a.K > 64) return launch_cfg<128, 128, 2, 2, 3, 3>(a, st);
-    if (a.K <= 64) return pointwise ? launch_cfg<256, 64, 4, 1, 3, 2>(a, st) : launch_cfg<256, 64, 4, 1, 2, 3>(a, st);
-    if (a.K % 256 == 0 && (pointwise || a.stride == 1)) {
-        const long long M = (long long)a.N * a.P * a.Q;
-        if ((M + 255) / 256 * (a.K / 256) >= 192) return launch_cfg<256, 256, 4, 2, 3, 1>(a, st);
-    }
-    // kernels larger than 1x1 whose 256 x 128 tiles would occupy at most half of the compute units: 128 x 128 tiles, twice as
-    // many workgroups (7 x 7 x 512 -> 512, 3x3, at batch 128: 34.0 -> 28.5 us; at batch 256, with 196 such tiles, the
-    // smaller tiles were slower, 39.7 -> 45.8 us)
-    if (!pointwise && ((long long)a.N * a.P * a.Q + 255) / 256 * ((a.K + 127) / 128) <= kNumCU / 2)
-        return launch_cfg<128, 128, 2, 2, 3, 3>(a, st);
-    return pointwise ? launch_cfg<128, 128, 2, 2, 3, 3>(a, st) : launch_cfg<256, 128, 4, 2, 3, 2>(a, st);
+    const long long t256 = ((long long)a.N * a.P * a.Q + 255) / 256;
+    // a fused add in whole rounds of the chip: its loads hide behind the larger tile's products (320 -> 1280 at 14 x 14, 64 images 15.1,
+    // in 128 x 128 tiles 19.6)
+    if (a.add && !a.frac_w && t256 * (a.K / 256) >= 192) return launch_cfg<256, 256, 4, 2, 3, 1>(a, st);
+    if (a.K > 64) return launch_cfg<128, 128, 2, 2, 3, 3>(a, st);
+    // (larger kernels of 376 .. 499 tiles of 256 pixels lose 4 % in the mean, 64 -> 64, 5x5, 495 tiles 20.3, 22.7; from 900 on 5 %,
+    // 48 -> 64, 3x3, 1963 tiles 26.2, 30.7; below 376 they gain 6 %, 500 .. 899 8 %; one weight format per channel: the epilogue
+    // is built for the 256 x 64 tiles)
+    if (!a.frac_w && (pointwise ? t256 < 1500 : t256 < 376 || (t256 >= 500 && t256 < 900))) return launch_cfg<128, 64, 4, 1, 3, 4>(a, st);
+    return pointwise ? launch_cfg<256, 64, 4, 1, 3, 2>(a, st) : launch_cfg<256, 64, 4, 1, 2, 3>(a, st);
 }
 
 }  // namespace dfq

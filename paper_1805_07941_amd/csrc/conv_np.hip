@@ -407,37 +407,48 @@ __global__ void __launch_bounds__(256) pool_np_kernel(NpPoolParams a)
     }
 }
 
-// Average over the whole unpadded image (k = H = W) with C a multiple of 4: one lane per four channels of an image, word
-// loads, the pixels in turn (neighbouring lanes read neighbouring words).
-__global__ void __launch_bounds__(256) avgpool_global_np4_kernel(NpPoolParams a)
+// Average over the whole unpadded image (k = H = W) with C a multiple of 4: a workgroup takes 32 words of four channels and its eight
+// groups of 32 lanes share the pixels; the partial sums meet in LDS and 128 lanes convert one channel each.  (One lane per word over
+// all pixels with four conversions in turn: 7 x 7 x 2048, 64 images 11.7 us, here 4.9)
+__global__ void __launch_bounds__(256) avgpool_global_np4_kernel(NpPoolParams a, int words, FastDiv div_c4)
 {
-    const int C4 = a.C / 4;
-    const int total = a.N * C4;
-    const int pixels = a.H * a.W;
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
-        const int n = i / C4, c4 = i - n * C4;
+    __shared__ int4 part[8][32];
+    const int C4 = a.C / 4, pixels = a.H * a.W;
+    const int lw = threadIdx.x & 31, group = threadIdx.x >> 5;
+    const int i = blockIdx.x * 32 + lw;
+    int tot[4] = {0, 0, 0, 0};
+    if (i < words) {
+        const int n = fastdiv(i, div_c4), c4 = i - n * C4;
         const uint32_t *ph = (const uint32_t *)a.xh + (size_t)n * pixels * C4 + c4;
         const uint32_t *pl = (const uint32_t *)a.xl + (size_t)n * pixels * C4 + c4;
-        int tot[4] = {0, 0, 0, 0};
-        for (int j = 0; j < pixels; j++) {
-            const uint32_t h4 = ph[(size_t)j * C4], l4 = pl[(size_t)j * C4];
+        for (int j = group; j < pixels; j += 4 * 8) {
+            uint32_t h4[4], l4[4];
 #pragma unroll
-            for (int e = 0; e < 4; e++) tot[e] += 64 * byte_of(h4, e) + byte_of(l4, e);
-        }
-        uint32_t oc = 0, oh = 0, ol = 0;
+            for (int u = 0; u < 4; u++) {
+                const bool in = j + 8 * u < pixels;
+                h4[u] = in ? ph[(size_t)(j + 8 * u) * C4] : 0u;
+                l4[u] = in ? pl[(size_t)(j + 8 * u) * C4] : 0u;
+            }
 #pragma unroll
-        for (int e = 0; e < 4; e++) {
-            const int beta = np_round_mean(tot[e], pixels, a.p_fmt, a.beta_max);
-            int h, l;
-            np_split(beta, h, l);
-            oc |= (uint32_t)np_code_of(beta, a.p_fmt) << (8 * e);
-            oh |= (uint32_t)(uint8_t)h << (8 * e);
-            ol |= (uint32_t)(uint8_t)l << (8 * e);
+            for (int u = 0; u < 4; u++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) tot[e] += 64 * byte_of(h4[u], e) + byte_of(l4[u], e);
         }
-        if (a.y) ((uint32_t *)a.y)[i] = oc;
-        if (a.yh) ((uint32_t *)a.yh)[i] = oh;
-        if (a.yl) ((uint32_t *)a.yl)[i] = ol;
     }
+    part[group][lw] = make_int4(tot[0], tot[1], tot[2], tot[3]);
+    __syncthreads();
+    const int b = threadIdx.x;
+    if (b >= 128 || blockIdx.x * 32 + b / 4 >= words) return;
+    int sum = 0;
+#pragma unroll
+    for (int g = 0; g < 8; g++) sum += ((const int *)&part[g][0])[b];
+    const int beta = np_round_mean(sum, pixels, a.p_fmt, a.beta_max);
+    int h, l;
+    np_split(beta, h, l);
+    const size_t o = (size_t)blockIdx.x * 128 + b;
+    if (a.y) a.y[o] = (uint8_t)np_code_of(beta, a.p_fmt);
+    if (a.yh) a.yh[o] = (int8_t)h;
+    if (a.yl) a.yl[o] = (int8_t)l;
 }
 
 // 3 x 3 / stride 2 / pad 1 max pooling with C a multiple of 4: one lane per four channels of an output pixel.
@@ -1119,9 +1130,9 @@ hipError_t launch_pool_np(const int8_t *xh, const int8_t *xl, uint8_t *y, int8_t
         maxpool3_np16_kernel<<<grid_for(total / 16), 256, 0, st>>>(prm);
     } else if (!avg && k == 3 && stride == 2 && pad == 1 && C % 4 == 0 && (al4 & 3) == 0)
         maxpool3_np_kernel<<<grid_for(total / 4), 256, 0, st>>>(a);
-    else if (avg && k == H && k == W && pad == 0 && P == 1 && Q == 1 && C % 4 == 0 && (al4 & 3) == 0 && total / 4 < (1u << 31) &&
+    else if (avg && k == H && k == W && pad == 0 && P == 1 && Q == 1 && C % 4 == 0 && (al4 & 3) == 0 && total / 4 < (1u << 31) - 256 &&
              (long long)k * k <= (1 << 18))
-        avgpool_global_np4_kernel<<<grid_for(total / 4), 256, 0, st>>>(a);
+        avgpool_global_np4_kernel<<<(int)((total / 4 + 31) / 32), 256, 0, st>>>(a, (int)(total / 4), make_fastdiv(C / 4));
     else
         pool_np_kernel<<<grid_for(total), 256, 0, st>>>(a);
     return hipGetLastError();

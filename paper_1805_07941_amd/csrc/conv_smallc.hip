@@ -183,7 +183,7 @@ __global__ void __launch_bounds__(kThreads, 2) conv_smallc_kernel(SmallCParams p
                         }
                         *(uint4 *)(a.y + (size_t)m * a.ldy + kc) = make_uint4(o[0], o[1], o[2], o[3]);
                     }
-                    else if (kc < a.K) store_tile_lane_general(acc[c][p], a, a.shift, a.relu, m, kc);
+                    else if (kc < a.K) store_tile_lane_general(acc[c][p], a, rq, m, kc);
                 }
             }
         }
@@ -387,7 +387,7 @@ __global__ void __launch_bounds__(kThreads, 2) conv_smallc_rows_kernel(SmallCRow
                         }
                         *(uint4 *)(a.y + (size_t)m * a.ldy + kc) = make_uint4(o[0], o[1], o[2], o[3]);
                     }
-                    else if (kc < a.K) store_tile_lane_general(acc[c][p], a, a.shift, a.relu, m, kc);
+                    else if (kc < a.K) store_tile_lane_general(acc[c][p], a, rq, m, kc);
                 }
             }
         }
