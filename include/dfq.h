@@ -451,6 +451,42 @@ int64_t dfq_mac_max_len(int q, int64_t bx, int64_t ex, int64_t by, int64_t ey); 
 int     dfq_add_acc_bits(int64_t N, int64_t bx, int64_t ex);                            /* Eq. 12 */
 int64_t dfq_add_max_len(int q, int64_t bx, int64_t ex);                                 /* Eq. 13 */
 
+/* ---- Calibration with the formats on the device ----------------------------------------------
+ * The steps of the single-batch calibration (Sec. 3) as calls that read the formats they need from device words and store
+ * the ones they choose there, by the rules of dfq_fmt_from_absmax_f32 / _i32 / _i32_channels (the (8, p) forms:
+ * dfq_np_frac_from_absmax_f32 / _u64), so that a whole network is calibrated without a synchronization.  Everything
+ * DEVICE unless said otherwise; a format is one int32 word (fractional length).  *err (zeroed by the caller) collects what
+ * the host forms refuse: bit 0 an infinite threshold, bit 1 formats too far apart; results are then meaningless.
+ * maxima, amax: words the caller has zeroed.
+ * dfq_cal_weights: formats of the weights w[rows][row_len] (per_row: one per row into w_frac[rows]; else one into w_frac[0],
+ *   gamma[rows] is scratch), their codes q and the bias b[rows] at the scale of input and weights.
+ * dfq_cal_quantize: the format of a float tensor from its largest magnitude (gamma[1] is scratch) and its codes.
+ * dfq_cal_rescale: acc[pixels][K], a convolution's sums at frac_in + w_frac (per_channel: w_frac[K], else w_frac[1]): the
+ *   output's format (fixed: fixed_frac) into *frac_out and the codes y; maxima[K].
+ * dfq_cal_add: the add of two int8 tensors; maximum[1].
+ * dfq_cal_concat: branch i's format is frac[idx[i]] (xs, Cs, idx: HOST arrays), the result's the coarsest branch's unless fixed.
+ * dfq_cal_np_weights, dfq_cal_np_quantize: codes and digit planes on (8, p); gamma as above.
+ * dfq_cal_conv_np, dfq_cal_add_np: the largest sum (amax[1]; a fixed output format needs none), the format, the digit planes. */
+dfq_status dfq_cal_weights(const float *w, const float *bias, size_t rows, size_t row_len, int per_row, float *gamma, const int32_t *frac_in,
+                           int8_t *q, int32_t *w_frac, int32_t *b, int32_t *err, dfq_stream stream);
+dfq_status dfq_cal_quantize(const float *x, size_t n, float *gamma, int8_t *q, int32_t *frac, int32_t *err, dfq_stream stream);
+dfq_status dfq_cal_rescale(const int32_t *acc, size_t pixels, int K, int relu, const int32_t *frac_in, const int32_t *w_frac, int per_channel,
+                           uint32_t *maxima, int fixed, int fixed_frac, int8_t *y, int32_t *frac_out, dfq_stream stream);
+dfq_status dfq_cal_add(const int8_t *a, const int32_t *frac_a, const int8_t *b, const int32_t *frac_b, size_t n, int relu, uint32_t *maximum,
+                       int8_t *y, int32_t *frac_out, int32_t *err, dfq_stream stream);
+dfq_status dfq_cal_concat(int nbranch, const int8_t *const *xs, const int *Cs, const int32_t *frac, const int *idx, int fixed, int fixed_frac,
+                          int8_t *y, int32_t *frac_out, size_t pixels, dfq_stream stream);
+dfq_status dfq_cal_np_weights(const float *w, const float *bias, size_t rows, size_t row_len, int p, float *gamma, const int32_t *frac_in,
+                              uint8_t *codes, int8_t *hi, int8_t *lo, int32_t *w_frac, int32_t *b, int32_t *err, dfq_stream stream);
+dfq_status dfq_cal_np_quantize(const float *x, size_t n, int p, float *gamma, int8_t *hi, int8_t *lo, int32_t *frac, int32_t *err,
+                               dfq_stream stream);
+dfq_status dfq_cal_conv_np(const int8_t *xh, const int8_t *xl, const int8_t *wh, const int8_t *wl, const int32_t *b, int8_t *yh, int8_t *yl,
+                           int N, int H, int W, int C, int K, int R, int S, int stride, int pad, int groups, const int32_t *frac_x,
+                           const int32_t *frac_w, uint64_t *amax, int fixed, int fixed_frac, int32_t *frac_y, int p, int relu, int32_t *err,
+                           dfq_stream stream);
+dfq_status dfq_cal_add_np(const int8_t *ah, const int8_t *al, const int32_t *frac_a, const int8_t *bh, const int8_t *bl, const int32_t *frac_b,
+                          size_t n, int p, int relu, uint64_t *amax, int8_t *yh, int8_t *yl, int32_t *frac_y, int32_t *err, dfq_stream stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -28,6 +28,8 @@ EXPORTS = [
     "dfq_absmax_f32", "dfq_absmax_i32", "dfq_fmt_from_absmax_f32", "dfq_fmt_from_absmax_f32_rows", "dfq_fmt_from_absmax_i32", "dfq_hist_shift", "dfq_fmt_from_absmax_i32_channels",
     "dfq_beta_max", "dfq_mac_acc_bits", "dfq_mac_max_len", "dfq_add_acc_bits", "dfq_add_max_len",
     "dfq_np_digits", "dfq_conv_np", "dfq_conv_np_variant", "dfq_np_frac_from_absmax_f32", "dfq_conv_q_add_lazy", "dfq_eltwise_np",
+    "dfq_cal_weights", "dfq_cal_quantize", "dfq_cal_rescale", "dfq_cal_add", "dfq_cal_concat",
+    "dfq_cal_np_weights", "dfq_cal_np_quantize", "dfq_cal_conv_np", "dfq_cal_add_np",
     "dfq_conv_np_absmax", "dfq_eltwise_np_absmax", "dfq_np_frac_from_absmax_u64", "dfq_pool_np", "dfq_stem_pack_x", "dfq_stem_pack_w", "dfq_conv_np_add",
     "dfq_conv_q_maxpool", "dfq_quantize_conv_q_maxpool", "dfq_conv_q_pc_maxpool", "dfq_quantize_conv_q_pc_maxpool", "dfq_quantize_conv_q",
 ]
@@ -126,6 +128,17 @@ def lib():
     L.dfq_stem_pack_w.restype = i32
     L.dfq_np_frac_from_absmax_f32.argtypes = [C.c_float, i32, i32, C.POINTER(C.c_int32)]
     for name in ("dfq_np_digits", "dfq_conv_np", "dfq_conv_np_variant", "dfq_np_frac_from_absmax_f32"):
+        getattr(L, name).restype = i32
+    L.dfq_cal_weights.argtypes = [vp, vp, sz, sz, i32] + [vp] * 7
+    L.dfq_cal_quantize.argtypes = [vp, sz] + [vp] * 5
+    L.dfq_cal_rescale.argtypes = [vp, sz, i32, i32, vp, vp, i32, vp, i32, i32, vp, vp, vp]
+    L.dfq_cal_add.argtypes = [vp] * 4 + [sz, i32] + [vp] * 5
+    L.dfq_cal_concat.argtypes = [i32] + [vp] * 4 + [i32, i32, vp, vp, sz, vp]
+    L.dfq_cal_np_weights.argtypes = [vp, vp, sz, sz, i32] + [vp] * 9
+    L.dfq_cal_np_quantize.argtypes = [vp, sz, i32] + [vp] * 6
+    L.dfq_cal_conv_np.argtypes = [vp] * 7 + [i32] * 10 + [vp] * 3 + [i32, i32, vp, i32, i32, vp, vp]
+    L.dfq_cal_add_np.argtypes = [vp] * 6 + [sz, i32, i32] + [vp] * 6
+    for name in ("dfq_cal_weights", "dfq_cal_quantize", "dfq_cal_rescale", "dfq_cal_add", "dfq_cal_concat", "dfq_cal_np_weights", "dfq_cal_np_quantize", "dfq_cal_conv_np", "dfq_cal_add_np"):
         getattr(L, name).restype = i32
     L.dfq_hist_shift.argtypes = [i64]
     L.dfq_hist_shift.restype = i32

@@ -32,6 +32,8 @@
 #include <type_traits>
 
 #include "conv_ring.hpp"
+#include "np_device.hpp"
+#include "reduce_device.hpp"
 
 namespace dfq {
 
@@ -142,33 +144,6 @@ __device__ __forceinline__ void put_sub(uint32_t &w, unsigned x, unsigned y)
     if constexpr (E == 1) asm("v_sub_u32_sdwa %0, %1, %2 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(x), "v"(y));
     if constexpr (E == 2) asm("v_sub_u32_sdwa %0, %1, %2 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(x), "v"(y));
     if constexpr (E == 3) asm("v_sub_u32_sdwa %0, %1, %2 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(x), "v"(y));
-}
-
-// Eq. 2 inverted: the sign-and-magnitude code of a representable integer (8 bits, p significand bits); +0 for 0.
-__device__ __forceinline__ unsigned np_code_of(int beta, int p)
-{
-    const int mag = beta < 0 ? -beta : beta;
-    if (mag == 0) return 0u;
-    const int msb = 31 - __clz(mag);
-    const unsigned code = msb < p ? (unsigned)mag : (((unsigned)(msb - p + 1) << p) | (((unsigned)mag >> (msb - p)) & ((1u << p) - 1u)));
-    return code | (beta < 0 ? 0x80u : 0u);
-}
-
-// Eq. 2: the integer of a code of the format (8, p)
-__device__ __forceinline__ int np_beta_of(unsigned code, int p)
-{
-    const unsigned m = code & ((1u << p) - 1u);
-    const unsigned e = (code >> p) & ((1u << (7 - p)) - 1u);
-    const int mag = e ? (int)(((1u << p) + m) << (e - 1)) : (int)m;
-    return (code & 0x80u) ? -mag : mag;
-}
-
-__device__ __forceinline__ void np_split(int beta, int &h, int &l)
-{
-    const int mag = beta < 0 ? -beta : beta;
-    const int hu = mag >> 6, lu = mag & 63;
-    h = beta < 0 ? -hu : hu;
-    l = beta < 0 ? -lu : lu;
 }
 
 // Four neighbouring channels of one pixel: accumulators -> one packed word of codes, of high digits, of low digits.
@@ -284,7 +259,21 @@ struct NpEltParams {
     int p_y;
     int beta_max;
     int relu;
+    // a calibration whose formats stay on the device: the operands' formats, the largest magnitude of the sum; the result's format is stored
+    const int32_t *cal_fa, *cal_fb;
+    const unsigned long long *cal_amax;
+    int32_t *cal_fy, *cal_err;
 };
+
+// the shifts of such an add: dfq_eltwise_np's limits, beyond which the call is refused at the end
+__device__ __forceinline__ int np_align(const int32_t *fa, const int32_t *fb, int &sa, int &sb, int32_t *err)
+{
+    const int a = *fa, b = *fb, F = max(a, b);
+    sa = min(F - a, 18);
+    sb = min(F - b, 18);
+    if (max(F - a, F - b) > 18 && blockIdx.x == 0 && threadIdx.x == 0) atomicOr(err, 2);
+    return F;
+}
 
 __device__ __forceinline__ void np_elt_one(int a_h, int a_l, int b_h, int b_l, const NpEltParams &q, unsigned &code, int &h, int &l)
 {
@@ -300,6 +289,15 @@ __device__ __forceinline__ void np_elt_one(int a_h, int a_l, int b_h, int b_l, c
 
 __global__ void __launch_bounds__(256) eltwise_np_kernel(NpEltParams q)
 {
+    if (q.cal_fa) {
+        const int F = np_align(q.cal_fa, q.cal_fb, q.sa, q.sb, q.cal_err);
+        const int fy = frac_from_int(*q.cal_amax, F, (unsigned long long)q.beta_max);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            *q.cal_fy = fy;
+            if (F - fy < -16 || F - fy > 31) atomicOr(q.cal_err, 2);
+        }
+        q.shift = min(max(F - fy, -16), 31);
+    }
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < q.n16; i += (size_t)gridDim.x * 256) {
         const uint4 ah = ((const uint4 *)q.ah)[i], al = ((const uint4 *)q.al)[i], bh = ((const uint4 *)q.bh)[i], bl = ((const uint4 *)q.bl)[i];
         const uint32_t wah[4] = {ah.x, ah.y, ah.z, ah.w}, wal[4] = {al.x, al.y, al.z, al.w};
@@ -334,16 +332,26 @@ __global__ void __launch_bounds__(256) eltwise_np_kernel(NpEltParams q)
     }
 }
 
-// Calibration: the largest magnitude of the exact aligned sum (after ReLU if asked), nothing stored.
-__global__ void __launch_bounds__(256) eltwise_np_absmax_kernel(const int8_t *ah, const int8_t *al, const int8_t *bh, const int8_t *bl, size_t n,
-                                                                 int sa, int sb, int relu, unsigned long long *amax)
+// Calibration: the largest magnitude of the exact aligned sum (after ReLU if asked), nothing stored.  Memory-bound, 16 values per lane and
+// access (a byte per lane and an atomic per wavefront: 4 x 40 x 40 x 256 46 us).
+__global__ void __launch_bounds__(256) eltwise_np_absmax_kernel(NpEltParams q, unsigned long long *amax)
 {
+    if (q.cal_fa) np_align(q.cal_fa, q.cal_fb, q.sa, q.sb, q.cal_err);
     unsigned mx = 0;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-        const int t = ((64 * (int)ah[i] + (int)al[i]) << sa) + ((64 * (int)bh[i] + (int)bl[i]) << sb);
-        const unsigned m = t < 0 ? (relu ? 0u : (unsigned)(-t)) : (unsigned)t;
-        mx = max(mx, m);
+    auto take = [&](int ah, int al, int bh, int bl) {
+        const int t = ((64 * ah + al) << q.sa) + ((64 * bh + bl) << q.sb);
+        mx = max(mx, t < 0 ? (q.relu ? 0u : (unsigned)(-t)) : (unsigned)t);
+    };
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < q.n16; i += (size_t)gridDim.x * 256) {
+        const uint4 ah = ((const uint4 *)q.ah)[i], al = ((const uint4 *)q.al)[i], bh = ((const uint4 *)q.bh)[i], bl = ((const uint4 *)q.bl)[i];
+        const uint32_t wah[4] = {ah.x, ah.y, ah.z, ah.w}, wal[4] = {al.x, al.y, al.z, al.w};
+        const uint32_t wbh[4] = {bh.x, bh.y, bh.z, bh.w}, wbl[4] = {bl.x, bl.y, bl.z, bl.w};
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) take(byte_of(wah[j], e), byte_of(wal[j], e), byte_of(wbh[j], e), byte_of(wbl[j], e));
     }
+    for (size_t i = q.n16 * 16 + (size_t)blockIdx.x * 256 + threadIdx.x; i < q.n; i += (size_t)gridDim.x * 256) take(q.ah[i], q.al[i], q.bh[i], q.bl[i]);
     wave_max_to(amax, (unsigned long long)mx);
 }
 
@@ -654,12 +662,26 @@ __global__ void __launch_bounds__(256) stem_pack_w_kernel(const int8_t *w, int8_
 
 // ---- direct form --------------------------------------------------------------------------------------------------
 
+// The layer's rescale shift: given, or - in a calibration whose formats stay on the device - from device words.
+__device__ __forceinline__ int np_layer_shift(const NpConvArgs &a)
+{
+    if (!a.cal_fx) return a.shift;
+    const int acc_frac = *a.cal_fx + *a.cal_fw;
+    const int fy = a.cal_fixed ? a.cal_fixed_frac : frac_from_int(*a.cal_amax, acc_frac, (unsigned long long)a.beta_max);
+    const int shift = acc_frac - fy;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *a.cal_fy = fy;
+        if (shift < -16 || shift > 48) atomicOr(a.cal_err, 2);           // refused at the end, as a call with these formats is
+    }
+    return min(max(shift, -16), 48);
+}
+
 __global__ void __launch_bounds__(256) conv_np_direct_kernel(NpConvArgs a)
 {
     const int Cg = a.C / a.groups;
     const int Kg = a.K / a.groups;
     const size_t total = (size_t)a.N * a.P * a.Q * a.K;
-    NpRound rnd = {a.shift, a.p_y, (float)a.beta_max, a.relu};
+    NpRound rnd = {a.amax ? 0 : np_layer_shift(a), a.p_y, (float)a.beta_max, a.relu};
     unsigned long long mx = 0;
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
         const int k = (int)(i % a.K);
@@ -928,8 +950,9 @@ __global__ void __launch_bounds__(256, OCC) conv_np_mfma_kernel(NpConvParams prm
     }
 
     // ---- epilogue: register r of a lane belongs to channel kc + r of pixel m
-    const NpRound rnd = {a.shift, a.p_y, (float)a.beta_max, a.relu};
-    const NpFast fr = {(unsigned)(1023 + a.p_y + a.shift), (unsigned)(1023 + a.shift + 11), ((unsigned)(52 - a.p_y) << 20) | 0x80000u, a.beta_max};
+    const int shift = ADD ? a.shift : np_layer_shift(a);
+    const NpRound rnd = {shift, a.p_y, (float)a.beta_max, a.relu};
+    const NpFast fr = {(unsigned)(1023 + a.p_y + shift), (unsigned)(1023 + shift + 11), ((unsigned)(52 - a.p_y) << 20) | 0x80000u, a.beta_max};
     auto finish = [&](auto fast, auto relu, auto codes) __attribute__((always_inline)) {
         constexpr bool FAST = decltype(fast)::value, RELU = decltype(relu)::value, CODES = decltype(codes)::value;
 #pragma unroll
@@ -1010,7 +1033,7 @@ __global__ void __launch_bounds__(256, OCC) conv_np_mfma_kernel(NpConvParams prm
         else finish_add(F_{});
         return;
     }
-    if (a.shift >= 7 && a.shift <= 36) {
+    if (shift >= 7 && shift <= 36) {
         if (a.y) {
             if (a.relu) finish(T_{}, T_{}, T_{});
             else finish(T_{}, F_{}, T_{});
@@ -1108,9 +1131,12 @@ static int grid_for(size_t work)
 }
 
 hipError_t launch_eltwise_np_absmax(const int8_t *ah, const int8_t *al, const int8_t *bh, const int8_t *bl, size_t n, int sa, int sb, int relu,
-                                    unsigned long long *amax, hipStream_t st)
+                                    unsigned long long *amax, hipStream_t st, const NpCalAdd &cal)
 {
-    eltwise_np_absmax_kernel<<<grid_for(n), 256, 0, st>>>(ah, al, bh, bl, n, sa, sb, relu, amax);
+    const uintptr_t al16 = (uintptr_t)ah | (uintptr_t)al | (uintptr_t)bh | (uintptr_t)bl;
+    NpEltParams q{ah, al, bh, bl, nullptr, nullptr, nullptr, (al16 & 15) ? 0 : n / 16, n, sa, sb, 0, 0, 0, relu, cal.fa, cal.fb, nullptr, nullptr, cal.err};
+    const int g = grid_for(q.n16 > 0 ? q.n16 : n);
+    eltwise_np_absmax_kernel<<<g < 1024 ? g : 1024, 256, 0, st>>>(q, amax);
     return hipGetLastError();
 }
 
@@ -1154,10 +1180,11 @@ hipError_t launch_stem_pack_w(const int8_t *w, int8_t *y, int K, int R, int S, i
 }
 
 hipError_t launch_eltwise_np(const int8_t *ah, const int8_t *al, const int8_t *bh, const int8_t *bl, uint8_t *y, int8_t *yh, int8_t *yl,
-                             size_t n, int sa, int sb, int shift, int p_y, int beta_max, int relu, hipStream_t st)
+                             size_t n, int sa, int sb, int shift, int p_y, int beta_max, int relu, hipStream_t st, const NpCalAdd &cal)
 {
     const uintptr_t al16 = (uintptr_t)ah | (uintptr_t)al | (uintptr_t)bh | (uintptr_t)bl | (uintptr_t)y | (uintptr_t)yh | (uintptr_t)yl;
-    NpEltParams q{ah, al, bh, bl, y, yh, yl, (al16 & 15) ? 0 : n / 16, n, sa, sb, shift, p_y, beta_max, relu};
+    NpEltParams q{ah, al, bh, bl, y, yh, yl, (al16 & 15) ? 0 : n / 16, n, sa, sb, shift, p_y, beta_max, relu,
+                  cal.fa, cal.fb, cal.amax, cal.fy, cal.err};
     size_t work = q.n16 > 0 ? q.n16 : n;
     size_t blocks = (work + 255) / 256;
     if (blocks > 256 * 16) blocks = 256 * 16;

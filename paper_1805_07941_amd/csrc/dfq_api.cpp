@@ -875,6 +875,116 @@ dfq_status dfq_fmt_from_absmax_i32_channels(const uint32_t *m, int K, int32_t fr
     return DFQ_OK;
 }
 
+// ---- calibration with the formats on the device
+
+dfq_status dfq_cal_weights(const float *w, const float *bias, size_t rows, size_t row_len, int per_row, float *gamma, const int32_t *frac_in,
+                           int8_t *q, int32_t *w_frac, int32_t *b, int32_t *err, dfq_stream stream)
+{
+    if (rows < 1 || rows >= ((size_t)1 << 31) || row_len < 1) return DFQ_ESHAPE;
+    if (!w || !bias || (!per_row && !gamma) || !frac_in || !q || !w_frac || !b || !err) return DFQ_EINVAL;
+    if (overlaps(w, rows * row_len * 4, q, rows * row_len) || overlaps(bias, rows * 4, b, rows * 4)) return DFQ_EINVAL;
+    return from_hip(launch_cal_weights(w, bias, rows, row_len, per_row, gamma, frac_in, q, w_frac, b, err, (hipStream_t)stream));
+}
+
+dfq_status dfq_cal_quantize(const float *x, size_t n, float *gamma, int8_t *q, int32_t *frac, int32_t *err, dfq_stream stream)
+{
+    if (!gamma || !frac || !err || (n && (!x || !q)) || overlaps(x, n * 4, q, n)) return DFQ_EINVAL;
+    return from_hip(launch_cal_quantize(x, n, gamma, q, frac, err, (hipStream_t)stream));
+}
+
+dfq_status dfq_cal_rescale(const int32_t *acc, size_t pixels, int K, int relu, const int32_t *frac_in, const int32_t *w_frac, int per_channel,
+                           uint32_t *maxima, int fixed, int fixed_frac, int8_t *y, int32_t *frac_out, dfq_stream stream)
+{
+    if (K < 1) return DFQ_ESHAPE;
+    if (fixed && !fmt_ok(dfq_fmt{8, fixed_frac})) return DFQ_EFMT;
+    if (!frac_in || !w_frac || (!fixed && !maxima) || !frac_out || (pixels && (!acc || !y))) return DFQ_EINVAL;
+    if (overlaps(acc, pixels * (size_t)K * 4, y, pixels * (size_t)K)) return DFQ_EINVAL;
+    return from_hip(launch_cal_rescale(acc, pixels, K, relu ? 1 : 0, frac_in, w_frac, per_channel, maxima, fixed, fixed_frac, y, frac_out,
+                                       (hipStream_t)stream));
+}
+
+dfq_status dfq_cal_add(const int8_t *a, const int32_t *frac_a, const int8_t *b, const int32_t *frac_b, size_t n, int relu, uint32_t *maximum,
+                       int8_t *y, int32_t *frac_out, int32_t *err, dfq_stream stream)
+{
+    if (!frac_a || !frac_b || !maximum || !frac_out || !err || (n && (!a || !b || !y))) return DFQ_EINVAL;
+    if (overlaps(a, n, y, n) || overlaps(b, n, y, n)) return DFQ_EINVAL;
+    return from_hip(launch_cal_add(a, frac_a, b, frac_b, n, relu ? 1 : 0, maximum, y, frac_out, err, (hipStream_t)stream));
+}
+
+dfq_status dfq_cal_concat(int nbranch, const int8_t *const *xs, const int *Cs, const int32_t *frac, const int *idx, int fixed, int fixed_frac,
+                          int8_t *y, int32_t *frac_out, size_t pixels, dfq_stream stream)
+{
+    if (nbranch < 1 || nbranch > 8 || !xs || !Cs || !frac || !idx || !frac_out) return DFQ_EINVAL;
+    if (fixed && !fmt_ok(dfq_fmt{8, fixed_frac})) return DFQ_EFMT;
+    long long ct = 0;
+    for (int i = 0; i < nbranch; i++) {
+        if (Cs[i] < 1) return DFQ_ESHAPE;
+        ct += Cs[i];
+    }
+    if (ct >= (1LL << 31)) return DFQ_ESHAPE;
+    for (int i = 0; i < nbranch; i++)
+        if (pixels && (!xs[i] || !y || overlaps(xs[i], pixels * (size_t)Cs[i], y, pixels * (size_t)ct))) return DFQ_EINVAL;
+    const CalConcat cal{frac, idx, fixed, fixed_frac, frac_out};
+    return from_hip(launch_concat(nbranch, xs, Cs, nullptr, y, (int)ct, 0, pixels, (hipStream_t)stream, cal));
+}
+
+dfq_status dfq_cal_np_weights(const float *w, const float *bias, size_t rows, size_t row_len, int p, float *gamma, const int32_t *frac_in,
+                              uint8_t *codes, int8_t *hi, int8_t *lo, int32_t *w_frac, int32_t *b, int32_t *err, dfq_stream stream)
+{
+    if (p < 4 || p > 7) return DFQ_EFMT;
+    if (rows < 1 || rows >= ((size_t)1 << 31) || row_len < 1) return DFQ_ESHAPE;
+    if (!w || !bias || !gamma || !frac_in || !codes || !hi || !lo || !w_frac || !b || !err) return DFQ_EINVAL;
+    return from_hip(launch_cal_np_weights(w, bias, rows, row_len, p, (int)dfq_beta_max(8, p), gamma, frac_in, codes, hi, lo, w_frac, b, err,
+                                          (hipStream_t)stream));
+}
+
+dfq_status dfq_cal_np_quantize(const float *x, size_t n, int p, float *gamma, int8_t *hi, int8_t *lo, int32_t *frac, int32_t *err,
+                               dfq_stream stream)
+{
+    if (p < 4 || p > 7) return DFQ_EFMT;
+    if (!gamma || !frac || !err || (n && (!x || !hi || !lo))) return DFQ_EINVAL;
+    return from_hip(launch_cal_np_quantize(x, n, p, (int)dfq_beta_max(8, p), gamma, hi, lo, frac, err, (hipStream_t)stream));
+}
+
+dfq_status dfq_cal_conv_np(const int8_t *xh, const int8_t *xl, const int8_t *wh, const int8_t *wl, const int32_t *b, int8_t *yh, int8_t *yl,
+                           int N, int H, int W, int C, int K, int R, int S, int stride, int pad, int groups, const int32_t *frac_x,
+                           const int32_t *frac_w, uint64_t *amax, int fixed, int fixed_frac, int32_t *frac_y, int p, int relu, int32_t *err,
+                           dfq_stream stream)
+{
+    if (!frac_x || !frac_w || !frac_y || !err || (!fixed && (!amax || ((uintptr_t)amax & 7)))) return DFQ_EINVAL;
+    NpConvArgs a{xh, xl, wh, wl, b, nullptr, yh, yl, N, H, W, C, K, R, S, stride, pad, groups, 0, 0, 0, p, 0, relu ? 1 : 0, nullptr, nullptr, 0, 0, 0, 0, nullptr};
+    if (fixed && (fixed_frac < -32 || fixed_frac > 32)) return DFQ_EFMT;
+    const dfq_status st = check_conv_np(a, 0, 0, 0);         // (the formats are placeholders: they are device words)
+    if (st != DFQ_OK) return st;
+    if (N == 0) return DFQ_EUNSUPPORTED;                     // no sums, no format
+    const bool mfma = conv_np_mfma_supports(a);
+    if (!fixed) {
+        NpConvArgs m = a;
+        m.amax = reinterpret_cast<unsigned long long *>(amax);
+        const hipError_t e = mfma ? launch_conv_np_mfma(m, (hipStream_t)stream) : launch_conv_np_direct(m, (hipStream_t)stream);
+        if (e != hipSuccess) return DFQ_EDEVICE;
+    }
+    a.cal_fx = frac_x;
+    a.cal_fw = frac_w;
+    a.cal_amax = reinterpret_cast<const unsigned long long *>(amax);
+    a.cal_fixed = fixed ? 1 : 0;
+    a.cal_fixed_frac = fixed_frac;
+    a.cal_fy = frac_y;
+    a.cal_err = err;
+    return from_hip(mfma ? launch_conv_np_mfma(a, (hipStream_t)stream) : launch_conv_np_direct(a, (hipStream_t)stream));
+}
+
+dfq_status dfq_cal_add_np(const int8_t *ah, const int8_t *al, const int32_t *frac_a, const int8_t *bh, const int8_t *bl, const int32_t *frac_b,
+                          size_t n, int p, int relu, uint64_t *amax, int8_t *yh, int8_t *yl, int32_t *frac_y, int32_t *err, dfq_stream stream)
+{
+    if (p < 4 || p > 7) return DFQ_EFMT;
+    if (!frac_a || !frac_b || !amax || ((uintptr_t)amax & 7) || !frac_y || !err || (n && (!ah || !al || !bh || !bl || !yh || !yl))) return DFQ_EINVAL;
+    const NpCalAdd cal{frac_a, frac_b, reinterpret_cast<const unsigned long long *>(amax), frac_y, err};
+    const hipError_t e = launch_eltwise_np_absmax(ah, al, bh, bl, n, 0, 0, relu ? 1 : 0, reinterpret_cast<unsigned long long *>(amax), (hipStream_t)stream, cal);
+    if (e != hipSuccess) return DFQ_EDEVICE;
+    return from_hip(launch_eltwise_np(ah, al, bh, bl, nullptr, yh, yl, n, 0, 0, 0, p, (int)dfq_beta_max(8, p), relu ? 1 : 0, (hipStream_t)stream, cal));
+}
+
 int64_t dfq_beta_max(int n, int p)
 {
     if (n < 2 || n > 32 || p < 0 || p > n - 1) return -1;

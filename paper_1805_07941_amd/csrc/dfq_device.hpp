@@ -58,4 +58,41 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
     return v;
 }
 
+// ---- float -> code
+__device__ __forceinline__ int quant_one(float x, float scale)
+{
+    // x * 2^f is exact in float (power-of-two scale) except on overflow, which saturates,
+    // and on underflow, which rounds to 0 either way.
+    float t = __builtin_rintf(x * scale);  // v_rndne_f32: ties to even
+    if (!(t == t)) return 0;               // NaN
+    t = fminf(fmaxf(t, -127.0f), 127.0f);
+    return (int)t;
+}
+
+__device__ __forceinline__ int saturate_i32(float t)
+{
+    if (!(t == t)) return 0;
+    if (t >= 2147483648.0f) return 2147483647;
+    if (t <= -2147483648.0f) return -2147483647;
+    return (int)t;
+}
+
+// x * 2^f rounded to an integer; two exact power-of-two factors, so that a sum of fractional lengths beyond 127 cannot overflow the
+// scale itself
+__device__ __forceinline__ int quant_i32_one(float x, int f)
+{
+    return saturate_i32(__builtin_rintf(x * ldexpf(1.0f, f / 2) * ldexpf(1.0f, f - f / 2)));
+}
+
+// The largest f <= min(acc_frac, 32) with m <= top * 2^(acc_frac - f), at least -32 (dfq_fmt_from_absmax_i32, dfq_np_frac_from_absmax_u64)
+__device__ __forceinline__ int frac_from_int(unsigned long long m, int acc_frac, unsigned long long top)
+{
+    int gap = 0;
+    if (m > top) {
+        gap = __clzll((long long)top) - __clzll((long long)m);       // m has that many bits more
+        if (m > (top << gap)) gap++;                                 // top << gap has the bits of m: no overflow
+    }
+    return max(min(acc_frac - gap, 32), -32);
+}
+
 }  // namespace dfq

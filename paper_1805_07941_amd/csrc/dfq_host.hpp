@@ -60,6 +60,27 @@ struct NpConvArgs {
     int add_shift;                 // that scale's fractional length minus the output's, 0..31
     int add_relu;                  // ReLU on the sum
     unsigned long long *amax;      // calibration: receives max |sum + bias| (after ReLU if relu) by atomic max
+    // calibration whose formats stay on the device: `shift` is then derived from the formats of input and weights and, unless the
+    // output's is fixed, the largest magnitude of the sums; the output's format is stored, limits that are not met raise *cal_err
+    const int32_t *cal_fx = nullptr, *cal_fw = nullptr;
+    const unsigned long long *cal_amax = nullptr;
+    int cal_fixed = 0, cal_fixed_frac = 0;
+    int32_t *cal_fy = nullptr, *cal_err = nullptr;
+};
+
+// The same for an add on digit planes, or fa == null.
+struct NpCalAdd {
+    const int32_t *fa = nullptr, *fb = nullptr;
+    const unsigned long long *amax = nullptr;
+    int32_t *fy = nullptr, *err = nullptr;
+};
+
+// A concat whose formats are device words (branch i: frac[idx[i]]), or frac == null.  The result's is the given one or the coarsest branch's.
+struct CalConcat {
+    const int32_t *frac = nullptr;
+    const int *idx = nullptr;
+    int fixed = 0, fixed_frac = 0;
+    int32_t *frac_out = nullptr;
 };
 
 hipError_t launch_quantize(const float *x, int8_t *q, size_t n, int frac, hipStream_t st);
@@ -70,7 +91,7 @@ hipError_t launch_dequantize_np(const uint8_t *q, float *x, size_t n, int nbits,
 hipError_t launch_eltwise(const int8_t *a, int fa, const int8_t *b, int fb, int8_t *y, int fy, int32_t *acc, size_t n,
                           int relu, hipStream_t st);
 hipError_t launch_concat(int nb, const int8_t *const *xs, const int *Cs, const int *fs, int8_t *y, int ldy, int fy,
-                         size_t pixels, hipStream_t st);
+                         size_t pixels, hipStream_t st, const CalConcat &cal = {});
 hipError_t launch_pool(const int8_t *x, int8_t *y, int mode, int N, int H, int W, int C, int P, int Q, int k, int stride,
                        int pad, int fin, int fout, hipStream_t st);
 hipError_t launch_absmax_f32(const float *x, size_t n, float *out, hipStream_t st);
@@ -82,7 +103,21 @@ hipError_t launch_fold_scale(const float *w, const float *b, size_t rows, size_t
                              float *w_out, float *b_out, hipStream_t st);
 hipError_t launch_absmax_f32_rows(const float *x, size_t rows, size_t row_len, float *out, hipStream_t st);
 hipError_t launch_hist_i32(const int32_t *x, size_t n, int relu, int shift, uint32_t *out, hipStream_t st);
-hipError_t launch_absmax_i32_channels(const int32_t *x, size_t pixels, int K, int relu, uint32_t *out, hipStream_t st);
+// cleared: the words of `out` hold zeros already
+hipError_t launch_absmax_i32_channels(const int32_t *x, size_t pixels, int K, int relu, uint32_t *out, hipStream_t st, bool cleared = false);
+// calibration with the formats on the device (calib.hip)
+hipError_t launch_cal_weights(const float *w, const float *bias, size_t rows, size_t row_len, int per_row, float *gamma, const int32_t *frac_in,
+                              int8_t *q, int32_t *w_frac, int32_t *b, int32_t *err, hipStream_t st);
+hipError_t launch_cal_np_weights(const float *w, const float *bias, size_t rows, size_t row_len, int p, int beta_max, float *gamma,
+                                 const int32_t *frac_in, uint8_t *codes, int8_t *hi, int8_t *lo, int32_t *w_frac, int32_t *b, int32_t *err,
+                                 hipStream_t st);
+hipError_t launch_cal_quantize(const float *x, size_t n, float *gamma, int8_t *q, int32_t *frac, int32_t *err, hipStream_t st);
+hipError_t launch_cal_np_quantize(const float *x, size_t n, int p, int beta_max, float *gamma, int8_t *hi, int8_t *lo, int32_t *frac, int32_t *err,
+                                  hipStream_t st);
+hipError_t launch_cal_rescale(const int32_t *acc, size_t pixels, int K, int relu, const int32_t *frac_in, const int32_t *w_frac, int per_channel,
+                              uint32_t *maxima, int fixed, int fixed_frac, int8_t *y, int32_t *frac_out, hipStream_t st);
+hipError_t launch_cal_add(const int8_t *a, const int32_t *fa, const int8_t *b, const int32_t *fb, size_t n, int relu, uint32_t *maximum, int8_t *y,
+                          int32_t *frac_out, int32_t *err, hipStream_t st);
 
 bool conv_direct_supports(const ConvArgs &a);
 hipError_t launch_conv_direct(const ConvArgs &a, hipStream_t st);
@@ -113,13 +148,13 @@ hipError_t launch_conv_np_mfma(const NpConvArgs &a, hipStream_t st);
 hipError_t launch_conv_np_direct(const NpConvArgs &a, hipStream_t st);
 hipError_t launch_clear_u64(unsigned long long *p, hipStream_t st);
 hipError_t launch_eltwise_np_absmax(const int8_t *ah, const int8_t *al, const int8_t *bh, const int8_t *bl, size_t n, int sa, int sb, int relu,
-                                    unsigned long long *amax, hipStream_t st);
+                                    unsigned long long *amax, hipStream_t st, const NpCalAdd &cal = {});
 hipError_t launch_pool_np(const int8_t *xh, const int8_t *xl, uint8_t *y, int8_t *yh, int8_t *yl, int avg, int N, int H, int W, int C, int k,
                           int stride, int pad, int P, int Q, int p_fmt, int beta_max, hipStream_t st);
 hipError_t launch_stem_pack_x(const int8_t *x, int8_t *y, int N, int H, int W, int C, int pad, int Hs, int Qs, hipStream_t st);
 hipError_t launch_stem_pack_w(const int8_t *w, int8_t *y, int K, int R, int S, int C, hipStream_t st);
 hipError_t launch_eltwise_np(const int8_t *ah, const int8_t *al, const int8_t *bh, const int8_t *bl, uint8_t *y, int8_t *yh, int8_t *yl,
-                             size_t n, int sa, int sb, int shift, int p_y, int beta_max, int relu, hipStream_t st);
+                             size_t n, int sa, int sb, int shift, int p_y, int beta_max, int relu, hipStream_t st, const NpCalAdd &cal = {});
 hipError_t launch_np_digits(const uint8_t *codes, size_t n, int p, int8_t *hi, int8_t *lo, hipStream_t st);
 bool conv_smallc_supports(const ConvArgs &a);
 hipError_t launch_conv_smallc(const ConvArgs &a, hipStream_t st);

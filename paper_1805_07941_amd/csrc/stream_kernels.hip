@@ -6,10 +6,10 @@
 #include "dfq_device.hpp"
 #include "dfq_host.hpp"
 #include "conv_epilogue.hpp"
+#include "np_device.hpp"
+#include "reduce_device.hpp"
 
 namespace dfq {
-
-static constexpr int kBlock = 256;
 
 static inline int grid_for(size_t work_items)
 {
@@ -23,16 +23,6 @@ static inline int grid_for(size_t work_items)
 // ------------------------------------------------------------------------------------------
 // quantize / dequantize
 // ------------------------------------------------------------------------------------------
-
-__device__ __forceinline__ int quant_one(float x, float scale)
-{
-    // x * 2^f is exact in float (power-of-two scale) except on overflow, which saturates,
-    // and on underflow, which rounds to 0 either way.
-    float t = __builtin_rintf(x * scale);  // v_rndne_f32: ties to even
-    if (!(t == t)) return 0;               // NaN
-    t = fminf(fmaxf(t, -127.0f), 127.0f);
-    return (int)t;
-}
 
 __global__ void __launch_bounds__(kBlock) quantize_vec4(const float4 *__restrict__ x, uint32_t *__restrict__ q,
                                                          size_t n4, float scale)
@@ -54,13 +44,7 @@ __global__ void __launch_bounds__(kBlock) quantize_i32_kernel(const float *__res
                                                                size_t n, float scale)
 {
     for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (size_t)gridDim.x * kBlock) {
-        float t = __builtin_rintf(x[i] * scale);   // exact product; overflow to Inf saturates below
-        int32_t c;
-        if (!(t == t)) c = 0;
-        else if (t >= 2147483648.0f) c = 2147483647;
-        else if (t <= -2147483648.0f) c = -2147483647;
-        else c = (int32_t)t;
-        q[i] = c;
+        q[i] = saturate_i32(__builtin_rintf(x[i] * scale));   // exact product; overflow to Inf saturates
     }
 }
 
@@ -86,33 +70,6 @@ __global__ void __launch_bounds__(kBlock) dequantize_scalar(const int8_t *__rest
 // sign, bits n-2 .. p the exponent field e, bits p-1 .. 0 the significand field m; value
 // 2^-frac * (e == 0 ? m : 2^(e-1) * (2^p + m)), every exponent code a number.
 // ------------------------------------------------------------------------------------------
-struct NpFmt {
-    int n, p;
-    float scale;      // 2^frac (quantize) or 2^-frac (dequantize)
-    float beta_max;   // Eq. 5; p+1 significant bits, exact in float
-};
-
-// Nearest representable magnitude, ties to the even significand.  v = |x| * 2^frac is exact in float; below
-// 2^(p+1) the representable values are the integers, in [2^(p+k), 2^(p+k+1)) the multiples of 2^k, so the
-// value is brought to an integer grid by an exact power-of-two factor, rounded by v_rndne_f32 and scaled back.
-__device__ __forceinline__ uint32_t np_quant_one(float x, const NpFmt &f)
-{
-    float v = x * f.scale;
-    if (!(v == v)) return 0u;                                        // NaN
-    const float a = fminf(fabsf(v), f.beta_max);
-    const int ex = (int)((__float_as_uint(a) >> 23) & 0xffu) - 127;  // floor(log2 a) for a >= 2^-126
-    const int k = max(ex - f.p, 0);
-    float r = ldexpf(__builtin_rintf(ldexpf(a, -k)), k);
-    r = fminf(r, f.beta_max);
-    if (r == 0.0f) return 0u;                                        // no negative zero
-    const uint32_t bits = __float_as_uint(r);
-    const int er = (int)((bits >> 23) & 0xffu) - 127;                // r = 2^er * 1.fraction, at most p fraction bits set
-    uint32_t code;
-    if (er < f.p) code = (uint32_t)(int)r;                           // subnormal: e = 0, m = r
-    else code = ((uint32_t)(er - f.p + 1) << f.p) | ((bits >> (23 - f.p)) & ((1u << f.p) - 1u));
-    return code | (v < 0.0f ? (1u << (f.n - 1)) : 0u);
-}
-
 __device__ __forceinline__ float np_dequant_one(uint32_t code, const NpFmt &f)
 {
     const uint32_t m = code & ((1u << f.p) - 1u);
@@ -166,15 +123,7 @@ __global__ void __launch_bounds__(kBlock) quantize_i32_rows_kernel(const float *
 {
     const size_t n = rows * row_len;
     for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (size_t)gridDim.x * kBlock) {
-        // two exact power-of-two factors, so that a sum of fractional lengths beyond 127 cannot overflow the scale itself
-        const int f = frac[i / row_len] + frac_add;
-        float t = __builtin_rintf(x[i] * ldexpf(1.0f, f / 2) * ldexpf(1.0f, f - f / 2));
-        int32_t c;
-        if (!(t == t)) c = 0;
-        else if (t >= 2147483648.0f) c = 2147483647;
-        else if (t <= -2147483648.0f) c = -2147483647;
-        else c = (int32_t)t;
-        q[i] = c;
+        q[i] = quant_i32_one(x[i], frac[i / row_len] + frac_add);
     }
 }
 
@@ -408,6 +357,11 @@ struct ConcatParams {
     int pieces[9];  // pieces of the branches before this one; pieces[nb]: of a whole pixel
     int nb;
     FastDiv div_pieces;
+    // formats in device words (calibration)
+    const int32_t *frac;
+    int idx[8];
+    int fixed, fixed_frac;
+    int32_t *frac_out;
 };
 
 // VEC bytes at any byte address.  Channel counts that are no multiple of VEC are covered by pieces that overlap: the last piece of a
@@ -423,9 +377,21 @@ struct Piece<1> {
 
 // ldy: bytes between consecutive pixels of y (>= the branches' channels together).  FAST: every branch's shift lies in [0, 23].
 // Memory-bound: 3 branches of 90 channels over 24 x 45 x 61 pixels (35 MB) took 43 us with byte accesses, now 10.
-template <int VEC, bool FAST>
+// DEV: the formats are device words; the result's is derived and stored.
+template <int VEC, bool FAST, bool DEV = false>
 __global__ void __launch_bounds__(kBlock) concat_kernel(ConcatParams p, int8_t *__restrict__ y, size_t pixels, int ldy)
 {
+    if constexpr (DEV) {
+        int fy = p.fixed ? p.fixed_frac : p.frac[p.idx[0]];
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+            p.s[j] = j < p.nb ? p.frac[p.idx[j]] : 0;
+            if (!p.fixed && j < p.nb) fy = min(fy, p.s[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < 8; j++) p.s[j] -= fy;
+        if (blockIdx.x == 0 && threadIdx.x == 0) *p.frac_out = fy;
+    }
     const size_t total = pixels * (size_t)p.pieces[p.nb];
     for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < total; i += (size_t)gridDim.x * kBlock) {
         const size_t px = total < (1ull << 31) ? (size_t)fastdiv((int)i, p.div_pieces) : i / (size_t)p.pieces[p.nb];
@@ -476,21 +442,27 @@ static void launch_concat_vec(ConcatParams &p, int8_t *y, int ldy, size_t pixels
     }
     p.div_pieces = make_fastdiv(p.pieces[p.nb]);
     const int g = grid_for(pixels * (size_t)p.pieces[p.nb]);
-    if (VEC > 1 && fast) concat_kernel<VEC, true><<<g, kBlock, 0, st>>>(p, y, pixels, ldy);
+    if (p.frac) concat_kernel<VEC, false, true><<<g, kBlock, 0, st>>>(p, y, pixels, ldy);
+    else if (VEC > 1 && fast) concat_kernel<VEC, true><<<g, kBlock, 0, st>>>(p, y, pixels, ldy);
     else concat_kernel<VEC, false><<<g, kBlock, 0, st>>>(p, y, pixels, ldy);
 }
 
 hipError_t launch_concat(int nb, const int8_t *const *xs, const int *Cs, const int *fs, int8_t *y, int ldy, int fy,
-                         size_t pixels, hipStream_t st)
+                         size_t pixels, hipStream_t st, const CalConcat &cal)
 {
     ConcatParams p{};
     p.nb = nb;
+    p.frac = cal.frac;
+    p.fixed = cal.fixed;
+    p.fixed_frac = cal.fixed_frac;
+    p.frac_out = cal.frac_out;
     int off = 0, least = Cs[0];
     for (int i = 0; i < nb; i++) {
         p.x[i] = xs[i];
         p.C[i] = Cs[i];
         p.off[i] = off;
-        p.s[i] = fs[i] - fy;
+        p.s[i] = cal.frac ? 0 : fs[i] - fy;
+        p.idx[i] = cal.frac ? cal.idx[i] : 0;
         off += Cs[i];
         least = Cs[i] < least ? Cs[i] : least;
     }
@@ -867,35 +839,6 @@ static inline int grid_for_reduction(size_t work_items)
     return g < 512 ? g : 512;
 }
 
-// The result of one of `sharers` workgroups that raise the same word.  A single one stores it, and nobody clears the word first;
-// up to one per compute unit send their atomics straight away (100000 values, 98 workgroups: 5.1 us, with a read before 5.6); of many, most see by a
-// read that theirs is no news - the maximum only grows - and spare the word the atomic.
-__device__ __forceinline__ void raise_to(uint32_t *out, uint32_t m, unsigned sharers)
-{
-    if (sharers == 1) *out = m;
-    else if (sharers <= 256 || m > __hip_atomic_load(out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(out, m);
-}
-
-__device__ __forceinline__ void block_max_to(uint32_t v, uint32_t *out)
-{
-    __shared__ uint32_t part[kBlock / kWave];
-    v = wave_max_u32(v);
-    if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t m = part[0];
-#pragma unroll
-        for (int i = 1; i < kBlock / kWave; i++) m = max(m, part[i]);
-        raise_to(out, m, gridDim.x);
-    }
-}
-
-__device__ __forceinline__ uint32_t float_magnitude(float v)
-{
-    const float a = fabsf(v);
-    return a == a ? __float_as_uint(a) : 0u;          // NaN elements are skipped
-}
-
 // 16 bytes at any boundary of four
 template <class T>
 struct __attribute__((packed, aligned(4))) Four {
@@ -916,11 +859,6 @@ __global__ void __launch_bounds__(kBlock) absmax_f32_kernel(const float *__restr
     }
     if (t < n % 4) m = max(m, float_magnitude(x[n4 * 4 + t]));
     block_max_to(m, out);
-}
-
-__device__ __forceinline__ uint32_t magnitude(int v, int relu)
-{
-    return v >= 0 ? (uint32_t)v : (relu ? 0u : (uint32_t)0 - (uint32_t)v);
 }
 
 __global__ void __launch_bounds__(kBlock) absmax_i32_kernel(const int32_t *__restrict__ x, size_t n, int relu, uint32_t *out)
@@ -1070,7 +1008,7 @@ hipError_t launch_hist_i32(const int32_t *x, size_t n, int relu, int shift, uint
     return hipGetLastError();
 }
 
-hipError_t launch_absmax_i32_channels(const int32_t *x, size_t pixels, int K, int relu, uint32_t *out, hipStream_t st)
+hipError_t launch_absmax_i32_channels(const int32_t *x, size_t pixels, int K, int relu, uint32_t *out, hipStream_t st, bool cleared)
 {
     const bool vec = K % 4 == 0 && aligned(x, 16);
     const int chunks = vec ? K / 4 : K, windows = (chunks + kWave - 1) / kWave, lanes = (chunks + windows - 1) / windows;
@@ -1078,7 +1016,7 @@ hipError_t launch_absmax_i32_channels(const int32_t *x, size_t pixels, int K, in
     const int target = windows < 8 ? 512 : 1024;
     const size_t rows = (size_t)(kBlock / lanes) * 4, full = (pixels + rows - 1) / rows, most = windows < target ? target / windows : 1;
     const unsigned gx = (unsigned)(full < most ? full : most);
-    if (gx != 1) clear_u32_n<<<(K + kBlock - 1) / kBlock, kBlock, 0, st>>>(out, K);        // one workgroup stores its maxima
+    if (gx != 1 && !cleared) clear_u32_n<<<(K + kBlock - 1) / kBlock, kBlock, 0, st>>>(out, K);        // one workgroup stores its maxima
     if (gx) {
         const dim3 grid(gx, (unsigned)(windows < 4096 ? windows : 4096));
         if (vec) absmax_i32_channels_kernel<4><<<grid, kBlock, 0, st>>>(x, pixels, K, relu, out, lanes, windows);

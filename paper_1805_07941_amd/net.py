@@ -125,6 +125,134 @@ def _threshold(acc: torch.Tensor, relu: bool, rule: str) -> int:
     return B.threshold_search(counts, j, m)[0]
 
 
+class FormatWords:
+    """The device words of a calibration that keeps its formats on the device: what its calls refused, a format per tensor, the weights'
+    formats, and the maxima the formats follow from.  Read back once, at the end."""
+
+    def __init__(self, net, device, w_words: int, maxima: int):
+        tensors = 1 + len(net.nodes)
+        self.words = torch.zeros(1 + tensors + w_words, dtype=torch.int32, device=device)
+        self.maxima = torch.zeros(maxima, dtype=torch.int64, device=device)     # 32-bit maxima take half a word each
+        self.err = self.words.data_ptr()
+        self.slot: Dict[str, int] = {net.input_name: 1}                         # tensor name -> its format's word
+        self._next, self._w, self._m = 2, 1 + tensors, 0
+
+    def new(self, name: str) -> int:
+        """Address of the format of a tensor that a call is about to choose."""
+        self.slot[name] = self._next
+        self._next += 1
+        return self.of(name)
+
+    def same(self, name: str, as_name: str):
+        self.slot[name] = self.slot[as_name]
+
+    def of(self, name: str) -> int:
+        return self.err + 4 * self.slot[name]
+
+    def weights(self, count: int) -> int:
+        """Index of the next `count` words for weight formats."""
+        self._w += count
+        return self._w - count
+
+    def maximum(self, count: int) -> int:
+        """Address of the next `count` zeroed 8-byte words for maxima."""
+        self._m += count
+        return self.maxima.data_ptr() + 8 * (self._m - count)
+
+    def read(self):
+        """All formats on the host (synchronizes); raises what the calls with these formats would have."""
+        got = self.words.cpu().numpy()
+        if got[0] & 1:
+            raise B.DfqError(B.EINVAL, "calibration: an infinite threshold")
+        if got[0] & 2:
+            raise B.DfqError(B.EFMT, "calibration: formats too far apart")
+        return got
+
+
+def _calibrate_on_device(net, x: torch.Tensor, device, keep_tensors: bool, per_channel: bool):
+    """calibrate() with rule "maxabs": every format is chosen on the device, from the maxima, by the kernels that use it, so the host
+    enqueues the whole network and waits once."""
+    L, call, st = B.lib(), B._check, B._stream(None)
+    qz = Quantized()
+    convs = [nd for nd in net.nodes if nd.op == "conv"]
+    channels = sum(nd.K for nd in convs)
+    F = FormatWords(net, device, channels if per_channel else len(convs), (channels + 1) // 2 + len(net.nodes))
+    gamma = torch.empty(max([nd.K for nd in convs] + [1]), dtype=torch.float32, device=device)
+    t: Dict[str, torch.Tensor] = {}
+    if net.input_is_int8 or net.fixed_f_input is not None:
+        f_in = net.f_input_codes if net.input_is_int8 else net.fixed_f_input
+        F.words[F.slot[net.input_name]].fill_(f_in)
+        t[net.input_name] = x if net.input_is_int8 else B.quantize(x, f_in)
+    else:
+        B._dev(x, torch.float32, "x")
+        q = torch.empty(x.shape, dtype=torch.int8, device=x.device)
+        call(L.dfq_cal_quantize(x.data_ptr(), x.numel(), gamma.data_ptr(), q.data_ptr(), F.of(net.input_name), F.err, st), "dfq_cal_quantize")
+        t[net.input_name] = q
+    last_use = _last_use(net)
+    groups, raw = float_weights(net, device), {}
+    w_at: Dict[str, tuple] = {}
+    for idx, nd in enumerate(net.nodes):
+        if nd.op == "conv":
+            src = nd.srcs[0]
+            if nd.name not in raw:
+                raw = next(groups)
+            wf, bf = raw.pop(nd.name)
+            B._dev(wf, torch.float32, "weights")
+            B._dev(bf, torch.float32, "bias")
+            K = int(wf.shape[0])
+            at = F.weights(K if per_channel else 1)
+            w_at[nd.name] = (at, K)
+            w, b = torch.empty(wf.shape, dtype=torch.int8, device=device), torch.empty(bf.shape, dtype=torch.int32, device=device)
+            qz.w[nd.name], qz.b[nd.name] = w, b
+            w_frac = F.err + 4 * at
+            call(L.dfq_cal_weights(wf.data_ptr(), bf.data_ptr(), K, wf.numel() // K, int(per_channel), gamma.data_ptr(), F.of(src), w.data_ptr(),
+                                   w_frac, b.data_ptr(), F.err, st), "dfq_cal_weights")
+            _, acc = B.conv_q(t[src], w, b, 0, 0, 0, nd.stride, nd.pad, nd.groups, nd.relu, want_y=False, want_acc=True, stream=st)
+            y = torch.empty(acc.shape, dtype=torch.int8, device=device)
+            fixed = nd.fixed_f_out is not None
+            call(L.dfq_cal_rescale(acc.data_ptr(), acc.numel() // K, K, int(nd.relu), F.of(src), w_frac, int(per_channel),
+                                   None if fixed else F.maximum((K + 1) // 2), int(fixed), nd.fixed_f_out if fixed else 0, y.data_ptr(),
+                                   F.new(nd.dst), st), "dfq_cal_rescale")
+            t[nd.dst] = y
+            del wf, bf, acc
+        elif nd.op == "eltwise":
+            a, b2 = (t[s] for s in nd.srcs)
+            y = torch.empty(a.shape, dtype=torch.int8, device=device)
+            fa, fb = (F.of(s) for s in nd.srcs)
+            call(L.dfq_cal_add(a.data_ptr(), fa, b2.data_ptr(), fb, a.numel(), int(nd.relu), F.maximum(1), y.data_ptr(), F.new(nd.dst), F.err, st),
+                 "dfq_cal_add")
+            t[nd.dst] = y
+        elif nd.op == "concat":
+            xs = [t[s] for s in nd.srcs]
+            Cs = [int(v.shape[-1]) for v in xs]
+            nb = len(xs)
+            y = torch.empty(xs[0].shape[:-1] + (sum(Cs),), dtype=torch.int8, device=device)
+            fixed = nd.fixed_f_out is not None
+            call(L.dfq_cal_concat(nb, (C.c_void_p * nb)(*[v.data_ptr() for v in xs]), (C.c_int * nb)(*Cs), F.err,
+                                  (C.c_int * nb)(*[F.slot[s] for s in nd.srcs]), int(fixed), nd.fixed_f_out if fixed else 0, y.data_ptr(),
+                                  F.new(nd.dst), y.numel() // sum(Cs), st), "dfq_cal_concat")
+            t[nd.dst] = y
+        elif nd.op in ("maxpool", "avgpool"):
+            src = nd.srcs[0]
+            F.same(nd.dst, src)
+            t[nd.dst] = B.pool_q(t[src], "max" if nd.op == "maxpool" else "avg", nd.R, nd.stride, nd.pad, 0, 0, stream=st)
+        else:
+            raise ValueError(nd.op)
+        if not keep_tensors:
+            for s in nd.srcs:
+                if last_use.get(s) == idx and s != net.output_name:
+                    t.pop(s, None)
+    got = F.read()
+    for name in [net.input_name] + [nd.dst for nd in net.nodes]:
+        qz.frac[name] = int(got[F.slot[name]])
+    for name, (at, K) in w_at.items():
+        if per_channel:
+            qz.w_frac[name], qz.w_frac_dev[name] = got[at:at + K], F.words[at:at + K]
+        else:
+            qz.w_frac[name] = int(got[at])
+    return qz, t
+
+
 def calibrate(net, x: torch.Tensor, device="cuda:0", keep_tensors: bool = True, per_channel: bool = False,
               rule: str = "maxabs", match_joins: bool = False):
     """x: float32 NHWC images (or int8 codes when the network takes codes).  Returns
@@ -137,6 +265,8 @@ def calibrate(net, x: torch.Tensor, device="cuda:0", keep_tensors: bool = True, 
     into the joined tensor)."""
     if rule not in ("maxabs", "search") or (rule == "search" and per_channel):
         raise ValueError("rule must be 'maxabs' or 'search' (the search with per-layer weight formats)")
+    if rule == "maxabs" and not match_joins and x.shape[0] > 0:
+        return _calibrate_on_device(net, x, device, keep_tensors, per_channel)
     qz = Quantized()
     biases = _quantize_weights(net, qz, device, per_channel)
     t: Dict[str, torch.Tensor] = {}

@@ -8,7 +8,7 @@ network's output).  Scales are chosen by ``dfq_np_frac_from_absmax_*`` from thre
 * weights: the finest power-of-two scale that holds max |w| of the layer; bias: an integer at the product scale of input
   and weights;
 * every layer runs on its already-quantized upstream tensors; its output scale comes from the largest magnitude of the
-  exact accumulator after the ReLU (``dfq_conv_np_absmax`` / ``dfq_eltwise_np_absmax``) with a rescale factor in (0, 1],
+  exact accumulator after the ReLU (``dfq_cal_conv_np`` / ``dfq_cal_add_np``) with a rescale factor in (0, 1],
   and only then is the accumulator converted, once;
 * pooling keeps the scale of its input.
 
@@ -23,7 +23,7 @@ from typing import Dict, Tuple
 import torch
 
 from . import binding as B
-from .net import float_weights
+from .net import FormatWords, float_weights
 
 
 @dataclass
@@ -56,61 +56,79 @@ def calibrate(net, x: torch.Tensor, p: int = 4, device="cuda:0"):
     """x: float32 NHWC images.  Returns (QuantizedNp, {tensor name: (hi, lo) digit planes of the calibration batch})."""
     if net.input_is_int8:
         raise ValueError("the (8, p) path starts from float inputs")
+    if x.shape[0] == 0:
+        raise B.DfqError(B.EINVAL, "calibration without images")
+    # every format is chosen on the device, from the maxima, by the kernels that use it: the host enqueues the whole network and waits once
+    L, call, st = B.lib(), B._check, B._stream(None)
     qz = QuantizedNp(p=p)
-    f_in = net.fixed_f_input if net.fixed_f_input is not None else B.np_frac_from_absmax_f32(float(B.absmax_f32(x).cpu()[0]), 8, p)
-    qz.frac[net.input_name] = f_in
-    t = {net.input_name: B.np_digits(B.quantize_np(x, 8, p, f_in), p)}
-    # thresholds of a group of layers are read back together (they depend on the weights alone), when its first layer is reached
-    groups, raw, w_frac = float_weights(net, device, fold=False), {}, {}
+    convs = [nd for nd in net.nodes if nd.op == "conv"]
+    F = FormatWords(net, device, len(convs), len(net.nodes))
+    gamma = torch.empty(max([nd.K for nd in convs] + [1]), dtype=torch.float32, device=device)
+    i8 = dict(dtype=torch.int8, device=device)
+    if net.fixed_f_input is not None:
+        F.words[F.slot[net.input_name]].fill_(net.fixed_f_input)
+        t = {net.input_name: B.np_digits(B.quantize_np(x, 8, p, net.fixed_f_input), p)}
+    else:
+        B._dev(x, torch.float32, "x")
+        hi, lo = torch.empty(x.shape, **i8), torch.empty(x.shape, **i8)
+        call(L.dfq_cal_np_quantize(x.data_ptr(), x.numel(), p, gamma.data_ptr(), hi.data_ptr(), lo.data_ptr(), F.of(net.input_name), F.err, st),
+             "dfq_cal_np_quantize")
+        t = {net.input_name: (hi, lo)}
+    groups, raw, w_at = float_weights(net, device, fold=False), {}, {}
     for nd in net.nodes:
         if nd.op == "conv":
             src = nd.srcs[0]
-            f_x = qz.frac[src]
             if nd.name not in raw:
                 raw = next(groups)
-                gamma = torch.empty(len(raw), dtype=torch.float32, device=device)
-                for i, (wf, _) in enumerate(raw.values()):
-                    B.absmax_f32(wf, out_dev=gamma[i:i + 1])
-                w_frac = {name: B.np_frac_from_absmax_f32(float(g), 8, p) for name, g in zip(raw, gamma.cpu().numpy())}
             wf, bf = raw.pop(nd.name)
-            f_w = w_frac[nd.name]
-            qz.w_frac[nd.name] = f_w
-            qz.w_codes[nd.name] = B.quantize_np(wf, 8, p, f_w)
-            wh, wl = B.np_digits(qz.w_codes[nd.name], p)
-            qz.b[nd.name] = B.quantize_i32(bf, f_x + f_w)
-            K = wh.shape[0]
+            B._dev(wf, torch.float32, "weights")
+            B._dev(bf, torch.float32, "bias")
+            K = int(wf.shape[0])
+            # the matrix-core kernel writes whole groups of 16 channels: the last layer gets all-zero filter rows up to
+            # the next multiple (their outputs are zeros behind the real ones and are never read)
+            padded = nd.dst == net.output_name and K % 16 and wf.shape[3] % 64 == 0 and nd.groups == 1 and not packs(net, nd)
+            Kp, make = ((K + 15) // 16 * 16, torch.zeros) if padded else (K, torch.empty)
+            qz.w_codes[nd.name] = torch.empty(wf.shape, dtype=torch.uint8, device=device)
+            wh, wl = (make((Kp,) + tuple(wf.shape[1:]), **i8) for _ in range(2))
+            b = qz.b[nd.name] = make((Kp,) + tuple(bf.shape[1:]), dtype=torch.int32, device=device)
+            w_at[nd.name] = F.weights(1)
+            w_frac = F.err + 4 * w_at[nd.name]
+            call(L.dfq_cal_np_weights(wf.data_ptr(), bf.data_ptr(), K, wf.numel() // K, p, gamma.data_ptr(), F.of(src),
+                                      qz.w_codes[nd.name].data_ptr(), wh.data_ptr(), wl.data_ptr(), w_frac, b.data_ptr(), F.err, st),
+                 "dfq_cal_np_weights")
             if packs(net, nd):
-                wh, wl = B.stem_pack_w(wh), B.stem_pack_w(wl)
-            elif nd.dst == net.output_name and K % 16 and wh.shape[3] % 64 == 0 and nd.groups == 1:
-                # the matrix-core kernel writes whole groups of 16 channels: the last layer gets all-zero filter rows up to
-                # the next multiple (their outputs are zeros behind the real ones and are never read)
-                Kp = (K + 15) // 16 * 16
-                wh, wl = [torch.cat([v, torch.zeros((Kp - K,) + tuple(v.shape[1:]), dtype=v.dtype, device=device)]) for v in (wh, wl)]
-                qz.b[nd.name] = torch.cat([qz.b[nd.name], torch.zeros(Kp - K, dtype=torch.int32, device=device)])
+                wh, wl = B.stem_pack_w(wh, stream=st), B.stem_pack_w(wl, stream=st)
             qz.w[nd.name] = (wh, wl)
             xh, xl, wh, wl, stride, pad = _conv_operands(net, nd, qz, t[src])
-            if nd.fixed_f_out is not None:
-                qz.frac[nd.dst] = nd.fixed_f_out
-            else:
-                m = B.conv_np_absmax(xh, xl, wh, wl, qz.b[nd.name], stride, pad, nd.groups, nd.relu)
-                qz.frac[nd.dst] = B.np_frac_from_absmax_u64(m, f_x + f_w, 8, p)
-            _, yh, yl = B.conv_np(xh, xl, wh, wl, qz.b[nd.name], f_x, f_w, qz.frac[nd.dst], p, stride, pad, nd.groups, nd.relu,
-                                  want_codes=False)
-            t[nd.dst] = (yh, yl) if yh.shape[3] == K else (yh[..., :K].contiguous(), yl[..., :K].contiguous())
+            N, H, W, Cc = xh.shape
+            R, S = int(wh.shape[1]), int(wh.shape[2])
+            P, Q = B.conv_out_hw(H, W, R, S, stride, pad)
+            yh, yl = torch.empty((N, P, Q, Kp), **i8), torch.empty((N, P, Q, Kp), **i8)
+            fixed = nd.fixed_f_out is not None
+            call(L.dfq_cal_conv_np(xh.data_ptr(), xl.data_ptr(), wh.data_ptr(), wl.data_ptr(), b.data_ptr(), yh.data_ptr(), yl.data_ptr(), N, H, W,
+                                   Cc, Kp, R, S, stride, pad, nd.groups, F.of(src), w_frac, None if fixed else F.maximum(1), int(fixed),
+                                   nd.fixed_f_out if fixed else 0, F.new(nd.dst), p, int(nd.relu), F.err, st), "dfq_cal_conv_np")
+            t[nd.dst] = (yh, yl) if Kp == K else (yh[..., :K].contiguous(), yl[..., :K].contiguous())
+            del wf, bf
         elif nd.op == "eltwise":
-            a, b = nd.srcs
-            fa, fb = qz.frac[a], qz.frac[b]
-            m = B.eltwise_np_absmax(*t[a], fa, *t[b], fb, nd.relu)
-            qz.frac[nd.dst] = B.np_frac_from_absmax_u64(m, max(fa, fb), 8, p)
-            _, yh, yl = B.eltwise_np(*t[a], fa, *t[b], fb, qz.frac[nd.dst], p, nd.relu, want_codes=False)
+            (ah, al), (bh, bl) = (t[s] for s in nd.srcs)
+            fa, fb = (F.of(s) for s in nd.srcs)
+            yh, yl = torch.empty(ah.shape, **i8), torch.empty(ah.shape, **i8)
+            call(L.dfq_cal_add_np(ah.data_ptr(), al.data_ptr(), fa, bh.data_ptr(), bl.data_ptr(), fb, ah.numel(), p, int(nd.relu), F.maximum(1),
+                                  yh.data_ptr(), yl.data_ptr(), F.new(nd.dst), F.err, st), "dfq_cal_add_np")
             t[nd.dst] = (yh, yl)
         elif nd.op in ("maxpool", "avgpool"):
             src = nd.srcs[0]
-            qz.frac[nd.dst] = qz.frac[src]
-            _, yh, yl = B.pool_np(*t[src], "max" if nd.op == "maxpool" else "avg", nd.R, nd.stride, nd.pad, p, want_codes=False)
+            F.same(nd.dst, src)
+            _, yh, yl = B.pool_np(*t[src], "max" if nd.op == "maxpool" else "avg", nd.R, nd.stride, nd.pad, p, want_codes=False, stream=st)
             t[nd.dst] = (yh, yl)
         else:
             raise NotImplementedError("%s on (8, p) codes" % nd.op)
+    got = F.read()
+    for name in [net.input_name] + [nd.dst for nd in net.nodes]:
+        qz.frac[name] = int(got[F.slot[name]])
+    for name, at in w_at.items():
+        qz.w_frac[name] = int(got[at])
     return qz, t
 
 
