@@ -26,6 +26,8 @@ namespace dfq {
 namespace {
 
 constexpr int kRagThreads = 256;
+constexpr int kLdsMost = 160 * 1024;
+constexpr int kNumUnits = 256;
 
 struct RagParams {
     ConvArgs a;
@@ -256,6 +258,278 @@ __global__ void __launch_bounds__(kRagThreads) conv_rag_kernel(RagParams prm)
     }
 }
 
+constexpr int kRowsBM = 128;
+
+// ---- the input's rows in LDS -------------------------------------------------------------------------------------------
+// groups == 1 and rows that fit: the image rows a tile of BM output pixels reads are brought to LDS once, padding columns and rows
+// outside the image as zeros, each row at a 16-byte boundary - whatever the channel count and the base's alignment.  Every kernel
+// row and every channel of the tile then reads its operands from there: an output pixel's window in a row is S*C contiguous
+// bytes that start anywhere, so a lane takes five aligned words and cuts its 16 bytes out with four byte alignments by an amount that
+// never changes (rows and pieces lie at multiples of 16).  What conv_rag_kernel does per 16 bytes, tap and channel tile - address,
+// border test, shift, LDS write - happens here once per 16 bytes of the input.  The weights take conv_rag_kernel's route through two LDS
+// stages.  The reduction runs in chunks of 32 bytes of a kernel row; behind the end of a row's S*C bytes the weights are zero.
+// A workgroup owns 128 pixels, a wavefront 32 of them and all 32 * CT channels of the tile.
+// Bound by the LDS: a lane's 16 bytes are five words wherever they start (34 LDS cycles per chunk and wavefront against 64 of the matrix
+// pipe).  16 x 57 x 43 x 83 -> 131, 3x3 (rotating inputs): conv_rag_kernel 24.9 us, here 20.0 (without stores 16.9, without the input's
+// rows 16.6, launch and addresses alone 4.2); 292 x 48 x 250 -> 9, 5x5 67.9, 38.0; 1950 pixels of 114 -> 292, 5x5 31.5, 21.1.
+// Tried: 96 .. 160 channels per tile (fewer workgroups: 20.7 .. 22 us), tiles of 64 pixels (28 us: nearly the same rows), a ring of
+// weights one step ahead (the same time).
+struct RowsParams {
+    ConvArgs a;
+    int M;
+    int seglen, seg_end;         // bytes of a window's row: S*C, and rounded up to whole chunks of 32
+    int nsteps;                  // steps of two chunks
+    int tiles_k;
+    int row_bytes, w_row, w_bytes;
+    int pitch;                   // LDS bytes of an image row
+    int vs, slots;               // LDS rows an output row advances by; LDS rows of an image
+    int stage_at;                // LDS byte of the weight stages
+    FastDiv div_tk, div_pq, div_q, div_pieces, div_slots, div_r;
+};
+
+template <int CT>
+__global__ void __launch_bounds__(kRagThreads) conv_rag_kernel_rows(RowsParams prm)
+{
+    constexpr int BM = kRowsBM, BK = 32 * CT;
+    constexpr bool kPartialW = BK * 4 < kRagThreads;
+    static_assert(BK * 4 <= kRagThreads, "one weight piece per lane and step");
+    constexpr int kAhead = 4, kRuns = 6;             // steps of weights in flight; runs of the input in flight
+    extern __shared__ uint4 lds[];
+    const ConvArgs &a = prm.a;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, lh = lane >> 5;
+    const int G = gridDim.x;
+    int lb = blockIdx.x;
+    {
+        const int per = G / 8, rem = G % 8, xcd = lb % 8, idx = lb / 8;
+        lb = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + idx;
+    }
+    const int pt = fastdiv(lb, prm.div_tk);
+    const int k0 = (lb - pt * prm.tiles_k) * BK, m0 = pt * BM;
+
+    // LDS row of output row p of image n: n * slots + p * vs (+ kernel row); the tile's first one is row 0
+    auto slot_of = [&](int m, int &q) {
+        const int n = fastdiv(m, prm.div_pq), pq = m - n * prm.div_pq.d;
+        const int p = fastdiv(pq, prm.div_q);
+        q = pq - p * a.Q;
+        return n * prm.slots + p * prm.vs;
+    };
+    int q_first, q_last, q_mine;
+    const int m_last = min(m0 + BM, prm.M) - 1;
+    const int u0 = __builtin_amdgcn_readfirstlane(slot_of(m0, q_first)), nrows = __builtin_amdgcn_readfirstlane(slot_of(m_last, q_last) + a.R - u0);
+    const int m = m0 + 32 * wave + l32;
+    const unsigned at = (unsigned)((slot_of(min(m, m_last), q_mine) - u0) * prm.pitch + q_mine * a.stride * a.C + 16 * lh);
+    const unsigned cut = at & 3u;
+    const char *xbase = (const char *)lds + (at & ~3u);
+
+    // ---- weights: lane's row tid/4 of a stage, piece tid%4.  Positions are scalars of the two chunks of a step: byte inside a weight
+    // row, and how many bytes of the window's row are left there.
+    const int lrow = tid >> 2, lp = tid & 3;
+    // (row order as in conv_rag_kernel: 16 consecutive channels end in each lane)
+    const int i32 = lrow & 31, k_mine = k0 + (lrow & ~31) + 16 * ((i32 >> 2) & 1) + 4 * (i32 >> 3) + (i32 & 3);
+    const int woff = min(k_mine, a.K - 1) * prm.w_row + 16 * (lp & 1);
+    int f_o = 0, f_seg = 0;                     // the next chunk: byte of the window's row; the row's first byte inside a weight row
+    u128 wv[kAhead];                            // steps on their way
+    int wd[kAhead], left0[kAhead], left1[kAhead];
+    const int wlast = prm.w_bytes - 16;
+    auto next_chunk = [&](int &byte, int &left) __attribute__((always_inline)) {
+        byte = f_seg + f_o;
+        left = f_seg < prm.w_row ? prm.seglen - f_o : 0;               // (past the last kernel row: nothing)
+        f_o += 32;
+        if (f_o == prm.seg_end) {
+            f_o = 0;
+            f_seg += prm.seglen;
+        }
+    };
+    auto fetch = [&](int f) __attribute__((always_inline)) {
+        int b0, b1;
+        next_chunk(b0, left0[f]);
+        next_chunk(b1, left1[f]);
+        const int b = woff + (lp < 2 ? b0 : b1), from = min(b, wlast);
+        wd[f] = b - from;
+        wv[f] = load16(a.w, (unsigned)from);
+    };
+    auto any = [](bool c) { return __builtin_amdgcn_ballot_w64(c) != 0; };
+    auto deposit = [&](int f, int stage) __attribute__((always_inline)) {
+        if (kPartialW && lrow >= BK) return;
+        uint4 *ws = lds + prm.stage_at / 16 + stage * (BK * 4);
+        u128 v = wv[f];
+        if (any(wd[f] != 0)) v = shift_bytes(v, wd[f]);
+        if (min(left0[f], left1[f]) < 32) {
+            const int valid = (lp < 2 ? left0[f] : left1[f]) - 16 * (lp & 1);
+            const unsigned long long part = (1ull << (8 * (valid & 7))) - 1ull;
+            const unsigned long long lo = (unsigned long long)v, hi = (unsigned long long)(v >> 64);
+            if (valid <= 0) v = 0;
+            else if (valid < 16) v = valid < 8 ? (u128)(lo & part) : ((u128)(hi & part) << 64) | lo;
+        }
+        *(u128 *)(ws + lrow * 4 + (lp ^ ((lrow >> 2) & 3))) = v;
+    };
+#pragma unroll
+    for (int f = 0; f < kAhead; f++)
+        if (f < prm.nsteps) fetch(f);
+
+    // ---- the tile's image rows, 64 pieces of a row per wavefront and load: everything about the row is scalar
+    {
+        const int per_row = prm.div_pieces.d, runs = (per_row + 63) / 64, total = nrows * runs, pad_bytes = a.pad * a.C, xlast = prm.row_bytes - 16;
+        int u = 0, run = wave;                  // wavefront v takes runs v, v + 4, ... of all rows together
+        while (run >= runs) { run -= runs; u++; }
+        for (int i0 = wave; i0 < total; i0 += 4 * kRuns) {
+            u128 v[kRuns];
+            int d[kRuns], to[kRuns];
+#pragma unroll
+            for (int e = 0; e < kRuns; e++) {
+                const int us = u0 + u, n = fastdiv(us, prm.div_slots), s = us - n * prm.slots;
+                const int p = a.stride >= a.R ? fastdiv(s, prm.div_r) : s;         // kernels that skip rows have no slots for them
+                const int ih = (a.stride >= a.R ? p * a.stride + s - p * a.R : s) - a.pad;
+                const bool row_in = i0 + 4 * e < total && (unsigned)ih < (unsigned)a.H;
+                const unsigned row = row_in ? (unsigned)(n * a.H + ih) * (unsigned)prm.row_bytes : 0u;
+                const int piece = run * 64 + lane, b = piece * 16 - pad_bytes, from = max(0, min(b, xlast));
+                to[e] = i0 + 4 * e < total && piece < per_row ? u * prm.pitch + piece * 16 : -1;
+                d[e] = row_in ? b - from : 16;
+                v[e] = load16(a.x, row + (unsigned)from);
+                run += 4;
+                while (run >= runs) { run -= runs; u++; }
+            }
+#pragma unroll
+            for (int e = 0; e < kRuns; e++) {
+                if (any(d[e] != 0)) v[e] = shift_bytes(v[e], d[e]);
+                if (to[e] >= 0) *(u128 *)((char *)lds + to[e]) = v[e];
+            }
+        }
+    }
+    deposit(0, 0);
+    if (kAhead < prm.nsteps) fetch(0);
+
+    v16i acc[CT];
+#pragma unroll
+    for (int c = 0; c < CT; c++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) acc[c][i] = 0;
+    const int swz = (l32 >> 2) & 3;
+    int xo = 0, xr = 0;                          // byte of the window's row, the kernel row's LDS bytes
+    const int xr_last = (a.R - 1) * prm.pitch;
+    // (a barrier that waits for LDS alone: the weights on their way stay there)
+    auto ring_barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    auto step = [&](int i, int f) __attribute__((always_inline)) {           // f: where the next step's weights are
+        const v4i *ws = (const v4i *)(lds + prm.stage_at / 16 + (f + 1 & 1) * (BK * 4));
+#pragma unroll
+        for (int kk = 0; kk < 2; kk++) {
+            const uint32_t *src = (const uint32_t *)(xbase + xr + xo);
+            uint32_t w5[5];
+#pragma unroll
+            for (int e = 0; e < 5; e++) w5[e] = src[e];
+            v4i wf[CT], xf;
+#pragma unroll
+            for (int c = 0; c < CT; c++) wf[c] = ws[(c * 32 + l32) * 4 + ((kk * 2 + lh) ^ swz)];
+#pragma unroll
+            for (int e = 0; e < 4; e++) xf[e] = (int)__builtin_amdgcn_alignbyte(w5[e + 1], w5[e], cut);
+#pragma unroll
+            for (int c = 0; c < CT; c++) acc[c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[c], xf, acc[c], 0, 0, 0);
+            xo += 32;
+            if (xo == prm.seg_end) {
+                xo = 0;
+                xr = min(xr + prm.pitch, xr_last);       // (an odd last chunk meets zero weights)
+            }
+        }
+        if (i + 1 < prm.nsteps) {
+            deposit(f, f & 1);                // the stage read one step ago; its readers have met at the barrier below
+            if (i + 1 + kAhead < prm.nsteps) fetch(f);
+            ring_barrier();
+        }
+    };
+    static_assert(kAhead % 2 == 0, "a step's stage is its number's parity");
+    ring_barrier();
+    for (int i = 0; i < prm.nsteps; i += kAhead) {
+#pragma unroll
+        for (int u = 0; u < kAhead; u++)
+            if (i + u < prm.nsteps) step(i + u, (u + 1) % kAhead);
+    }
+    settle_accumulators<CT>(&acc[0]);
+
+    Requant rq;
+    rq.init(a.shift, a.relu);
+    const bool lean = rq.fast && !a.frac_w && !a.acc_out;
+    if (m >= prm.M) return;
+#pragma unroll
+    for (int c = 0; c < CT; c++) {
+        const int kc = k0 + c * 32 + 16 * lh;
+        if (kc >= a.K) continue;
+        const int count = min(16, a.K - kc);
+        int bv[16];
+        load_bias16(a, kc, bv);
+#pragma unroll
+        for (int i = 0; i < 16; i++) acc[c][i] += bv[i];
+        if (lean) {
+            const uint4 r = requant_tile_lane_fast(acc[c], rq);
+            store_bytes(Bytes16{{r.x, r.y, r.z, r.w}}, a.y + (size_t)m * a.ldy + kc, count);
+        } else {
+            store_tile_lane_ragged(acc[c], a, m, kc, count);
+        }
+    }
+}
+
+// LDS bytes of a tile's rows (with the words behind the last window), at worst
+long long rows_bytes(const ConvArgs &a)
+{
+    constexpr int bm = kRowsBM;
+    const int vs = a.stride < a.R ? a.stride : a.R;
+    const long long out_rows = (bm - 2) / a.Q + 2, images = (out_rows - 2) / a.P + 1;
+    const long long rows = (out_rows - 1) * vs + a.R + images * (a.R - vs);
+    const long long pitch = ((long long)((a.Q - 1) * a.stride + a.S) * a.C + 15) / 16 * 16;
+    return rows * pitch + 64;
+}
+
+// Channel tiles (of 32) of conv_rag_kernel_rows for a call, or 0: conv_rag_kernel.  Fitted to 726 layers (3x3 to 7x7, 3 to 400 channels,
+// strides 1 and 2; plain, formats per channel, sums), each under both: 216 lie behind the line, 18 % faster in the mean, eight of them more
+// than 4 % slower, by 12 % at most.  Below ten steps, or 16 where rows and columns are skipped, staging the rows costs what it saves
+// (39456 pixels of 51 -> 63, 1x1: 7.4 us, with rows 9.9; 3072 of 63 -> 62, 3x3 / 2: 9.2, 13.4); rows of more than 72 KB leave one
+// workgroup per unit (123200 pixels of 182 -> 12, 3x3: 36.0, 53.6).  Tiles of 32 channels while they are at most two per unit (1950 pixels of
+// 114 -> 292, 5x5: 21.1 us, of 64 channels 23.9), else 64 (7670 of 164 -> 169, 5x5: 53.7, 33.5).
+int rows_tile(const ConvArgs &a)
+{
+    const long long steps = ((long long)a.R * ((a.S * a.C + 31) / 32) + 1) / 2;
+    if (a.groups != 1 || steps < (a.stride > 1 ? 16 : 10) || a.R * a.S < 9 || rows_bytes(a) > 72 * 1024) return 0;
+    const long long tiles_p = ((long long)a.N * a.P * a.Q + kRowsBM - 1) / kRowsBM, tiles = tiles_p * ((a.K + 31) / 32);
+    // (a lane has one pixel for every format it fetches, or for every sum's address: many tiles with formats per channel or sums lose,
+    // 81648 pixels of 86 -> 97, 3x3, per channel 34.0 us, here 38.4; 85500 of 58 -> 25, 5x5 / 2, 30.0, 41.5)
+    if ((a.frac_w || a.acc_out) && tiles_p > 400) return 0;
+    return tiles <= 2 * kNumUnits ? 1 : 2;
+}
+
+template <int CT>
+hipError_t launch_rows(const ConvArgs &a, hipStream_t st)
+{
+    constexpr int BM = kRowsBM, BK = 32 * CT;
+    RowsParams prm{};
+    prm.a = a;
+    prm.M = a.N * a.P * a.Q;
+    prm.seglen = a.S * a.C;
+    prm.seg_end = (prm.seglen + 31) / 32 * 32;
+    prm.nsteps = (a.R * (prm.seg_end / 32) + 1) / 2;
+    prm.tiles_k = (a.K + BK - 1) / BK;
+    prm.row_bytes = a.W * a.C;
+    prm.w_row = a.R * prm.seglen;
+    prm.w_bytes = a.K * prm.w_row;
+    prm.pitch = (((a.Q - 1) * a.stride + a.S) * a.C + 15) / 16 * 16;
+    prm.vs = a.stride < a.R ? a.stride : a.R;
+    prm.slots = (a.P - 1) * prm.vs + a.R;
+    prm.stage_at = (int)rows_bytes(a);
+    prm.div_tk = make_fastdiv(prm.tiles_k);
+    prm.div_pq = make_fastdiv(a.P * a.Q);
+    prm.div_q = make_fastdiv(a.Q);
+    prm.div_pieces = make_fastdiv(prm.pitch / 16);
+    prm.div_slots = make_fastdiv(prm.slots);
+    prm.div_r = make_fastdiv(a.R);
+    const size_t lds_bytes = (size_t)prm.stage_at + 2 * BK * 64;
+    const long long grid = (prm.M + (long long)BM - 1) / BM * prm.tiles_k;
+    if (grid > 0x7fffffffLL || lds_bytes > kLdsMost) return hipErrorInvalidValue;
+    static const hipError_t attr = hipFuncSetAttribute((const void *)conv_rag_kernel_rows<CT>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsMost);
+    if (attr != hipSuccess) return attr;
+    conv_rag_kernel_rows<CT><<<(unsigned)grid, kRagThreads, lds_bytes, st>>>(prm);
+    return hipGetLastError();
+}
+
 template <int BM, int BK>
 hipError_t launch_rag(RagParams &prm, hipStream_t st)
 {
@@ -314,6 +588,8 @@ bool conv_rag_pays(const ConvArgs &a)
 
 static hipError_t launch_images(const ConvArgs &a, hipStream_t st)
 {
+    const int rows_ct = rows_tile(a);
+    if (rows_ct) return rows_ct == 1 ? launch_rows<1>(a, st) : launch_rows<2>(a, st);
     RagParams prm{};
     prm.a = a;
     prm.M = a.N * a.P * a.Q;
