@@ -466,7 +466,9 @@ int64_t dfq_add_max_len(int q, int64_t bx, int64_t ex);                         
  * dfq_cal_add: the add of two int8 tensors; maximum[1].
  * dfq_cal_concat: branch i's format is frac[idx[i]] (xs, Cs, idx: HOST arrays), the result's the coarsest branch's unless fixed.
  * dfq_cal_np_weights, dfq_cal_np_quantize: codes and digit planes on (8, p); gamma as above.
- * dfq_cal_conv_np, dfq_cal_add_np: the largest sum (amax[1]; a fixed output format needs none), the format, the digit planes. */
+ * dfq_cal_conv_np, dfq_cal_add_np: the largest sum (amax[DFQ_CAL_AMAX_WORDS]: sixteen words a cache line apart share the atomics; a
+ *   fixed output format needs none), the format, the digit planes. */
+#define DFQ_CAL_AMAX_WORDS 256
 dfq_status dfq_cal_weights(const float *w, const float *bias, size_t rows, size_t row_len, int per_row, float *gamma, const int32_t *frac_in,
                            int8_t *q, int32_t *w_frac, int32_t *b, int32_t *err, dfq_stream stream);
 dfq_status dfq_cal_quantize(const float *x, size_t n, float *gamma, int8_t *q, int32_t *frac, int32_t *err, dfq_stream stream);

@@ -17,6 +17,7 @@ LIB_PATH = os.path.join(_HERE, "libdfq.so")
 
 OK, EINVAL, ESHAPE, EFMT, EUNSUPPORTED, EDEVICE = range(6)
 POOL_MAX, POOL_AVG = 0, 1
+CAL_AMAX_WORDS = 256          # DFQ_CAL_AMAX_WORDS
 CONV_AUTO, CONV_DIRECT, CONV_MFMA, CONV_DEPTHWISE, CONV_SMALLC, CONV_POINTWISE, CONV_GROUPED, CONV_RAGGED, CONV_SPLIT = range(9)
 CONV_VARIANT_NAMES = {CONV_AUTO: "auto", CONV_DIRECT: "direct", CONV_MFMA: "mfma",
                       CONV_DEPTHWISE: "depthwise", CONV_SMALLC: "smallc", CONV_POINTWISE: "pointwise",

@@ -24,7 +24,7 @@
 // conv_np_mfma_kernel: implicit GEMM, one tile of BP pixels x BC channels per workgroup of four wavefronts, the
 // reduction axis in 64-byte steps through a ring of two or three LDS stages of 2 (BP + BC) rows filled by direct
 // global -> LDS loads that many steps ahead; rows are 64 bytes with the 16-byte pieces XOR-swizzled as in the int8
-// kernels; two or three workgroups share a compute unit.  With ADD the element-wise add that follows the layer
+// kernels; up to three workgroups share a compute unit.  Where C is a multiple of 128 a step is a whole cache line of every row.  With ADD the element-wise add that follows the layer
 // (Eq. 10) runs in the epilogue.
 // With AMAX it is the calibration pass: the same sums, nothing stored but the largest magnitude.
 // conv_np_direct_kernel: one output per lane, any geometry (groups, C not a multiple of 64).
@@ -39,163 +39,6 @@ namespace dfq {
 
 namespace {
 
-// ---- scalar pieces ------------------------------------------------------------------------------------------------
-
-struct NpRound {
-    int shift;          // f_x + f_w - f_y
-    int p;              // significand bits of the output format
-    float beta_max;     // Eq. 5 for the output format (at most 12 bits: exact in float)
-    int relu;
-};
-
-// The accumulator value v times 2^-shift, rounded to the nearest integer representable with p + 1 significant bits
-// (step 1 below 2^(p+1)), ties to the even significand, magnitude clamped to beta_max.  |v| < 2^62.
-// The magnitude is first cut to 23 bits with a sticky bit for what was cut (the rounding position is at least 15
-// bits above it), which a float holds exactly; the rest is the conversion of a float to the format: scale by an exact
-// power of two so that the step becomes 1, round to nearest even, scale back.
-__device__ __forceinline__ int np_round_acc(long long v, const NpRound &f)
-{
-    if (f.relu && v < 0) v = 0;
-    const bool neg = v < 0;
-    const unsigned long long a = neg ? (unsigned long long)(-v) : (unsigned long long)v;
-    const int lz = a ? __clzll((long long)a) : 64;
-    const int t = max(41 - lz, 0);                       // bits to cut: the leading bit goes to position 22
-    unsigned m = (unsigned)(a >> t);
-    if (((unsigned long long)m << t) != a) m |= 1u;      // sticky
-    float x = ldexpf((float)m, t - f.shift);
-    x = fminf(x, f.beta_max);
-    const int ex = (int)((__float_as_uint(x) >> 23) & 0xffu) - 127;
-    const int k = max(ex - f.p, 0);
-    float r = ldexpf(__builtin_rintf(ldexpf(x, -k)), k);
-    r = fminf(r, f.beta_max);
-    const int beta = (int)r;
-    return neg ? -beta : beta;
-}
-
-// The same rounding for the matrix-core kernel's epilogue when 7 <= shift <= 36, through the double-precision adder.  The
-// accumulator is V = 64 * T + c with T and c int32 (|V| < 2^37): a double holds it exactly.  With e the binade of |V| the
-// result's step is 2^(e' - p) in units of V, e' = max(e, p + shift) (below 2^(p+1) output units the step is one unit).
-// Adding M = 1.5 * 2^(e' + 52 - p) puts V into a binade whose unit in the last place is exactly that step, so the adder's
-// own round-to-nearest-even does the rounding (M is an even multiple of the step: the parity of the sum's last bit is the
-// parity of the quotient q = round(V / step), i.e. of the significand field), and q is the low word of the sum's bit
-// pattern (the mantissa field holds 2^51 + q).  The result is q * 2^k, k = e' - p - shift.  Values beyond every format
-// of this path (e' capped at p + shift + 11 - p: at least 2^12 output units) still give a q * 2^k >= 2^12 that fits 31
-// bits because shift >= 7, and the clamp that follows cuts them.  Returns the signed integer before the clamp.
-struct NpFast {
-    unsigned base_b;     // biased exponent of the smallest e': 1023 + p + shift
-    unsigned top_b;      // base_b + 11 - p
-    unsigned m_const;    // ((52 - p) << 20) | 0x80000: exponent offset and the mantissa bit of the factor 1.5
-    int bmax;
-};
-
-__device__ __forceinline__ int np_round_fast(int T, int c, const NpFast &f)
-{
-    const double x = __builtin_fma((double)T, 64.0, (double)c);
-    const unsigned e_b = __builtin_amdgcn_ubfe((unsigned)__double2hiint(x), 20u, 11u);
-    unsigned eb;
-    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(eb) : "v"(e_b), "s"(f.base_b), "v"(f.top_b));      // clamp to [base_b, top_b]
-    const double M = __hiloint2double((int)((eb << 20) + f.m_const), 0);
-    const int q = __double2loint(x + M);
-    return q << (eb - f.base_b);
-}
-
-// The conversion of a 32-bit sum t (|t| < 2^30) times 2^-shift, 0 <= shift <= 31, by the same device: (double)t is exact.
-__device__ __forceinline__ int np_round_fast_i32(int t, const NpFast &f)
-{
-    const double x = (double)t;
-    const unsigned e_b = __builtin_amdgcn_ubfe((unsigned)__double2hiint(x), 20u, 11u);
-    unsigned eb;
-    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(eb) : "v"(e_b), "s"(f.base_b), "v"(f.top_b));
-    const double M = __hiloint2double((int)((eb << 20) + f.m_const), 0);
-    const int q = __double2loint(x + M);
-    return q << (eb - f.base_b);
-}
-
-// byte E of w = low byte of (v >> sh), of (v & msk), of (x - y): the operation writes its result's low byte straight
-// into the packed word (sub-dword destination select), the other bytes are kept
-template <int E>
-__device__ __forceinline__ void put_shr(uint32_t &w, unsigned sh, unsigned v)
-{
-    if constexpr (E == 0) asm("v_lshrrev_b32_sdwa %0, %1, %2 dst_sel:BYTE_0 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(sh), "v"(v));
-    if constexpr (E == 1) asm("v_lshrrev_b32_sdwa %0, %1, %2 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(sh), "v"(v));
-    if constexpr (E == 2) asm("v_lshrrev_b32_sdwa %0, %1, %2 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(sh), "v"(v));
-    if constexpr (E == 3) asm("v_lshrrev_b32_sdwa %0, %1, %2 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(sh), "v"(v));
-}
-template <int E>
-__device__ __forceinline__ void put_ashr(uint32_t &w, unsigned sh, int v)
-{
-    if constexpr (E == 0) asm("v_ashrrev_i32_sdwa %0, %1, %2 dst_sel:BYTE_0 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(sh), "v"(v));
-    if constexpr (E == 1) asm("v_ashrrev_i32_sdwa %0, %1, %2 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(sh), "v"(v));
-    if constexpr (E == 2) asm("v_ashrrev_i32_sdwa %0, %1, %2 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(sh), "v"(v));
-    if constexpr (E == 3) asm("v_ashrrev_i32_sdwa %0, %1, %2 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(sh), "v"(v));
-}
-template <int E>
-__device__ __forceinline__ void put_and(uint32_t &w, unsigned msk, unsigned v)
-{
-    if constexpr (E == 0) asm("v_and_b32_sdwa %0, %1, %2 dst_sel:BYTE_0 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(msk), "v"(v));
-    if constexpr (E == 1) asm("v_and_b32_sdwa %0, %1, %2 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(msk), "v"(v));
-    if constexpr (E == 2) asm("v_and_b32_sdwa %0, %1, %2 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(msk), "v"(v));
-    if constexpr (E == 3) asm("v_and_b32_sdwa %0, %1, %2 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(msk), "v"(v));
-}
-template <int E>
-__device__ __forceinline__ void put_sub(uint32_t &w, unsigned x, unsigned y)
-{
-    if constexpr (E == 0) asm("v_sub_u32_sdwa %0, %1, %2 dst_sel:BYTE_0 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(x), "v"(y));
-    if constexpr (E == 1) asm("v_sub_u32_sdwa %0, %1, %2 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(x), "v"(y));
-    if constexpr (E == 2) asm("v_sub_u32_sdwa %0, %1, %2 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(x), "v"(y));
-    if constexpr (E == 3) asm("v_sub_u32_sdwa %0, %1, %2 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD" : "+v"(w) : "v"(x), "v"(y));
-}
-
-// Four neighbouring channels of one pixel: accumulators -> one packed word of codes, of high digits, of low digits.
-// FAST: 7 <= shift <= 36 (32-bit rounding above), else the 64-bit form; RELU and CODES (codes wanted) as template
-// parameters keep the sign handling and the encoding out of the variants that do not need them.
-template <bool FAST, bool RELU, bool CODES, int E>
-__device__ __forceinline__ void np_finish_one(int A, int Cc, int Bm, const NpRound &rnd, const NpFast &fr, int p_y, uint32_t &wc,
-                                              uint32_t &whi, uint32_t &wlo)
-{
-    const int T = (A << 6) + Bm;                         // 64 A + B (the bias sits in the start values of B and C)
-    int beta;
-    if constexpr (FAST) {
-        beta = np_round_fast(T, Cc, fr);
-        asm("v_med3_i32 %0, %1, %2, %3" : "=v"(beta) : "v"(beta), "s"(RELU ? 0 : -fr.bmax), "v"(fr.bmax));
-    } else {
-        beta = np_round_acc((long long)T * 64 + (long long)Cc, rnd);
-    }
-    if constexpr (RELU) {
-        put_shr<E>(whi, 6u, (unsigned)beta);
-        put_and<E>(wlo, 63u, (unsigned)beta);
-        if constexpr (CODES) wc |= np_code_of(beta, p_y) << (8 * E);
-    } else {
-        // digits of the sign of beta: h = trunc(beta / 64), l = beta - 64 h
-        const int t = beta + ((beta >> 31) & 63);
-        put_ashr<E>(whi, 6u, t);
-        put_sub<E>(wlo, (unsigned)beta, (unsigned)t & ~63u);
-        if constexpr (CODES) wc |= np_code_of(beta, p_y) << (8 * E);
-    }
-}
-
-// The fused join: the layer's result (32-bit rounding, clamp with the layer's own ReLU as the lower bound), aligned with
-// the other operand's integer 64 h + l, summed, converted a second time and split into digits.
-template <bool RELU_OUT, int E>
-__device__ __forceinline__ void np_finish_add_one(int A, int Cc, int Bm, uint32_t oh4, uint32_t ol4, int lo1, int sa, int sb, const NpFast &fr,
-                                                  const NpFast &fr2, uint32_t &whi, uint32_t &wlo)
-{
-    int beta = np_round_fast((A << 6) + Bm, Cc, fr);
-    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(beta) : "v"(beta), "s"(lo1), "v"(fr.bmax));
-    const int other = 64 * byte_of(oh4, E) + byte_of(ol4, E);
-    const int t = (beta << sa) + (other << sb);
-    int r = np_round_fast_i32(t, fr2);
-    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(r), "s"(RELU_OUT ? 0 : -fr2.bmax), "v"(fr2.bmax));
-    if constexpr (RELU_OUT) {
-        put_shr<E>(whi, 6u, (unsigned)r);
-        put_and<E>(wlo, 63u, (unsigned)r);
-    } else {
-        const int u = r + ((r >> 31) & 63);
-        put_ashr<E>(whi, 6u, u);
-        put_sub<E>(wlo, (unsigned)r, (unsigned)u & ~63u);
-    }
-}
-
 // ---- codes -> digit planes ----------------------------------------------------------------------------------------
 
 __global__ void __launch_bounds__(256) np_digits_kernel(const uint8_t *__restrict__ codes, size_t n, int p, int8_t *__restrict__ hi,
@@ -207,18 +50,6 @@ __global__ void __launch_bounds__(256) np_digits_kernel(const uint8_t *__restric
         hi[i] = (int8_t)h;
         lo[i] = (int8_t)l;
     }
-}
-
-// Maximum of m over the wavefront's lanes, then one atomic max per wavefront into *dst (the word starts at zero).
-__device__ __forceinline__ void wave_max_to(unsigned long long *dst, unsigned long long m)
-{
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        const unsigned long long other = __shfl_xor(m, o, 64);
-        m = other > m ? other : m;
-    }
-    // the maximum only grows: most wavefronts see that theirs is no news and spare the one word the atomic
-    if ((threadIdx.x & 63) == 0 && m > __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(dst, m);
 }
 
 __global__ void clear_u64_kernel(unsigned long long *p) { *p = 0ull; }
@@ -263,6 +94,7 @@ struct NpEltParams {
     const int32_t *cal_fa, *cal_fb;
     const unsigned long long *cal_amax;
     int32_t *cal_fy, *cal_err;
+    int amax_words;              // words the maximum is spread over (NpConvArgs::amax_words)
 };
 
 // the shifts of such an add: dfq_eltwise_np's limits, beyond which the call is refused at the end
@@ -291,7 +123,7 @@ __global__ void __launch_bounds__(256) eltwise_np_kernel(NpEltParams q)
 {
     if (q.cal_fa) {
         const int F = np_align(q.cal_fa, q.cal_fb, q.sa, q.sb, q.cal_err);
-        const int fy = frac_from_int(*q.cal_amax, F, (unsigned long long)q.beta_max);
+        const int fy = frac_from_int(spread_max(q.cal_amax, q.amax_words), F, (unsigned long long)q.beta_max);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             *q.cal_fy = fy;
             if (F - fy < -16 || F - fy > 31) atomicOr(q.cal_err, 2);
@@ -352,7 +184,7 @@ __global__ void __launch_bounds__(256) eltwise_np_absmax_kernel(NpEltParams q, u
             for (int e = 0; e < 4; e++) take(byte_of(wah[j], e), byte_of(wal[j], e), byte_of(wbh[j], e), byte_of(wbl[j], e));
     }
     for (size_t i = q.n16 * 16 + (size_t)blockIdx.x * 256 + threadIdx.x; i < q.n; i += (size_t)gridDim.x * 256) take(q.ah[i], q.al[i], q.bh[i], q.bl[i]);
-    wave_max_to(amax, (unsigned long long)mx);
+    block_max_to(amax, (unsigned long long)mx, q.amax_words);
 }
 
 // ---- pooling on digit planes ----------------------------------------------------------------------------------------
@@ -662,20 +494,6 @@ __global__ void __launch_bounds__(256) stem_pack_w_kernel(const int8_t *w, int8_
 
 // ---- direct form --------------------------------------------------------------------------------------------------
 
-// The layer's rescale shift: given, or - in a calibration whose formats stay on the device - from device words.
-__device__ __forceinline__ int np_layer_shift(const NpConvArgs &a)
-{
-    if (!a.cal_fx) return a.shift;
-    const int acc_frac = *a.cal_fx + *a.cal_fw;
-    const int fy = a.cal_fixed ? a.cal_fixed_frac : frac_from_int(*a.cal_amax, acc_frac, (unsigned long long)a.beta_max);
-    const int shift = acc_frac - fy;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        *a.cal_fy = fy;
-        if (shift < -16 || shift > 48) atomicOr(a.cal_err, 2);           // refused at the end, as a call with these formats is
-    }
-    return min(max(shift, -16), 48);
-}
-
 __global__ void __launch_bounds__(256) conv_np_direct_kernel(NpConvArgs a)
 {
     const int Cg = a.C / a.groups;
@@ -715,7 +533,7 @@ __global__ void __launch_bounds__(256) conv_np_direct_kernel(NpConvArgs a)
         if (a.yh) a.yh[i] = (int8_t)h;
         if (a.yl) a.yl[i] = (int8_t)l;
     }
-    if (a.amax) wave_max_to(a.amax, mx);
+    if (a.amax) block_max_to(a.amax, mx, a.amax_words);
 }
 
 // ---- matrix-core form ---------------------------------------------------------------------------------------------
@@ -730,18 +548,21 @@ struct NpConvParams {
     FastDiv div_q, div_p, div_tc;
 };
 
-template <int BP, int BC, int OCC, int NSTAGES, bool ADD, bool AMAX>
+// STEP 128: a step is a whole cache line of every row (a compute unit draws 52 bytes a clock from L2 that way and 29 in half lines), the
+// ring one stage for three workgroups per compute unit, or three for one.
+template <int BP, int BC, int OCC, int NSTAGES, bool ADD, bool AMAX, int STEP>
 __global__ void __launch_bounds__(256, OCC) conv_np_mfma_kernel(NpConvParams prm)
 {
-    static_assert(NSTAGES == 2 || NSTAGES == 3, "ring depth");
-    constexpr int ROWS = 2 * BP + 2 * BC;                 // LDS rows of 64 bytes per stage: x_h, x_l, w_h, w_l
+    static_assert(STEP == 64 ? NSTAGES == 2 || NSTAGES == 3 : STEP == 128 && (NSTAGES == 1 || NSTAGES == 3), "ring depth");
+    constexpr int ROWS = 2 * BP + 2 * BC;                 // LDS rows of STEP bytes per stage: x_h, x_l, w_h, w_l
     constexpr int XH = 0, XL = BP, WH = 2 * BP, WL = 2 * BP + BC;
-    constexpr int XJ = BP / 64, WJ = BC / 64;             // 16-row chunks per wavefront, operand plane and step
+    constexpr int PIECES = STEP / 16, RPC = 64 / PIECES;  // 16-byte pieces of a row; rows one wavefront-wide load fills (a chunk)
+    constexpr int XJ = BP / (4 * RPC), WJ = BC / (4 * RPC);   // chunks per wavefront, operand plane and step
     constexpr int LPW = 2 * XJ + 2 * WJ;                  // loads per wavefront and step
     static_assert(BP % 64 == 0 && BC % 64 == 0, "whole chunks for four wavefronts");
     constexpr int WP = BP / 2, WC = BC / 2;               // wavefront tile (2 x 2 wavefronts)
     constexpr int PT = WP / 32, CT = WC / 32;
-    static_assert(PT * CT == 4 || (PT * CT == 2 && OCC >= 2), "twelve accumulator tiles per wavefront, or six with two workgroups per compute unit");
+    static_assert(PT * CT == 2, "six accumulator tiles per wavefront");
 
     extern __shared__ uint4 lds[];
     const NpConvArgs &a = prm.a;
@@ -765,13 +586,13 @@ __global__ void __launch_bounds__(256, OCC) conv_np_mfma_kernel(NpConvParams prm
     const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) char *)(char *)&lds[0];
 
     // ---- producer: lane l of a wavefront-wide load supplies row l/4 of a 16-row chunk, physical piece l%4, which holds
-    // logical piece (l%4) ^ ((row>>2)&3)
-    const int lrow = lane >> 2;
-    const int lp = (lane & 3) ^ ((lane >> 4) & 3);
-    int ih0[XJ], iw0[XJ], xbase[XJ];
+    // logical piece (l%4) ^ ((row>>2)&3); steps of 128 bytes: row l/8 of 8, piece (l%8) ^ ((row>>1)&7), bit 3 of the row being the wavefront's
+    const int lrow = lane / PIECES;
+    const int lp = STEP == 64 ? (lane & 3) ^ ((lane >> 4) & 3) : (lane & 7) ^ ((lane >> 4) | ((wave & 1) << 2));
+    int ih0[XJ], iw0[XJ], xbase[XJ];              // (steps of 128 bytes: bits of ih0 are the kernel rows and columns outside the image)
 #pragma unroll
     for (int j = 0; j < XJ; j++) {
-        const int m = pt * BP + 16 * (wave + 4 * j) + lrow;
+        const int m = pt * BP + RPC * (wave + 4 * j) + lrow;
         if (m < prm.M) {
             const int t = fastdiv(m, prm.div_q);
             const int oq = m - t * a.Q;
@@ -780,8 +601,14 @@ __global__ void __launch_bounds__(256, OCC) conv_np_mfma_kernel(NpConvParams prm
             ih0[j] = op * a.stride - a.pad;
             iw0[j] = oq * a.stride - a.pad;
             xbase[j] = ((n * a.H + ih0[j]) * a.W + iw0[j]) * a.C + lp * 16;
+            if (STEP == 128) {
+                // R, S <= 16: kernel row r outside: bit r, kernel column s: bit 16 + s
+                const int rlo = max(0, -ih0[j]), rhi = min(a.R, a.H - ih0[j]), clo = max(0, -iw0[j]), chi = min(a.S, a.W - iw0[j]);
+                const unsigned rows = rhi > rlo ? ((1u << (rhi - rlo)) - 1u) << rlo : 0u, cols = chi > clo ? ((1u << (chi - clo)) - 1u) << clo : 0u;
+                ih0[j] = (int)~(rows | (cols << 16));
+            }
         } else {
-            ih0[j] = -(1 << 28);      // no kernel row is inside the image
+            ih0[j] = STEP == 128 ? -1 : -(1 << 28);      // no kernel row is inside the image
             iw0[j] = 0;
             xbase[j] = 0;
         }
@@ -791,27 +618,32 @@ __global__ void __launch_bounds__(256, OCC) conv_np_mfma_kernel(NpConvParams prm
     for (int j = 0; j < WJ; j++) {
         // LDS row i = 8g + 4h + e of a 32-row group receives channel 16h + 4g + e: the matrix instruction then leaves 16
         // consecutive channels in each lane
-        const int rr = 16 * (wave + 4 * j) + lrow;
+        const int rr = RPC * (wave + 4 * j) + lrow;
         const int i32 = rr & 31;
         const int k = ct * BC + (rr & ~31) + 16 * ((i32 >> 2) & 1) + 4 * (i32 >> 3) + (i32 & 3);
         woff[j] = k < a.K ? (unsigned)(k * (a.R * a.S * a.C) + lp * 16) : kOutOfRange;
     }
     int p_r = 0, p_s = 0, p_c = 0, p_it = 0;     // kernel row, kernel column, channel step and index of the step fetched next
     auto issue = [&](int stage) __attribute__((always_inline)) {
-        const int tap_off = (p_r * a.W + p_s) * a.C + p_c * kStepBytes;
-        const unsigned sbase = lds_base + (unsigned)(stage * ROWS) * 64u + (unsigned)wave * 1024u;
+        const int tap_off = (p_r * a.W + p_s) * a.C + p_c * STEP;
+        const unsigned sbase = lds_base + (unsigned)(stage * ROWS * STEP) + (unsigned)wave * 1024u;
 #pragma unroll
         for (int j = 0; j < XJ; j++) {
-            const bool ok = (unsigned)(ih0[j] + p_r) < (unsigned)a.H && (unsigned)(iw0[j] + p_s) < (unsigned)a.W;
-            const unsigned off = ok ? (unsigned)(xbase[j] + tap_off) : kOutOfRange;
-            load_piece_to_lds(off, xh_rsrc, (unsigned)__builtin_amdgcn_readfirstlane((int)(sbase + (unsigned)(XH * 64 + j * 4096))));
-            load_piece_to_lds(off, xl_rsrc, (unsigned)__builtin_amdgcn_readfirstlane((int)(sbase + (unsigned)(XL * 64 + j * 4096))));
+            unsigned off;
+            if (STEP == 128) {
+                off = (unsigned)(xbase[j] + tap_off) | (unsigned)(__builtin_amdgcn_sbfe(ih0[j], p_r, 1) | __builtin_amdgcn_sbfe(ih0[j], 16 + p_s, 1));
+            } else {
+                const bool ok = (unsigned)(ih0[j] + p_r) < (unsigned)a.H && (unsigned)(iw0[j] + p_s) < (unsigned)a.W;
+                off = ok ? (unsigned)(xbase[j] + tap_off) : kOutOfRange;
+            }
+            load_piece_to_lds(off, xh_rsrc, (unsigned)__builtin_amdgcn_readfirstlane((int)(sbase + (unsigned)(XH * STEP + j * 4096))));
+            load_piece_to_lds(off, xl_rsrc, (unsigned)__builtin_amdgcn_readfirstlane((int)(sbase + (unsigned)(XL * STEP + j * 4096))));
         }
-        const unsigned step_off = (unsigned)p_it * kStepBytes;
+        const unsigned step_off = (unsigned)p_it * STEP;
 #pragma unroll
         for (int j = 0; j < WJ; j++) {
-            load_piece_to_lds(woff[j] + step_off, wh_rsrc, (unsigned)__builtin_amdgcn_readfirstlane((int)(sbase + (unsigned)(WH * 64 + j * 4096))));
-            load_piece_to_lds(woff[j] + step_off, wl_rsrc, (unsigned)__builtin_amdgcn_readfirstlane((int)(sbase + (unsigned)(WL * 64 + j * 4096))));
+            load_piece_to_lds(woff[j] + step_off, wh_rsrc, (unsigned)__builtin_amdgcn_readfirstlane((int)(sbase + (unsigned)(WH * STEP + j * 4096))));
+            load_piece_to_lds(woff[j] + step_off, wl_rsrc, (unsigned)__builtin_amdgcn_readfirstlane((int)(sbase + (unsigned)(WL * STEP + j * 4096))));
         }
         ++p_it;
         if (++p_c == prm.csteps) {
@@ -826,7 +658,7 @@ __global__ void __launch_bounds__(256, OCC) conv_np_mfma_kernel(NpConvParams prm
     // ---- consumer
     const int wp0 = (wave & 1) * WP, wc0 = (wave >> 1) * WC;
     const int l32 = lane & 31, lh = lane >> 5;
-    const int swz = (l32 >> 2) & 3;
+    const int swz = STEP == 64 ? (l32 >> 2) & 3 : (l32 >> 1) & 7;
     v16i accA[CT][PT], accC[CT][PT], accB[CT][PT];
     // the bias b = 64 * (b >> 6) + (b & 63) starts the accumulators of the middle and the low products
 #pragma unroll
@@ -861,36 +693,108 @@ __global__ void __launch_bounds__(256, OCC) conv_np_mfma_kernel(NpConvParams prm
         v4i xh[PT], xl[PT];
     };
     Half f0, f1;
+    // (steps of 128 bytes: bits 5 and 6 of a lane's LDS address are the piece's, so k-step kk is one XOR away; kept out of registers)
+    unsigned lane_at = (unsigned)(l32 * STEP + ((lh ^ swz) * 16));
     auto read_half = [&](Half &f, int kk, int stage) __attribute__((always_inline)) {
-        const v4i *st = (const v4i *)lds + stage * ROWS * kPieces;
-        const int g = (kk * 2 + lh) ^ swz;
+        unsigned at = lane_at;
+        if (STEP == 128) asm volatile("v_xor_b32 %0, %1, %2" : "=v"(at) : "n"(0), "v"(lane_at));
+        const char *st = (const char *)lds + stage * (ROWS * STEP) + (at ^ (unsigned)(kk * 32));
 #pragma unroll
         for (int c = 0; c < CT; c++) {
-            const int row = wc0 + c * 32 + l32;
-            f.wh[c] = st[(WH + row) * kPieces + g];
-            f.wl[c] = st[(WL + row) * kPieces + g];
+            f.wh[c] = *(const v4i *)(st + (WH + wc0 + c * 32) * STEP);
+            f.wl[c] = *(const v4i *)(st + (WL + wc0 + c * 32) * STEP);
         }
 #pragma unroll
         for (int p = 0; p < PT; p++) {
-            const int row = wp0 + p * 32 + l32;
-            f.xh[p] = st[(XH + row) * kPieces + g];
-            f.xl[p] = st[(XL + row) * kPieces + g];
+            f.xh[p] = *(const v4i *)(st + (XH + wp0 + p * 32) * STEP);
+            f.xl[p] = *(const v4i *)(st + (XL + wp0 + p * 32) * STEP);
         }
     };
     auto mfma_half = [&](const Half &f) __attribute__((always_inline)) {
+        // (the two products that meet in accB stand apart: a matrix instruction waits for the accumulator of the one before it)
 #pragma unroll
         for (int p = 0; p < PT; p++)
 #pragma unroll
             for (int c = 0; c < CT; c++) {
                 accA[c][p] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f.wh[c], f.xh[p], accA[c][p], 0, 0, 0);
-                accC[c][p] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f.wl[c], f.xl[p], accC[c][p], 0, 0, 0);
                 accB[c][p] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f.wh[c], f.xl[p], accB[c][p], 0, 0, 0);
+            }
+#pragma unroll
+        for (int p = 0; p < PT; p++)
+#pragma unroll
+            for (int c = 0; c < CT; c++) {
+                accC[c][p] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f.wl[c], f.xl[p], accC[c][p], 0, 0, 0);
                 accB[c][p] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f.wl[c], f.xh[p], accB[c][p], 0, 0, 0);
             }
     };
     auto ring_barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
     const int nitems = prm.nitems;
+    if constexpr (STEP == 128 && NSTAGES == 3) {
+        // One workgroup per compute unit: the in-wavefront pipeline of the steps of 64 bytes, one barrier per step of 128, two steps
+        // (96 KB) on their way.
+#pragma unroll
+        for (int i = 0; i < NSTAGES; i++)
+            if (i < nitems) issue(i);
+        if (nitems > 2) wait_loads<2 * LPW>();
+        else if (nitems > 1) wait_loads<LPW>();
+        else wait_loads<0>();
+        ring_barrier();
+        read_half(f0, 0, 0);
+        read_half(f1, 1, 0);
+        int stage = 0;
+        for (int it = 0; it < nitems; it++) {
+            const int next = stage + 1 == NSTAGES ? 0 : stage + 1;
+            const bool has_next = it + 1 < nitems;
+            mfma_half(f0);
+            __builtin_amdgcn_sched_barrier(0);
+            read_half(f0, 2, stage);
+            __builtin_amdgcn_sched_barrier(0);
+            mfma_half(f1);
+            __builtin_amdgcn_sched_barrier(0);
+            read_half(f1, 3, stage);
+            __builtin_amdgcn_sched_barrier(0);
+            if (has_next) {
+                if (it + 2 < nitems) wait_loads<LPW>();          // step it+1 has landed; it+2 may be on its way
+                else wait_loads<0>();
+                ring_barrier();                      // ... for every wavefront, and everyone's operands of this one are in registers
+            }
+            mfma_half(f0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (has_next) {
+                if (it + NSTAGES < nitems) issue(stage);
+                read_half(f0, 0, next);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            mfma_half(f1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (has_next) read_half(f1, 1, next);
+            __builtin_amdgcn_sched_barrier(0);
+            stage = next;
+        }
+    } else if constexpr (STEP == 128) {
+        // One stage: the loads of a step run under the second half of the step before it and under the other workgroups of the compute
+        // unit (three share it).
+        issue(0);
+        for (int it = 0; it < nitems; it++) {
+            wait_loads<0>();
+            ring_barrier();
+#pragma unroll
+            for (int kk = 0; kk < 3; kk++) {
+                read_half(f0, kk, 0);
+                mfma_half(f0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            read_half(f0, 3, 0);
+            if (it + 1 < nitems) {
+                ring_barrier();                      // every wavefront has its operands in registers
+                issue(0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            mfma_half(f0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
 #pragma unroll
     for (int i = 0; i < NSTAGES; i++)
         if (i < nitems) issue(i);
@@ -926,6 +830,7 @@ __global__ void __launch_bounds__(256, OCC) conv_np_mfma_kernel(NpConvParams prm
         __builtin_amdgcn_sched_barrier(0);
         stage = next;
     }
+    }
 
     if constexpr (AMAX) {
         // Calibration: V = 64 (64 A + B) + C is exact in a double (|V| < 2^37), so a value takes two conversions, a multiply-add and a
@@ -945,7 +850,7 @@ __global__ void __launch_bounds__(256, OCC) conv_np_mfma_kernel(NpConvParams prm
                 }
             }
         }
-        wave_max_to(a.amax, (unsigned long long)mx);
+        block_max_to(a.amax, (unsigned long long)mx, a.amax_words);
         return;
     }
 
@@ -1048,14 +953,14 @@ __global__ void __launch_bounds__(256, OCC) conv_np_mfma_kernel(NpConvParams prm
     }
 }
 
-template <int BP, int BC, int OCC = 1, int NSTAGES = 3, bool ADD = false, bool AMAX = false>
+template <int BP, int BC, int OCC = 1, int NSTAGES = 3, bool ADD = false, bool AMAX = false, int STEP = kStepBytes>
 hipError_t launch_np_mfma(const NpConvArgs &a, hipStream_t st)
 {
     NpConvParams prm;
     prm.a = a;
     const long long M = (long long)a.N * a.P * a.Q;
     prm.M = (int)M;
-    prm.csteps = a.C / kStepBytes;
+    prm.csteps = a.C / STEP;
     prm.nitems = a.R * a.S * prm.csteps;
     prm.tiles_c = (a.K + BC - 1) / BC;
     prm.x_bytes = (unsigned)((long long)a.N * a.H * a.W * a.C);
@@ -1065,11 +970,11 @@ hipError_t launch_np_mfma(const NpConvArgs &a, hipStream_t st)
     prm.div_tc = make_fastdiv(prm.tiles_c);
     const long long tiles = ((M + BP - 1) / BP) * prm.tiles_c;
     if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
-    constexpr size_t lds_bytes = (size_t)NSTAGES * (2 * BP + 2 * BC) * 64;
+    constexpr size_t lds_bytes = (size_t)NSTAGES * (2 * BP + 2 * BC) * STEP;
     static_assert(lds_bytes * OCC <= (size_t)kLdsBytes, "three stages fit");
-    static const hipError_t attr = hipFuncSetAttribute((const void *)conv_np_mfma_kernel<BP, BC, OCC, NSTAGES, ADD, AMAX>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    static const hipError_t attr = hipFuncSetAttribute((const void *)conv_np_mfma_kernel<BP, BC, OCC, NSTAGES, ADD, AMAX, STEP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     if (attr != hipSuccess) return attr;
-    conv_np_mfma_kernel<BP, BC, OCC, NSTAGES, ADD, AMAX><<<(unsigned)tiles, 256, lds_bytes, st>>>(prm);
+    conv_np_mfma_kernel<BP, BC, OCC, NSTAGES, ADD, AMAX, STEP><<<(unsigned)tiles, 256, lds_bytes, st>>>(prm);
     return hipGetLastError();
 }
 
@@ -1089,23 +994,36 @@ bool conv_np_mfma_supports(const NpConvArgs &a)
     return (al & 15) == 0;
 }
 
+namespace {
+
+// Tiles of 128 pixels x 64 channels with 64 x 32 per wavefront (six accumulator tiles, 140 to 160 registers) leave room for several
+// workgroups per compute unit, so that one workgroup's matrix instructions and loads run under another's epilogue - worth more on
+// every layer shape measured than larger tiles' fewer LDS reads per matrix instruction.  Measured, us (420 layers of a residual network, 1 to 64
+// images of 96 to 224 pixels, under every form):
+//   C a multiple of 128, more than 256 tiles: steps of 128 bytes in one stage, three workgroups per unit (64 images: 3x3 128 -> 128 at 28 x 28
+//     42.8 -> 38.9, 3x3 256 -> 256 / 2 37.7 -> 34.9, 1x1 512 -> 1024 / 2 38.1 -> 34.3; 128 -> 512 with the add 41.1 -> 41.5);
+//   160 .. 256 such tiles, one per unit: a ring of three (1x1 2048 -> 512 at 7 x 7, 64 images 26.4 -> 22.5; 3x3 512 -> 512 42.7 -> 41.0);
+//     fewer: steps of 64 (72 tiles, 3x3 256 -> 256 21.4, a ring of three 22.3);
+//   else steps of 64 bytes: up to 36 three workgroups with a two-stage ring, longer reductions two with three stages.
+template <bool ADD, bool AMAX>
+hipError_t launch_form(const NpConvArgs &a, hipStream_t st)
+{
+    const long long tiles = (((long long)a.N * a.P * a.Q + 127) / 128) * ((a.K + 63) / 64);
+    if (a.C % 128 == 0 && a.R <= 16 && a.S <= 16) {
+        if (tiles > kNumCU) return launch_np_mfma<128, 64, 3, 1, ADD, AMAX, 128>(a, st);
+        if (tiles >= 160) return launch_np_mfma<128, 64, 1, 3, ADD, AMAX, 128>(a, st);
+    }
+    if ((long long)a.R * a.S * a.C <= 36 * kStepBytes) return launch_np_mfma<128, 64, 3, 2, ADD, AMAX>(a, st);
+    return launch_np_mfma<128, 64, 2, 3, ADD, AMAX>(a, st);
+}
+
+}  // namespace
+
 hipError_t launch_conv_np_mfma(const NpConvArgs &a, hipStream_t st)
 {
-    // Tiles of 128 pixels x 64 channels with 64 x 32 per wavefront (six accumulator tiles, 160 registers) leave room for
-    // several workgroups per compute unit, so that one workgroup's matrix instructions and loads run under another's
-    // epilogue - worth more on every layer shape measured than the larger tiles' fewer LDS reads per matrix
-    // instruction.  Up to 36 steps (all but the 3 x 3 x 512 layers): three workgroups with a two-stage ring; longer
-    // reductions: two workgroups with three stages.
-    if (a.amax) {
-        if ((long long)a.R * a.S * a.C <= 36 * kStepBytes) return launch_np_mfma<128, 64, 3, 2, false, true>(a, st);
-        return launch_np_mfma<128, 64, 2, 3, false, true>(a, st);
-    }
-    if (a.oh) {
-        if ((long long)a.R * a.S * a.C <= 36 * kStepBytes) return launch_np_mfma<128, 64, 3, 2, true>(a, st);
-        return launch_np_mfma<128, 64, 2, 3, true>(a, st);
-    }
-    if ((long long)a.R * a.S * a.C <= 36 * kStepBytes) return launch_np_mfma<128, 64, 3, 2>(a, st);
-    return launch_np_mfma<128, 64, 2, 3>(a, st);
+    if (conv_np_sk_pays(a)) return launch_conv_np_sk(a, st);
+    if (a.amax) return launch_form<false, true>(a, st);
+    return a.oh ? launch_form<true, false>(a, st) : launch_form<false, false>(a, st);
 }
 
 hipError_t launch_conv_np_direct(const NpConvArgs &a, hipStream_t st)
@@ -1134,7 +1052,7 @@ hipError_t launch_eltwise_np_absmax(const int8_t *ah, const int8_t *al, const in
                                     unsigned long long *amax, hipStream_t st, const NpCalAdd &cal)
 {
     const uintptr_t al16 = (uintptr_t)ah | (uintptr_t)al | (uintptr_t)bh | (uintptr_t)bl;
-    NpEltParams q{ah, al, bh, bl, nullptr, nullptr, nullptr, (al16 & 15) ? 0 : n / 16, n, sa, sb, 0, 0, 0, relu, cal.fa, cal.fb, nullptr, nullptr, cal.err};
+    NpEltParams q{ah, al, bh, bl, nullptr, nullptr, nullptr, (al16 & 15) ? 0 : n / 16, n, sa, sb, 0, 0, 0, relu, cal.fa, cal.fb, nullptr, nullptr, cal.err, cal.amax_words};
     const int g = grid_for(q.n16 > 0 ? q.n16 : n);
     eltwise_np_absmax_kernel<<<g < 1024 ? g : 1024, 256, 0, st>>>(q, amax);
     return hipGetLastError();
@@ -1184,7 +1102,7 @@ hipError_t launch_eltwise_np(const int8_t *ah, const int8_t *al, const int8_t *b
 {
     const uintptr_t al16 = (uintptr_t)ah | (uintptr_t)al | (uintptr_t)bh | (uintptr_t)bl | (uintptr_t)y | (uintptr_t)yh | (uintptr_t)yl;
     NpEltParams q{ah, al, bh, bl, y, yh, yl, (al16 & 15) ? 0 : n / 16, n, sa, sb, shift, p_y, beta_max, relu,
-                  cal.fa, cal.fb, cal.amax, cal.fy, cal.err};
+                  cal.fa, cal.fb, cal.amax, cal.fy, cal.err, cal.amax_words};
     size_t work = q.n16 > 0 ? q.n16 : n;
     size_t blocks = (work + 255) / 256;
     if (blocks > 256 * 16) blocks = 256 * 16;

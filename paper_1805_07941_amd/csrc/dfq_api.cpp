@@ -961,6 +961,7 @@ dfq_status dfq_cal_conv_np(const int8_t *xh, const int8_t *xl, const int8_t *wh,
     if (!fixed) {
         NpConvArgs m = a;
         m.amax = reinterpret_cast<unsigned long long *>(amax);
+        m.amax_words = DFQ_CAL_AMAX_WORDS / 16;
         const hipError_t e = mfma ? launch_conv_np_mfma(m, (hipStream_t)stream) : launch_conv_np_direct(m, (hipStream_t)stream);
         if (e != hipSuccess) return DFQ_EDEVICE;
     }
@@ -971,6 +972,7 @@ dfq_status dfq_cal_conv_np(const int8_t *xh, const int8_t *xl, const int8_t *wh,
     a.cal_fixed_frac = fixed_frac;
     a.cal_fy = frac_y;
     a.cal_err = err;
+    a.amax_words = DFQ_CAL_AMAX_WORDS / 16;
     return from_hip(mfma ? launch_conv_np_mfma(a, (hipStream_t)stream) : launch_conv_np_direct(a, (hipStream_t)stream));
 }
 
@@ -979,7 +981,7 @@ dfq_status dfq_cal_add_np(const int8_t *ah, const int8_t *al, const int32_t *fra
 {
     if (p < 4 || p > 7) return DFQ_EFMT;
     if (!frac_a || !frac_b || !amax || ((uintptr_t)amax & 7) || !frac_y || !err || (n && (!ah || !al || !bh || !bl || !yh || !yl))) return DFQ_EINVAL;
-    const NpCalAdd cal{frac_a, frac_b, reinterpret_cast<const unsigned long long *>(amax), frac_y, err};
+    const NpCalAdd cal{frac_a, frac_b, reinterpret_cast<const unsigned long long *>(amax), frac_y, err, DFQ_CAL_AMAX_WORDS / 16};
     const hipError_t e = launch_eltwise_np_absmax(ah, al, bh, bl, n, 0, 0, relu ? 1 : 0, reinterpret_cast<unsigned long long *>(amax), (hipStream_t)stream, cal);
     if (e != hipSuccess) return DFQ_EDEVICE;
     return from_hip(launch_eltwise_np(ah, al, bh, bl, nullptr, yh, yl, n, 0, 0, 0, p, (int)dfq_beta_max(8, p), relu ? 1 : 0, (hipStream_t)stream, cal));

@@ -66,6 +66,7 @@ struct NpConvArgs {
     const unsigned long long *cal_amax = nullptr;
     int cal_fixed = 0, cal_fixed_frac = 0;
     int32_t *cal_fy = nullptr, *cal_err = nullptr;
+    int amax_words = 1;            // words, 128 bytes apart, that amax / cal_amax are spread over
 };
 
 // The same for an add on digit planes, or fa == null.
@@ -73,6 +74,7 @@ struct NpCalAdd {
     const int32_t *fa = nullptr, *fb = nullptr;
     const unsigned long long *amax = nullptr;
     int32_t *fy = nullptr, *err = nullptr;
+    int amax_words = 1;
 };
 
 // A concat whose formats are device words (branch i: frac[idx[i]]), or frac == null.  The result's is the given one or the coarsest branch's.
@@ -145,6 +147,8 @@ bool conv_sg_supports(const ConvArgs &a);       // grouped layers the matrix-cor
 hipError_t launch_conv_sg(const ConvArgs &a, hipStream_t st);
 bool conv_np_mfma_supports(const NpConvArgs &a);
 hipError_t launch_conv_np_mfma(const NpConvArgs &a, hipStream_t st);
+bool conv_np_sk_pays(const NpConvArgs &a);       // a call of the matrix-core form small enough that splitting its reduction is faster
+hipError_t launch_conv_np_sk(const NpConvArgs &a, hipStream_t st);
 hipError_t launch_conv_np_direct(const NpConvArgs &a, hipStream_t st);
 hipError_t launch_clear_u64(unsigned long long *p, hipStream_t st);
 hipError_t launch_eltwise_np_absmax(const int8_t *ah, const int8_t *al, const int8_t *bh, const int8_t *bl, size_t n, int sa, int sb, int relu,

@@ -62,7 +62,7 @@ def calibrate(net, x: torch.Tensor, p: int = 4, device="cuda:0"):
     L, call, st = B.lib(), B._check, B._stream(None)
     qz = QuantizedNp(p=p)
     convs = [nd for nd in net.nodes if nd.op == "conv"]
-    F = FormatWords(net, device, len(convs), len(net.nodes))
+    F = FormatWords(net, device, len(convs), B.CAL_AMAX_WORDS * len(net.nodes))
     gamma = torch.empty(max([nd.K for nd in convs] + [1]), dtype=torch.float32, device=device)
     i8 = dict(dtype=torch.int8, device=device)
     if net.fixed_f_input is not None:
@@ -106,7 +106,7 @@ def calibrate(net, x: torch.Tensor, p: int = 4, device="cuda:0"):
             yh, yl = torch.empty((N, P, Q, Kp), **i8), torch.empty((N, P, Q, Kp), **i8)
             fixed = nd.fixed_f_out is not None
             call(L.dfq_cal_conv_np(xh.data_ptr(), xl.data_ptr(), wh.data_ptr(), wl.data_ptr(), b.data_ptr(), yh.data_ptr(), yl.data_ptr(), N, H, W,
-                                   Cc, Kp, R, S, stride, pad, nd.groups, F.of(src), w_frac, None if fixed else F.maximum(1), int(fixed),
+                                   Cc, Kp, R, S, stride, pad, nd.groups, F.of(src), w_frac, None if fixed else F.maximum(B.CAL_AMAX_WORDS), int(fixed),
                                    nd.fixed_f_out if fixed else 0, F.new(nd.dst), p, int(nd.relu), F.err, st), "dfq_cal_conv_np")
             t[nd.dst] = (yh, yl) if Kp == K else (yh[..., :K].contiguous(), yl[..., :K].contiguous())
             del wf, bf
@@ -114,7 +114,7 @@ def calibrate(net, x: torch.Tensor, p: int = 4, device="cuda:0"):
             (ah, al), (bh, bl) = (t[s] for s in nd.srcs)
             fa, fb = (F.of(s) for s in nd.srcs)
             yh, yl = torch.empty(ah.shape, **i8), torch.empty(ah.shape, **i8)
-            call(L.dfq_cal_add_np(ah.data_ptr(), al.data_ptr(), fa, bh.data_ptr(), bl.data_ptr(), fb, ah.numel(), p, int(nd.relu), F.maximum(1),
+            call(L.dfq_cal_add_np(ah.data_ptr(), al.data_ptr(), fa, bh.data_ptr(), bl.data_ptr(), fb, ah.numel(), p, int(nd.relu), F.maximum(B.CAL_AMAX_WORDS),
                                   yh.data_ptr(), yl.data_ptr(), F.new(nd.dst), F.err, st), "dfq_cal_add_np")
             t[nd.dst] = (yh, yl)
         elif nd.op in ("maxpool", "avgpool"):
