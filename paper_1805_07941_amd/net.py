@@ -45,18 +45,60 @@ def _read_f32(t: torch.Tensor) -> float:
 WEIGHT_GROUP_BYTES = 256 << 20
 
 
+# Uploads go through two pinned pieces of this size, one being filled while the other is on its way.
+STAGING_BYTES = 4 << 20
+
+
+def _to_device(arrays, device):
+    """Host arrays as device tensors.  float32 arrays share one allocation and travel through pinned memory: a copy out of pageable
+    memory runs at 20 to 30 GB/s and 15 us whatever it holds, with the host waiting (17 MB in 54 arrays: 1.0 ms, through pinned pieces
+    0.6)."""
+    if torch.device(device).type != "cuda" or any(a.dtype != np.float32 for a in arrays):
+        return [torch.from_numpy(a).to(device) for a in arrays]
+    sizes, flat = [], []                                  # words of every array and of the gap behind it, up to 256 bytes
+    for a in arrays:
+        sizes += [a.size, -a.size % 64]
+        flat.append(np.ascontiguousarray(a).reshape(-1))
+    total = sum(sizes)
+    dst = torch.empty(total, dtype=torch.float32, device=device)
+    piece = min(STAGING_BYTES // 4, max(total, 1))
+    stages = [torch.empty(piece, dtype=torch.float32, pin_memory=True) for _ in range(2 if total > piece else 1)]
+    views, sent = [t.numpy() for t in stages], [torch.cuda.Event() for _ in stages]
+    turn, at, used = 0, 0, 0                              # the piece being filled, where it goes, how much it holds
+
+    def send():
+        nonlocal turn, at, used
+        dst[at:at + used].copy_(stages[turn][:used], non_blocking=True)
+        sent[turn].record()
+        turn, at, used = (turn + 1) % len(stages), at + used, 0
+        sent[turn].synchronize()                          # (an event that was never recorded is complete)
+
+    for a, gap in zip(flat, sizes[1::2]):
+        done = 0
+        while done < a.size:
+            n = min(a.size - done, piece - used)
+            if n > 65536:
+                stages[turn][used:used + n].copy_(torch.from_numpy(a[done:done + n]))         # by all cores
+            else:
+                views[turn][used:used + n] = a[done:done + n]
+            done, used = done + n, used + n
+            if used == piece:
+                send()
+        skip = min(gap, piece - used)
+        used += skip
+        if used == piece:
+            send()
+            used = gap - skip
+    if used:
+        send()
+    return [t.view(a.shape) for t, a in zip(dst.split(sizes)[::2], arrays)]
+
+
 def _upload(layers, net, device, fold: bool) -> Dict[str, tuple]:
-    """[(node, weights, bias)] as {name: (weights, bias)} on the device.  The many small bias vectors travel as one array: an upload
-    costs 15 us whatever it holds.  (Arrays that are no float32 vectors go one by one, so that each keeps its type.)"""
-    bias = [b for _, _, b in layers]
-    if all(b.dtype == np.float32 and b.ndim == 1 for b in bias):
-        joined = torch.from_numpy(np.concatenate(bias)).to(device)
-        bias = joined.split([b.size for b in bias])
-    else:
-        bias = [torch.from_numpy(b).to(device) for b in bias]
+    """[(node, weights, bias)] as {name: (weights, bias)} on the device."""
+    moved = _to_device([w for _, w, _ in layers] + [b for _, _, b in layers], device)
     out = {}
-    for (nd, w, _), bf in zip(layers, bias):
-        wf = torch.from_numpy(w).to(device)
+    for (nd, _, _), wf, bf in zip(layers, moved, moved[len(layers):]):
         if fold and getattr(net, "scale_layers", False):
             # the affine layer behind the convolution is folded into the float weights before they are quantized
             scale, shift = net.scale_shift(nd)
