@@ -489,6 +489,20 @@ dfq_status dfq_cal_conv_np(const int8_t *xh, const int8_t *xl, const int8_t *wh,
 dfq_status dfq_cal_add_np(const int8_t *ah, const int8_t *al, const int32_t *frac_a, const int8_t *bh, const int8_t *bl, const int32_t *frac_b,
                           size_t n, int p, int relu, uint64_t *amax, int8_t *yh, int8_t *yl, int32_t *frac_y, int32_t *err, dfq_stream stream);
 
+/* ---- A pass as one call ----------------------------------------------------------------------
+ * A plan is a fixed sequence of calls; issued one by one from a scripting language their marshalling costs more than their
+ * launches.  A record holds a call's number (dfq_call_number of the function's name, HOST; -1 for one that is no stream
+ * call) and its arguments but the stream in order, each as 64 bits: integers, pointers as numbers, a dfq_fmt by its fractional length.
+ * dfq_run_calls makes the calls in order on the stream and stops at the first that is refused: its status is returned and
+ * its index stored in *failed (may be null).  DFQ_EINVAL for a record with an unknown number or a wrong count of arguments. */
+#define DFQ_CALL_ARGS 30
+typedef struct {
+    int32_t call, count;
+    int64_t arg[DFQ_CALL_ARGS];
+} dfq_call;
+int dfq_call_number(const char *name);
+dfq_status dfq_run_calls(const dfq_call *calls, size_t n, size_t *failed, dfq_stream stream);
+
 #ifdef __cplusplus
 }
 #endif

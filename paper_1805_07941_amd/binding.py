@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from array import array
 from typing import Optional, Sequence
 
 import torch
@@ -18,6 +19,7 @@ LIB_PATH = os.path.join(_HERE, "libdfq.so")
 OK, EINVAL, ESHAPE, EFMT, EUNSUPPORTED, EDEVICE = range(6)
 POOL_MAX, POOL_AVG = 0, 1
 CAL_AMAX_WORDS = 256          # DFQ_CAL_AMAX_WORDS
+CALL_ARGS = 30                # DFQ_CALL_ARGS
 CONV_AUTO, CONV_DIRECT, CONV_MFMA, CONV_DEPTHWISE, CONV_SMALLC, CONV_POINTWISE, CONV_GROUPED, CONV_RAGGED, CONV_SPLIT = range(9)
 CONV_VARIANT_NAMES = {CONV_AUTO: "auto", CONV_DIRECT: "direct", CONV_MFMA: "mfma",
                       CONV_DEPTHWISE: "depthwise", CONV_SMALLC: "smallc", CONV_POINTWISE: "pointwise",
@@ -29,6 +31,7 @@ EXPORTS = [
     "dfq_absmax_f32", "dfq_absmax_i32", "dfq_fmt_from_absmax_f32", "dfq_fmt_from_absmax_f32_rows", "dfq_fmt_from_absmax_i32", "dfq_hist_shift", "dfq_fmt_from_absmax_i32_channels",
     "dfq_beta_max", "dfq_mac_acc_bits", "dfq_mac_max_len", "dfq_add_acc_bits", "dfq_add_max_len",
     "dfq_np_digits", "dfq_conv_np", "dfq_conv_np_variant", "dfq_np_frac_from_absmax_f32", "dfq_conv_q_add_lazy", "dfq_eltwise_np",
+    "dfq_call_number", "dfq_run_calls",
     "dfq_cal_weights", "dfq_cal_quantize", "dfq_cal_rescale", "dfq_cal_add", "dfq_cal_concat",
     "dfq_cal_np_weights", "dfq_cal_np_quantize", "dfq_cal_conv_np", "dfq_cal_add_np",
     "dfq_conv_np_absmax", "dfq_eltwise_np_absmax", "dfq_np_frac_from_absmax_u64", "dfq_pool_np", "dfq_stem_pack_x", "dfq_stem_pack_w", "dfq_conv_np_add",
@@ -130,6 +133,8 @@ def lib():
     L.dfq_np_frac_from_absmax_f32.argtypes = [C.c_float, i32, i32, C.POINTER(C.c_int32)]
     for name in ("dfq_np_digits", "dfq_conv_np", "dfq_conv_np_variant", "dfq_np_frac_from_absmax_f32"):
         getattr(L, name).restype = i32
+    L.dfq_call_number.argtypes, L.dfq_call_number.restype = [C.c_char_p], i32
+    L.dfq_run_calls.argtypes, L.dfq_run_calls.restype = [vp, sz, C.POINTER(sz), vp], i32
     L.dfq_cal_weights.argtypes = [vp, vp, sz, sz, i32] + [vp] * 7
     L.dfq_cal_quantize.argtypes = [vp, sz] + [vp] * 5
     L.dfq_cal_rescale.argtypes = [vp, sz, i32, i32, vp, vp, i32, vp, i32, i32, vp, vp, vp]
@@ -195,6 +200,32 @@ def _dev(t: torch.Tensor, dtype, name: str):
     if not t.is_cuda or t.dtype != dtype or not t.is_contiguous():
         raise TypeError(f"{name}: expected a contiguous CUDA tensor of {dtype}")
     return t
+
+
+# ---- a pass as one call ------------------------------------------------------------ #
+class CallList:
+    """[(C function, its arguments but the stream)] as one library call.  Holds what the arguments point to on the host."""
+    _numbers = {}
+
+    def __init__(self, calls):
+        words = []
+        for fn, args in calls:
+            name = fn.__name__
+            number = self._numbers.get(name)
+            if number is None:
+                number = self._numbers[name] = lib().dfq_call_number(name.encode())
+            words.append((number & 0xffffffff) | len(args) << 32)
+            words += [a if type(a) is int else 0 if a is None else a.frac if type(a) is Fmt else C.addressof(a) if isinstance(a, C.Array) else int(a)
+                      for a in args]
+            words += [0] * (CALL_ARGS - len(args))
+        self._held, self._count = calls, len(calls)
+        self._records = array("q", words)
+        self._failed = C.c_size_t()
+
+    def run(self, stream: int):
+        rc = lib().dfq_run_calls(self._records.buffer_info()[0], self._count, C.byref(self._failed), stream)
+        if rc != OK:
+            raise DfqError(rc, self._held[self._failed.value][0].__name__)
 
 
 # ---- conversions ------------------------------------------------------------------ #

@@ -3,6 +3,10 @@
 #include "dfq.h"
 
 #include <cmath>
+#include <cstring>
+#include <tuple>
+#include <type_traits>
+#include <utility>
 
 #include "dfq_host.hpp"
 
@@ -1023,6 +1027,79 @@ int64_t dfq_add_max_len(int q, int64_t bx, int64_t ex)
     if (q < 2 || q > 63 || bx < 1 || ex < 0) return -1;
     if (ex == 0) return (((int64_t)1 << (q - 1)) - 1) / bx;
     return ((int64_t)1 << (q - 1)) / (bx + ex);
+}
+
+// ---- a pass as one call
+
+}  // extern "C"
+
+namespace {
+
+template <class T>
+inline T argument(int64_t v)
+{
+    if constexpr (std::is_pointer_v<T>) return reinterpret_cast<T>((uintptr_t)v);
+    else if constexpr (std::is_same_v<T, dfq_fmt>) return dfq_fmt{8, (int32_t)v};
+    else if constexpr (std::is_enum_v<T>) return (T)(int)v;
+    else return (T)v;
+}
+
+// the arguments of a record in place of those of F, the stream behind them
+template <auto F>
+struct Thunk;
+template <class... A, dfq_status (*F)(A...)>
+struct Thunk<F> {
+    static constexpr int kCount = (int)sizeof...(A) - 1;
+    static_assert(kCount <= DFQ_CALL_ARGS, "a record holds the arguments");
+    template <size_t... I>
+    static dfq_status run(const int64_t *v, dfq_stream st, std::index_sequence<I...>)
+    {
+        using Types = std::tuple<A...>;
+        return F(argument<std::tuple_element_t<I, Types>>(v[I])..., st);
+    }
+    static dfq_status call(const int64_t *v, dfq_stream st) { return run(v, st, std::make_index_sequence<kCount>{}); }
+};
+
+struct CallEntry {
+    const char *name;
+    dfq_status (*call)(const int64_t *, dfq_stream);
+    int count;
+};
+#define DFQ_ENTRY(f) {#f, Thunk<f>::call, Thunk<f>::kCount}
+const CallEntry kCalls[] = {
+    DFQ_ENTRY(dfq_quantize), DFQ_ENTRY(dfq_dequantize), DFQ_ENTRY(dfq_conv_q), DFQ_ENTRY(dfq_conv_q_pc), DFQ_ENTRY(dfq_conv_q_add),
+    DFQ_ENTRY(dfq_conv_q_pc_add), DFQ_ENTRY(dfq_conv_q_add_lazy), DFQ_ENTRY(dfq_quantize_conv_q), DFQ_ENTRY(dfq_conv_q_maxpool),
+    DFQ_ENTRY(dfq_conv_q_pc_maxpool), DFQ_ENTRY(dfq_quantize_conv_q_maxpool), DFQ_ENTRY(dfq_quantize_conv_q_pc_maxpool),
+    DFQ_ENTRY(dfq_eltwise_q), DFQ_ENTRY(dfq_concat_q_into), DFQ_ENTRY(dfq_pool_q), DFQ_ENTRY(dfq_quantize_np), DFQ_ENTRY(dfq_dequantize_np),
+    DFQ_ENTRY(dfq_np_digits), DFQ_ENTRY(dfq_conv_np), DFQ_ENTRY(dfq_conv_np_add), DFQ_ENTRY(dfq_eltwise_np), DFQ_ENTRY(dfq_pool_np),
+    DFQ_ENTRY(dfq_stem_pack_x)};
+#undef DFQ_ENTRY
+constexpr int kNumCalls = (int)(sizeof(kCalls) / sizeof(kCalls[0]));
+
+}  // namespace
+
+extern "C" {
+
+int dfq_call_number(const char *name)
+{
+    for (int i = 0; name && i < kNumCalls; i++)
+        if (!std::strcmp(name, kCalls[i].name)) return i;
+    return -1;
+}
+
+dfq_status dfq_run_calls(const dfq_call *calls, size_t n, size_t *failed, dfq_stream stream)
+{
+    if (n && !calls) return DFQ_EINVAL;
+    for (size_t i = 0; i < n; i++) {
+        const dfq_call &c = calls[i];
+        const bool known = c.call >= 0 && c.call < kNumCalls && c.count == kCalls[c.call].count;
+        const dfq_status st = known ? kCalls[c.call].call(c.arg, stream) : DFQ_EINVAL;
+        if (st != DFQ_OK) {
+            if (failed) *failed = i;
+            return st;
+        }
+    }
+    return DFQ_OK;
 }
 
 }  // extern "C"

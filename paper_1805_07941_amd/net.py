@@ -816,6 +816,7 @@ class Plan:
         key = (x.data_ptr(), tuple(x.shape))
         if self._calls_key != key:
             self._calls = self._build_calls(x)
+            self._list = B.CallList(self._calls)
             self._calls_key = key
             self._graph = None
         return self._calls
@@ -823,11 +824,8 @@ class Plan:
     def run(self, x: torch.Tensor, stream=None) -> torch.Tensor:
         """One pass: x float32 images [batch,H,W,C] (or int8 codes).  Enqueues every library call
         on the stream and returns the float logits buffer (no synchronization)."""
-        st = B._stream(stream)
-        for fn, args in self._calls_for(x):
-            rc = fn(*args, st)
-            if rc != B.OK:
-                raise B.DfqError(rc, fn.__name__)
+        self._calls_for(x)
+        self._list.run(B._stream(stream))
         return self.logits
 
     def run_graph(self, x: torch.Tensor) -> torch.Tensor:

@@ -259,16 +259,14 @@ class NpPlan:
         key = x.data_ptr()
         if self._calls_key != key:
             self._calls, self._calls_key, self._graph = self._build_calls(x), key, None
+            self._list = B.CallList(self._calls)
         return self._calls
 
     def run(self, x: torch.Tensor, stream=None) -> torch.Tensor:
         """One pass over float32 images [batch,H,W,C]: enqueues every library call and returns the float logits buffer
         (no synchronization)."""
-        st = B._stream(stream)
-        for fn, args in self._calls_for(x):
-            rc = fn(*args, st)
-            if rc != B.OK:
-                raise B.DfqError(rc, fn.__name__)
+        self._calls_for(x)
+        self._list.run(B._stream(stream))
         return self.logits
 
     def run_graph(self, x: torch.Tensor) -> torch.Tensor:
