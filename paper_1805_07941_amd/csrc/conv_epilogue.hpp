@@ -214,7 +214,7 @@ __device__ __forceinline__ void store_bytes(const Bytes16 &o, int8_t *dst, int c
 __device__ __forceinline__ void store_sums(const v16i &v, const ConvArgs &a, long long m, int kc, int count)
 {
     int32_t *dst = a.acc_out + (size_t)m * a.K + kc;
-    if ((a.K & 3) == 0 && ((uintptr_t)a.acc_out & 15) == 0) {    // kc is a multiple of four, so count is one too
+    if (((a.K | kc | count) & 3) == 0 && ((uintptr_t)a.acc_out & 15) == 0) {    // (a group's first channel may be any)
 #pragma unroll
         for (int r = 0; r < 16; r += 4)
             if (r < count) *(int4 *)(dst + r) = make_int4(v[r], v[r + 1], v[r + 2], v[r + 3]);

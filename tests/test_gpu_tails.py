@@ -80,3 +80,15 @@ def test_global_average_of_digit_planes(B, shape, p):
     y, yh, yl = B.pool_np(*planes(B, x, p), "avg", k, 1, 0, p)
     assert np.array_equal(host(y), ry)
     assert np.array_equal(64 * host(yh).astype(np.int64) + host(yl), rbeta)
+
+
+@pytest.mark.parametrize("shape", [(2, 9, 11, 24, 36, 3, 12), (3, 8, 7, 18, 36, 1, 6), (1, 13, 9, 36, 28, 3, 4)], ids=lambda s: "x".join(map(str, s)))
+def test_sums_of_groups_that_start_anywhere(B, shape):
+    """K is a multiple of four and the outputs of a group are not: a group's sums must not reach into the next one's."""
+    N, H, W, C, K, R, g = shape
+    rng = np.random.default_rng(sum(shape))
+    x, w = rng.integers(-128, 128, (N, H, W, C)).astype(np.int8), rng.integers(-128, 128, (K, R, R, C // g)).astype(np.int8)
+    b = rng.integers(-2 ** 15, 2 ** 15, (K,)).astype(np.int32)
+    y_ref, acc_ref = orc.conv_q(x, w, b, 4, 7, 4, 1, R // 2, g, True, want_acc=True)
+    y, acc = B.conv_q(dev(x), dev(w), dev(b), 4, 7, 4, 1, R // 2, g, True, want_acc=True, variant=B.CONV_RAGGED)
+    assert np.array_equal(host(acc), acc_ref) and np.array_equal(host(y), y_ref)
