@@ -134,6 +134,15 @@ bool conv_grouped_supports(const ConvArgs &a)
     return true;
 }
 
+// Fitted to 199 layers to 13 % in the mean; the matrix-core form (conv_sg.hip) is not meant.
+double conv_grouped_time(const ConvArgs &a)
+{
+    const double taps = (double)a.R * a.S, quads = a.C / a.groups / 4, outputs = (double)a.N * a.P * a.Q * a.K;
+    const double items = (double)a.N * a.P * ((a.Q + kPX - 1) / kPX) * a.K, rounds = items > 524288 ? items / 524288 : 1.0;
+    return 3433.0 + 0.157 * a.K * taps * quads * 4 + items * (4.71e-3 + 0.407e-3 * taps * quads) + 47.5 * rounds * taps * quads +
+           (a.frac_w || a.acc_out ? 0.22e-3 * outputs : 0.0);
+}
+
 hipError_t launch_conv_grouped(const ConvArgs &a, hipStream_t st)
 {
     // whole groups inside blocks of 64 channels, lean epilogue: the matrix cores take the layer (conv_sg.hip)

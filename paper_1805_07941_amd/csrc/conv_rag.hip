@@ -558,6 +558,29 @@ bool conv_rag_supports(const ConvArgs &a)
     return (((long long)a.P * a.Q + 63) / 64) * a.groups * ((a.K / a.groups + 31) / 32) < (1LL << 31);
 }
 
+double conv_direct_time(const ConvArgs &a)
+{
+    const double Cg = a.C / a.groups, taps = (double)a.R * a.S, outputs = (double)a.N * a.P * a.Q * a.K;
+    return 2990.0 + taps * (100.0 + 70.0 * Cg) + outputs * 0.0035 + outputs * taps * Cg * (taps > 1 && (Cg > 2 || taps >= 16) ? 58e-5 : 44e-5);
+}
+
+double conv_rag_time(const ConvArgs &a)
+{
+    const long long Cg = a.C / a.groups, Kg = a.K / a.groups, taps = (long long)a.R * a.S;
+    const double M = (double)a.N * a.P * a.Q;
+    const long long pieces = a.groups == 1 ? a.R * ((a.S * Cg + 15) / 16) : taps * ((Cg + 15) / 16), steps = (pieces + 3) / 4;
+    const int bm = Kg <= 32 ? 128 : 64;
+    const double tiles = (double)((long long)(M + bm - 1) / bm) * a.groups * ((Kg + 31) / 32), tail = tiles > 1280 ? tiles - 1280 : 0;
+    double here = 3630.0 + 725.0 * steps + tiles * (1.36 + 1.4 * steps) + 1.1 * tail * steps;
+    // the general epilogue, by the outputs a lane has of a group (870 pixels, 1x1, 8 groups of 18 -> 16, formats per channel: 6.7 us, 4.7;
+    // accumulators of 24180 pixels in 12 groups of 3 -> 24 47.3, 34.9; of 45288 pixels in four groups of 31 -> 5 9.9, 42.0)
+    if (a.acc_out || a.frac_w || a.shift < 0 || a.shift > 23) {
+        const double part = (Kg < 16 ? Kg : 16) / 16.0, shares = part * tiles * (Kg <= 32 ? 1.0 : 0.5);
+        here += a.acc_out ? 900.0 * part + 5.8 * shares : 1200.0 + 1000.0 * part + 2.4 * shares;
+    }
+    return here;
+}
+
 // Against one output per lane (conv_direct.hip).  A tile has at least 32 output channels of one group and 16 bytes for every tap of
 // one, so with few channels in a group most of its products are padding, while the other kernel's time grows with the products that
 // are wanted.  Both times as fitted to 6000 layers (1 to 64 groups of 1 .. 64 -> 1 .. 256 channels, 1x1 to 5x5, 25 to 100000 pixels), in
@@ -571,25 +594,14 @@ bool conv_rag_pays(const ConvArgs &a)
     const long long Cg = a.C / a.groups, Kg = a.K / a.groups, taps = (long long)a.R * a.S;
     if ((a.groups > 1 && Kg < 3) || !conv_rag_supports(a)) return false;
     if (taps * Cg < 4 && Kg < 12) return false;
-    const double M = (double)a.N * a.P * a.Q, outputs = M * a.K;
-    const double direct = 2990.0 + taps * (100.0 + 70.0 * Cg) + outputs * 0.0035 + outputs * taps * Cg * (taps > 1 && (Cg > 2 || taps >= 16) ? 58e-5 : 44e-5);
-    const long long pieces = a.groups == 1 ? a.R * ((a.S * Cg + 15) / 16) : taps * ((Cg + 15) / 16), steps = (pieces + 3) / 4;
-    const int bm = Kg <= 32 ? 128 : 64;
-    const double tiles = (double)((long long)(M + bm - 1) / bm) * a.groups * ((Kg + 31) / 32), tail = tiles > 1280 ? tiles - 1280 : 0;
-    double here = 3630.0 + 725.0 * steps + tiles * (1.36 + 1.4 * steps) + 1.1 * tail * steps;
-    // the general epilogue, by the outputs a lane has of a group (870 pixels, 1x1, 8 groups of 18 -> 16, formats per channel: 6.7 us, 4.7;
-    // accumulators of 24180 pixels in 12 groups of 3 -> 24 47.3, 34.9; of 45288 pixels in four groups of 31 -> 5 9.9, 42.0)
-    if (a.acc_out || a.frac_w || a.shift < 0 || a.shift > 23) {
-        const double part = (Kg < 16 ? Kg : 16) / 16.0, shares = part * tiles * (Kg <= 32 ? 1.0 : 0.5);
-        here += a.acc_out ? 900.0 * part + 5.8 * shares : 1200.0 + 1000.0 * part + 2.4 * shares;
-    }
-    return direct * 15.0 > here * 16.0;
+    return conv_direct_time(a) * 15.0 > conv_rag_time(a) * 16.0;
 }
 
 static hipError_t launch_images(const ConvArgs &a, hipStream_t st)
 {
     const int rows_ct = rows_tile(a);
     if (rows_ct) return rows_ct == 1 ? launch_rows<1>(a, st) : launch_rows<2>(a, st);
+    if (a.groups > 1 && conv_rag_groups_time(a) < 0.9 * conv_rag_time(a)) return launch_conv_rag_groups(a, st);
     RagParams prm{};
     prm.a = a;
     prm.M = a.N * a.P * a.Q;

@@ -89,6 +89,7 @@ dfq_conv_variant select_variant(const ConvArgs &a)
     if (conv_pw_supports(a)) return DFQ_CONV_POINTWISE;
     if (conv_mfma_supports(a)) return DFQ_CONV_MFMA;
     if (conv_smallc_supports(a)) return DFQ_CONV_SMALLC;
+    if (conv_rag_groups_pays(a)) return DFQ_CONV_RAGGED;
     if (conv_grouped_supports(a)) return DFQ_CONV_GROUPED;
     if (conv_rag_pays(a)) return DFQ_CONV_RAGGED;
     return DFQ_CONV_DIRECT;

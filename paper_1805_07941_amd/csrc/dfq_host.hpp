@@ -126,6 +126,11 @@ hipError_t launch_conv_direct(const ConvArgs &a, hipStream_t st);
 bool conv_rag_supports(const ConvArgs &a);      // any channel count, grouping and alignment on the matrix cores
 bool conv_rag_pays(const ConvArgs &a);          // it supports the call and beats the direct kernel on it
 hipError_t launch_conv_rag(const ConvArgs &a, hipStream_t st);
+double conv_rag_time(const ConvArgs &a);         // nanoseconds of conv_rag_kernel, and of one output per lane (fitted, grouped layers too)
+double conv_direct_time(const ConvArgs &a);
+double conv_rag_groups_time(const ConvArgs &a);  // of a grouped layer taken several groups at a time, by launch_conv_rag() where that is less
+bool conv_rag_groups_pays(const ConvArgs &a);    // and less than any other kernel's
+hipError_t launch_conv_rag_groups(const ConvArgs &a, hipStream_t st);
 bool conv_mfma_supports(const ConvArgs &a);
 bool conv_mfma_lean(const ConvArgs &a);      // the result, its address and the shifts suit the lean epilogue
 bool conv_mfma_fuses(const ConvArgs &a);     // a.add set: the dense kernel has a fused form for this call
@@ -143,6 +148,7 @@ bool conv_pw_supports(const ConvArgs &a);
 hipError_t launch_conv_pw(const ConvArgs &a, hipStream_t st);
 bool conv_grouped_supports(const ConvArgs &a);
 hipError_t launch_conv_grouped(const ConvArgs &a, hipStream_t st);
+double conv_grouped_time(const ConvArgs &a);    // nanoseconds (fitted)
 bool conv_sg_supports(const ConvArgs &a);       // grouped layers the matrix-core form (blocks of 64 channels) takes
 hipError_t launch_conv_sg(const ConvArgs &a, hipStream_t st);
 bool conv_np_mfma_supports(const NpConvArgs &a);
