@@ -64,6 +64,29 @@ __device__ __forceinline__ u128 shift_bytes(u128 v, int d)
     return d >= 0 ? v >> (8 * d) : v << (-8 * d);
 }
 
+// The end of a tile for formats per channel that all lie within the four-instruction rounding: no branch in a channel, and the formats
+// fetched anew for each of a lane's pixels (48 registers otherwise).
+__device__ __forceinline__ void store_lane_formats(const v16i &v, const ConvArgs &a, int m, int kc, int count)
+{
+    const int *f = a.frac_w + kc;
+    Bytes16 o;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        asm volatile("" : "+v"(f));
+        int4 s = make_int4(f[min(4 * j, count - 1)], f[min(4 * j + 1, count - 1)], f[min(4 * j + 2, count - 1)], f[min(4 * j + 3, count - 1)]);
+        s = make_int4(s.x + a.shift, s.y + a.shift, s.z + a.shift, s.w + a.shift);
+        const int4 hi = make_int4(127 << s.x, 127 << s.y, 127 << s.z, 127 << s.w);
+        const int4 badd = make_int4(max((1 << s.x) >> 1, 1) - 1, max((1 << s.y) >> 1, 1) - 1, max((1 << s.z) >> 1, 1) - 1, max((1 << s.w) >> 1, 1) - 1);
+        o.w[j] = requant_four_per_channel(v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3], s, hi, badd, a.relu);
+    }
+    store_bytes(o, a.y + (size_t)m * a.ldy + kc, count);
+}
+
+__device__ __forceinline__ bool formats_are_fast(const ConvArgs &a)
+{
+    return a.frac_w && !a.acc_out && a.y && a.shift + a.frac_w_lo >= 0 && a.shift + a.frac_w_hi <= 23;
+}
+
 // CONTIG: groups == 1, a segment is a whole kernel row
 template <int BM, int BK, bool CONTIG>
 __global__ void __launch_bounds__(kRagThreads) conv_rag_kernel(RagParams prm)
@@ -234,6 +257,7 @@ __global__ void __launch_bounds__(kRagThreads) conv_rag_kernel(RagParams prm)
     Requant rq;
     rq.init(a.shift, a.relu);
     const bool lean = rq.fast && !a.frac_w && !a.acc_out;         // one shift for the launch, int8 result only
+    const bool formats = formats_are_fast(a);
 #pragma unroll
     for (int c = 0; c < CT; c++) {
         const int kl = kg0 + wc0 + c * 32 + 16 * lh;        // first of the lane's 16 channels, inside the group
@@ -251,6 +275,8 @@ __global__ void __launch_bounds__(kRagThreads) conv_rag_kernel(RagParams prm)
             if (lean) {
                 const uint4 o = requant_tile_lane_fast(acc[c][p], rq);
                 store_bytes(Bytes16{{o.x, o.y, o.z, o.w}}, a.y + (size_t)m * a.ldy + kc, count);
+            } else if (formats) {
+                store_lane_formats(acc[c][p], a, m, kc, count);
             } else {
                 store_tile_lane_ragged(acc[c][p], a, m, kc, count);
             }
@@ -449,7 +475,7 @@ __global__ void __launch_bounds__(kRagThreads) conv_rag_kernel_rows(RowsParams p
 
     Requant rq;
     rq.init(a.shift, a.relu);
-    const bool lean = rq.fast && !a.frac_w && !a.acc_out;
+    const bool lean = rq.fast && !a.frac_w && !a.acc_out, formats = formats_are_fast(a);
     if (m >= prm.M) return;
 #pragma unroll
     for (int c = 0; c < CT; c++) {
@@ -463,6 +489,8 @@ __global__ void __launch_bounds__(kRagThreads) conv_rag_kernel_rows(RowsParams p
         if (lean) {
             const uint4 r = requant_tile_lane_fast(acc[c], rq);
             store_bytes(Bytes16{{r.x, r.y, r.z, r.w}}, a.y + (size_t)m * a.ldy + kc, count);
+        } else if (formats) {
+            store_lane_formats(acc[c], a, m, kc, count);
         } else {
             store_tile_lane_ragged(acc[c], a, m, kc, count);
         }
@@ -489,12 +517,15 @@ long long rows_bytes(const ConvArgs &a)
 int rows_tile(const ConvArgs &a)
 {
     const long long steps = ((long long)a.R * ((a.S * a.C + 31) / 32) + 1) / 2;
-    if (a.groups != 1 || steps < (a.stride > 1 ? 16 : 10) || a.R * a.S < 9 || rows_bytes(a) > 72 * 1024) return 0;
     const long long tiles_p = ((long long)a.N * a.P * a.Q + kRowsBM - 1) / kRowsBM, tiles = tiles_p * ((a.K + 31) / 32);
+    // (with one tile for a unit more rows cost nothing: 2 x 76 x 51 of 181 -> 48, 3x3 19.1 us, with rows 14.9; 48 x 21 x 29 of 316 -> 11, 5x5 79.8,
+    // 48.6; but 12 x 35 x 9 of 118 -> 16, 3x3 / 2 15.6, 18.5)
+    const long long most = tiles <= kNumUnits && (a.stride == 1 || a.R * a.S >= 25) ? 148 * 1024 : 72 * 1024;
+    if (a.groups != 1 || steps < (a.stride > 1 ? 16 : 10) || a.R * a.S < 9 || rows_bytes(a) > most) return 0;
     // (a lane has one pixel for every format it fetches, or for every sum's address: many tiles with formats per channel or sums lose,
     // 81648 pixels of 86 -> 97, 3x3, per channel 34.0 us, here 38.4; 85500 of 58 -> 25, 5x5 / 2, 30.0, 41.5)
     if ((a.frac_w || a.acc_out) && tiles_p > 400) return 0;
-    return tiles <= 2 * kNumUnits ? 1 : 2;
+    return a.K <= 32 || tiles <= 2 * kNumUnits ? 1 : 2;
 }
 
 template <int CT>
@@ -595,6 +626,15 @@ bool conv_rag_pays(const ConvArgs &a)
     if ((a.groups > 1 && Kg < 3) || !conv_rag_supports(a)) return false;
     if (taps * Cg < 4 && Kg < 12) return false;
     return conv_direct_time(a) * 15.0 > conv_rag_time(a) * 16.0;
+}
+
+// Layers whose kernel rows are at most 32 bytes (conv_smallc.hip takes every one) with more than a first layer's channels: that kernel's tiles
+// of 64 channels and its packed weights pay from many tiles on only.  Of 86 such layers 60 are faster here, 1.26 times in the mean (8 x 18 x 14
+// of 9 -> 68, 3x3 7.9 us, here 5.1; 26 x 14 x 7 of 26 -> 117, 1x1 / 2 6.5, 4.5); above the line 164 x 33 x 25 of 6 -> 9, 5x5 10.2, 11.5.
+bool conv_rag_small(const ConvArgs &a)
+{
+    if (a.groups != 1 || a.C < 5 || a.frac_w || (a.acc_out && a.K <= 32) || !conv_rag_supports(a)) return false;
+    return conv_rag_time(a) < 9500.0;
 }
 
 static hipError_t launch_images(const ConvArgs &a, hipStream_t st)

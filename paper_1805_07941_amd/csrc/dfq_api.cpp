@@ -88,7 +88,7 @@ dfq_conv_variant select_variant(const ConvArgs &a)
     if (conv_depthwise_supports(a)) return DFQ_CONV_DEPTHWISE;
     if (conv_pw_supports(a)) return DFQ_CONV_POINTWISE;
     if (conv_mfma_supports(a)) return DFQ_CONV_MFMA;
-    if (conv_smallc_supports(a)) return DFQ_CONV_SMALLC;
+    if (conv_smallc_supports(a)) return conv_rag_small(a) ? DFQ_CONV_RAGGED : DFQ_CONV_SMALLC;
     if (conv_rag_groups_pays(a)) return DFQ_CONV_RAGGED;
     if (conv_grouped_supports(a)) return DFQ_CONV_GROUPED;
     if (conv_rag_pays(a)) return DFQ_CONV_RAGGED;

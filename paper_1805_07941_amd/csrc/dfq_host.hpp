@@ -126,6 +126,7 @@ hipError_t launch_conv_direct(const ConvArgs &a, hipStream_t st);
 bool conv_rag_supports(const ConvArgs &a);      // any channel count, grouping and alignment on the matrix cores
 bool conv_rag_pays(const ConvArgs &a);          // it supports the call and beats the direct kernel on it
 hipError_t launch_conv_rag(const ConvArgs &a, hipStream_t st);
+bool conv_rag_small(const ConvArgs &a);         // a layer of few channels that it takes faster than conv_smallc
 double conv_rag_time(const ConvArgs &a);         // nanoseconds of conv_rag_kernel, and of one output per lane (fitted, grouped layers too)
 double conv_direct_time(const ConvArgs &a);
 double conv_rag_groups_time(const ConvArgs &a);  // of a grouped layer taken several groups at a time, by launch_conv_rag() where that is less
