@@ -322,7 +322,7 @@ Shape choose(const ConvArgs &a)
     // Fitted to 1300 layer sizes: this kernel takes 3 us + (2 + 0.4 n) ns per 32 x 32 tile; the general one, while its tiles do not
     // fill the chip, 3 us + 0.28 us per 128 bytes of the reduction in steps of that length, 0.7 us in steps of 64, and up
     // to 22 us more where a ragged K takes its general epilogue (5x5 448 -> 832 at 45 x 77, one image, a format per channel:
-    // 72.7, here 94.7; 176 -> 36 at 9 x 62, 82 images 46.8, here 40.6).  Its 64 x 64 tiles for at most 1024 pixels, six stages
+    // 72.7, here 94.7; 176 -> 36 at 9 x 62, 82 images 46.8, here 40.6; fitted while that epilogue stored single bytes).  Its 64 x 64 tiles for at most 1024 pixels, six stages
     // in flight, do as well as the long steps (96 -> 576, 980 pixels 4.1, here 4.9; 320 -> 320 4.3, 4.8), and so does any of its
     // tiles where the reduction is a single step (64 -> 64 at 56 x 56, one image 3.9, 4.4).  At the line: 3x3 256 -> 256 at 14 x 14, four images 8.4 -> 5.8 us, twelve
     // (592 tiles) 8.45 against 8.0; 1x1 512 -> 256 at 28 x 28, one image 4.4 -> 4.3, four 4.7 against 6.2; 3x3 64 -> 64 at
