@@ -115,6 +115,8 @@ def float_weights(net, device, fold: bool = True):
         if nd.op != "conv":
             continue
         w, b = net.weights(nd)
+        if b.size < w.shape[0]:
+            raise B.DfqError(B.ESHAPE, "%s: %d bias values for %d filters" % (nd.name, b.size, w.shape[0]))
         if group and held + w.nbytes > WEIGHT_GROUP_BYTES:
             yield _upload(group, net, device, fold)
             group, held = [], 0
@@ -213,7 +215,9 @@ class FormatWords:
 
 def _calibrate_on_device(net, x: torch.Tensor, device, keep_tensors: bool, per_channel: bool):
     """calibrate() with rule "maxabs": every format is chosen on the device, from the maxima, by the kernels that use it, so the host
-    enqueues the whole network and waits once."""
+    enqueues the whole network and waits once.  None where a layer's weights or bias have another shape than the graph says: the words of the
+    formats are counted by the graph, and what such arrays give is calibrate()'s own loop's to say.  The calls take addresses, so what the layers'
+    wrappers check of tensors that meet is checked here."""
     L, call, st = B.lib(), B._check, B._stream(None)
     qz = Quantized()
     convs = [nd for nd in net.nodes if nd.op == "conv"]
@@ -223,6 +227,10 @@ def _calibrate_on_device(net, x: torch.Tensor, device, keep_tensors: bool, per_c
     t: Dict[str, torch.Tensor] = {}
     if net.input_is_int8 or net.fixed_f_input is not None:
         f_in = net.f_input_codes if net.input_is_int8 else net.fixed_f_input
+        if net.input_is_int8:
+            B._dev(x, torch.int8, "x")
+            if not -32 <= f_in <= 32:
+                raise B.DfqError(B.EFMT, "calibrate (the format of the input's codes)")
         F.words[F.slot[net.input_name]].fill_(f_in)
         t[net.input_name] = x if net.input_is_int8 else B.quantize(x, f_in)
     else:
@@ -242,6 +250,8 @@ def _calibrate_on_device(net, x: torch.Tensor, device, keep_tensors: bool, per_c
             B._dev(wf, torch.float32, "weights")
             B._dev(bf, torch.float32, "bias")
             K = int(wf.shape[0])
+            if K != nd.K or tuple(bf.shape) != (K,):
+                return None
             at = F.weights(K if per_channel else 1)
             w_at[nd.name] = (at, K)
             w, b = torch.empty(wf.shape, dtype=torch.int8, device=device), torch.empty(bf.shape, dtype=torch.int32, device=device)
@@ -259,6 +269,8 @@ def _calibrate_on_device(net, x: torch.Tensor, device, keep_tensors: bool, per_c
             del wf, bf, acc
         elif nd.op == "eltwise":
             a, b2 = (t[s] for s in nd.srcs)
+            if a.shape != b2.shape:
+                raise B.DfqError(B.ESHAPE, "eltwise_q (shapes differ)")
             y = torch.empty(a.shape, dtype=torch.int8, device=device)
             fa, fb = (F.of(s) for s in nd.srcs)
             call(L.dfq_cal_add(a.data_ptr(), fa, b2.data_ptr(), fb, a.numel(), int(nd.relu), F.maximum(1), y.data_ptr(), F.new(nd.dst), F.err, st),
@@ -266,6 +278,8 @@ def _calibrate_on_device(net, x: torch.Tensor, device, keep_tensors: bool, per_c
             t[nd.dst] = y
         elif nd.op == "concat":
             xs = [t[s] for s in nd.srcs]
+            if any(v.shape[:-1] != xs[0].shape[:-1] for v in xs):
+                raise B.DfqError(B.ESHAPE, "concat_q (pixel grids differ)")
             Cs = [int(v.shape[-1]) for v in xs]
             nb = len(xs)
             y = torch.empty(xs[0].shape[:-1] + (sum(Cs),), dtype=torch.int8, device=device)
@@ -308,7 +322,9 @@ def calibrate(net, x: torch.Tensor, device="cuda:0", keep_tensors: bool = True, 
     if rule not in ("maxabs", "search") or (rule == "search" and per_channel):
         raise ValueError("rule must be 'maxabs' or 'search' (the search with per-layer weight formats)")
     if rule == "maxabs" and not match_joins and x.shape[0] > 0:
-        return _calibrate_on_device(net, x, device, keep_tensors, per_channel)
+        done = _calibrate_on_device(net, x, device, keep_tensors, per_channel)
+        if done is not None:
+            return done
     qz = Quantized()
     biases = _quantize_weights(net, qz, device, per_channel)
     t: Dict[str, torch.Tensor] = {}
@@ -339,7 +355,7 @@ def calibrate(net, x: torch.Tensor, device="cuda:0", keep_tensors: bool = True, 
                 # and the output format is the finest that holds every channel's maximum
                 f_wk, fw_dev = qz.w_frac[nd.name], qz.w_frac_dev[nd.name]
                 f_range = (int(f_wk.min()), int(f_wk.max()))
-                qz.b[nd.name] = B.quantize_i32_rows(bf, fw_dev, f_in)
+                qz.b[nd.name] = B.quantize_i32_rows(bf[:len(f_wk)], fw_dev, f_in)        # (a format for every value)
                 w, b = qz.w[nd.name], qz.b[nd.name]
                 if nd.fixed_f_out is not None:
                     qz.frac[nd.dst] = nd.fixed_f_out
