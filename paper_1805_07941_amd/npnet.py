@@ -84,6 +84,8 @@ def calibrate(net, x: torch.Tensor, p: int = 4, device="cuda:0"):
             B._dev(wf, torch.float32, "weights")
             B._dev(bf, torch.float32, "bias")
             K = int(wf.shape[0])
+            if K > gamma.numel():                        # (more filters than the graph says)
+                gamma = torch.empty(K, dtype=torch.float32, device=device)
             # the matrix-core kernel writes whole groups of 16 channels: the last layer gets all-zero filter rows up to
             # the next multiple (their outputs are zeros behind the real ones and are never read)
             padded = nd.dst == net.output_name and K % 16 and wf.shape[3] % 64 == 0 and nd.groups == 1 and not packs(net, nd)
@@ -101,6 +103,8 @@ def calibrate(net, x: torch.Tensor, p: int = 4, device="cuda:0"):
             qz.w[nd.name] = (wh, wl)
             xh, xl, wh, wl, stride, pad = _conv_operands(net, nd, qz, t[src])
             N, H, W, Cc = xh.shape
+            if wh.shape[3] * nd.groups != Cc:            # (the calls take addresses: what the wrappers check of operands that meet)
+                raise ValueError("operand shapes do not match")
             R, S = int(wh.shape[1]), int(wh.shape[2])
             P, Q = B.conv_out_hw(H, W, R, S, stride, pad)
             yh, yl = torch.empty((N, P, Q, Kp), **i8), torch.empty((N, P, Q, Kp), **i8)
@@ -113,6 +117,8 @@ def calibrate(net, x: torch.Tensor, p: int = 4, device="cuda:0"):
         elif nd.op == "eltwise":
             (ah, al), (bh, bl) = (t[s] for s in nd.srcs)
             fa, fb = (F.of(s) for s in nd.srcs)
+            if ah.shape != bh.shape:
+                raise ValueError("operand shapes do not match")
             yh, yl = torch.empty(ah.shape, **i8), torch.empty(ah.shape, **i8)
             call(L.dfq_cal_add_np(ah.data_ptr(), al.data_ptr(), fa, bh.data_ptr(), bl.data_ptr(), fb, ah.numel(), p, int(nd.relu), F.maximum(B.CAL_AMAX_WORDS),
                                   yh.data_ptr(), yl.data_ptr(), F.new(nd.dst), F.err, st), "dfq_cal_add_np")

@@ -8,6 +8,7 @@ torch = pytest.importorskip("torch")
 import workloads as wl
 from paper_1805_07941_amd import binding as B
 from paper_1805_07941_amd import net as int8net
+from paper_1805_07941_amd import npnet
 
 
 class Recorder:
@@ -128,6 +129,58 @@ def test_codes_as_the_input(library):
         library.calls.clear()
 
 
+def _np(net):
+    return npnet.calibrate(net, _x(net), device="cpu")
+
+
+def test_np_consistent_network_passes(library):
+    _np(_net())
+    assert {"dfq_cal_np_weights", "dfq_cal_conv_np", "dfq_cal_add_np"} <= set(library.calls)
+
+
+@pytest.mark.parametrize("layer", ["a", "b"])
+def test_np_short_bias(library, layer):
+    with pytest.raises(B.DfqError) as e:
+        _np(_net(change={layer: lambda w, b: (w, b[:-1])}))
+    assert e.value.status == B.ESHAPE and "dfq_cal_np_weights" not in library.calls
+
+
+def test_np_input_channels(library):
+    with pytest.raises(ValueError):
+        _np(_net(change={"a": lambda w, b: (np.ascontiguousarray(w[..., :5]), b)}))
+    assert "dfq_cal_conv_np" not in library.calls
+
+
+def test_np_operands_of_a_join(library):
+    net = _net()
+    net.nodes[1].stride = 2
+    with pytest.raises(ValueError):
+        _np(net)
+    assert "dfq_cal_conv_np" in library.calls and "dfq_cal_add_np" not in library.calls
+
+
+def test_np_more_filters_than_the_graph_says(library, monkeypatch):
+    """The scratch of a layer's thresholds holds one for each of its filters."""
+    sizes = {}
+    empty = torch.empty
+
+    def record(*args, **kw):
+        t = empty(*args, **kw)
+        sizes[t.data_ptr()] = t.numel()
+        return t
+
+    def weights(w, bias, rows, row_len, p, gamma, *rest):
+        library.calls.append("dfq_cal_np_weights")
+        assert sizes[gamma] >= rows
+        return B.OK
+    monkeypatch.setattr(torch, "empty", record)
+    library.dfq_cal_np_weights = weights
+    net = _net(change={"b": lambda w, b: (np.concatenate([w] * 40), np.concatenate([b] * 40))})
+    with pytest.raises(ValueError):                      # the add: 8 and 320 channels
+        _np(net)
+    assert library.calls.count("dfq_cal_np_weights") == 2
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("per_channel", [False, True])
 def test_a_longer_bias_gives_what_its_first_values_give(per_channel):
@@ -140,3 +193,7 @@ def test_a_longer_bias_gives_what_its_first_values_give(per_channel):
     for name, b in want.b.items():
         assert torch.equal(b, got.b[name][:len(b)]) and torch.equal(want.w[name], got.w[name])
     assert all(torch.equal(tw[k], tg[k]) for k in tw)
+    if not per_channel:
+        want, tw = npnet.calibrate(_net(), x)
+        got, tg = npnet.calibrate(_net(change={"b": longer}), x)
+        assert want.frac == got.frac and all(torch.equal(u, v) for k in tw for u, v in zip(tw[k], tg[k]))
