@@ -4,6 +4,7 @@
 
 #include <cmath>
 #include <cstring>
+#include <initializer_list>
 #include <tuple>
 #include <type_traits>
 #include <utility>
@@ -21,6 +22,23 @@ inline bool overlaps(const void *a, size_t na, const void *b, size_t nb)
     if (!a || !b || !na || !nb) return false;
     uintptr_t pa = (uintptr_t)a, pb = (uintptr_t)b;
     return pa < pb + nb && pb < pa + na;
+}
+
+struct Span {
+    const void *at;
+    size_t bytes;
+};
+
+// every output apart from every input and from every other output
+inline bool apart(std::initializer_list<Span> ins, std::initializer_list<Span> outs)
+{
+    for (const Span *o = outs.begin(); o != outs.end(); o++) {
+        for (const Span &i : ins)
+            if (overlaps(o->at, o->bytes, i.at, i.bytes)) return false;
+        for (const Span *other = o + 1; other != outs.end(); other++)
+            if (overlaps(o->at, o->bytes, other->at, other->bytes)) return false;
+    }
+    return true;
 }
 
 // bytes from the first to the last one touched of `pixels` rows of K bytes, ld bytes apart: a channel slice of a wider tensor ends
@@ -939,6 +957,8 @@ dfq_status dfq_cal_np_weights(const float *w, const float *bias, size_t rows, si
     if (p < 4 || p > 7) return DFQ_EFMT;
     if (rows < 1 || rows >= ((size_t)1 << 31) || row_len < 1) return DFQ_ESHAPE;
     if (!w || !bias || !gamma || !frac_in || !codes || !hi || !lo || !w_frac || !b || !err) return DFQ_EINVAL;
+    const size_t n = rows * row_len;
+    if (!apart({{w, n * 4}, {bias, rows * 4}}, {{codes, n}, {hi, n}, {lo, n}, {b, rows * 4}})) return DFQ_EINVAL;
     return from_hip(launch_cal_np_weights(w, bias, rows, row_len, p, (int)dfq_beta_max(8, p), gamma, frac_in, codes, hi, lo, w_frac, b, err,
                                           (hipStream_t)stream));
 }
@@ -948,6 +968,7 @@ dfq_status dfq_cal_np_quantize(const float *x, size_t n, int p, float *gamma, in
 {
     if (p < 4 || p > 7) return DFQ_EFMT;
     if (!gamma || !frac || !err || (n && (!x || !hi || !lo))) return DFQ_EINVAL;
+    if (!apart({{x, n * 4}}, {{hi, n}, {lo, n}})) return DFQ_EINVAL;
     return from_hip(launch_cal_np_quantize(x, n, p, (int)dfq_beta_max(8, p), gamma, hi, lo, frac, err, (hipStream_t)stream));
 }
 
@@ -986,6 +1007,7 @@ dfq_status dfq_cal_add_np(const int8_t *ah, const int8_t *al, const int32_t *fra
 {
     if (p < 4 || p > 7) return DFQ_EFMT;
     if (!frac_a || !frac_b || !amax || ((uintptr_t)amax & 7) || !frac_y || !err || (n && (!ah || !al || !bh || !bl || !yh || !yl))) return DFQ_EINVAL;
+    if (!apart({{ah, n}, {al, n}, {bh, n}, {bl, n}}, {{yh, n}, {yl, n}})) return DFQ_EINVAL;
     const NpCalAdd cal{frac_a, frac_b, reinterpret_cast<const unsigned long long *>(amax), frac_y, err, DFQ_CAL_AMAX_WORDS / 16};
     const hipError_t e = launch_eltwise_np_absmax(ah, al, bh, bl, n, 0, 0, relu ? 1 : 0, reinterpret_cast<unsigned long long *>(amax), (hipStream_t)stream, cal);
     if (e != hipSuccess) return DFQ_EDEVICE;

@@ -181,6 +181,28 @@ def test_np_more_filters_than_the_graph_says(library, monkeypatch):
     assert library.calls.count("dfq_cal_np_weights") == 2
 
 
+def test_np_results_apart_from_the_operands():
+    """Every result of the (8, p) calls where it meets an operand or another result: refused before anything is launched."""
+    L = B.lib()
+    M = 1 << 20
+    # addresses in order of the arguments, with the bytes behind them: 4 rows of 8 values, 32 values
+    weights = [M, 2 * M, 4, 8, 4, 3 * M, 4 * M, 5 * M, 6 * M, 7 * M, 8 * M, 9 * M, 10 * M, None]
+    for out, other, distance in ((5 + 2, 0, 127), (8, 0, 64), (9, 0, 1), (7, 8, 31), (8, 9, -31), (9, 7, 5), (11, 1, 15), (11, 7, 31), (7, 1, 3), (11, 0, 127)):
+        args = list(weights)
+        args[out] = args[other] + distance
+        assert L.dfq_cal_np_weights(*args) == B.EINVAL, (out, other)
+    quantize = [M, 32, 4, 2 * M, 3 * M, 4 * M, 5 * M, 6 * M, None]
+    for out, other, distance in ((4, 0, 127), (5, 0, 0), (5, 4, 31)):
+        args = list(quantize)
+        args[out] = args[other] + distance
+        assert L.dfq_cal_np_quantize(*args) == B.EINVAL, (out, other)
+    add = [M, 2 * M, 3 * M, 4 * M, 5 * M, 6 * M, 32, 4, 0, 7 * M, 8 * M, 9 * M, 10 * M, 11 * M, None]
+    for out, other, distance in ((10, 0, 31), (10, 1, 0), (10, 3, -31), (10, 4, 8), (11, 0, 0), (11, 4, 1), (11, 10, 31)):
+        args = list(add)
+        args[out] = args[other] + distance
+        assert L.dfq_cal_add_np(*args) == B.EINVAL, (out, other)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("per_channel", [False, True])
 def test_a_longer_bias_gives_what_its_first_values_give(per_channel):
