@@ -831,8 +831,15 @@ class Plan:
     def _calls_for(self, x: torch.Tensor):
         key = (x.data_ptr(), tuple(x.shape))
         if self._calls_key != key:
-            self._calls = self._build_calls(x)
-            self._list = B.CallList(self._calls)
+            built = self._calls_key
+            if built is not None and built[1] == key[1] and (built[0] - key[0]) % 256 == 0:
+                # another tensor of that shape and alignment: the same calls (which kernels fuse depends on nothing else of it)
+                self._calls = self._list.rebind(x.data_ptr())
+                if self.net.input_is_int8:
+                    self.buf[self.net.input_name] = x
+            else:
+                self._calls = self._build_calls(x)
+                self._list = B.CallList(self._calls, x.data_ptr())
             self._calls_key = key
             self._graph = None
         return self._calls

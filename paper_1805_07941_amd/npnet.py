@@ -264,8 +264,12 @@ class NpPlan:
             raise ValueError("x must be a contiguous float32 device tensor of the plan's input shape")
         key = x.data_ptr()
         if self._calls_key != key:
-            self._calls, self._calls_key, self._graph = self._build_calls(x), key, None
-            self._list = B.CallList(self._calls)
+            if self._calls is None:
+                self._calls = self._build_calls(x)
+                self._list = B.CallList(self._calls, key)
+            else:
+                self._calls = self._list.rebind(key)
+            self._calls_key, self._graph = key, None
         return self._calls
 
     def run(self, x: torch.Tensor, stream=None) -> torch.Tensor:
