@@ -69,7 +69,7 @@ def _to_device(arrays, device):
     def send():
         nonlocal turn, at, used
         dst[at:at + used].copy_(stages[turn][:used], non_blocking=True)
-        sent[turn].record()
+        sent[turn].record(torch.cuda.current_stream(device))      # (the stream of the copy: the destination's device need not be the current one)
         turn, at, used = (turn + 1) % len(stages), at + used, 0
         sent[turn].synchronize()                          # (an event that was never recorded is complete)
 

@@ -74,3 +74,31 @@ def test_results_do_not_depend_on_the_groups(monkeypatch, per_channel):
     for name in ta:
         assert torch.equal(ta[name], tb[name])
         assert all(torch.equal(u, v) for u, v in zip(xa[name], xb[name]))
+
+
+def test_a_pinned_piece_is_awaited_on_the_device_it_travels_to(monkeypatch):
+    """Uploads to a device that is not the current one: the events stand on the destination's stream, where the copies are."""
+    log = []
+    empty = torch.empty
+
+    class Event:
+        def __init__(self):
+            self.mark = None
+
+        def record(self, stream=None):
+            self.mark = len(log)
+            log.append(("record", stream))
+
+        def synchronize(self):
+            log.append(("wait", self.mark))
+
+    monkeypatch.setattr(torch, "empty", lambda *a, device=None, pin_memory=False, **kw: empty(*a, **kw))
+    monkeypatch.setattr(torch.cuda, "Event", Event)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: ("stream of", str(device)))
+    monkeypatch.setattr(int8net, "STAGING_BYTES", 4096)
+    rng = np.random.default_rng(2)
+    arrays = [rng.standard_normal(n).astype(np.float32) for n in (700, 5, 3000, 64, 1023, 1, 2048)]
+    got = int8net._to_device(arrays, "cuda:1")
+    assert all(np.array_equal(g.numpy(), a) for g, a in zip(got, arrays))
+    records = [entry[1] for entry in log if entry[0] == "record"]
+    assert len(records) > 4 and set(records) == {("stream of", "cuda:1")}
