@@ -17,6 +17,7 @@
 // Bound by the tiles' chain of load, LDS, barrier, products and store: 1.4 us of a unit for each.
 #include "conv_epilogue.hpp"
 #include "dfq_host.hpp"
+#include "input_piece.hpp"
 
 namespace dfq {
 
@@ -188,7 +189,7 @@ __global__ void __launch_bounds__(kGroupsThreads, 4) conv_rag_kernel_groups(Grou
             const bool in = i < total && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
             const unsigned b = in ? (unsigned)(n * a.H + ih) * (unsigned)prm.row_bytes + (unsigned)(iw * a.C + c0 + 16 * j) : 0u;
             const unsigned from = min(b, (unsigned)prm.x_last);
-            xd[e] = in ? (int)(b - from) : -1;
+            xd[e] = piece_move(in, b, from);
             xto[e] = i < total ? (u * prm.wp + c) * prm.pitch + 16 * j : -1;
             const GroupsPiece t = *(const GroupsPiece *)(a.x + from);
             xv[e] = ((u128)t.hi << 64) | t.lo;
