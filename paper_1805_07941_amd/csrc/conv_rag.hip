@@ -20,6 +20,7 @@
 // ALUs busy 60 % of the time and the matrix pipes 12 %; 20 x 28 x 28 x 250 -> 250, 1x1: 2.49 ms -> 10.5 us; 19 x 14 x 13 in 32 groups of
 // 13 -> 3, 3x3: 63 -> 11 us.
 #include "conv_epilogue.hpp"
+#include "rag_images.hpp"
 
 namespace dfq {
 
@@ -665,14 +666,8 @@ static hipError_t launch_images(const ConvArgs &a, hipStream_t st)
 
 hipError_t launch_conv_rag(const ConvArgs &a, hipStream_t st)
 {
-    // as many images per launch as 31-bit byte offsets into the input and 31-bit pixel and tile numbers reach
     const long long image = (long long)a.H * a.W * a.C, pixels = (long long)a.P * a.Q;
-    const long long margin = ((long long)a.pad + a.R) * a.W * a.C;
-    const long long tiles = (pixels / 64 + 1) * a.groups * ((a.K / a.groups + 31) / 32);
-    long long most = ((1LL << 31) - 1 - margin) / image;
-    most = most < ((1LL << 31) - 257) / pixels ? most : ((1LL << 31) - 257) / pixels;
-    most = most < ((1LL << 31) - 1) / tiles ? most : ((1LL << 31) - 1) / tiles;
-    if (most < 1) most = 1;
+    const long long most = rag_images(a.H, a.W, a.C, a.K, a.R, a.stride, a.pad, a.groups, a.P, a.Q);
     for (long long n = 0; n < a.N; n += most) {
         ConvArgs part = a;
         part.N = (int)(a.N - n < most ? a.N - n : most);
