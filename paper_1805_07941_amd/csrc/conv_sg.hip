@@ -227,8 +227,17 @@ hipError_t launch_blk(SgParams &prm, hipStream_t st)
 template <int NTAPS, int NSTAGES>
 hipError_t launch_sg(SgParams &prm, hipStream_t st)
 {
-    if (prm.a.C % 128 == 0) return prm.Cg == 64 ? launch_blk<NTAPS, NSTAGES, 128, 2>(prm, st) : launch_blk<NTAPS, NSTAGES, 128, 1>(prm, st);
-    return prm.Cg == 64 ? launch_blk<NTAPS, NSTAGES, 64, 2>(prm, st) : launch_blk<NTAPS, NSTAGES, 64, 1>(prm, st);
+    const bool wide = prm.a.C % 128 == 0;
+    if (prm.Cg == 64) {        // at most 64 KB of weights (conv_grouped_supports): six taps in 128 channels, four in 192
+        if constexpr (NTAPS <= 6) {
+            if (wide) return launch_blk<NTAPS, NSTAGES, 128, 2>(prm, st);
+        }
+        if constexpr (NTAPS <= 4) {
+            if (!wide) return launch_blk<NTAPS, NSTAGES, 64, 2>(prm, st);
+        }
+        return hipErrorInvalidValue;
+    }
+    return wide ? launch_blk<NTAPS, NSTAGES, 128, 1>(prm, st) : launch_blk<NTAPS, NSTAGES, 64, 1>(prm, st);
 }
 
 }  // namespace

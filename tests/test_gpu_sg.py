@@ -1,5 +1,7 @@
 """Grouped layers on the matrix cores (conv_sg.hip) against the oracle: every group size and tap count, both widths of a channel block, one tile and
 several per workgroup, ragged last tiles."""
+import re
+
 import numpy as np
 import pytest
 
@@ -7,6 +9,7 @@ torch = pytest.importorskip("torch")
 
 import oracle as orc
 
+from test_gpu_dispatch import launched
 from test_gpu_ops import B, dev, host            # noqa: F401  (B is a fixture)
 
 pytestmark = pytest.mark.gpu
@@ -24,7 +27,23 @@ SHAPES = [
     (24, 60, 59, 128, 64, 2, 3, 1, 0),
     (50, 60, 45, 64, 32, 1, 1, 1, 0),            # the form with one stage
     (9, 61, 60, 384, 16, 3, 3, 1, 1),
+    (3, 9, 8, 128, 16, 1, 1, 1, 0),              # the other triples of taps, width and group that there are
+    (45, 60, 45, 128, 64, 1, 1, 1, 0),
+    (4, 7, 9, 192, 64, 1, 1, 1, 0),
+    (3, 10, 9, 64, 16, 4, 1, 1, 1),
+    (2, 11, 9, 128, 64, 4, 1, 2, 0),
+    (3, 9, 10, 64, 16, 2, 3, 1, 1),
 ]
+
+
+def test_every_form_is_reached(B):
+    calls = []
+    for N, H, W, C, Cg, R, S, st, pad in SHAPES:
+        x, w = (torch.zeros(s, dtype=torch.int8, device="cuda") for s in ((N, H, W, C), (C, R, S, Cg)))
+        calls.append(lambda x=x, w=w, a=(st, pad, C // Cg): B.conv_q(x, w, None, 4, 8, 4, *a, variant=B.CONV_GROUPED))
+    seen = {tuple(int(v) for v in m) for name in launched(calls) for m in re.findall(r"conv_sg_kernel<(\d), \d, (\d+), (\d), \d>", name)}
+    # (the weights of a grouped layer are at most 64 KB: groups of 64 have six taps in 128 channels, four in 192)
+    assert seen == {(taps, width, 1) for taps in (1, 4, 6, 9) for width in (64, 128)} | {(1, 64, 2), (4, 64, 2), (1, 128, 2), (4, 128, 2), (6, 128, 2)}
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
