@@ -1,10 +1,13 @@
 """The forms of the (8, p) matrix-core convolution - split reduction, steps of 64 and of 128 bytes - against the one-output-per-lane kernel, at
 the edges of their tiles and steps: plain, with the add, and the calibration's maximum, with formats given and on the device."""
+import re
+
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
 
+from test_gpu_dispatch import launched
 from test_gpu_npconv import B, dev, host            # noqa: F401  (B is a fixture)
 
 pytestmark = pytest.mark.gpu
@@ -19,6 +22,9 @@ SHAPES = [
     (3, 13, 11, 128, 80, 3, 3, 1, 2),            # ragged pixel and channel tiles
     (5, 14, 14, 256, 256, 3, 3, 1, 1),           # 32 x 32, four
     (2, 28, 27, 64, 96, 5, 3, 1, 1),
+    (2, 14, 14, 1024, 256, 1, 1, 1, 0),          # 32 x 32, eight, unpadded 1x1
+    (5, 14, 14, 512, 512, 1, 1, 1, 0),           # ... four
+    (5, 14, 14, 192, 384, 3, 3, 1, 1),           # ... four, taps that a step straddles
     (9, 14, 15, 128, 512, 1, 1, 1, 0),           # one step
     (18, 28, 28, 128, 128, 3, 3, 1, 1),          # ring of three
     (27, 14, 14, 1024, 256, 1, 1, 1, 0),
@@ -28,6 +34,19 @@ SHAPES = [
     (21, 30, 31, 192, 80, 3, 3, 1, 1),           # steps of 64 bytes
     (40, 9, 9, 128, 272, 17, 1, 1, 8),           # more kernel rows than the masks of 128-byte steps hold
 ]
+
+
+def test_every_form_of_the_split_reduction_is_reached(B):
+    seen = set()
+    calls = []
+    for N, H, W, C, K, R, S, st, pad in SHAPES:
+        x, w = (torch.zeros(s, dtype=torch.int8, device="cuda") for s in ((N, H, W, C), (K, R, S, C)))
+        calls.append(lambda x=x, w=w, a=(st, pad): B.conv_np(x, x, w, w, None, 8, 8, 8, 4, *a, variant=B.CONV_MFMA))
+    for name in launched(calls):
+        seen.update(re.findall(r"conv_np_sk_kernel<(\d, \d, \d, \d, \d)>", name))
+        seen.update(re.findall(r"conv_np_mfma_kernel<128, 64, (\d, \d), false, false, (?:64|128)>", name))
+    assert seen == {"1, 1, 8, 2, 0", "1, 1, 8, 2, 1", "1, 1, 8, 2, 2", "2, 2, 8, 1, 0", "2, 2, 8, 1, 1", "2, 2, 8, 1, 2", "2, 2, 4, 1, 0", "2, 2, 4, 1, 1",
+                    "2, 2, 4, 1, 2", "3, 2", "3, 1", "1, 3"}
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))

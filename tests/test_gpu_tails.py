@@ -1,5 +1,7 @@
 """Channel tails of the dense kernel (whole groups of sixteen past a tile's last full part, single channels), its accumulator dump, and
 the pooling kernels that share reads between windows or pixels between lanes: against the oracle at the edges of their tiles."""
+import re
+
 import numpy as np
 import pytest
 
@@ -8,6 +10,7 @@ torch = pytest.importorskip("torch")
 import oracle as orc
 import oracle.npconv as NC
 
+from test_gpu_dispatch import launched
 from test_gpu_npnet import planes
 from test_gpu_ops import B, dev, host            # noqa: F401  (B is a fixture)
 
@@ -47,8 +50,54 @@ def test_channel_tails(B, geo, K):
                           orc.conv_q(x, w, b, 4, 24, 4, st, pad, 1, False)[0])
 
 
-@pytest.mark.parametrize("shape", [(9, 28, 27, 192), (40, 33, 31, 45), (12, 45, 61, 90), (70, 29, 30, 17), (4, 1, 300, 900), (3, 301, 1, 1000)],
-                         ids=lambda s: "x".join(map(str, s)))
+# Tile shapes (pixels, channels, bytes of a step) that the layers above are too small for.
+LARGE = [
+    (90, 14, 13, 128, 80, 1, "128, 64, 128"),
+    (60, 15, 13, 128, 176, 3, "128, 64, 128"),
+    (100, 32, 32, 16, 48, 3, "256, 64, 64"),
+    (400, 31, 32, 16, 48, 1, "256, 64, 64"),
+]
+
+
+@pytest.mark.parametrize("shape", LARGE, ids=lambda s: "x".join(map(str, s[:6])))
+def test_channel_tails_of_large_layers(B, shape):
+    """Against one output per lane: the shape's last full group of sixteen and none behind it, with the kernel that ran."""
+    N, H, W, C, K, R, tile = shape
+    g = torch.Generator(device="cuda").manual_seed(K + N)
+    x, w = (torch.randint(-128, 128, s, generator=g, device="cuda").to(torch.int8) for s in ((N, H, W, C), (K, R, R, C)))
+    b = torch.randint(-2 ** 15, 2 ** 15, (K,), generator=g, device="cuda").to(torch.int32)
+    shift = int(np.log2(R * np.sqrt(C) * 70 * 70 / 40))
+    want = B.conv_q(x, w, b, 4, shift, 4, 1, R // 2, 1, True, variant=B.CONV_DIRECT)[0]
+    wide = torch.full((N, H, W, K + 32), 77, dtype=torch.int8, device="cuda")
+    run = lambda: B.conv_q(x, w, b, 4, shift, 4, 1, R // 2, 1, True, out=wide.view(-1)[16:], ldy=K + 32, variant=B.CONV_MFMA)
+    run()
+    assert torch.equal(wide[..., 16:16 + K], want)
+    assert bool((wide[..., :16] == 77).all()) and bool((wide[..., 16 + K:] == 77).all())
+    (name,) = launched([run])
+    m = re.search(r"conv_mfma_kernel<(\d+), (\d+), .* (\d+)>", name)
+    assert ", ".join(m.groups()) == tile
+
+
+# the first seven in strips of four rows (with a padding at least; the last two of them images of one row and of one column)
+POOLS = [(40, 28, 27, 192), (80, 33, 31, 45), (24, 45, 61, 90), (150, 29, 30, 17), (3, 112, 97, 180), (4, 1, 300, 900), (16, 301, 1, 1000),
+         (9, 28, 27, 192), (40, 33, 31, 45), (12, 45, 61, 90), (70, 29, 30, 17), (3, 301, 1, 1000)]
+
+
+def test_strips_are_reached(B):
+    calls = [lambda x=torch.zeros(s, dtype=torch.int8, device="cuda"): B.pool_q(x, "max", 3, 1, 1, 4, 4) for s in POOLS]
+    calls[0]()
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        for call in calls:
+            call()
+        torch.cuda.synchronize()
+    names = [e.name for e in sorted((e for e in prof.events() if "pool" in e.name), key=lambda e: e.time_range.start)]
+    if not names:
+        pytest.skip("the device's activity is not recorded here")
+    assert ["maxpool3_s1_kernel" in name for name in names] == [True] * 7 + [False] * 5
+
+
+@pytest.mark.parametrize("shape", POOLS, ids=lambda s: "x".join(map(str, s)))
 @pytest.mark.parametrize("pad", [0, 1, 2])
 def test_max_pool_strips(B, shape, pad):
     if min(shape[1:3]) + 2 * pad < 3:
