@@ -710,7 +710,7 @@ hipError_t launch_conv_mfma(const ConvArgs &a, hipStream_t st)
     //          slower on all but one (96 -> 128, 3x3, 64 images of 28 x 28: 15.0 -> 13.1 us; 16 -> 128, 5x5, 45 images of 56 x 56 23.9 ->
     //          19.3; the one: 192 -> 192, 3x3, 195 tiles of 256 pixels 28.6, 31.2).
     // K <= 64: 128 x 64 tiles (wavefronts of 32 x 64), four workgroups per CU, mean 5 % faster than 256 x 64 - except where those
-    //          leave the last round of long chains fuller, or stream many tiles of a few steps (lines below).
+    //          leave a unit's last tile fuller, or stream many tiles of a few steps (lines below).
     const bool pointwise = a.R == 1 && a.S == 1;
     switch (choose_wide(a)) {
         case Wide::t64: return launch_cfg<64, 64, 2, 2, 3, 3, 128>(a, st);
@@ -729,10 +729,13 @@ hipError_t launch_conv_mfma(const ConvArgs &a, hipStream_t st)
     // in 128 x 128 tiles 19.6)
     if (a.add && !a.frac_w && t256 * (a.K / 256) >= 192) return launch_cfg<256, 256, 4, 2, 3, 1>(a, st);
     if (a.K > 64) return launch_cfg<128, 128, 2, 2, 3, 3>(a, st);
-    // (larger kernels of 376 .. 499 tiles of 256 pixels lose 4 % in the mean, 64 -> 64, 5x5, 495 tiles 20.3, 22.7; from 900 on 5 %,
-    // 48 -> 64, 3x3, 1963 tiles 26.2, 30.7; below 376 they gain 6 %, 500 .. 899 8 %; one weight format per channel: the epilogue
-    // is built for the 256 x 64 tiles)
-    if (!a.frac_w && (pointwise ? t256 < 1500 : t256 < 376 || (t256 >= 500 && t256 < 900))) return launch_cfg<128, 64, 4, 1, 3, 4>(a, st);
+    // Larger kernels by the 128-pixel tiles of a unit; 128 x 64 bring a fifth more rows per product than 256 x 64.  Time against those, mean of
+    // 33985 layers of 16 .. 640 -> 8 .. 64 channels: one and two tiles 0.80 and 0.87 (twice the workgroups); odd numbers, where the
+    // last 256-pixel tile would be half empty, 3: 0.95, 5: 0.94, 7: 0.90, 9: 0.98, 11: 0.92; six 0.98; other even numbers 4: 1.06, 8 and 10: 1.02, 12: 1.04;
+    // beyond, 1.00 to 1.05.  (One weight format per output channel: the epilogue is built for the 256 x 64 tiles.)
+    const long long per_unit = (((long long)a.N * a.P * a.Q + 127) / 128 + kNumCU - 1) / kNumCU;
+    const bool halves = per_unit <= 2 || per_unit == 6 || (per_unit % 2 == 1 && per_unit < 12);
+    if (!a.frac_w && (pointwise ? t256 < 1500 : halves)) return launch_cfg<128, 64, 4, 1, 3, 4>(a, st);
     return pointwise ? launch_cfg<256, 64, 4, 1, 3, 2>(a, st) : launch_cfg<256, 64, 4, 1, 2, 3>(a, st);
 }
 

@@ -54,7 +54,12 @@ def test_channel_tails(B, geo, K):
 LARGE = [
     (90, 14, 13, 128, 80, 1, "128, 64, 128"),
     (60, 15, 13, 128, 176, 3, "128, 64, 128"),
-    (100, 32, 32, 16, 48, 3, "256, 64, 64"),
+    (100, 32, 32, 16, 48, 3, "256, 64, 64"),     # four tiles of 128 pixels to a unit
+    (130, 32, 32, 16, 48, 3, "128, 64, 64"),     # five
+    (180, 32, 32, 16, 48, 3, "128, 64, 64"),     # six
+    (251, 32, 32, 16, 48, 3, "256, 64, 64"),     # eight
+    (260, 32, 32, 16, 48, 3, "128, 64, 64"),     # nine
+    (420, 32, 32, 16, 48, 3, "256, 64, 64"),     # fourteen
     (400, 31, 32, 16, 48, 1, "256, 64, 64"),
 ]
 
