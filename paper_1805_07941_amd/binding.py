@@ -202,6 +202,9 @@ def _dev(t: torch.Tensor, dtype, name: str):
     return t
 
 
+_ZEROS = [0] * CALL_ARGS
+
+
 # ---- a pass as one call ------------------------------------------------------------ #
 class CallList:
     """[(C function, its arguments but the stream)] as one library call.  Holds what the arguments point to on the host.  input_ptr: the address
@@ -210,48 +213,47 @@ class CallList:
 
     def __init__(self, calls, input_ptr: Optional[int] = None):
         words, arrays = [], {}                                # arrays of addresses by their own
+
+        def of_array(a):
+            at = C.addressof(a)
+            if a._type_ is C.c_void_p:
+                arrays[at] = a
+            return at
+
         for fn, args in calls:
             name = fn.__name__
             number = self._numbers.get(name)
             if number is None:
                 number = self._numbers[name] = lib().dfq_call_number(name.encode())
             words.append((number & 0xffffffff) | len(args) << 32)
-            for a in args:
-                kind = type(a)
-                if kind is int:
-                    words.append(a)
-                elif a is None:
-                    words.append(0)
-                elif kind is Fmt:
-                    words.append(a.frac)
-                elif isinstance(a, C.Array):
-                    words.append(C.addressof(a))
-                    if a._type_ is C.c_void_p:
-                        arrays[words[-1]] = a
-                else:
-                    words.append(int(a))
-            words += [0] * (CALL_ARGS - len(args))
+            words += [a if type(a) is int else a.frac if type(a) is Fmt else 0 if a is None else of_array(a) if isinstance(a, C.Array) else int(a)
+                      for a in args]
+            words += _ZEROS[len(args):]
         self._held, self._count = calls, len(calls)
-        self._at = []                                         # where the input's address stands: word, element of an array or None
-        if input_ptr is not None:
-            for value, elements in [(input_ptr, [None])] + [(at, [e for e, v in enumerate(a) if v == input_ptr]) for at, a in arrays.items()]:
-                self._at += [(w, e) for w in self._find(words, value) for e in elements]
+        self._input, self._arrays, self._at = input_ptr, arrays, None
         self._records = array("q", words)
         self._failed = C.c_size_t()
 
-    @staticmethod
-    def _find(words, value: int):
-        """Positions of an address among the arguments (numbers and sizes are no addresses)."""
-        at = -1
-        try:
-            while True:
+    def _places(self):
+        """Where the input's address stands among the words: (word, element of an array or None).  (Numbers and sizes are no addresses.)"""
+        words = self._records.tolist()
+
+        def find(value):
+            at = -1
+            for _ in range(words.count(value)):
                 at = words.index(value, at + 1)
                 yield at
-        except ValueError:
-            pass
+        at = [(w, None) for w in find(self._input)]
+        for address, a in self._arrays.items():
+            elements = [e for e, v in enumerate(a) if v == self._input]
+            if elements:
+                at += [(w, e) for w in find(address) for e in elements]
+        return at
 
     def rebind(self, input_ptr: int):
         """The same calls on an input at another address.  Returns them as a new list of pairs."""
+        if self._at is None:
+            self._at = self._places()
         calls = list(self._held)
         fresh = {}                                            # (the arrays of the calls before stay as they are)
         for w, e in self._at:
