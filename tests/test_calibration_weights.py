@@ -76,29 +76,39 @@ def test_results_do_not_depend_on_the_groups(monkeypatch, per_channel):
         assert all(torch.equal(u, v) for u, v in zip(xa[name], xb[name]))
 
 
-def test_a_pinned_piece_is_awaited_on_the_device_it_travels_to(monkeypatch):
-    """Uploads to a device that is not the current one: the events stand on the destination's stream, where the copies are."""
-    log = []
-    empty = torch.empty
+@pytest.mark.parametrize("pieces", [1, 2, 4])
+def test_a_pinned_piece_is_awaited_on_the_device_it_travels_to(monkeypatch, pieces):
+    """Uploads to a device that is not the current one, with copies that happen as late as they may: when their stream is awaited."""
+    empty, copy = torch.empty, torch.Tensor.copy_
+    pending, waits = [], []
 
-    class Event:
-        def __init__(self):
-            self.mark = None
-
-        def record(self, stream=None):
-            self.mark = len(log)
-            log.append(("record", stream))
+    class Stream:
+        def __init__(self, device):
+            self.device = str(device)
 
         def synchronize(self):
-            log.append(("wait", self.mark))
+            waits.append(self.device)
+            while pending:
+                copy(*pending.pop(0))
+
+    def late(dst, src, non_blocking=False):
+        if not non_blocking:
+            return copy(dst, src)
+        pending.append((dst, src))
+        return dst
 
     monkeypatch.setattr(torch, "empty", lambda *a, device=None, pin_memory=False, **kw: empty(*a, **kw))
-    monkeypatch.setattr(torch.cuda, "Event", Event)
-    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: ("stream of", str(device)))
+    monkeypatch.setattr(torch.Tensor, "copy_", late)
+    monkeypatch.setattr(torch.cuda, "current_stream", Stream)
     monkeypatch.setattr(int8net, "STAGING_BYTES", 4096)
+    monkeypatch.setattr(int8net, "STAGING_PIECES", pieces)
     rng = np.random.default_rng(2)
-    arrays = [rng.standard_normal(n).astype(np.float32) for n in (700, 5, 3000, 64, 1023, 1, 2048)]
-    got = int8net._to_device(arrays, "cuda:1")
-    assert all(np.array_equal(g.numpy(), a) for g, a in zip(got, arrays))
-    records = [entry[1] for entry in log if entry[0] == "record"]
-    assert len(records) > 4 and set(records) == {("stream of", "cuda:1")}
+    for sizes in ((700, 5, 3000, 64, 1023, 1, 2048), (1024,) * 8, (70000, 3), (1, 2, 3), (4096,), (1000, 1, 1023)):
+        arrays = [rng.standard_normal(n).astype(np.float32) for n in sizes]
+        got = int8net._to_device(arrays, "cuda:1")
+        sent = sum(-(-n // 64) * 64 for n in sizes)
+        assert waits == ["cuda:1"] * ((-(-sent // 1024) - 1) // pieces)           # none behind the last piece
+        waits.clear()
+        Stream("end").synchronize()
+        waits.clear()
+        assert all(np.array_equal(g.numpy(), a) for g, a in zip(got, arrays))
