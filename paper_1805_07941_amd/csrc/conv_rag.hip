@@ -604,7 +604,7 @@ double conv_rag_time(const ConvArgs &a)
     const int bm = Kg <= 32 ? 128 : 64;
     const double tiles = (double)((long long)(M + bm - 1) / bm) * a.groups * ((Kg + 31) / 32), tail = tiles > 1280 ? tiles - 1280 : 0;
     double here = 3630.0 + 725.0 * steps + tiles * (1.36 + 1.4 * steps) + 1.1 * tail * steps;
-    // the general epilogue, by the outputs a lane has of a group (870 pixels, 1x1, 8 groups of 18 -> 16, formats per channel: 6.7 us, 4.7;
+    // the general epilogue, by the outputs a lane has of a group, as fitted while it stored a byte or a sum at a time (870 pixels, 1x1, 8 groups of 18 -> 16, formats per channel: 6.7 us, 4.7;
     // accumulators of 24180 pixels in 12 groups of 3 -> 24 47.3, 34.9; of 45288 pixels in four groups of 31 -> 5 9.9, 42.0)
     if (a.acc_out || a.frac_w || a.shift < 0 || a.shift > 23) {
         const double part = (Kg < 16 ? Kg : 16) / 16.0, shares = part * tiles * (Kg <= 32 ? 1.0 : 0.5);

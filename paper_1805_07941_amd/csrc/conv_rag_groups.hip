@@ -12,8 +12,8 @@
 //            taps that skip are then no different from others).
 // conv_rag_kernel, one group at a time, fetches and shifts every piece of the input once per tap and group and fills 32 rows of the matrix
 // instruction with a group's few outputs.  203 x 16 x 29, 32 groups of 5 -> 5, 5x5: 335 us there, here 33; 19 x 45 x 69, 8 groups of 6 -> 6, 5x5 51,
-// 12; depthwise with a channel count of no 16-byte pieces, 8 x 44 x 70 x 382, 3x3 103 (conv_depthwise.hip), 27.  Code size counts for small
-// layers: divisions with a branch for 1 and both shifts of a piece in all their copies were 24 KB and 2 us on a layer of one tile (5.3 us).
+// 12; depthwise with a channel count that is no multiple of four, 8 x 44 x 70 x 382, 3x3, formats per channel 103 (conv_direct.hip), 27.  Code
+// size counts for small layers: divisions with a branch for 1 and both shifts of a piece in all their copies were 24 KB and 2 us on a layer of one tile (5.3 us).
 // Bound by the tiles' chain of load, LDS, barrier, products and store: 1.4 us of a unit for each.
 #include "conv_epilogue.hpp"
 #include "dfq_host.hpp"
@@ -363,7 +363,8 @@ double conv_rag_groups_time(const ConvArgs &a)
 // A tenth is for the fit.  Of the 690 layers 386 lie behind the line, 1.9 times as fast in the mean, 13 of them more than 4 % slower, by 22 %
 // at most: 203 x 16 x 29, 32 groups of 5 -> 5, 5x5 335 us (one group at a time), here 33; 207 x 59 x 14, 4 groups of 4 -> 16, 5x5 59.3
 // (conv_grouped.hip), 18.4; 84 x 37 x 15, 32 groups of 2 -> 3, 3x3 / 2 20.1 (conv_direct.hip), 8.5.  On the other side 51 x 25 x 11, 8 groups of
-// 12 -> 4, 3x3 6.3 (conv_grouped.hip), here 9.3.
+// 12 -> 4, 3x3 6.3 (conv_grouped.hip), here 9.3.  (Depthwise layers that conv_depthwise.hip takes - 3x3, C a multiple of four, words aligned - are
+// not asked about: that kernel's time is not fitted.)
 bool conv_rag_groups_pays(const ConvArgs &a)
 {
     if (a.groups < 2) return false;

@@ -130,7 +130,7 @@ bool conv_rag_small(const ConvArgs &a);         // a layer of few channels that 
 double conv_rag_time(const ConvArgs &a);         // nanoseconds of conv_rag_kernel, and of one output per lane (fitted, grouped layers too)
 double conv_direct_time(const ConvArgs &a);
 double conv_rag_groups_time(const ConvArgs &a);  // of a grouped layer taken several groups at a time, by launch_conv_rag() where that is less
-bool conv_rag_groups_pays(const ConvArgs &a);    // and less than any other kernel's
+bool conv_rag_groups_pays(const ConvArgs &a);    // and less than conv_grouped's, conv_rag's and conv_direct's
 hipError_t launch_conv_rag_groups(const ConvArgs &a, hipStream_t st);
 bool conv_mfma_supports(const ConvArgs &a);
 bool conv_mfma_lean(const ConvArgs &a);      // the result, its address and the shifts suit the lean epilogue
