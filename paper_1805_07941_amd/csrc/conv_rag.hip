@@ -498,15 +498,19 @@ __global__ void __launch_bounds__(kRagThreads) conv_rag_kernel_rows(RowsParams p
     }
 }
 
-// LDS bytes of a tile's rows (with the words behind the last window), at worst
-long long rows_bytes(const ConvArgs &a)
+// A tile's rows at worst: how many, the LDS bytes of one, and of all with the words behind the last window.
+struct TileRows {
+    long long rows, pitch, bytes;
+};
+
+TileRows tile_rows(const ConvArgs &a)
 {
     constexpr int bm = kRowsBM;
     const int vs = a.stride < a.R ? a.stride : a.R;
     const long long out_rows = (bm - 2) / a.Q + 2, images = (out_rows - 2) / a.P + 1;
     const long long rows = (out_rows - 1) * vs + a.R + images * (a.R - vs);
     const long long pitch = ((long long)((a.Q - 1) * a.stride + a.S) * a.C + 15) / 16 * 16;
-    return rows * pitch + 64;
+    return {rows, pitch, rows * pitch + 64};
 }
 
 // Channel tiles (of 32) of conv_rag_kernel_rows for a call, or 0: conv_rag_kernel.  Fitted to 726 layers (3x3 to 7x7, 3 to 400 channels,
@@ -522,7 +526,13 @@ int rows_tile(const ConvArgs &a)
     // (with one tile for a unit more rows cost nothing: 2 x 76 x 51 of 181 -> 48, 3x3 19.1 us, with rows 14.9; 48 x 21 x 29 of 316 -> 11, 5x5 79.8,
     // 48.6; but 12 x 35 x 9 of 118 -> 16, 3x3 / 2 15.6, 18.5)
     const long long most = tiles <= kNumUnits && (a.stride == 1 || a.R * a.S >= 25) ? 148 * 1024 : 72 * 1024;
-    if (a.groups != 1 || steps < (a.stride > 1 ? 16 : 10) || a.R * a.S < 9 || rows_bytes(a) > most) return 0;
+    const TileRows t = tile_rows(a);
+    if (a.groups != 1 || steps < (a.stride > 1 ? 16 : 10) || a.R * a.S < 9 || t.bytes > most) return 0;
+    // The rows come in runs of 64 pieces, 24 runs at a time; six steps pay for one such round, and images of a few columns or pixels have many
+    // (117 x 51 x 3 of 61 -> 64, 5x5 / 3, 17 rounds and 25 steps: 19.7 us, with rows 55.3; 54 x 49 x 8 of 71 -> 180, 5x5 / 2, 6 and 30: 22.8, 38.2; 585
+    // layers: 0.86 of the time in the mean with this line and without, 8 instead of 59 more than 8 % slower)
+    const long long rounds = (t.rows * ((t.pitch / 16 + 63) / 64) + 23) / 24;
+    if (6 * rounds > steps) return 0;
     // (a lane has one pixel for every format it fetches, or for every sum's address: many tiles with formats per channel or sums lose,
     // 81648 pixels of 86 -> 97, 3x3, per channel 34.0 us, here 38.4; 85500 of 58 -> 25, 5x5 / 2, 30.0, 41.5)
     if ((a.frac_w || a.acc_out) && tiles_p > 400) return 0;
@@ -546,7 +556,7 @@ hipError_t launch_rows(const ConvArgs &a, hipStream_t st)
     prm.pitch = (((a.Q - 1) * a.stride + a.S) * a.C + 15) / 16 * 16;
     prm.vs = a.stride < a.R ? a.stride : a.R;
     prm.slots = (a.P - 1) * prm.vs + a.R;
-    prm.stage_at = (int)rows_bytes(a);
+    prm.stage_at = (int)tile_rows(a).bytes;
     prm.div_tk = make_fastdiv(prm.tiles_k);
     prm.div_pq = make_fastdiv(a.P * a.Q);
     prm.div_q = make_fastdiv(a.Q);
@@ -642,7 +652,7 @@ static hipError_t launch_images(const ConvArgs &a, hipStream_t st)
 {
     const int rows_ct = rows_tile(a);
     if (rows_ct) return rows_ct == 1 ? launch_rows<1>(a, st) : launch_rows<2>(a, st);
-    if (a.groups > 1 && conv_rag_groups_time(a) < 0.9 * conv_rag_time(a)) return launch_conv_rag_groups(a, st);
+    if (conv_rag_groups_faster(a)) return launch_conv_rag_groups(a, st);
     RagParams prm{};
     prm.a = a;
     prm.M = a.N * a.P * a.Q;

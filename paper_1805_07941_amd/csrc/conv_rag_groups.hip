@@ -344,27 +344,71 @@ hipError_t launch_form(GroupsParams &prm, const GroupsForm &f, hipStream_t st)
 
 }  // namespace
 
-// Nanoseconds, fitted to 690 layers (2 to 32 groups of 1 .. 64 -> 1 .. 64 channels, 1x1 to 5x5, 25 to 400000 pixels; plain, formats per channel,
-// sums) to 16 % in the mean: pieces a lane brings in and matrix instructions of a tile, the same over the tiles of a unit, and 1.4 us for
-// each of those.  A layer this kernel does not take costs more than any.
+// Nanoseconds of three kernels on grouped layers, each fitted to what 2700 to 4100 layers of a random mix took (2 to 640 groups of 1 .. 64 -> 1 .. 64
+// channels, 1x1 to 5x5, strides to 3, images from 1 x 3 to 90 x 90; plain, formats per channel, sums, shifts beyond the packed rounding), to 7 to 10 % in
+// the mean.  This kernel: matrix instructions of a tile, and for every tile of a unit the pieces a lane brings in, the instructions, 1.1 us and
+// what its end takes; alone on a unit a tile hides less.  A layer it does not take costs more than any.
 double conv_rag_groups_time(const ConvArgs &a)
 {
     if (a.groups < 2 || !conv_rag_supports(a)) return 1e30;
     const GroupsForm f = groups_choose(a);
     if (!f.pt) return 1e30;
-    const int Kg = a.K / a.groups;
+    const int Kg = a.K / a.groups, outputs = Kg <= 32 ? f.per_block * Kg : 32;
     const double blocks = Kg <= 32 ? (a.groups + f.per_block - 1) / f.per_block : (double)a.groups * ((Kg + 31) / 32);
     const double tiles = (double)(((long long)a.N * a.P * a.Q + 128 * f.pt - 1) / (128 * f.pt)) * blocks;
     const double load = tiles > kGroupsUnits ? tiles / kGroupsUnits : 1.0;
     const double pieces = (double)f.rows / f.pitch * f.np / kGroupsThreads, products = (double)((a.R * a.S * f.np + 1) / 2) * f.pt;
-    return 3556.0 + 83.0 * pieces + 106.0 * products + load * (90.0 * pieces + 13.6 * products + 1428.0);
+    double tile = 159.0 * pieces + (2 * (f.lds + 512) > kGroupsLds ? 42.0 : 22.0) * products + 1082.0, once = 4454.0 + 86.0 * products;
+    // sums go out a dword at a time unless a group's channels start and end on four (6 x 67 x 83 x 638, 1x1 / 2: 50.1 us, one output per lane 27.4)
+    if (a.acc_out) {
+        const bool words = a.K % 4 == 0 && (Kg <= 32 ? outputs : Kg) % 4 == 0;
+        tile += (words ? 1170.0 : 3770.0) * outputs / 32;
+    } else if (out_any(a)) {
+        tile += 326.0;
+        once += 1915.0;
+    } else if (a.frac_w) {
+        tile += 437.0 * f.pt;
+    }
+    return once + load * tile;
 }
 
-// A tenth is for the fit.  Of the 690 layers 386 lie behind the line, 1.9 times as fast in the mean, 13 of them more than 4 % slower, by 22 %
-// at most: 203 x 16 x 29, 32 groups of 5 -> 5, 5x5 335 us (one group at a time), here 33; 207 x 59 x 14, 4 groups of 4 -> 16, 5x5 59.3
+namespace {
+
+// conv_rag_kernel, one group at a time
+double one_group_time(const ConvArgs &a)
+{
+    const long long Cg = a.C / a.groups, Kg = a.K / a.groups, M = (long long)a.N * a.P * a.Q;
+    const double steps = (double)(((long long)a.R * a.S * ((Cg + 15) / 16) + 3) / 4);
+    const long long wide = (M + 127) / 128 * a.groups * ((Kg + 63) / 64);
+    const bool narrow = Kg <= 32, large = !narrow && wide >= 512;                          // 128 x 32, 128 x 64 or 64 x 64 tiles
+    const double tiles = narrow ? (double)((M + 127) / 128 * a.groups) : large ? (double)wide : (double)((M + 63) / 64 * a.groups * ((Kg + 63) / 64));
+    const double load = tiles > kGroupsUnits ? tiles / kGroupsUnits : 1.0;
+    double tile = narrow ? 351.0 * steps + 804.0 : large ? 332.0 * steps + 1253.0 : 310.0 * steps + 294.0;
+    double once = 4261.0 + (narrow ? 298.0 : large ? 222.0 : 236.0) * steps;
+    if (a.acc_out || a.frac_w || out_any(a)) {
+        const double part = (Kg < 16 ? Kg : 16) / 16.0;
+        tile += part * (a.acc_out ? (large ? 5027.0 : 883.0) : out_any(a) ? 488.0 : 899.0);
+        once += 1176.0 * part;
+    }
+    return once + load * tile;
+}
+
+// conv_direct_kernel, one output per lane; taps outside the image cost nothing
+double one_output_time(const ConvArgs &a)
+{
+    const double Cg = a.C / a.groups, outputs = (double)a.N * a.P * a.Q * a.K;
+    const double taps = (double)(a.R < a.H ? a.R : a.H) * (a.S < a.W ? a.S : a.W);
+    return 3821.0 + taps * (92.7 + 76.8 * Cg) + outputs * (4.12e-3 + taps * (3.55e-5 + 5.76e-4 * Cg));
+}
+
+}  // namespace
+
+bool conv_rag_groups_faster(const ConvArgs &a) { return a.groups > 1 && conv_rag_groups_time(a) < 0.9 * one_group_time(a); }
+
+// A tenth is for the fit.  203 x 16 x 29, 32 groups of 5 -> 5, 5x5 335 us (one group at a time), here 33; 207 x 59 x 14, 4 groups of 4 -> 16, 5x5 59.3
 // (conv_grouped.hip), 18.4; 84 x 37 x 15, 32 groups of 2 -> 3, 3x3 / 2 20.1 (conv_direct.hip), 8.5.  On the other side 51 x 25 x 11, 8 groups of
-// 12 -> 4, 3x3 6.3 (conv_grouped.hip), here 9.3.  (Depthwise layers that conv_depthwise.hip takes - 3x3, C a multiple of four, words aligned - are
-// not asked about: that kernel's time is not fitted.)
+// 12 -> 4, 3x3 6.3 (conv_grouped.hip), here 9.3; 217 x 53 x 16, 4 groups of 64 -> 64, 3x3 / 3 16.4 (one group at a time), 38.4.  (Depthwise layers
+// that conv_depthwise.hip takes - 3x3, C a multiple of four, words aligned - are not asked about: that kernel's time is not fitted.)
 bool conv_rag_groups_pays(const ConvArgs &a)
 {
     if (a.groups < 2) return false;
@@ -373,9 +417,7 @@ bool conv_rag_groups_pays(const ConvArgs &a)
         if (conv_sg_supports(a)) return false;
         other = conv_grouped_time(a);
     } else {
-        other = conv_rag_time(a);
-        const double direct = conv_direct_time(a);
-        if (direct < other || !conv_rag_pays(a)) other = direct;
+        other = conv_rag_pays(a) ? one_group_time(a) : one_output_time(a);
     }
     // one or two inputs to several outputs: the direct kernel's fit is coarse there (28 x 28 x 32 -> 96, 8 images, 9.0 us by it, 9.9 measured)
     const bool few = a.C / a.groups <= 2 && a.K > a.C;

@@ -129,8 +129,9 @@ hipError_t launch_conv_rag(const ConvArgs &a, hipStream_t st);
 bool conv_rag_small(const ConvArgs &a);         // a layer of few channels that it takes faster than conv_smallc
 double conv_rag_time(const ConvArgs &a);         // nanoseconds of conv_rag_kernel, and of one output per lane (fitted, grouped layers too)
 double conv_direct_time(const ConvArgs &a);
-double conv_rag_groups_time(const ConvArgs &a);  // of a grouped layer taken several groups at a time, by launch_conv_rag() where that is less
-bool conv_rag_groups_pays(const ConvArgs &a);    // and less than conv_grouped's, conv_rag's and conv_direct's
+double conv_rag_groups_time(const ConvArgs &a);  // of a grouped layer taken several groups at a time (fitted)
+bool conv_rag_groups_faster(const ConvArgs &a);  // less than one group at a time takes: launch_conv_rag() does so
+bool conv_rag_groups_pays(const ConvArgs &a);    // and less than the kernel takes that would run it: conv_grouped, conv_rag or conv_direct
 hipError_t launch_conv_rag_groups(const ConvArgs &a, hipStream_t st);
 bool conv_mfma_supports(const ConvArgs &a);
 bool conv_mfma_lean(const ConvArgs &a);      // the result, its address and the shifts suit the lean epilogue

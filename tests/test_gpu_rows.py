@@ -14,34 +14,39 @@ from test_gpu_ragged import _case, _odd
 pytestmark = pytest.mark.gpu
 
 SHAPES = [
-    # N  H   W   C    K   R  S  st pad
+    # N  H   W    C    K   R  S  st pad
     (5, 7, 9, 71, 33, 3, 3, 1, 1),              # a tile crosses three images; ten steps and a half
-    (19, 3, 3, 75, 31, 3, 3, 1, 1),             # fifteen images in a tile
-    (40, 1, 1, 83, 40, 3, 3, 1, 1),             # one pixel per image, all padding but one tap
+    (19, 3, 12, 73, 31, 3, 3, 1, 1),            # five images in a tile
+    (40, 1, 16, 51, 40, 5, 5, 1, 2),            # images of one row
     (2, 33, 41, 83, 131, 3, 3, 1, 1),
     (2, 19, 21, 97, 64, 3, 5, 1, 2),            # wider than high
     (3, 24, 23, 69, 70, 5, 3, 2, 2),
-    (2, 31, 131, 39, 65, 3, 9, 3, 1),           # stride = the kernel's height: rows have no slot twice
-    (2, 30, 139, 39, 32, 3, 9, 5, 1),           # stride beyond it: rows in between have none
-    (3, 17, 60, 29, 33, 5, 7, 6, 2),
+    (2, 31, 131, 39, 65, 3, 15, 3, 7),          # stride = the kernel's height: rows have no slot twice
+    (2, 30, 139, 29, 32, 3, 15, 5, 1),          # stride beyond it: rows in between have none
+    (3, 9, 60, 67, 40, 1, 9, 1, 4),             # a kernel of one row, images with rows of padding alone
     (1, 12, 70, 45, 20, 5, 5, 1, 4),            # padding as wide as the kernel allows outputs for
     (30, 30, 31, 79, 96, 3, 3, 1, 1),           # more tiles than two per unit: 64 channels each
     (44, 28, 28, 107, 100, 3, 3, 1, 1),
     (1, 15, 16, 33, 7, 35, 3, 1, 17),           # many kernel rows
-    (1, 9, 128, 83, 9, 3, 3, 1, 1),             # rows of 10 KB
+    (1, 9, 128, 83, 9, 5, 5, 1, 2),             # rows of 10 KB
 ]
-# the same kinds where the rows do not fit
-TOO_LARGE = [
+# the same kinds where the rows do not fit, or take too many rounds of loads for their steps
+ELSEWHERE = [
     (40, 1, 1, 130, 40, 3, 3, 1, 1),
     (2, 29, 31, 123, 65, 3, 3, 3, 1),
     (2, 30, 31, 117, 32, 3, 3, 5, 1),
+    (19, 3, 3, 75, 31, 3, 3, 1, 1),
+    (40, 1, 1, 83, 40, 3, 3, 1, 1),
+    (2, 31, 131, 39, 65, 3, 9, 3, 1),
+    (3, 17, 60, 29, 33, 5, 7, 6, 2),
+    (1, 9, 128, 83, 9, 3, 3, 1, 1),
 ]
 
 
 def test_kernels_of_the_shapes(B):
     """Which kernel the calls below reach, read from the device's records: these tests are about conv_rag_kernel_rows."""
     calls = []
-    for N, H, W, C, K, R, S, st, pad in SHAPES + TOO_LARGE:
+    for N, H, W, C, K, R, S, st, pad in SHAPES + ELSEWHERE:
         x = torch.randint(-128, 128, (N, H, W, C), dtype=torch.int8, device="cuda")
         w = torch.randint(-128, 128, (K, R, S, C), dtype=torch.int8, device="cuda")
         f = torch.full((K,), 8, dtype=torch.int32, device="cuda")
@@ -50,10 +55,10 @@ def test_kernels_of_the_shapes(B):
                   lambda x=x, w=w, f=f, a=(st, pad, 1): B.conv_q_pc(x, w, None, 4, f, 4, *a, True, frac_w_range=(8, 8))]
     got = launched(calls)
     assert len(got) == len(calls)
-    assert ["conv_rag_kernel_rows" in name for name in got] == [True] * (3 * len(SHAPES)) + [False] * (3 * len(TOO_LARGE))
+    assert ["conv_rag_kernel_rows" in name for name in got] == [True] * (3 * len(SHAPES)) + [False] * (3 * len(ELSEWHERE))
 
 
-@pytest.mark.parametrize("shape", SHAPES + TOO_LARGE, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", SHAPES + ELSEWHERE, ids=lambda s: "x".join(map(str, s)))
 def test_rows(B, shape):
     N, H, W, C, K, R, S, st, pad = shape
     rng = np.random.default_rng(sum(shape))
