@@ -25,7 +25,7 @@ SHAPES = [
     (41, 59, 57, 64, 8, 3, 3, 1, 1),             # two tiles per workgroup, ragged
     (23, 57, 59, 128, 4, 4, 1, 1, 1),
     (24, 60, 59, 128, 64, 2, 3, 1, 0),
-    (50, 60, 45, 64, 32, 1, 1, 1, 0),            # the form with one stage
+    (50, 60, 45, 64, 32, 1, 1, 1, 0),            # one tap: a tile to a workgroup
     (9, 61, 60, 384, 16, 3, 3, 1, 1),
     (3, 9, 8, 128, 16, 1, 1, 1, 0),              # the other triples of taps, width and group that there are
     (45, 60, 45, 128, 64, 1, 1, 1, 0),
