@@ -254,6 +254,8 @@ __device__ __forceinline__ void store_tile_lane_ragged(const v16i &v, const Conv
     Bytes16 o;
 #pragma unroll
     for (int j = 0; j < 4; j++) {
+        o.w[j] = 0;
+        if (4 * j >= count) continue;                     // (the rescale is most of the work: tails of few channels)
         int q[4];
 #pragma unroll
         for (int e = 0; e < 4; e++) {
