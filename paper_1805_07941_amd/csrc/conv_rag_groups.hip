@@ -412,15 +412,16 @@ bool conv_rag_groups_faster(const ConvArgs &a) { return a.groups > 1 && conv_rag
 bool conv_rag_groups_pays(const ConvArgs &a)
 {
     if (a.groups < 2) return false;
+    const bool few = a.C / a.groups <= 2 && a.K > a.C;
     double other;
     if (conv_grouped_supports(a)) {
         if (conv_sg_supports(a)) return false;
         other = conv_grouped_time(a);
     } else {
-        other = conv_rag_pays(a) ? one_group_time(a) : one_output_time(a);
+        // one or two inputs to several outputs: conv_direct_time() is the fit that holds there (251 such layers took 1.00 of it in the mean,
+        // 1x1 to 5x5, but 0.83 of one_output_time(), which sent 8 x 28 x 28, 32 groups of 2 -> 3, 3x3 here; 11.9 us measured, 12.0 and 15.0 by the two)
+        other = conv_rag_pays(a) ? one_group_time(a) : few ? conv_direct_time(a) : one_output_time(a);
     }
-    // one or two inputs to several outputs: the direct kernel's fit is coarse there (28 x 28 x 32 -> 96, 8 images, 9.0 us by it, 9.9 measured)
-    const bool few = a.C / a.groups <= 2 && a.K > a.C;
     return conv_rag_groups_time(a) < (few ? 0.5 : 0.9) * other;
 }
 
