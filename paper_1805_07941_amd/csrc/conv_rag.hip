@@ -614,8 +614,10 @@ double conv_rag_time(const ConvArgs &a)
     const int bm = Kg <= 32 ? 128 : 64;
     const double tiles = (double)((long long)(M + bm - 1) / bm) * a.groups * ((Kg + 31) / 32), tail = tiles > 1280 ? tiles - 1280 : 0;
     double here = 3630.0 + 725.0 * steps + tiles * (1.36 + 1.4 * steps) + 1.1 * tail * steps;
-    // the general epilogue, by the outputs a lane has of a group, as fitted while it stored a byte or a sum at a time (870 pixels, 1x1, 8 groups of 18 -> 16, formats per channel: 6.7 us, 4.7;
-    // accumulators of 24180 pixels in 12 groups of 3 -> 24 47.3, 34.9; of 45288 pixels in four groups of 31 -> 5 9.9, 42.0)
+    // the general epilogue, by the outputs a lane has of a group, as fitted while it stored a byte or a sum at a time (870 pixels, 1x1, 8 groups of
+    // 18 -> 16, formats per channel: 6.7 us, 4.7; accumulators of 24180 pixels in 12 groups of 3 -> 24 47.3, 34.9; of 45288 pixels in four groups of 31 -> 5
+    // 9.9, 42.0).  It stores words now, and the line still lies well: of conv_rag and one output per lane 643 layers (183 of them ungrouped) take 1.007
+    // of the better in the mean with sums and 1.014 with shifts past 23; plain ones 1.011.
     if (a.acc_out || a.frac_w || a.shift < 0 || a.shift > 23) {
         const double part = (Kg < 16 ? Kg : 16) / 16.0, shares = part * tiles * (Kg <= 32 ? 1.0 : 0.5);
         here += a.acc_out ? 900.0 * part + 5.8 * shares : 1200.0 + 1000.0 * part + 2.4 * shares;

@@ -320,9 +320,12 @@ Shape choose(const ConvArgs &a)
     if (t16 <= 512) return Shape::t16;
     const int n = (a.R * a.S * a.C + kRow - 1) / kRow;
     // Fitted to 1300 layer sizes: this kernel takes 3 us + (2 + 0.4 n) ns per 32 x 32 tile; the general one, while its tiles do not
-    // fill the chip, 3 us + 0.28 us per 128 bytes of the reduction in steps of that length, 0.7 us in steps of 64, and up
-    // to 22 us more where a ragged K takes its general epilogue (5x5 448 -> 832 at 45 x 77, one image, a format per channel:
-    // 72.7, here 94.7; 176 -> 36 at 9 x 62, 82 images 46.8, here 40.6; fitted while that epilogue stored single bytes).  Its 64 x 64 tiles for at most 1024 pixels, six stages
+    // fill the chip, 3 us + 0.28 us per 128 bytes of the reduction in steps of that length, 0.7 us in steps of 64, 0.8 where K, a
+    // multiple of 16, leaves its last channel tile partly empty (3x3 448 -> 224 at 31 x 27, 15 images 23.1, here 38.3), and up to 22 us
+    // more where a ragged K takes its general epilogue (5x5 448 -> 832 at 45 x 77, one image, a format per channel: 72.7, here 94.7; 3x3
+    // 528 -> 248 at 43 x 7, 16 images 37.7, here 26.4).  Of 506 layers whose K is no whole tile but a multiple of 16 the choice is 1.005
+    // of the better in the mean, 10 of them more than 8 % off (priced as a ragged K 1.015 and 27); of 117 ragged ones 1.003 and 1; with
+    // sums, where every K takes the general epilogue, 1.011 and 14 of 373.  Its 64 x 64 tiles for at most 1024 pixels, six stages
     // in flight, do as well as the long steps (96 -> 576, 980 pixels 4.1, here 4.9; 320 -> 320 4.3, 4.8), and so does any of its
     // tiles where the reduction is a single step (64 -> 64 at 56 x 56, one image 3.9, 4.4).  At the line: 3x3 256 -> 256 at 14 x 14, four images 8.4 -> 5.8 us, twelve
     // (592 tiles) 8.45 against 8.0; 1x1 512 -> 256 at 28 x 28, one image 4.4 -> 4.3, four 4.7 against 6.2; 3x3 64 -> 64 at
@@ -333,7 +336,9 @@ Shape choose(const ConvArgs &a)
         // images: 4.0 against 6.8)
         if (conv_pw_supports(a) && a.C % kRow) return Shape::none;
         if (!(conv_mfma_lean(a) && a.K % 64 == 0 && (M <= 1024 || n == 1)))
-            price = 700LL * n + (a.K % (a.K <= 64 ? 64 : 128) ? 700LL * (n < 32 ? n : 32) : 0);
+            price = a.K % (a.K <= 64 ? 64 : 128) == 0 ? 700LL * n
+                    : conv_mfma_lean(a) && !a.frac_w && a.K % 16 == 0 ? 800LL * n
+                                                                     : 700LL * n + 700LL * (n < 32 ? n : 32);
     }
     if (t32 * (20 + 4 * n) > price * 10) return Shape::none;
     return t32_shape(t32, n);

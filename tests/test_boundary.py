@@ -394,6 +394,15 @@ def test_kernel_selection(B):
     assert s(1, 8, 8, 64, 64, 3, 3, 1, 1, 64) == B.CONV_DEPTHWISE
 
 
+def test_kernel_selection_at_channel_tails(B):
+    """A K that is a multiple of 16 leaves the dense kernel its short epilogue, whole channel tiles or not; any other K does not."""
+    s = B.conv_q_select
+    assert s(15, 31, 27, 448, 224, 3, 3, 1, 1, 1) == B.CONV_MFMA
+    assert s(10, 40, 40, 96, 80, 3, 3, 1, 1, 1) == B.CONV_MFMA
+    assert s(16, 43, 7, 528, 248, 3, 3, 1, 1, 1) == B.CONV_SPLIT
+    assert s(1, 31, 27, 448, 224, 3, 3, 1, 1, 1) == B.CONV_SPLIT
+
+
 def test_binding_fails_loudly_without_the_library(B, monkeypatch):
     monkeypatch.setattr(B, "_lib", None)
     monkeypatch.setattr(B, "LIB_PATH", "/nonexistent/libdfq.so")
