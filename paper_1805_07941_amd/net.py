@@ -45,11 +45,13 @@ def _read_f32(t: torch.Tensor) -> float:
 WEIGHT_GROUP_BYTES = 256 << 20
 
 
-# Uploads go through at most this many pinned pieces of this size: filled and sent one after the other, awaited together before the first is
-# filled again.  A wait costs more than the pieces' pinning saves: 17 MB and the calibration behind it 1.65 ms with four pieces and one wait,
-# 1.45 with none; 33 MB 1.9 (two), 1.53 (none).  A process pins what its largest upload needs, once: 64 MB 10.5 ms with the copies, four pieces 6.9.
+# Uploads go through pinned pieces of this size, filled and sent one after the other.  As many as the upload needs, up to STAGING_PIECES: a wait
+# costs more than the pieces' pinning saves, 17 MB and the calibration behind it 1.65 ms with four pieces and one wait, 1.45 with
+# none; 33 MB 1.9 (two), 1.53 (none).  A larger upload waits in any case and takes STAGING_WAITING pieces, awaited together before the first is
+# filled again: 98 MB 2.6 ms by either count, but 12.8 and 17.0 the first time, when a process pins them.
 STAGING_BYTES = 4 << 20
 STAGING_PIECES = 16
+STAGING_WAITING = 4
 
 
 def _to_device(arrays, device):
@@ -66,7 +68,9 @@ def _to_device(arrays, device):
     total = sum(sizes)
     dst = torch.empty(total, dtype=torch.float32, device=device)
     piece = min(STAGING_BYTES // 4, max(total, 1))
-    stages = [torch.empty(piece, dtype=torch.float32, pin_memory=True) for _ in range(max(1, min(STAGING_PIECES, -(-total // piece))))]
+    needed = max(1, -(-total // piece))
+    pieces = needed if needed <= STAGING_PIECES else min(STAGING_WAITING, STAGING_PIECES)
+    stages = [torch.empty(piece, dtype=torch.float32, pin_memory=True) for _ in range(pieces)]
     views = [t.numpy() for t in stages]
     turn, at, used = 0, 0, 0                              # the piece being filled, where it goes, how much it holds
 

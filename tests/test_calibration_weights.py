@@ -112,3 +112,16 @@ def test_a_pinned_piece_is_awaited_on_the_device_it_travels_to(monkeypatch, piec
         Stream("end").synchronize()
         waits.clear()
         assert all(np.array_equal(g.numpy(), a) for g, a in zip(got, arrays))
+
+
+def test_pinned_pieces_of_an_upload(monkeypatch):
+    """As many as an upload needs while it needs no wait; four where it waits in any case."""
+    empty, pinned = torch.empty, []
+    monkeypatch.setattr(torch, "empty", lambda *a, device=None, pin_memory=False, **kw: (pinned.append(a) if pin_memory else None, empty(*a, **kw))[1])
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device: type("Stream", (), {"synchronize": lambda self: None})())
+    monkeypatch.setattr(int8net, "STAGING_BYTES", 4096)
+    for words, pieces in ((0, 1), (64, 1), (1024, 1), (1025, 2), (16 * 1024, 16), (16 * 1024 + 1, 4), (100 * 1024, 4)):
+        a = np.arange(words, dtype=np.float32)
+        (got,) = int8net._to_device([a], "cuda:0")
+        assert len(pinned) == pieces and np.array_equal(got.numpy(), a)
+        pinned.clear()
